@@ -202,23 +202,25 @@ Saved plan_saved(const Dims &D, size_t Tf, Bump &s) {
 struct FwdWs {
   // inference rows
   bf16_t *a_i, *q_i, *k_i, *v_i, *o_i, *b_i, *hm_i;
-  float *qkv_i, *x1_i, *dec_partial;
+  float *qkv_i, *x1_i, *dec_partial, *ss;      // ss: partial sums of squares of the x1 rows (few-row path)
   // fine-tune rows
   float *qkv_f;
   bf16_t *a_lo, *q_lo, *k_lo, *v_lo, *o_lo, *b_lo, *hm_lo;
 };
 FwdWs plan_fwd(const Dims &D, size_t Ti, size_t Tf, int n_decode, int max_ctx, int decode_chunk, Bump &w) {
   FwdWs F;
-  F.a_i = w.take<bf16_t>(Ti * D.d);
+  const size_t Tr = align_up(Ti, 16);      // rows of the buffers that may be in fragment order (whole 16-row tiles)
+  F.a_i = w.take<bf16_t>(Tr * D.d);
   F.qkv_i = w.take<float>(Ti * D.nqkv);
   F.q_i = w.take<bf16_t>(Ti * D.qd);
   F.k_i = w.take<bf16_t>(Ti * D.kd);
   F.v_i = w.take<bf16_t>(Ti * D.kd);
-  F.o_i = w.take<bf16_t>(Ti * D.qd);
+  F.o_i = w.take<bf16_t>(Tr * D.qd);
   F.x1_i = w.take<float>(Ti * D.d);
-  F.b_i = w.take<bf16_t>(Ti * D.d);
-  F.hm_i = w.take<bf16_t>(Ti * D.F);
+  F.b_i = w.take<bf16_t>(Tr * D.d);
+  F.hm_i = w.take<bf16_t>(Tr * D.F);
   F.dec_partial = w.take<float>(decode_partial_floats(n_decode, D.Hq, D.Hkv, D.hd, max_ctx, decode_chunk));
+  F.ss = w.take<float>(Ti <= SKINNY_MAX_ROWS ? Ti * skinny_parts(D.d) : 0);
   F.qkv_f = w.take<float>(Tf * D.nqkv);
   F.a_lo = w.take<bf16_t>(Tf * D.d);
   F.q_lo = w.take<bf16_t>(Tf * D.qd);
@@ -372,7 +374,7 @@ struct LogitWs {
 };
 LogitWs plan_logits(const Dims &D, size_t n, Bump &w) {
   LogitWs P;
-  P.n_hi = w.take<bf16_t>(n * D.d);
+  P.n_hi = w.take<bf16_t>((n <= SKINNY_MAX_ROWS ? align_up(n, 16) : n) * D.d);      // whole tiles of the fragment order
   P.e_hi = D.bf ? nullptr : w.take<bf16_t>((size_t)D.V * D.d);
   return P;
 }
@@ -688,6 +690,23 @@ size_t mace_workspace_bytes(mace_handle_t h, int32_t n_tokens, int32_t n_ft_toke
   return align_up(m, 256) + 256;
 }
 
+static bool skinny_fits(const Dims &D, long long rows) {
+  const long long lim = 1ll << 31;
+  return D.bf && rows <= SKINNY_MAX_ROWS && (long long)D.nqkv * D.d < lim && (long long)D.F * D.d < lim && (long long)D.d * D.qd < lim;
+}
+static int run_skinny(mace_ctx *h, const SkinnyParams &p, int asrc, int epi, double flops, hipStream_t st, const char *where) {
+  prof_mark(h, st, T_GEMM_NT, flops);
+  HIP_TRY(launch_skinny(p, asrc, epi, st), where);
+  if (h->plan.size() < 256) {
+    mace_gemm_plan_t r;
+    memset(&r, 0, sizeof(r));
+    snprintf(r.name, sizeof(r.name), "%s", where);
+    r.tile_m = p.M; r.tile_n = 16; r.k_splits = 1;
+    r.m = p.M; r.n = epi == SK_E_SWIGLU ? 2ll * p.N : p.N; r.k = p.K;
+    h->plan.push_back(r);
+  }
+  return MACE_OK;
+}
 static int next_token_logits_impl(mace_handle_t h, const float *y, const int32_t *row_idx, int32_t n, const void *g_final, const void *w_lm,
                                   float *logits_out, int32_t *next_token, void *workspace, size_t workspace_bytes, void *stream) {
   const Dims D(h->m);
@@ -702,9 +721,17 @@ static int next_token_logits_impl(mace_handle_t h, const float *y, const int32_t
     HIP_TRY(launch_split_f32((const float *)w_lm, (size_t)D.V * D.d, P.e_hi, nullptr, st), "split E");
     e_hi = P.e_hi;
   }
+  const bool skinny = n <= SKINNY_MAX_ROWS && D.bf && (long long)D.V * D.d < (1ll << 31);
   prof_mark(h, st, T_RMSNORM);
-  HIP_TRY(launch_rmsnorm_fwd(y, false, row_idx, g_final, D.bf, n, D.d, h->m.rms_eps, P.n_hi, nullptr, nullptr, st), "final rmsnorm");
-  {
+  HIP_TRY(launch_rmsnorm_fwd(y, false, row_idx, g_final, D.bf, n, D.d, h->m.rms_eps, P.n_hi, nullptr, nullptr, st, skinny), "final rmsnorm");
+  if (skinny) {
+    SkinnyParams p;
+    memset(&p, 0, sizeof(p));
+    p.M = n; p.N = D.V; p.K = D.d;
+    p.a = P.n_hi;
+    p.w[0] = e_hi; p.c = logits_out;
+    TRY(run_skinny(h, p, SK_A_FRAG, SK_E_F32, 2.0 * n * D.V * D.d, st, "next-token logits gemm"));
+  } else {
     GemmParams p = gp_init(D.d, D.d, D.d, D.V);
     gp_group(p, P.n_hi, nullptr, logits_out, nullptr, n, 1);
     gp_seg(p, e_hi, nullptr, D.V, 0);
@@ -838,6 +865,74 @@ int mace_kv_cache_gather(mace_handle_t h, const mace_kv_cache_t *cache, const in
   return MACE_OK;
 }
 
+// Attention of the inference rows: prefill (causal; behind a cached prefix through the block tables), decode (paged).
+static int inference_attention(mace_handle_t h, const Dims &D, const BatchInfo &I, const mace_batch_t *batch, const mace_kv_cache_t *cache,
+                               const FwdWs &F, hipStream_t st, bool o_frag = false) {
+  prof_mark(h, st, T_ATTN_PREFILL, 4.0 * D.hd * D.Hq * I.pairs_prefill);
+  if (I.prefix && batch->n_prefill > 0)
+    HIP_TRY(launch_attn_fwd_paged(F.q_i, cache->k, cache->v, cache->num_blocks, cache->block_size, batch->prefill_block_tables, batch->max_blocks_per_prefill,
+                                  batch->prefill_prefix_lens, batch->seg_offsets, 0, batch->n_prefill, I.max_prefill, D.Hq, D.Hkv, D.hd, F.o_i, st, o_frag), "prefix-shared prefill attention");
+  else
+    HIP_TRY(launch_attn_fwd(F.q_i, F.k_i, F.v_i, nullptr, nullptr, nullptr, batch->seg_offsets, 0, batch->n_prefill, I.max_prefill, D.Hq, D.Hkv, D.hd, F.o_i, nullptr, nullptr, st, nullptr, nullptr, o_frag), "prefill attention");
+  if (I.Td > 0) {
+    double kv_tokens = 0.0;
+    for (int i = 0; i < I.Td; ++i) kv_tokens += (double)batch->context_lens_host[i] + 1.0;
+    prof_mark(h, st, T_ATTN_DECODE, 4.0 * kv_tokens * D.Hq * D.hd, kv_tokens * 2.0 * D.Hkv * D.hd * (D.bf ? 2.0 : 4.0));
+    HIP_TRY(launch_attn_decode(F.q_i + (size_t)I.Tp * D.qd, cache->k, cache->v, D.bf, cache->num_blocks, cache->block_size, batch->block_tables, batch->max_blocks_per_req,
+                               batch->context_lens, I.Td, I.max_ctx, D.Hq, D.Hkv, D.hd, F.dec_partial, o_frag ? F.o_i : F.o_i + (size_t)I.Tp * D.qd, batch->decode_head_norms, st, h->decode_chunk,
+                               o_frag ? I.Tp : -1), "decode attention");
+  }
+  return MACE_OK;
+}
+
+// Forward of a batch of a few inference rows and nothing else (a serving iteration between retraining jobs): every
+// product is bound by its weight stream, so it runs on the kernel built for that (gemm_skinny.hip) with the row-wise
+// steps around it folded in.
+static int layer_fwd_skinny(mace_handle_t h, const Dims &D, const BatchInfo &I, const mace_layer_w_t *w, const mace_batch_t *batch,
+                            mace_kv_cache_t *cache, const void *x, float *y, const FwdWs &F, hipStream_t st) {
+  const bool fuse_norm = I.Ti <= SKINNY_NORM_ROWS;
+  const double rows2 = 2.0 * I.Ti;
+  SkinnyParams z;
+  memset(&z, 0, sizeof(z));
+  z.M = I.Ti; z.eps = h->m.rms_eps;
+  {
+    SkinnyParams p = z;
+    p.N = D.nqkv; p.K = D.d;
+    p.w[0] = (const bf16_t *)w->wq; p.w[1] = (const bf16_t *)w->wk; p.w[2] = (const bf16_t *)w->wv;
+    p.Hq = D.Hq; p.Hkv = D.Hkv; p.hd = D.hd;
+    p.positions = batch->positions; p.inv_freq = h->inv_freq; p.slots = batch->slot_mapping;
+    p.q = F.q_i; p.k = F.k_i; p.v = F.v_i;
+    p.cache_k = cache->k; p.cache_v = cache->v; p.num_slots = cache->num_blocks * cache->block_size; p.block_size = cache->block_size;
+    p.a = x; p.gain = (const bf16_t *)w->g_attn;
+    if (!fuse_norm) {
+      prof_mark(h, st, T_RMSNORM);
+      HIP_TRY(launch_rmsnorm_fwd(x, true, nullptr, w->g_attn, true, I.Ti, D.d, h->m.rms_eps, F.a_i, nullptr, nullptr, st, true), "rmsnorm1");
+      p.a = F.a_i;
+    }
+    TRY(run_skinny(h, p, fuse_norm ? SK_A_NORM_BF16 : SK_A_FRAG, SK_E_QKV, rows2 * D.nqkv * D.d, st, "qkv gemm"));
+  }
+  TRY(inference_attention(h, D, I, batch, cache, F, st, true));
+  {
+    SkinnyParams p = z;
+    p.N = D.d; p.K = D.qd; p.a = F.o_i; p.w[0] = (const bf16_t *)w->wo; p.c = F.x1_i; p.resid = x; p.resid_kind = 2;
+    p.next_a = F.b_i; p.next_gain = (const bf16_t *)w->g_mlp; p.ss_out = F.ss;
+    TRY(run_skinny(h, p, SK_A_FRAG, SK_E_F32, rows2 * D.d * D.qd, st, "o gemm"));
+  }
+  {
+    SkinnyParams p = z;
+    p.N = D.F; p.K = D.d; p.w[0] = (const bf16_t *)w->w_gate; p.w[1] = (const bf16_t *)w->w_up; p.c = F.hm_i;
+    p.a = F.b_i; p.ss_in = F.ss; p.ss_n = skinny_parts(D.d);
+    TRY(run_skinny(h, p, SK_A_FRAG, SK_E_SWIGLU, rows2 * 2 * D.F * D.d, st, "gate/up gemm"));
+  }
+  {
+    SkinnyParams p = z;
+    p.N = D.d; p.K = D.F; p.a = F.hm_i; p.w[0] = (const bf16_t *)w->w_down; p.c = y; p.resid = F.x1_i; p.resid_kind = 1;
+    TRY(run_skinny(h, p, SK_A_FRAG, SK_E_F32, rows2 * D.d * D.F, st, "down gemm"));
+  }
+  prof_mark(h, st, -1);
+  return MACE_OK;
+}
+
 static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_lora_t *lora, const mace_batch_t *batch,
                           mace_kv_cache_t *cache, const void *x, float *y, void *saved, void *workspace,
                           size_t workspace_bytes, void *stream) {
@@ -888,6 +983,7 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     prof_mark(h, st, T_MISC);
     TRY(prepare_lora(D, lora, L, 1.0f, st));
   }
+  if (!lora && I.Tf == 0 && skinny_fits(D, I.Ti)) return layer_fwd_skinny(h, D, I, w, batch, cache, x, y, F, st);
   Saved S = plan_saved(D, I.Tf, svb);
   const int np_ft = D.bf ? 2 : 3;
   const size_t es = D.bf ? 2 : 4;
@@ -961,19 +1057,7 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
                               nullptr, nullptr, nullptr, D.bf, 0, 1, st), "rope ft");
   }
   // 4. attention: prefill (causal), decode (paged), fine-tune (causal, split operands, LSE kept)
-  prof_mark(h, st, T_ATTN_PREFILL, 4.0 * D.hd * D.Hq * I.pairs_prefill);
-  if (I.prefix && batch->n_prefill > 0)
-    HIP_TRY(launch_attn_fwd_paged(F.q_i, cache->k, cache->v, cache->num_blocks, cache->block_size, batch->prefill_block_tables, batch->max_blocks_per_prefill,
-                                  batch->prefill_prefix_lens, batch->seg_offsets, 0, batch->n_prefill, I.max_prefill, D.Hq, D.Hkv, D.hd, F.o_i, st), "prefix-shared prefill attention");
-  else
-    HIP_TRY(launch_attn_fwd(F.q_i, F.k_i, F.v_i, nullptr, nullptr, nullptr, batch->seg_offsets, 0, batch->n_prefill, I.max_prefill, D.Hq, D.Hkv, D.hd, F.o_i, nullptr, nullptr, st), "prefill attention");
-  if (I.Td > 0) {
-    double kv_tokens = 0.0;
-    for (int i = 0; i < I.Td; ++i) kv_tokens += (double)batch->context_lens_host[i] + 1.0;
-    prof_mark(h, st, T_ATTN_DECODE, 4.0 * kv_tokens * D.Hq * D.hd, kv_tokens * 2.0 * D.Hkv * D.hd * (D.bf ? 2.0 : 4.0));
-    HIP_TRY(launch_attn_decode(F.q_i + (size_t)I.Tp * D.qd, cache->k, cache->v, D.bf, cache->num_blocks, cache->block_size, batch->block_tables, batch->max_blocks_per_req,
-                               batch->context_lens, I.Td, I.max_ctx, D.Hq, D.Hkv, D.hd, F.dec_partial, F.o_i + (size_t)I.Tp * D.qd, batch->decode_head_norms, st, h->decode_chunk), "decode attention");
-  }
+  TRY(inference_attention(h, D, I, batch, cache, F, st));
   prof_mark(h, st, T_ATTN_FT, 4.0 * D.hd * D.Hq * I.pairs_ft);
   HIP_TRY(launch_attn_fwd(S.q, S.k, S.v, F.q_lo, F.k_lo, F.v_lo, batch->seg_offsets + batch->n_prefill + batch->n_decode, I.Ti, batch->n_ft_seq, I.max_ft, D.Hq, D.Hkv, D.hd, S.o, F.o_lo, S.lse, st, batch->ft_excl_lo, batch->ft_excl_hi), "ft attention");
   // 5. output projection + residual (adapter variant: t = o A_o^T beside it, then x1 += (scale t) B_o^T)

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const bf16_t *__restri
 template <int HD>
 __global__ __launch_bounds__(HD) void attn_decode_combine_kernel(const float *__restrict__ partial,
                                                                  const int32_t *__restrict__ ctx_lens, int Hq, int nsplit, int chunk,
-                                                                 bf16_t *__restrict__ out, float *__restrict__ norms) {
+                                                                 bf16_t *__restrict__ out, float *__restrict__ norms, int frag_row0) {
   const int req = blockIdx.x, h = blockIdx.y, e = threadIdx.x;
   const int ns = min(nsplit, (ctx_lens[req] + 1 + chunk - 1) / chunk);
   const float *src = partial + ((size_t)req * Hq + h) * nsplit * (HD + 2);
@@ -220,7 +220,7 @@ __global__ __launch_bounds__(HD) void attn_decode_combine_kernel(const float *__
     ao += src[s * (HD + 2) + e] * a;
   }
   const float v = lo > 0.f ? ao / lo : 0.f;
-  out[((size_t)req * Hq + h) * HD + e] = f2bf(v);
+  out[frag_row0 >= 0 ? frag_index(frag_row0 + req, h * HD + e, Hq * HD) : ((size_t)req * Hq + h) * HD + e] = f2bf(v);
   if (norms) {                                   // L2 norm of the head's output vector (fp32 values)
     __shared__ float red[2];
     float s = wave_sum(v * v);
@@ -280,7 +280,7 @@ size_t decode_partial_floats(int n_decode, int Hq, int Hkv, int hd, int max_cont
 hipError_t launch_attn_decode(const bf16_t *q, const void *cache_k, const void *cache_v, bool cache_bf16,
                               long long num_blocks, int block_size, const int32_t *block_tables, int max_blocks_per_req,
                               const int32_t *ctx_lens, int n_decode, int max_context, int Hq, int Hkv, int hd,
-                              float *partial, bf16_t *out, float *norms, hipStream_t st, int chunk_tokens) {
+                              float *partial, bf16_t *out, float *norms, hipStream_t st, int chunk_tokens, int frag_row0) {
   if (n_decode <= 0) return hipSuccess;
   if (n_decode > 65535 || Hkv > 65535 || Hq > 65535) return hipErrorInvalidValue;
   int bshift = 0;
@@ -299,7 +299,7 @@ hipError_t launch_attn_decode(const bf16_t *q, const void *cache_k, const void *
   if (!ok) return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (hd == 64) hipLaunchKernelGGL((attn_decode_combine_kernel<64>), dim3(n_decode, Hq), dim3(64), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms);
-  else hipLaunchKernelGGL((attn_decode_combine_kernel<128>), dim3(n_decode, Hq), dim3(128), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms);
+  if (hd == 64) hipLaunchKernelGGL((attn_decode_combine_kernel<64>), dim3(n_decode, Hq), dim3(64), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
+  else hipLaunchKernelGGL((attn_decode_combine_kernel<128>), dim3(n_decode, Hq), dim3(128), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
   return hipGetLastError();
 }

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
                                                            const int32_t *__restrict__ seg, int row_base, int Hq, int Hkv,
                                                            bf16_t *__restrict__ o_hi, bf16_t *__restrict__ o_lo,
                                                            float *__restrict__ lse, const PagedKV pg,
-                                                           const int32_t *__restrict__ excl_lo, const int32_t *__restrict__ excl_hi) {
+                                                           const int32_t *__restrict__ excl_lo, const int32_t *__restrict__ excl_hi, int o_frag) {
   static_assert(!(PAGED && SPLIT), "paged K/V are single bf16 operands");
   constexpr int NT = SPLIT ? 2 : 1;
   constexpr int QB = 32 * NW;
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
         uint32_t h0, l0, h1, l1;
         split_pk_bf16(oacc[t][4 * rq] * inv, oacc[t][4 * rq + 1] * inv, h0, l0);
         split_pk_bf16(oacc[t][4 * rq + 2] * inv, oacc[t][4 * rq + 3] * inv, h1, l1);
-        const size_t o = ob + t * 32 + 8 * rq + 4 * g;
+        const size_t o = o_frag ? frag_index(r0 + qi, h * HD + t * 32 + 8 * rq + 4 * g, Hq * HD) : ob + t * 32 + 8 * rq + 4 * g;
         *(uint2 *)(o_hi + o) = make_uint2(h0, h1);
         if (o_lo) *(uint2 *)(o_lo + o) = make_uint2(l0, l1);
       }
@@ -223,7 +223,7 @@ template <int HD, bool SPLIT, int NW, bool PAGED = false>
 hipError_t launch_t(const bf16_t *q_hi, const bf16_t *k_hi, const bf16_t *v_hi, const bf16_t *q_lo, const bf16_t *k_lo,
                     const bf16_t *v_lo, const int32_t *seg, int row_base, int n_seq, int max_len, int Hq, int Hkv,
                     bf16_t *o_hi, bf16_t *o_lo, float *lse, hipStream_t st, const PagedKV pg = PagedKV{},
-                    const int32_t *excl_lo = nullptr, const int32_t *excl_hi = nullptr) {
+                    const int32_t *excl_lo = nullptr, const int32_t *excl_hi = nullptr, bool o_frag = false) {
   constexpr int NT = SPLIT ? 2 : 1;
   constexpr size_t lds = (size_t)2 * 2 * NT * KB * HD * sizeof(bf16_t);
   static DeviceOnce attr_done;
@@ -233,7 +233,7 @@ hipError_t launch_t(const bf16_t *q_hi, const bf16_t *k_hi, const bf16_t *v_hi, 
     attr_done.set();
   }
   dim3 grid(Hq, n_seq, cdiv(max_len, 32 * NW));
-  hipLaunchKernelGGL((attn_fwd_kernel<HD, SPLIT, NW, PAGED>), grid, dim3(64 * NW), lds, st, q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, Hq, Hkv, o_hi, o_lo, lse, pg, excl_lo, excl_hi);
+  hipLaunchKernelGGL((attn_fwd_kernel<HD, SPLIT, NW, PAGED>), grid, dim3(64 * NW), lds, st, q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, Hq, Hkv, o_hi, o_lo, lse, pg, excl_lo, excl_hi, o_frag ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -242,28 +242,28 @@ hipError_t launch_t(const bf16_t *q_hi, const bf16_t *k_hi, const bf16_t *v_hi, 
 hipError_t launch_attn_fwd(const bf16_t *q_hi, const bf16_t *k_hi, const bf16_t *v_hi, const bf16_t *q_lo,
                            const bf16_t *k_lo, const bf16_t *v_lo, const int32_t *seg, int row_base, int n_seq,
                            int max_len, int Hq, int Hkv, int hd, bf16_t *o_hi, bf16_t *o_lo, float *lse,
-                           hipStream_t st, const int32_t *excl_lo, const int32_t *excl_hi) {
+                           hipStream_t st, const int32_t *excl_lo, const int32_t *excl_hi, bool o_frag) {
   if (n_seq <= 0 || max_len <= 0) return hipSuccess;
   if (n_seq > 65535 || max_len > 65535 * 64 || ((excl_lo == nullptr) != (excl_hi == nullptr))) return hipErrorInvalidValue;
   const bool split = q_lo != nullptr;
   if (split && (!k_lo || !v_lo)) return hipErrorInvalidValue;
   // two-term operands at head dim 128 need 128 KB of LDS per block: 8 waves share it
-  if (hd == 64) return split ? launch_t<64, true, 4>(q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, n_seq, max_len, Hq, Hkv, o_hi, o_lo, lse, st, PagedKV{}, excl_lo, excl_hi)
-                             : launch_t<64, false, 4>(q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, n_seq, max_len, Hq, Hkv, o_hi, o_lo, lse, st, PagedKV{}, excl_lo, excl_hi);
-  if (hd == 128) return split ? launch_t<128, true, 8>(q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, n_seq, max_len, Hq, Hkv, o_hi, o_lo, lse, st, PagedKV{}, excl_lo, excl_hi)
-                              : launch_t<128, false, 4>(q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, n_seq, max_len, Hq, Hkv, o_hi, o_lo, lse, st, PagedKV{}, excl_lo, excl_hi);
+  if (hd == 64) return split ? launch_t<64, true, 4>(q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, n_seq, max_len, Hq, Hkv, o_hi, o_lo, lse, st, PagedKV{}, excl_lo, excl_hi, o_frag)
+                             : launch_t<64, false, 4>(q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, n_seq, max_len, Hq, Hkv, o_hi, o_lo, lse, st, PagedKV{}, excl_lo, excl_hi, o_frag);
+  if (hd == 128) return split ? launch_t<128, true, 8>(q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, n_seq, max_len, Hq, Hkv, o_hi, o_lo, lse, st, PagedKV{}, excl_lo, excl_hi, o_frag)
+                              : launch_t<128, false, 4>(q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, seg, row_base, n_seq, max_len, Hq, Hkv, o_hi, o_lo, lse, st, PagedKV{}, excl_lo, excl_hi, o_frag);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_attn_fwd_paged(const bf16_t *q, const void *cache_k, const void *cache_v, long long num_blocks, int block_size,
                                  const int32_t *block_tables, int max_blocks, const int32_t *prefix_lens, const int32_t *seg,
-                                 int row_base, int n_seq, int max_len, int Hq, int Hkv, int hd, bf16_t *o, hipStream_t st) {
+                                 int row_base, int n_seq, int max_len, int Hq, int Hkv, int hd, bf16_t *o, hipStream_t st, bool o_frag) {
   if (n_seq <= 0 || max_len <= 0) return hipSuccess;
   if (n_seq > 65535 || max_len > 65535 * 64 || block_size <= 0 || (block_size & (block_size - 1)) || max_blocks <= 0) return hipErrorInvalidValue;
   int bshift = 0;
   while ((1 << bshift) < block_size) ++bshift;
   const PagedKV pg{(const bf16_t *)cache_k, (const bf16_t *)cache_v, block_tables, prefix_lens, num_blocks, max_blocks, bshift};
-  if (hd == 64) return launch_t<64, false, 4, true>(q, nullptr, nullptr, nullptr, nullptr, nullptr, seg, row_base, n_seq, max_len, Hq, Hkv, o, nullptr, nullptr, st, pg);
-  if (hd == 128) return launch_t<128, false, 4, true>(q, nullptr, nullptr, nullptr, nullptr, nullptr, seg, row_base, n_seq, max_len, Hq, Hkv, o, nullptr, nullptr, st, pg);
+  if (hd == 64) return launch_t<64, false, 4, true>(q, nullptr, nullptr, nullptr, nullptr, nullptr, seg, row_base, n_seq, max_len, Hq, Hkv, o, nullptr, nullptr, st, pg, nullptr, nullptr, o_frag);
+  if (hd == 128) return launch_t<128, false, 4, true>(q, nullptr, nullptr, nullptr, nullptr, nullptr, seg, row_base, n_seq, max_len, Hq, Hkv, o, nullptr, nullptr, st, pg, nullptr, nullptr, o_frag);
   return hipErrorInvalidValue;
 }

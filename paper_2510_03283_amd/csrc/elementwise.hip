@@ -26,7 +26,7 @@ __device__ __forceinline__ void st4_split(bf16_t *hi, bf16_t *lo, size_t i, cons
 // ------------------------------------------------------------------ RMSNorm forward
 template <bool XBF, bool GBF>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const void *x, const int32_t *row_idx, const void *g, int d,
-                                                          float eps, bf16_t *hi, bf16_t *lo, float *rstd) {
+                                                          float eps, bf16_t *hi, bf16_t *lo, float *rstd, int frag) {
   __shared__ float red[4];
   const int r = blockIdx.x;
   const size_t xin = (size_t)(row_idx ? row_idx[r] : r) * d, xo = (size_t)r * d;
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const void *x, const i
     ld4<GBF>(g, k, gg);
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = v[j] * rs * gg[j];
-    st4_split(hi, lo, xo + k, v);
+    st4_split(hi, lo, frag ? frag_index(r, k, d) : xo + k, v);
   }
 }
 
@@ -270,13 +270,13 @@ __global__ __launch_bounds__(256) void fill_f32_kernel(float *dst, size_t n, flo
 }  // namespace
 
 hipError_t launch_rmsnorm_fwd(const void *x, bool x_bf16, const int32_t *row_idx, const void *g, bool g_bf16, int rows,
-                              int d, float eps, bf16_t *hi, bf16_t *lo, float *rstd, hipStream_t st) {
+                              int d, float eps, bf16_t *hi, bf16_t *lo, float *rstd, hipStream_t st, bool frag) {
   if (rows <= 0) return hipSuccess;
   dim3 grid(rows), blk(256);
-  if (x_bf16 && g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<true, true>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd);
-  else if (!x_bf16 && g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<false, true>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd);
-  else if (!x_bf16 && !g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<false, false>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd);
-  else hipLaunchKernelGGL((rmsnorm_fwd_kernel<true, false>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd);
+  if (x_bf16 && g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<true, true>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd, frag ? 1 : 0);
+  else if (!x_bf16 && g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<false, true>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd, frag ? 1 : 0);
+  else if (!x_bf16 && !g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<false, false>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd, frag ? 1 : 0);
+  else hipLaunchKernelGGL((rmsnorm_fwd_kernel<true, false>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd, frag ? 1 : 0);
   return hipGetLastError();
 }
 

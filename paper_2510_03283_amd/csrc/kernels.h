@@ -9,7 +9,8 @@
 // input row row_idx[r] when row_idx is non-null), g is fp32 or bf16 [d].  rstd (nullable) gets
 // the row scale.
 hipError_t launch_rmsnorm_fwd(const void *x, bool x_bf16, const int32_t *row_idx, const void *g, bool g_bf16,
-                              int rows, int d, float eps, bf16_t *hi, bf16_t *lo, float *rstd, hipStream_t st);
+                              int rows, int d, float eps, bf16_t *hi, bf16_t *lo, float *rstd, hipStream_t st, bool frag = false);
+// frag: hi in fragment order (common.h), d % 32 == 0, no lo.
 // RMSNorm backward.  dx_out[out_row] = resid[r] + rstd*(dy*g) - x*rstd^3*mean((dy*g)*x), where
 // out_row = row_idx ? row_idx[r] : r and x is read at the same row; resid (nullable) fp32.
 // dg_partial [n_part, d] receives per-block partial sums of dy*x*rstd (reduce with
@@ -41,6 +42,41 @@ hipError_t launch_split_f32(const float *src, size_t n, bf16_t *hi, bf16_t *lo, 
 hipError_t launch_fill_f32(float *dst, size_t n, float v, hipStream_t st);
 // out[i] = sum_s part[s * n + i], n % 4 == 0 (partial sums of a split-K GEMM, fixed order).
 hipError_t launch_sum_partials(const float *part, int n_part, size_t n, float *out, hipStream_t st);
+
+// ---- gemm_skinny.hip --------------------------------------------------------------------------
+// C[m, n] = sum_k A[m, k] W[n, k] for at most SKINNY_MAX_ROWS rows, W bf16 [N, K] read once; see the file for the
+// forms.  K a multiple of 64, N of 16; weights below 4 GB.
+constexpr int SKINNY_MAX_ROWS = 64, SKINNY_NORM_ROWS = 16;
+// A: bf16 in fragment order (frag_index); or RMSNorm of row-major bf16 rows (gain bf16, eps), at most SKINNY_NORM_ROWS
+enum { SK_A_FRAG, SK_A_NORM_BF16 };
+enum { SK_E_F32, SK_E_SWIGLU, SK_E_QKV };
+struct SkinnyParams {
+  const void *a;            // activations
+  const bf16_t *gain;
+  float eps;
+  int M, N, K;
+  const bf16_t *w[3];       // F32: [N, K]; SWIGLU: gate and up, [N, K] each; QKV: Wq, Wk, Wv (N = (Hq + 2 Hkv) hd)
+  void *c;                  // F32: fp32 [M, N]; SWIGLU: silu(gate) * up as bf16 in fragment order
+  const void *resid;        // F32: added to c, same shape; resid_kind 0 none, 1 fp32, 2 bf16
+  int resid_kind;
+  // F32, for a product behind RMSNorm of c (all null otherwise): next_a = bf16(c * next_gain) in fragment order,
+  // ss_out[m][skinny_parts(N)] = partial sums of the squares of row m.  SWIGLU: ss_in [M][ss_n] such sums, a is the
+  // unscaled next_a (null: a is normalised)
+  void *next_a;
+  const bf16_t *next_gain;
+  float *ss_out;
+  const float *ss_in;
+  int ss_n;
+  // QKV: rotated q, k and plain v as bf16, k and v also into the paged cache (slots outside it are skipped)
+  int Hq, Hkv, hd, block_size;
+  const int32_t *positions, *slots;
+  const double *inv_freq;
+  bf16_t *q, *k, *v;
+  void *cache_k, *cache_v;
+  long long num_slots;
+};
+int skinny_parts(int N);
+hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t st);
 
 // ---- lora.hip ---------------------------------------------------------------------------------
 // dst[dst_rows, dst_cols] as bf16 (hi, nullable lo) = zeros with up to three source matrices
@@ -75,7 +111,8 @@ hipError_t launch_kv_gather(const void *cache_k, const void *cache_v, bool bf16,
 hipError_t launch_attn_fwd(const bf16_t *q_hi, const bf16_t *k_hi, const bf16_t *v_hi, const bf16_t *q_lo,
                            const bf16_t *k_lo, const bf16_t *v_lo, const int32_t *seg, int row_base, int n_seq,
                            int max_len, int Hq, int Hkv, int hd, bf16_t *o_hi, bf16_t *o_lo, float *lse,
-                           hipStream_t st, const int32_t *excl_lo = nullptr, const int32_t *excl_hi = nullptr);
+                           hipStream_t st, const int32_t *excl_lo = nullptr, const int32_t *excl_hi = nullptr, bool o_frag = false);
+// o_frag: o_hi in fragment order (common.h), row index = row in q.
 // excl_lo / excl_hi (nullable, device [n_seq], rows relative to the sequence start): queries at or
 // beyond excl_hi[s] do not see keys excl_lo[s] .. excl_hi[s]-1 (shared-prompt preference pairs).
 // The same for requests with a cached prefix: keys and values of request s are positions
@@ -83,7 +120,7 @@ hipError_t launch_attn_fwd(const bf16_t *q_hi, const bf16_t *k_hi, const bf16_t 
 // been appended already); query j of the request sits at position prefix_lens[s] + j.
 hipError_t launch_attn_fwd_paged(const bf16_t *q, const void *cache_k, const void *cache_v, long long num_blocks, int block_size,
                                  const int32_t *block_tables, int max_blocks, const int32_t *prefix_lens, const int32_t *seg,
-                                 int row_base, int n_seq, int max_len, int Hq, int Hkv, int hd, bf16_t *o, hipStream_t st);
+                                 int row_base, int n_seq, int max_len, int Hq, int Hkv, int hd, bf16_t *o, hipStream_t st, bool o_frag = false);
 // ---- attn_decode.hip -------------------------------------------------------------------------
 // One query row per request against its paged context of ctx_len[r]+1 tokens.  q bf16
 // [n_decode, Hq*hd] (rows of the decode class), out bf16 same shape.  partial: fp32 scratch of
@@ -92,7 +129,8 @@ size_t decode_partial_floats(int n_decode, int Hq, int Hkv, int hd, int max_cont
 hipError_t launch_attn_decode(const bf16_t *q, const void *cache_k, const void *cache_v, bool cache_bf16,
                               long long num_blocks, int block_size, const int32_t *block_tables, int max_blocks_per_req,
                               const int32_t *ctx_lens, int n_decode, int max_context, int Hq, int Hkv, int hd,
-                              float *partial, bf16_t *out, float *norms, hipStream_t st, int chunk_tokens = 0);
+                              float *partial, bf16_t *out, float *norms, hipStream_t st, int chunk_tokens = 0, int frag_row0 = -1);
+// frag_row0 >= 0: out is in fragment order (common.h) and request r is its row frag_row0 + r.
 // chunk_tokens: context tokens per block, 0 = chosen from the grid size, else a power of two in 512..4096.
 // Running mean of the head norms, prune predicate and last-used bookkeeping (elementwise, n x H).
 hipError_t launch_head_norm_stats(const float *norms, const int32_t *t_count, int n, int H, float *abar, int32_t *last_used,
