@@ -198,6 +198,22 @@ Saved plan_saved(const Dims &D, size_t Tf, Bump &s) {
   return S;
 }
 
+// Room for the partial results of products whose reduction is cut into slices (gemm_pick_splits).  One pool per stream
+// of a call: a partial result is read by the launch behind its product and gone.  What a product of these rows can ask
+// for, at most 256 MB.
+struct PartPool {
+  float *base;
+  size_t floats;
+};
+PartPool take_pool(Bump &w, size_t want) {
+  PartPool p;
+  p.floats = want < ((size_t)64 << 20) ? want : (size_t)64 << 20;
+  p.base = w.take<float>(p.floats);
+  return p;
+}
+size_t row_pool_floats(const Dims &D, size_t rows) { return rows * 8 * (size_t)std::max(D.nqkv, D.d); }
+size_t weight_pool_floats(const Dims &D) { return 4 * std::max((size_t)D.F, (size_t)D.nqkv) * D.d; }
+
 // ---------------------------------------------------------------- forward scratch
 struct FwdWs {
   // inference rows
@@ -206,6 +222,7 @@ struct FwdWs {
   // fine-tune rows
   float *qkv_f;
   bf16_t *a_lo, *q_lo, *k_lo, *v_lo, *o_lo, *b_lo, *hm_lo;
+  PartPool pool, side_pool;
 };
 FwdWs plan_fwd(const Dims &D, size_t Ti, size_t Tf, int n_decode, int max_ctx, int decode_chunk, Bump &w) {
   FwdWs F;
@@ -229,6 +246,8 @@ FwdWs plan_fwd(const Dims &D, size_t Ti, size_t Tf, int n_decode, int max_ctx, i
   F.o_lo = w.take<bf16_t>(Tf * D.qd);
   F.b_lo = w.take<bf16_t>(Tf * D.d);
   F.hm_lo = w.take<bf16_t>(Tf * D.F);
+  F.pool = take_pool(w, row_pool_floats(D, Ti + Tf));
+  F.side_pool = take_pool(w, (Ti + Tf) * 16 * 192);      // adapter products: 64 or 192 columns
   return F;
 }
 
@@ -237,6 +256,7 @@ struct BwdWs {
   bf16_t *dy_bf, *dhm, *dgu, *dx1_bf, *dattn, *dqkv;
   float *db, *dx1, *dvec, *da, *dg_part;
   float2 *cs;      // rotary (cos, sin) of every fine-tune row, [Tf, hd/2]
+  PartPool pool, side_pool;
 };
 BwdWs plan_bwd(const Dims &D, size_t Tf, Bump &w) {
   BwdWs B;
@@ -252,6 +272,8 @@ BwdWs plan_bwd(const Dims &D, size_t Tf, Bump &w) {
   B.dqkv = w.take<bf16_t>(Tf * D.nqkv);
   B.da = w.take<float>(Tf * D.d);
   B.dg_part = w.take<float>((size_t)(DG_PARTS + COLSUM_SLICES) * D.d);     // partial rows + scratch of their column sum
+  B.pool = take_pool(w, row_pool_floats(D, Tf));
+  B.side_pool = take_pool(w, std::max(weight_pool_floats(D), Tf * 16 * 192));
   return B;
 }
 
@@ -338,7 +360,8 @@ int prepare_lora(const Dims &D, const mace_lora_t *l, const LoraWs &L, float b_s
 struct DpoWs {
   int32_t *row_idx, *label, *seq_id, *partner, *vseq_off, *vprompt;   // the last three: shared-prompt layout only
   bf16_t *n_hi, *n_lo, *dl, *e_hi, *e_lo;
-  float *rstd, *logits, *logp_t, *lse, *dlogp, *dn, *dn_part, *dg_part;
+  float *rstd, *logits, *logp_t, *lse, *dlogp, *dn, *dg_part;
+  PartPool pool;
 };
 DpoWs plan_dpo(const Dims &D, size_t R, size_t n_seq, Bump &w) {
   DpoWs P;
@@ -357,7 +380,7 @@ DpoWs plan_dpo(const Dims &D, size_t R, size_t n_seq, Bump &w) {
   P.dlogp = w.take<float>(n_seq);
   P.dl = w.take<bf16_t>(R * D.V);
   P.dn = w.take<float>(R * D.d);
-  P.dn_part = w.take<float>(R * D.d * (size_t)(gemm_suggest_k_splits((int)R, D.d, D.V) > 1 ? gemm_suggest_k_splits((int)R, D.d, D.V) : 0));
+  P.pool = take_pool(w, R * 8 * (size_t)D.d);
   P.dg_part = w.take<float>((size_t)(DG_PARTS + COLSUM_SLICES) * D.d);
   if (!D.bf) {
     P.e_hi = w.take<bf16_t>((size_t)D.V * D.d);
@@ -395,7 +418,7 @@ int run_gemm(mace_ctx *h, int LA, int LB, GemmParams &p, hipStream_t st, const c
     snprintf(r.name, sizeof(r.name), "%s", where);
     r.layout = LA == 1 ? 2 : (LB == 1 ? 1 : 0);
     r.tile_m = p.tile_m; r.tile_n = p.tile_n;
-    r.k_splits = p.k_splits > 1 ? p.k_splits : 1;
+    r.k_splits = std::max(1, std::max(p.k_splits[0], std::max(p.k_splits[1], p.k_splits[2])));
     r.on_side_stream = h->side && st == h->side ? 1 : 0;
     for (int g = 0; g < p.n_mg; ++g) r.m += p.mg[g].M;
     for (int sg = 0; sg < p.n_ns; ++sg) r.n += p.ns[sg].N;
@@ -404,19 +427,54 @@ int run_gemm(mace_ctx *h, int LA, int LB, GemmParams &p, hipStream_t st, const c
   }
   return MACE_OK;
 }
+int max_splits(const int *ks) { return std::max(ks[0], std::max(ks[1], ks[2])); }
+// A product with its reduction cut into slices where that pays: `plain` is `base` with fp32 output, no residual and no fused
+// epilogue.  On true it has been issued and out[g] holds the partial results of row group g (plain's ldc); otherwise nothing
+// has been issued and the caller launches `base`.  extra_us: what the consumer of the parts costs beyond that of `base`.
+int run_gemm_parts(mace_ctx *h, int LA, int LB, const GemmParams &base, const GemmParams &plain, const PartPool &pool, double extra_us,
+                   hipStream_t st, const char *where, Parts out[3], bool &done) {
+  done = false;
+  GemmParams p = plain;
+  if (!pool.floats || !gemm_pick_splits(LA, LB, base, plain, pool.floats, extra_us, p.k_splits)) return MACE_OK;
+  p.resid_kind = 0;
+  size_t off = 0;
+  for (int g = 0; g < p.n_mg; ++g) {
+    const size_t n = (size_t)p.mg[g].M * p.ldc;
+    out[g] = Parts{pool.base + off, p.k_splits[g], n};
+    p.mg[g].c = pool.base + off;
+    p.mg[g].resid = nullptr;
+    p.mg[g].c_split_stride = (long long)n;
+    off += n * p.k_splits[g];
+  }
+  done = true;
+  return run_gemm(h, LA, LB, p, st, where);
+}
 // A weight-gradient GEMM ([M, N] out of K rows) that nothing later in the call depends on: issued on
 // the side stream (see mace_ctx) when the products of the main chain around it are small.  Those
 // have about (K / 256) x (min(M, N) / 256) output tiles; from two tiles per CU on they fill the chip
 // by themselves, and a second resident GEMM only splits the CUs and the L2 between two working
 // sets (measured: 2.5 - 3 % slower at 12 K and 64 K rows of a 7B-class layer, 2 % faster at 1.5 K
 // and 3.5 K rows).
-int run_gemm_side(mace_ctx *h, int LA, int LB, GemmParams &p, hipStream_t st, const char *where) {
+int run_gemm_side(mace_ctx *h, int LA, int LB, GemmParams &p, const PartPool &pool, hipStream_t st, const char *where) {
   long long M = 0, N = 0;
   for (int g = 0; g < p.n_mg; ++g) M += p.mg[g].M;
   for (int s = 0; s < p.n_ns; ++s) N += p.ns[s].N;
   const bool main_chain_small = (double)p.K * (double)std::min(M, N) < 2.0 * 256 * 65536.0;
   hipStream_t s2 = main_chain_small ? side_fork(h, st) : st;
-  const int rc = run_gemm(h, LA, LB, p, s2, where);
+  Parts part[3];
+  bool done = false;
+  GemmParams plain = p;
+  plain.resid_kind = 0;
+  int rc = run_gemm_parts(h, LA, LB, p, plain, pool, 5.0, s2, where, part, done);
+  if (done && rc == MACE_OK) {
+    SumRange r[3];
+    for (int g = 0; g < p.n_mg; ++g) r[g] = SumRange{part[g], p.resid_kind ? (const float *)p.mg[g].resid : nullptr, p.mg[g].c, part[g].stride};
+    prof_mark(h, s2, T_MISC);
+    const hipError_t e = launch_sum_parts(r, p.n_mg, false, s2);
+    if (e != hipSuccess) return hip_fail(e, where);
+  } else if (rc == MACE_OK) {
+    rc = run_gemm(h, LA, LB, p, s2, where);
+  }
   if (rc == MACE_OK && s2 != st) prof_mark(h, s2, -1);
   return rc;
 }
@@ -723,7 +781,8 @@ static int next_token_logits_impl(mace_handle_t h, const float *y, const int32_t
   }
   const bool skinny = n <= SKINNY_MAX_ROWS && D.bf && (long long)D.V * D.d < (1ll << 31);
   prof_mark(h, st, T_RMSNORM);
-  HIP_TRY(launch_rmsnorm_fwd(y, false, row_idx, g_final, D.bf, n, D.d, h->m.rms_eps, P.n_hi, nullptr, nullptr, st, skinny), "final rmsnorm");
+  const NormRows nr = {y, false, row_idx, {}, nullptr, P.n_hi, nullptr, nullptr, n, skinny};
+  HIP_TRY(launch_rmsnorm_fwd(&nr, 1, g_final, D.bf, D.d, h->m.rms_eps, st), "final rmsnorm");
   if (skinny) {
     SkinnyParams p;
     memset(&p, 0, sizeof(p));
@@ -906,7 +965,8 @@ static int layer_fwd_skinny(mace_handle_t h, const Dims &D, const BatchInfo &I, 
     p.a = x; p.gain = (const bf16_t *)w->g_attn;
     if (!fuse_norm) {
       prof_mark(h, st, T_RMSNORM);
-      HIP_TRY(launch_rmsnorm_fwd(x, true, nullptr, w->g_attn, true, I.Ti, D.d, h->m.rms_eps, F.a_i, nullptr, nullptr, st, true), "rmsnorm1");
+      const NormRows nr = {x, true, nullptr, {}, nullptr, F.a_i, nullptr, nullptr, I.Ti, true};
+      HIP_TRY(launch_rmsnorm_fwd(&nr, 1, w->g_attn, true, D.d, h->m.rms_eps, st), "rmsnorm1");
       p.a = F.a_i;
     }
     TRY(run_skinny(h, p, fuse_norm ? SK_A_NORM_BF16 : SK_A_FRAG, SK_E_QKV, rows2 * D.nqkv * D.d, st, "qkv gemm"));
@@ -930,6 +990,21 @@ static int layer_fwd_skinny(mace_handle_t h, const Dims &D, const BatchInfo &I, 
     TRY(run_skinny(h, p, SK_A_FRAG, SK_E_F32, rows2 * D.d * D.F, st, "down gemm"));
   }
   prof_mark(h, st, -1);
+  return MACE_OK;
+}
+
+// t = u A^T of the adapter variant: row group 0 the fine-tune rows, 1 the inference rows (either may be empty).
+static int run_adapter_product(mace_ctx *h, GemmParams &p, int Tf, int Ti, int cols, float *t, const PartPool &pool, hipStream_t st,
+                               const char *where, Parts &t_f, Parts &t_i) {
+  Parts part[3];
+  bool done;
+  TRY(run_gemm_parts(h, 0, 0, p, p, pool, 0.0, st, where, part, done));
+  t_i = Parts{t, 1, 0};
+  t_f = Parts{t + (size_t)Ti * cols, 1, 0};
+  if (!done) return run_gemm(h, 0, 0, p, st, where);
+  int g = 0;
+  if (Tf > 0) t_f = part[g++];
+  if (Ti > 0) t_i = part[g];
   return MACE_OK;
 }
 
@@ -990,11 +1065,13 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
   const char *xb = (const char *)x;
   const int resid_x = D.bf ? 2 : 1;
 
-  // 1. RMSNorm (attention)
+  // 1. RMSNorm (attention), both classes of rows in one launch
   prof_mark(h, st, T_RMSNORM);
-  HIP_TRY(launch_rmsnorm_fwd(x, D.bf, nullptr, w->g_attn, D.bf, I.Ti, D.d, h->m.rms_eps, F.a_i, nullptr, nullptr, st), "rmsnorm1");
-  prof_mark(h, st, T_RMSNORM);
-  HIP_TRY(launch_rmsnorm_fwd(xb + (size_t)I.Ti * D.d * es, D.bf, nullptr, w->g_attn, D.bf, I.Tf, D.d, h->m.rms_eps, S.a, F.a_lo, S.rstd1, st), "rmsnorm1 ft");
+  {
+    const NormRows nr[2] = {{x, D.bf, nullptr, {}, nullptr, F.a_i, nullptr, nullptr, I.Ti, false},
+                            {xb + (size_t)I.Ti * D.d * es, D.bf, nullptr, {}, nullptr, S.a, F.a_lo, S.rstd1, I.Tf, false}};
+    HIP_TRY(launch_rmsnorm_fwd(nr, 2, w->g_attn, D.bf, D.d, h->m.rms_eps, st), "rmsnorm1");
+  }
   // 2. QKV projection, all rows in one launch.  Adapter variant: t = a [A_q; A_k; A_v]^T is a skinny
   // product that runs beside the main one on the side stream; then qkv += (scale t) blockdiag(B)^T.
   if (lora) {
@@ -1003,16 +1080,18 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(p, S.a, F.a_lo, L.t_qkv + (size_t)I.Ti * 3 * LR, nullptr, I.Tf, np_ft);
     gp_group(p, F.a_i, nullptr, L.t_qkv, nullptr, I.Ti, 1);
     gp_seg(p, L.aqkv_hi, L.aqkv_lo, 3 * LR, 0);
-    TRY(run_gemm(h, 0, 0, p, s2, "lora t_qkv gemm"));
+    Parts t_i, t_f;
+    TRY(run_adapter_product(h, p, I.Tf, I.Ti, 3 * LR, L.t_qkv, F.side_pool, s2, "lora t_qkv gemm", t_f, t_i));
     prof_mark(h, s2, T_MISC);
-    HIP_TRY(launch_scale_split(L.t_qkv, (size_t)I.Ti * 3 * LR, lora->scale, L.tq_hi, nullptr, s2), "lora t_qkv split");
-    HIP_TRY(launch_scale_split(L.t_qkv + (size_t)I.Ti * 3 * LR, (size_t)I.Tf * 3 * LR, lora->scale, S.tq, L.tq_lo, s2), "lora t_qkv split ft");
+    HIP_TRY(launch_scale_split(t_i, (size_t)I.Ti * 3 * LR, lora->scale, L.tq_hi, nullptr, s2), "lora t_qkv split");
+    HIP_TRY(launch_scale_split(t_f, (size_t)I.Tf * 3 * LR, lora->scale, S.tq, L.tq_lo, s2), "lora t_qkv split ft");
     if (s2 != st) prof_mark(h, s2, -1);
   }
   // Where the product runs on the four-wave kernel (and no adapter correction has to be added to it first), the
   // rotary embedding and the operand split of the fine-tune rows happen in its epilogue: those rows of qkv never
   // exist in fp32, and their angle table takes the place of the fp32 buffer.
   bool rope_fused = false;
+  Parts qkv_i = {F.qkv_i, 1, 0}, qkv_f = {F.qkv_f, 1, 0};
   {
     GemmParams p = gp_init(D.d, D.d, D.d, D.nqkv);
     gp_group(p, S.a, F.a_lo, F.qkv_f, nullptr, I.Tf, np_ft);
@@ -1020,21 +1099,30 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_seg(p, W.hi[W_Q], W.lo[W_Q], D.qd, 0);
     gp_seg(p, W.hi[W_K], W.lo[W_K], D.kd, D.qd);
     gp_seg(p, W.hi[W_V], W.lo[W_V], D.kd, D.qd + D.kd);
+    GemmParams pr = p;
     if (!lora && D.hd == 128 && I.Tf > 0) {
-      GemmParams pr = p;
       pr.mg[0].rope = 1;
       pr.rope_cs = F.qkv_f;
       pr.ns[0].rope_hi = S.q; pr.ns[0].rope_lo = F.q_lo; pr.ns[0].rope_rot = 1;
       pr.ns[1].rope_hi = S.k; pr.ns[1].rope_lo = F.k_lo; pr.ns[1].rope_rot = 1;
       pr.ns[2].rope_hi = S.v; pr.ns[2].rope_lo = F.v_lo; pr.ns[2].rope_rot = 0;
-      if (gemm_uses_four_wave(0, 0, pr)) {
-        prof_mark(h, st, T_ROPE);
-        HIP_TRY(launch_rope_table(batch->positions + I.Ti, h->inv_freq, I.Tf, D.hd, (float2 *)F.qkv_f, st), "rope table");
-        TRY(run_gemm(h, 0, 0, pr, st, "qkv gemm + rope"));
-        rope_fused = true;
-      }
+      rope_fused = gemm_uses_four_wave(0, 0, pr);
     }
-    if (!rope_fused) TRY(run_gemm(h, 0, 0, p, st, "qkv gemm"));
+    Parts part[3];
+    bool done = false;
+    if (!lora) TRY(run_gemm_parts(h, 0, 0, rope_fused ? pr : p, p, F.pool, 0.0, st, "qkv gemm", part, done));
+    if (done) {
+      rope_fused = false;
+      int g = 0;
+      if (I.Tf > 0) qkv_f = part[g++];
+      if (I.Ti > 0) qkv_i = part[g];
+    } else if (rope_fused) {
+      prof_mark(h, st, T_ROPE);
+      HIP_TRY(launch_rope_table(batch->positions + I.Ti, h->inv_freq, I.Tf, D.hd, (float2 *)F.qkv_f, st), "rope table");
+      TRY(run_gemm(h, 0, 0, pr, st, "qkv gemm + rope"));
+    } else {
+      TRY(run_gemm(h, 0, 0, p, st, "qkv gemm"));
+    }
   }
   if (lora) {
     HIP_TRY(side_join(h, st), "join side stream");
@@ -1046,15 +1134,12 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     TRY(run_gemm(h, 0, 0, p2, st, "lora qkv gemm"));
   }
   // 3. RoPE, operand split, KV append of the inference rows
-  if (I.Ti > 0) {
+  if (I.Ti > 0 || !rope_fused) {
+    const RopeRows rr[2] = {{qkv_i, batch->positions, batch->slot_mapping, F.q_i, F.k_i, F.v_i, nullptr, nullptr, nullptr, I.Ti},
+                            {qkv_f, batch->positions + I.Ti, nullptr, S.q, S.k, S.v, F.q_lo, F.k_lo, F.v_lo, rope_fused ? 0 : I.Tf}};
     prof_mark(h, st, T_ROPE);
-    HIP_TRY(launch_rope_split(F.qkv_i, batch->positions, h->inv_freq, I.Ti, D.Hq, D.Hkv, D.hd, F.q_i, F.k_i, F.v_i, nullptr, nullptr, nullptr,
-                              batch->slot_mapping, cache->k, cache->v, D.bf, cache->num_blocks * cache->block_size, cache->block_size, st), "rope");
-  }
-  if (!rope_fused) {
-    prof_mark(h, st, T_ROPE);
-    HIP_TRY(launch_rope_split(F.qkv_f, batch->positions + I.Ti, h->inv_freq, I.Tf, D.Hq, D.Hkv, D.hd, S.q, S.k, S.v, F.q_lo, F.k_lo, F.v_lo,
-                              nullptr, nullptr, nullptr, D.bf, 0, 1, st), "rope ft");
+    HIP_TRY(launch_rope_split(rr, 2, h->inv_freq, D.Hq, D.Hkv, D.hd, I.Ti ? cache->k : nullptr, I.Ti ? cache->v : nullptr, D.bf,
+                              I.Ti ? cache->num_blocks * cache->block_size : 0, I.Ti ? cache->block_size : 1, st), "rope");
   }
   // 4. attention: prefill (causal), decode (paged), fine-tune (causal, split operands, LSE kept)
   TRY(inference_attention(h, D, I, batch, cache, F, st));
@@ -1067,19 +1152,31 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(p, S.o, F.o_lo, L.t_o + (size_t)I.Ti * LR, nullptr, I.Tf, np_ft);
     gp_group(p, F.o_i, nullptr, L.t_o, nullptr, I.Ti, 1);
     gp_seg(p, L.ao_hi, L.ao_lo, LR, 0);
-    TRY(run_gemm(h, 0, 0, p, s2, "lora t_o gemm"));
+    Parts t_i, t_f;
+    TRY(run_adapter_product(h, p, I.Tf, I.Ti, LR, L.t_o, F.side_pool, s2, "lora t_o gemm", t_f, t_i));
     prof_mark(h, s2, T_MISC);
-    HIP_TRY(launch_scale_split(L.t_o, (size_t)I.Ti * LR, lora->scale, L.to_hi, nullptr, s2), "lora t_o split");
-    HIP_TRY(launch_scale_split(L.t_o + (size_t)I.Ti * LR, (size_t)I.Tf * LR, lora->scale, S.to, L.to_lo, s2), "lora t_o split ft");
+    HIP_TRY(launch_scale_split(t_i, (size_t)I.Ti * LR, lora->scale, L.to_hi, nullptr, s2), "lora t_o split");
+    HIP_TRY(launch_scale_split(t_f, (size_t)I.Tf * LR, lora->scale, S.to, L.to_lo, s2), "lora t_o split ft");
     if (s2 != st) prof_mark(h, s2, -1);
   }
+  NormRows n2[2] = {{F.x1_i, false, nullptr, {}, nullptr, F.b_i, nullptr, nullptr, I.Ti, false},
+                    {S.x1, false, nullptr, {}, nullptr, S.b, F.b_lo, S.rstd2, I.Tf, false}};
   {
     GemmParams p = gp_init(D.qd, D.qd, D.qd, D.d);
     p.resid_kind = resid_x; p.ldr = D.d;
     gp_group(p, S.o, F.o_lo, S.x1, xb + (size_t)I.Ti * D.d * es, I.Tf, np_ft);
     gp_group(p, F.o_i, nullptr, F.x1_i, x, I.Ti, 1);
     gp_seg(p, W.hi[W_O], W.lo[W_O], D.d, 0);
-    TRY(run_gemm(h, 0, 0, p, st, "o gemm"));
+    Parts part[3];
+    bool done = false;
+    if (!lora) TRY(run_gemm_parts(h, 0, 0, p, p, F.pool, 0.0, st, "o gemm", part, done));
+    if (!done) {
+      TRY(run_gemm(h, 0, 0, p, st, "o gemm"));
+    } else {      // RMSNorm adds the slices and the residual
+      int g = 0;
+      if (I.Tf > 0) { n2[1].parts = part[g++]; n2[1].x = xb + (size_t)I.Ti * D.d * es; n2[1].x_bf16 = D.bf; n2[1].v_out = S.x1; }
+      if (I.Ti > 0) { n2[0].parts = part[g]; n2[0].x = x; n2[0].x_bf16 = D.bf; n2[0].v_out = F.x1_i; }
+    }
   }
   if (lora) {
     HIP_TRY(side_join(h, st), "join side stream");
@@ -1092,9 +1189,7 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
   }
   // 6. RMSNorm (MLP), gate/up projection, SwiGLU, down projection + residual
   prof_mark(h, st, T_RMSNORM);
-  HIP_TRY(launch_rmsnorm_fwd(F.x1_i, false, nullptr, w->g_mlp, D.bf, I.Ti, D.d, h->m.rms_eps, F.b_i, nullptr, nullptr, st), "rmsnorm2");
-  prof_mark(h, st, T_RMSNORM);
-  HIP_TRY(launch_rmsnorm_fwd(S.x1, false, nullptr, w->g_mlp, D.bf, I.Tf, D.d, h->m.rms_eps, S.b, F.b_lo, S.rstd2, st), "rmsnorm2 ft");
+  HIP_TRY(launch_rmsnorm_fwd(n2, 2, w->g_mlp, D.bf, D.d, h->m.rms_eps, st), "rmsnorm2");
   {
     // gate and up projections with SwiGLU in the epilogue: hm = silu(G) * U leaves the kernel as bf16
     // (two terms for the fine-tune rows, whose G and U are kept as bf16 for the backward pass)
@@ -1105,7 +1200,22 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(p, F.b_i, nullptr, F.hm_i, nullptr, I.Ti, 1);
     gp_seg(p, W.hi[W_G], W.lo[W_G], D.F, 0);
     gp_seg(p, W.hi[W_U], W.lo[W_U], D.F, D.F);
-    TRY(run_gemm(h, 0, 0, p, st, "gate/up gemm"));
+    GemmParams plain = p;
+    plain.swiglu = plain.out_bf16 = 0;
+    plain.ldc = 2 * D.F;
+    Parts part[3];
+    bool done;
+    TRY(run_gemm_parts(h, 0, 0, p, plain, F.pool, 5.0, st, "gate/up gemm", part, done));
+    if (!done) {
+      TRY(run_gemm(h, 0, 0, p, st, "gate/up gemm"));
+    } else {
+      SwigluRows sr[2] = {{{}, F.hm_i, nullptr, nullptr, 0}, {{}, S.hm, F.hm_lo, S.gu, 0}};
+      int g = 0;
+      if (I.Tf > 0) { sr[1].gu_in = part[g++]; sr[1].rows = I.Tf; }
+      if (I.Ti > 0) { sr[0].gu_in = part[g]; sr[0].rows = I.Ti; }
+      prof_mark(h, st, T_SWIGLU);
+      HIP_TRY(launch_swiglu_fwd(sr, 2, D.F, st), "swiglu");
+    }
   }
   {
     GemmParams p = gp_init(D.F, D.F, D.F, D.d);
@@ -1113,7 +1223,19 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(p, S.hm, F.hm_lo, y + (size_t)I.Ti * D.d, S.x1, I.Tf, np_ft);
     gp_group(p, F.hm_i, nullptr, y, F.x1_i, I.Ti, 1);
     gp_seg(p, W.hi[W_D], W.lo[W_D], D.d, 0);
-    TRY(run_gemm(h, 0, 0, p, st, "down gemm"));
+    Parts part[3];
+    bool done;
+    TRY(run_gemm_parts(h, 0, 0, p, p, F.pool, 5.0, st, "down gemm", part, done));
+    if (!done) {
+      TRY(run_gemm(h, 0, 0, p, st, "down gemm"));
+    } else {
+      SumRange sr[2] = {};
+      int g = 0;
+      if (I.Tf > 0) { sr[1] = SumRange{part[g], S.x1, y + (size_t)I.Ti * D.d, (size_t)I.Tf * D.d}; ++g; }
+      if (I.Ti > 0) sr[0] = SumRange{part[g], F.x1_i, y, (size_t)I.Ti * D.d};
+      prof_mark(h, st, T_MISC);
+      HIP_TRY(launch_sum_parts(sr, 2, false, st), "down partial sums");
+    }
   }
   prof_mark(h, st, -1);
   return MACE_OK;
@@ -1129,6 +1251,29 @@ int mace_hybrid_layer_fwd_lora(mace_handle_t h, const mace_layer_w_t *w, const m
                                size_t workspace_bytes, void *stream) {
   if (!lora) return fail(MACE_INVALID_ARG, "lora is null");
   return layer_fwd_impl(h, w, lora, batch, cache, x, y, saved, workspace, workspace_bytes, stream);
+}
+
+// A product with one row group and bf16 output, cut into slices where that pays (a second launch then adds and rounds).
+static int run_gemm_bf16_parts(mace_ctx *h, GemmParams &p, const PartPool &pool, hipStream_t st, const char *where) {
+  GemmParams plain = p;
+  plain.out_bf16 = 0;
+  Parts part[3];
+  bool done;
+  TRY(run_gemm_parts(h, 0, 1, p, plain, pool, 5.0, st, where, part, done));
+  if (!done) return run_gemm(h, 0, 1, p, st, where);
+  const SumRange sr = {part[0], nullptr, p.mg[0].c, part[0].stride};
+  prof_mark(h, st, T_MISC);
+  HIP_TRY(launch_sum_parts(&sr, 1, true, st), where);
+  return MACE_OK;
+}
+
+// A weight-gradient shaped adapter product (TN): the padded result, or its slices, for launch_extract.
+static int run_adapter_grad(mace_ctx *h, GemmParams &p, const PartPool &pool, hipStream_t st, const char *where, Parts &out) {
+  Parts part[3];
+  bool done;
+  TRY(run_gemm_parts(h, 1, 1, p, p, pool, 0.0, st, where, part, done));
+  out = done ? part[0] : Parts{(const float *)p.mg[0].c, 1, 0};
+  return done ? MACE_OK : run_gemm(h, 1, 1, p, st, where);
 }
 
 static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_lora_t *lora, const mace_batch_t *batch,
@@ -1182,16 +1327,22 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(pf, B.dy_bf, nullptr, B.dgu, nullptr, Tf, 1);
     pf.mg[0].c_gu = (void *)S.gu;
     gp_seg(pf, W.hi[W_D], nullptr, D.F, 0);
-    if (gemm_uses_four_wave(0, 1, pf)) {
+    GemmParams p = gp_init(D.d, D.d, D.F, D.F);
+    p.out_bf16 = 1;
+    gp_group(p, B.dy_bf, nullptr, B.dhm, nullptr, Tf, 1);
+    gp_seg(p, W.hi[W_D], nullptr, D.F, 0);
+    GemmParams plain = p;
+    plain.out_bf16 = 0;
+    const bool fused = gemm_uses_four_wave(0, 1, pf);
+    Parts part[3];
+    bool done;
+    TRY(run_gemm_parts(h, 0, 1, fused ? pf : p, plain, B.pool, fused ? 5.0 : 0.0, st, "dhm gemm", part, done));
+    if (!done && fused) {
       TRY(run_gemm(h, 0, 1, pf, st, "dhm gemm + swiglu bwd"));
     } else {
-      GemmParams p = gp_init(D.d, D.d, D.F, D.F);
-      p.out_bf16 = 1;
-      gp_group(p, B.dy_bf, nullptr, B.dhm, nullptr, Tf, 1);
-      gp_seg(p, W.hi[W_D], nullptr, D.F, 0);
-      TRY(run_gemm(h, 0, 1, p, st, "dhm gemm"));
+      if (!done) TRY(run_gemm(h, 0, 1, p, st, "dhm gemm"));
       prof_mark(h, st, T_SWIGLU);
-      HIP_TRY(launch_swiglu_bwd(B.dhm, S.gu, Tf, D.F, B.dgu, st), "swiglu bwd");
+      HIP_TRY(launch_swiglu_bwd(done ? nullptr : B.dhm, done ? part[0] : Parts{}, S.gu, Tf, D.F, B.dgu, st), "swiglu bwd");
     }
   }
   if (grads->w_down) {
@@ -1199,9 +1350,10 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     p.resid_kind = acc;
     gp_group(p, B.dy_bf, nullptr, grads->w_down, grads->w_down, D.d, 1);
     gp_seg(p, S.hm, nullptr, D.F, 0);
-    TRY(run_gemm_side(h, 1, 1, p, st, "dWd gemm"));
+    TRY(run_gemm_side(h, 1, 1, p, B.side_pool, st, "dWd gemm"));
   }
   // db = dG Wg + dU Wu ; dWg = dG^T b ; dWu = dU^T b
+  Parts db = {B.db, 1, 0};
   {
     // one product over the stacked reduction [dG | dU] x [Wg ; Wu]
     GemmParams p = gp_init(2 * D.F, 2 * D.F, D.d, D.d);
@@ -1210,7 +1362,11 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     p.n_kseg = 2;
     p.kseg_b[0] = W.hi[W_G]; p.kseg_b[1] = W.hi[W_U];
     p.kseg_start[0] = 0; p.kseg_start[1] = D.F; p.kseg_start[2] = 2 * D.F;
-    TRY(run_gemm(h, 0, 1, p, st, "db gemm"));
+    Parts part[3];
+    bool done;
+    TRY(run_gemm_parts(h, 0, 1, p, p, B.pool, 0.0, st, "db gemm", part, done));
+    if (done) db = part[0];
+    else TRY(run_gemm(h, 0, 1, p, st, "db gemm"));
   }
   if (grads->w_gate || grads->w_up) {
     GemmParams p = gp_init(Tf, 2 * D.F, D.d, D.d);
@@ -1218,11 +1374,11 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     if (grads->w_gate) gp_group(p, B.dgu, nullptr, grads->w_gate, grads->w_gate, D.F, 1);
     if (grads->w_up) gp_group(p, B.dgu + D.F, nullptr, grads->w_up, grads->w_up, D.F, 1);
     gp_seg(p, S.b, nullptr, D.d, 0);
-    TRY(run_gemm_side(h, 1, 1, p, st, "dWg/dWu gemm"));
+    TRY(run_gemm_side(h, 1, 1, p, B.side_pool, st, "dWg/dWu gemm"));
   }
   // RMSNorm (MLP) backward: dx1 = dy + ...
   prof_mark(h, st, T_RMSNORM);
-  HIP_TRY(launch_rmsnorm_bwd(B.db, S.x1, false, nullptr, w->g_mlp, D.bf, S.rstd2, dy_ft, Tf, D.d, B.dx1, B.dx1_bf, B.dg_part, n_part, st), "rmsnorm2 bwd");
+  HIP_TRY(launch_rmsnorm_bwd(db, S.x1, false, nullptr, w->g_mlp, D.bf, S.rstd2, dy_ft, Tf, D.d, B.dx1, B.dx1_bf, B.dg_part, n_part, st), "rmsnorm2 bwd");
   if (grads->g_mlp) { prof_mark(h, st, T_MISC); HIP_TRY(launch_colsum(B.dg_part, n_part, D.d, B.dg_part + (size_t)DG_PARTS * D.d, grads->g_mlp, acc, st), "dg2");
   }
   // attention output projection.  Adapter variant: dt = dx1 (s B_o) is a skinny product that runs
@@ -1233,7 +1389,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     p.out_bf16 = 1;
     gp_group(p, B.dx1_bf, nullptr, L.dto, nullptr, Tf, 1);
     gp_seg(p, L.bo_hi, nullptr, LR, 0);
-    TRY(run_gemm(h, 0, 1, p, s2, "lora dt_o gemm"));
+    TRY(run_gemm_bf16_parts(h, p, B.side_pool, s2, "lora dt_o gemm"));
     if (s2 != st) prof_mark(h, s2, -1);
   }
   {
@@ -1241,14 +1397,25 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     p.out_bf16 = 1;
     gp_group(p, B.dx1_bf, nullptr, B.dattn, nullptr, Tf, 1);
     gp_seg(p, W.hi[W_O], nullptr, D.qd, 0);
-    TRY(run_gemm(h, 0, 1, p, st, "dattn gemm"));
+    GemmParams plain = p;
+    plain.out_bf16 = 0;
+    Parts part[3];
+    bool done = false;
+    if (!lora) TRY(run_gemm_parts(h, 0, 1, p, plain, B.pool, 5.0, st, "dattn gemm", part, done));
+    if (!done) {
+      TRY(run_gemm(h, 0, 1, p, st, "dattn gemm"));
+    } else {
+      const SumRange sr = {part[0], nullptr, B.dattn, (size_t)Tf * D.qd};
+      prof_mark(h, st, T_MISC);
+      HIP_TRY(launch_sum_parts(&sr, 1, true, st), "dattn partial sums");
+    }
   }
   if (grads->wo) {
     GemmParams p = gp_init(Tf, D.d, D.qd, D.qd);
     p.resid_kind = acc;
     gp_group(p, B.dx1_bf, nullptr, grads->wo, grads->wo, D.d, 1);
     gp_seg(p, S.o, nullptr, D.qd, 0);
-    TRY(run_gemm_side(h, 1, 1, p, st, "dWo gemm"));
+    TRY(run_gemm_side(h, 1, 1, p, B.side_pool, st, "dWo gemm"));
   }
   if (lora) {
     HIP_TRY(side_join(h, st), "join side stream");
@@ -1264,9 +1431,10 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       GemmParams p = gp_init(Tf, D.d, LR, LR);
       gp_group(p, B.dx1_bf, nullptr, L.dbo, nullptr, D.d, 1);
       gp_seg(p, S.to, nullptr, LR, 0);
-      TRY(run_gemm(h, 1, 1, p, s2, "lora dB_o gemm"));
+      Parts gr;
+      TRY(run_adapter_grad(h, p, B.side_pool, s2, "lora dB_o gemm", gr));
       prof_mark(h, s2, T_MISC);
-      HIP_TRY(launch_extract(L.dbo, LR, 0, 0, D.d, lora->rank, 1.0f, lgrads->b_o, acc, s2), "lora dB_o");
+      HIP_TRY(launch_extract(gr, LR, 0, 0, D.d, lora->rank, 1.0f, lgrads->b_o, acc, s2), "lora dB_o");
       if (s2 != st) prof_mark(h, s2, -1);
     }
     if (lgrads->a_o) {
@@ -1274,9 +1442,10 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       GemmParams p = gp_init(Tf, LR, D.qd, D.qd);
       gp_group(p, L.dto, nullptr, L.dao, nullptr, LR, 1);
       gp_seg(p, S.o, nullptr, D.qd, 0);
-      TRY(run_gemm(h, 1, 1, p, s2, "lora dA_o gemm"));
+      Parts gr;
+      TRY(run_adapter_grad(h, p, B.side_pool, s2, "lora dA_o gemm", gr));
       prof_mark(h, s2, T_MISC);
-      HIP_TRY(launch_extract(L.dao, D.qd, 0, 0, lora->rank, D.qd, 1.0f, lgrads->a_o, acc, s2), "lora dA_o");
+      HIP_TRY(launch_extract(gr, D.qd, 0, 0, lora->rank, D.qd, 1.0f, lgrads->a_o, acc, s2), "lora dA_o");
       if (s2 != st) prof_mark(h, s2, -1);
     }
   }
@@ -1288,6 +1457,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
   HIP_TRY(launch_attn_bwd(S.q, S.k, S.v, S.o, B.dattn, S.lse, batch->seg_offsets + batch->n_prefill + batch->n_decode, I.Ti, batch->n_ft_seq, I.max_ft, Tf,
                           D.Hq, D.Hkv, D.hd, B.dvec, B.cs, B.dqkv, st, batch->ft_excl_lo, batch->ft_excl_hi), "attention bwd");
   // da = dq Wq + dk Wk + dv Wv ; dWq, dWk, dWv
+  Parts da = {B.da, 1, 0};
   {
     const bf16_t *as[3] = {B.dqkv, B.dqkv + D.qd, B.dqkv + D.qd + D.kd};
     const int ks[3] = {D.qd, D.kd, D.kd};
@@ -1299,7 +1469,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       p.out_bf16 = 1;
       gp_group(p, B.dqkv, nullptr, L.dtq, nullptr, Tf, 1);
       gp_seg(p, L.bblk_hi, nullptr, 3 * LR, 0);
-      TRY(run_gemm(h, 0, 1, p, s2, "lora dt_qkv gemm"));
+      TRY(run_gemm_bf16_parts(h, p, B.side_pool, s2, "lora dt_qkv gemm"));
       if (s2 != st) prof_mark(h, s2, -1);
     }
     {
@@ -1310,7 +1480,11 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       p.n_kseg = 3;
       for (int i = 0; i < 3; ++i) p.kseg_b[i] = W.hi[wi[i]];
       p.kseg_start[0] = 0; p.kseg_start[1] = ks[0]; p.kseg_start[2] = ks[0] + ks[1]; p.kseg_start[3] = ks[0] + ks[1] + ks[2];
-      TRY(run_gemm(h, 0, 1, p, st, "da gemm"));
+      Parts part[3];
+      bool done = false;
+      if (!lora) TRY(run_gemm_parts(h, 0, 1, p, p, B.pool, 0.0, st, "da gemm", part, done));
+      if (done) da = part[0];
+      else TRY(run_gemm(h, 0, 1, p, st, "da gemm"));
     }
     if (lora) {
       HIP_TRY(side_join(h, st), "join side stream");
@@ -1326,13 +1500,14 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
         GemmParams p = gp_init(Tf, D.nqkv, 3 * LR, 3 * LR);
         gp_group(p, B.dqkv, nullptr, L.dbblk, nullptr, D.nqkv, 1);
         gp_seg(p, S.tq, nullptr, 3 * LR, 0);
-        TRY(run_gemm(h, 1, 1, p, s2, "lora dB_qkv gemm"));
+        Parts gr;
+        TRY(run_adapter_grad(h, p, B.side_pool, s2, "lora dB_qkv gemm", gr));
         float *dst[3] = {lgrads->b_q, lgrads->b_k, lgrads->b_v};
         const int r0[3] = {0, D.qd, D.qd + D.kd}, nr[3] = {D.qd, D.kd, D.kd};
         for (int i = 0; i < 3; ++i)
           if (dst[i]) {
             prof_mark(h, s2, T_MISC);
-            HIP_TRY(launch_extract(L.dbblk, 3 * LR, r0[i], i * LR, nr[i], lora->rank, 1.0f, dst[i], acc, s2), "lora dB_qkv");
+            HIP_TRY(launch_extract(gr, 3 * LR, r0[i], i * LR, nr[i], lora->rank, 1.0f, dst[i], acc, s2), "lora dB_qkv");
           }
         if (s2 != st) prof_mark(h, s2, -1);
       }
@@ -1341,12 +1516,13 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
         GemmParams p = gp_init(Tf, 3 * LR, D.d, D.d);
         gp_group(p, L.dtq, nullptr, L.daqkv, nullptr, 3 * LR, 1);
         gp_seg(p, S.a, nullptr, D.d, 0);
-        TRY(run_gemm(h, 1, 1, p, s2, "lora dA_qkv gemm"));
+        Parts gr;
+        TRY(run_adapter_grad(h, p, B.side_pool, s2, "lora dA_qkv gemm", gr));
         float *dst[3] = {lgrads->a_q, lgrads->a_k, lgrads->a_v};
         for (int i = 0; i < 3; ++i)
           if (dst[i]) {
             prof_mark(h, s2, T_MISC);
-            HIP_TRY(launch_extract(L.daqkv, D.d, i * LR, 0, lora->rank, D.d, 1.0f, dst[i], acc, s2), "lora dA_qkv");
+            HIP_TRY(launch_extract(gr, D.d, i * LR, 0, lora->rank, D.d, 1.0f, dst[i], acc, s2), "lora dA_qkv");
           }
         if (s2 != st) prof_mark(h, s2, -1);
       }
@@ -1358,12 +1534,12 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       if (grads->wk) gp_group(p, as[1], nullptr, grads->wk, grads->wk, D.kd, 1);
       if (grads->wv) gp_group(p, as[2], nullptr, grads->wv, grads->wv, D.kd, 1);
       gp_seg(p, S.a, nullptr, D.d, 0);
-      TRY(run_gemm_side(h, 1, 1, p, st, "dWqkv gemm"));
+      TRY(run_gemm_side(h, 1, 1, p, B.side_pool, st, "dWqkv gemm"));
     }
   }
   // RMSNorm (attention) backward: dx = dx1 + ...
   prof_mark(h, st, T_RMSNORM);
-  HIP_TRY(launch_rmsnorm_bwd(B.da, (const char *)x + (size_t)I.Ti * D.d * es, D.bf, nullptr, w->g_attn, D.bf, S.rstd1, B.dx1, Tf, D.d, dx_ft, nullptr, B.dg_part, n_part, st), "rmsnorm1 bwd");
+  HIP_TRY(launch_rmsnorm_bwd(da, (const char *)x + (size_t)I.Ti * D.d * es, D.bf, nullptr, w->g_attn, D.bf, S.rstd1, B.dx1, Tf, D.d, dx_ft, nullptr, B.dg_part, n_part, st), "rmsnorm1 bwd");
   if (grads->g_attn) { prof_mark(h, st, T_MISC); HIP_TRY(launch_colsum(B.dg_part, n_part, D.d, B.dg_part + (size_t)DG_PARTS * D.d, grads->g_attn, acc, st), "dg1");
   }
   prof_mark(h, st, -1);
@@ -1451,7 +1627,8 @@ static int dpo_impl(mace_handle_t h, const float *h_ft, const void *g_final, con
     else
       HIP_TRY(launch_loss_rows(ft_seq_offsets, prompt_lens, token_ids, n_seq, P.row_idx, P.label, P.seq_id, st), "loss rows");
     prof_mark(h, st, T_RMSNORM);
-    HIP_TRY(launch_rmsnorm_fwd(h_ft, false, P.row_idx, g_final, D.bf, Ri, D.d, h->m.rms_eps, P.n_hi, P.n_lo, P.rstd, st), "final rmsnorm");
+    const NormRows nr = {h_ft, false, P.row_idx, {}, nullptr, P.n_hi, P.n_lo, P.rstd, Ri, false};
+    HIP_TRY(launch_rmsnorm_fwd(&nr, 1, g_final, D.bf, D.d, h->m.rms_eps, st), "final rmsnorm");
     GemmParams p = gp_init(D.d, D.d, D.d, D.V);
     gp_group(p, P.n_hi, P.n_lo, P.logits, nullptr, Ri, one_pass ? 1 : (D.bf ? 2 : 3));
     gp_seg(p, e_hi, e_lo, D.V, 0);
@@ -1460,14 +1637,20 @@ static int dpo_impl(mace_handle_t h, const float *h_ft, const void *g_final, con
     prof_mark(h, st, T_LOGSOFTMAX, 0.0, (double)Ri * D.V * (want_grad ? 6.0 : 4.0));
     HIP_TRY(launch_logsoftmax_dl(P.logits, Ri, D.V, P.label, P.logp_t, P.lse, want_grad ? P.dl : nullptr, st), "log-softmax");
     if (need_u) {
-      // u = dl E: small output, reduction over the whole vocabulary: slice k so that every CU has work
-      const int ks = gemm_suggest_k_splits(Ri, D.d, D.V);
+      // u = dl E: small output, reduction over the whole vocabulary
       GemmParams q = gp_init(D.V, D.V, D.d, D.d);
-      gp_group(q, P.dl, nullptr, ks > 1 ? P.dn_part : P.dn, nullptr, Ri, 1);
+      gp_group(q, P.dl, nullptr, P.dn, nullptr, Ri, 1);
       gp_seg(q, e_hi, nullptr, D.d, 0);
-      if (ks > 1) { q.k_splits = ks; q.c_split_stride = (long long)Ri * D.d; }
-      TRY(run_gemm(h, 0, 1, q, st, "dn gemm"));
-      if (ks > 1) { prof_mark(h, st, T_MISC); HIP_TRY(launch_sum_partials(P.dn_part, ks, (size_t)Ri * D.d, P.dn, st), "dn partial sums"); }
+      Parts part[3];
+      bool done;
+      TRY(run_gemm_parts(h, 0, 1, q, q, P.pool, 5.0, st, "dn gemm", part, done));
+      if (!done) {
+        TRY(run_gemm(h, 0, 1, q, st, "dn gemm"));
+      } else {
+        const SumRange sr = {part[0], nullptr, P.dn, (size_t)Ri * D.d};
+        prof_mark(h, st, T_MISC);
+        HIP_TRY(launch_sum_parts(&sr, 1, false, st), "dn partial sums");
+      }
       if (one_pass) { prof_mark(h, st, T_MISC); HIP_TRY(launch_logp_correct(P.n_lo, P.dn, Ri, D.d, P.logp_t, st), "log-probability correction"); }
     }
   }
@@ -1495,7 +1678,7 @@ static int dpo_impl(mace_handle_t h, const float *h_ft, const void *g_final, con
     p.resid_kind = acc;
     gp_group(p, P.dl, nullptr, dw_lm, dw_lm, D.V, 1);
     gp_seg(p, n_c, nullptr, D.d, 0);
-    TRY(run_gemm_side(h, 1, 1, p, st, "dE gemm"));
+    TRY(run_gemm_side(h, 1, 1, p, PartPool{}, st, "dE gemm"));
   }
   if (dh_ft || dg_final) {
     const int n_part = Ri < DG_PARTS ? Ri : DG_PARTS;
@@ -1505,11 +1688,11 @@ static int dpo_impl(mace_handle_t h, const float *h_ft, const void *g_final, con
     if (shared) {
       // two loss rows of a pair (the first token of either response) land on the same stored row: norm backward
       // in place on the dense rows, then a scatter that adds the two
-      HIP_TRY(launch_rmsnorm_bwd(P.dn, h_ft, false, P.row_idx, g_final, D.bf, P.rstd, nullptr, Ri, D.d, P.dn, nullptr, P.dg_part, n_part, st, 1), "final rmsnorm bwd");
+      HIP_TRY(launch_rmsnorm_bwd(Parts{P.dn, 1, 0}, h_ft, false, P.row_idx, g_final, D.bf, P.rstd, nullptr, Ri, D.d, P.dn, nullptr, P.dg_part, n_part, st, 1), "final rmsnorm bwd");
       if (dh_ft) { prof_mark(h, st, T_MISC); HIP_TRY(launch_scatter_rows(P.dn, P.row_idx, P.partner, Ri, D.d, dh_ft, st), "scatter dh");
       }
     } else
-    HIP_TRY(launch_rmsnorm_bwd(P.dn, h_ft, false, P.row_idx, g_final, D.bf, P.rstd, nullptr, Ri, D.d, dx_dst, nullptr, P.dg_part, n_part, st), "final rmsnorm bwd");
+    HIP_TRY(launch_rmsnorm_bwd(Parts{P.dn, 1, 0}, h_ft, false, P.row_idx, g_final, D.bf, P.rstd, nullptr, Ri, D.d, dx_dst, nullptr, P.dg_part, n_part, st), "final rmsnorm bwd");
     if (dg_final) { prof_mark(h, st, T_MISC); HIP_TRY(launch_colsum(P.dg_part, n_part, D.d, P.dg_part + (size_t)DG_PARTS * D.d, dg_final, acc, st), "dg_final");
     }
   }

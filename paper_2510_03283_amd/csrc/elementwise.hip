@@ -23,29 +23,56 @@ __device__ __forceinline__ void st4_split(bf16_t *hi, bf16_t *lo, size_t i, cons
   if (lo) *(uint2 *)(lo + i) = make_uint2(pack2(l[0], l[1]), pack2(l[2], l[3]));
 }
 
+__device__ __forceinline__ float4 ld4_parts(const Parts &s, size_t i) {
+  float4 v = *(const float4 *)(s.p + i);
+  for (int k = 1; k < s.n; ++k) {
+    const float4 w = *(const float4 *)(s.p + (size_t)k * s.stride + i);
+    v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+  }
+  return v;
+}
+
 // ------------------------------------------------------------------ RMSNorm forward
-template <bool XBF, bool GBF>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const void *x, const int32_t *row_idx, const void *g, int d,
-                                                          float eps, bf16_t *hi, bf16_t *lo, float *rstd, int frag) {
+// One block per row; NV float4 chunks per thread (d <= 1024 NV) stay in registers between the reduction and the output.
+template <int NV>
+__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const NormRows g0, const NormRows g1, const void *gain, int g_bf16, int d, float eps) {
   __shared__ float red[4];
-  const int r = blockIdx.x;
-  const size_t xin = (size_t)(row_idx ? row_idx[r] : r) * d, xo = (size_t)r * d;
+  const bool second = (int)blockIdx.x >= g0.rows;
+  const NormRows &G = second ? g1 : g0;
+  const int r = second ? (int)blockIdx.x - g0.rows : (int)blockIdx.x;
+  const size_t xin = (size_t)(G.row_idx ? G.row_idx[r] : r) * d, xo = (size_t)r * d;
+  float v[NV][4];
   float ss = 0.f;
-  for (int k = 4 * threadIdx.x; k < d; k += 1024) {
-    float v[4];
-    ld4<XBF>(x, xin + k, v);
-    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int k = 4 * threadIdx.x + 1024 * i;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[i][j] = 0.f;
+    if (k < d) {
+      if (G.x_bf16) ld4<true>(G.x, xin + k, v[i]);
+      else ld4<false>(G.x, xin + k, v[i]);
+      if (G.parts.p) {
+        const float4 s = ld4_parts(G.parts, xo + k);
+        v[i][0] = s.x + v[i][0]; v[i][1] = s.y + v[i][1]; v[i][2] = s.z + v[i][2]; v[i][3] = s.w + v[i][3];
+        *(float4 *)(G.v_out + xo + k) = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
+      }
+      ss += v[i][0] * v[i][0] + v[i][1] * v[i][1] + v[i][2] * v[i][2] + v[i][3] * v[i][3];
+    }
   }
   ss = block_sum<256>(ss, red);
   const float rs = 1.0f / sqrtf(ss / (float)d + eps);
-  if (rstd && threadIdx.x == 0) rstd[r] = rs;
-  for (int k = 4 * threadIdx.x; k < d; k += 1024) {
-    float v[4], gg[4];
-    ld4<XBF>(x, xin + k, v);
-    ld4<GBF>(g, k, gg);
+  if (G.rstd && threadIdx.x == 0) G.rstd[r] = rs;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = v[j] * rs * gg[j];
-    st4_split(hi, lo, frag ? frag_index(r, k, d) : xo + k, v);
+  for (int i = 0; i < NV; ++i) {
+    const int k = 4 * threadIdx.x + 1024 * i;
+    if (k < d) {
+      float gg[4];
+      if (g_bf16) ld4<true>(gain, k, gg);
+      else ld4<false>(gain, k, gg);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[i][j] = v[i][j] * rs * gg[j];
+      st4_split(G.hi, G.lo, G.frag ? frag_index(r, k, d) : xo + k, v[i]);
+    }
   }
 }
 
@@ -55,7 +82,7 @@ constexpr int RB_MAXV = 8;   // d <= 8192
 // chunks per thread (d <= 1024 NV): the row of dy and of x stays in registers between the reduction
 // and the output pass, and g is read once per block.
 template <bool XBF, bool GBF, int NV>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const float *dy, const void *x, const int32_t *row_idx,
+__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const Parts dy, const void *x, const int32_t *row_idx,
                                                           const void *g, const float *rstd, const float *resid,
                                                           int rows, int d, float *dx_out, bf16_t *dx_bf,
                                                           float *dg_partial, int dense_out) {
@@ -77,7 +104,8 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const float *dy, const
 #pragma unroll
       for (int j = 0; j < 4; ++j) dv[i][j] = xv[i][j] = rr[i][j] = 0.f;
       if (k < d) {
-        ld4<false>(dy, yr + k, dv[i]);
+        const float4 t = ld4_parts(dy, yr + k);
+        dv[i][0] = t.x; dv[i][1] = t.y; dv[i][2] = t.z; dv[i][3] = t.w;
         ld4<XBF>(x, xr + k, xv[i]);
         if (resid) ld4<false>(resid, yr + k, rr[i]);
       }
@@ -134,70 +162,70 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float *part, int n_pa
 }
 
 // ------------------------------------------------------------------ rotary embedding
-// cs[i] = (cos, sin) of pos * inv_freq[i]; the angle is formed and reduced in fp64.
-__device__ __forceinline__ void rope_table(float2 *cs, int pos, const double *inv_freq, int half) {
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    double s, c;
-    sincos((double)pos * inv_freq[i], &s, &c);
-    cs[i] = make_float2((float)c, (float)s);
-  }
-  __syncthreads();
-}
-
+// One block per row.  A thread takes four neighbouring elements i .. i + 3 of a head and their partners i + hd/2 ..;
+// the row's (cos, sin) table is formed once in LDS.
 template <bool CBF>
-__global__ __launch_bounds__(256) void rope_split_kernel(const float *qkv, const int32_t *positions,
-                                                         const double *inv_freq, int Hq, int Hkv, int hd, bf16_t *q_hi,
-                                                         bf16_t *k_hi, bf16_t *v_hi, bf16_t *q_lo, bf16_t *k_lo,
-                                                         bf16_t *v_lo, const int32_t *slot_mapping, void *cache_k,
-                                                         void *cache_v, long long num_slots, int block_size) {
+__global__ __launch_bounds__(256) void rope_split_kernel(const RopeRows g0, const RopeRows g1, const double *inv_freq, int Hq, int Hkv, int hd,
+                                                         void *cache_k, void *cache_v, long long num_slots, int block_size) {
   __shared__ float2 cs[64];
-  const int r = blockIdx.x, half = hd >> 1;
-  rope_table(cs, positions[r], inv_freq, half);
+  const bool second = (int)blockIdx.x >= g0.rows;
+  const RopeRows &G = second ? g1 : g0;
+  const int r = second ? (int)blockIdx.x - g0.rows : (int)blockIdx.x, half = hd >> 1;
+  if ((int)threadIdx.x < half) cs[threadIdx.x] = rope_angle((double)G.positions[r] * inv_freq[threadIdx.x]);
+  __syncthreads();
   const int qd = Hq * hd, kd = Hkv * hd, nq = qd + 2 * kd;
-  const float *in = qkv + (size_t)r * nq;
+  const size_t in = (size_t)r * nq;
   long long slot = -1;
-  if (slot_mapping) {
-    slot = slot_mapping[r];
+  if (G.slot_mapping) {
+    slot = G.slot_mapping[r];
     if (slot >= num_slots) slot = -1;
   }
   const long long cbase = slot >= 0 ? (slot / block_size) * (long long)Hkv * block_size * hd + (slot % block_size) * (long long)hd : 0;
-  const int npair = (Hq + Hkv) * half;
-  for (int idx = threadIdx.x; idx < npair; idx += 256) {
-    const int head = idx / half, i = idx - head * half;
-    const float a = in[head * hd + i], b = in[head * hd + i + half];
-    const float2 t = cs[i];
-    const float ra = a * t.x - b * t.y, rb = b * t.x + a * t.y;
-    bf16_t ha, la, hb, lb;
-    split_bf(ra, ha, la);
-    split_bf(rb, hb, lb);
+  // four elements e .. e + 3 of kv head kh to the cache
+  auto to_cache = [&](void *cache, int kh, int e, const float *v, uint2 w) {
+    const long long c = cbase + (long long)kh * block_size * hd + e;
+    if constexpr (CBF) *(uint2 *)((bf16_t *)cache + c) = w;
+    else *(float4 *)((float *)cache + c) = make_float4(v[0], v[1], v[2], v[3]);
+  };
+  auto put = [&](bf16_t *hi, bf16_t *lo, size_t o, const float *v) -> uint2 {
+    uint32_t h0, l0, h1, l1;
+    split_pk_bf16(v[0], v[1], h0, l0);
+    split_pk_bf16(v[2], v[3], h1, l1);
+    *(uint2 *)(hi + o) = make_uint2(h0, h1);
+    if (lo) *(uint2 *)(lo + o) = make_uint2(l0, l1);
+    return make_uint2(h0, h1);
+  };
+  const int qpr = half >> 2;                             // quads of pairs per head
+  for (int idx = threadIdx.x; idx < (Hq + Hkv) * qpr; idx += 256) {
+    const int head = idx / qpr, i = (idx - head * qpr) * 4;
+    const float4 a = ld4_parts(G.qkv, in + head * hd + i), b = ld4_parts(G.qkv, in + head * hd + i + half);
+    const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+    float ra[4], rb[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float2 t = cs[i + e];
+      ra[e] = av[e] * t.x - bv[e] * t.y;
+      rb[e] = bv[e] * t.x + av[e] * t.y;
+    }
     if (head < Hq) {
       const size_t o = (size_t)r * qd + head * hd + i;
-      q_hi[o] = ha; q_hi[o + half] = hb;
-      if (q_lo) { q_lo[o] = la; q_lo[o + half] = lb; }
+      put(G.q_hi, G.q_lo, o, ra);
+      put(G.q_hi, G.q_lo, o + half, rb);
     } else {
       const int kh = head - Hq;
       const size_t o = (size_t)r * kd + kh * hd + i;
-      k_hi[o] = ha; k_hi[o + half] = hb;
-      if (k_lo) { k_lo[o] = la; k_lo[o + half] = lb; }
+      const uint2 wa = put(G.k_hi, G.k_lo, o, ra), wb = put(G.k_hi, G.k_lo, o + half, rb);
       if (slot >= 0) {
-        const long long c = cbase + (long long)kh * block_size * hd + i;
-        if constexpr (CBF) { ((bf16_t *)cache_k)[c] = ha; ((bf16_t *)cache_k)[c + half] = hb; }
-        else { ((float *)cache_k)[c] = ra; ((float *)cache_k)[c + half] = rb; }
+        to_cache(cache_k, kh, i, ra, wa);
+        to_cache(cache_k, kh, i + half, rb, wb);
       }
     }
   }
-  for (int idx = threadIdx.x; idx < kd; idx += 256) {
-    const float v = in[qd + kd + idx];
-    bf16_t h, l;
-    split_bf(v, h, l);
-    v_hi[(size_t)r * kd + idx] = h;
-    if (v_lo) v_lo[(size_t)r * kd + idx] = l;
-    if (slot >= 0) {
-      const int kh = idx / hd, e = idx - kh * hd;
-      const long long c = cbase + (long long)kh * block_size * hd + e;
-      if constexpr (CBF) ((bf16_t *)cache_v)[c] = h;
-      else ((float *)cache_v)[c] = v;
-    }
+  for (int idx = 4 * threadIdx.x; idx < kd; idx += 1024) {
+    const float4 v4 = ld4_parts(G.qkv, in + qd + kd + idx);
+    const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+    const uint2 w = put(G.v_hi, G.v_lo, (size_t)r * kd + idx, v);
+    if (slot >= 0) to_cache(cache_v, idx / hd, idx % hd, v, w);
   }
 }
 
@@ -205,21 +233,28 @@ __global__ __launch_bounds__(64) void rope_table_kernel(const int32_t *__restric
                                                         int half, float2 *__restrict__ cs) {
   const int r = blockIdx.x, i = threadIdx.x;
   if (i >= half) return;
-  double sn, c;
-  sincos((double)positions[r] * inv_freq[i], &sn, &c);
-  cs[(size_t)r * half + i] = make_float2((float)c, (float)sn);
+  cs[(size_t)r * half + i] = rope_angle((double)positions[r] * inv_freq[i]);
 }
 
 // ------------------------------------------------------------------ SwiGLU
 // 8 hidden units per thread (16-byte accesses); F % 8 == 0.
-__global__ __launch_bounds__(256) void swiglu_bwd_kernel(const bf16_t *__restrict__ dhm, const bf16_t *__restrict__ gu, int F,
+__global__ __launch_bounds__(256) void swiglu_bwd_kernel(const bf16_t *__restrict__ dhm, const Parts parts, const bf16_t *__restrict__ gu, int F,
                                                          bf16_t *__restrict__ dgu) {
   const int r = blockIdx.x;
   const int k = 8 * (blockIdx.y * 256 + threadIdx.x);
   if (k >= F) return;
   const uint4 gq = *(const uint4 *)(gu + (size_t)r * 2 * F + k), uq = *(const uint4 *)(gu + (size_t)r * 2 * F + F + k);
-  const uint4 dq = *(const uint4 *)(dhm + (size_t)r * F + k);
-  const uint32_t gw[4] = {gq.x, gq.y, gq.z, gq.w}, uw[4] = {uq.x, uq.y, uq.z, uq.w}, dw[4] = {dq.x, dq.y, dq.z, dq.w};
+  float dv[8];
+  if (dhm) {
+    const uint4 dq = *(const uint4 *)(dhm + (size_t)r * F + k);
+    const uint32_t dw[4] = {dq.x, dq.y, dq.z, dq.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { dv[2 * j] = __uint_as_float(dw[j] << 16); dv[2 * j + 1] = __uint_as_float(dw[j] & 0xffff0000u); }
+  } else {
+    const float4 a = ld4_parts(parts, (size_t)r * F + k), b = ld4_parts(parts, (size_t)r * F + k + 4);
+    dv[0] = a.x; dv[1] = a.y; dv[2] = a.z; dv[3] = a.w; dv[4] = b.x; dv[5] = b.y; dv[6] = b.z; dv[7] = b.w;
+  }
+  const uint32_t gw[4] = {gq.x, gq.y, gq.z, gq.w}, uw[4] = {uq.x, uq.y, uq.z, uq.w};
   uint32_t og[4], ou[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -228,7 +263,7 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const bf16_t *__restric
     for (int e = 0; e < 2; ++e) {
       const float g = e ? __uint_as_float(gw[j] & 0xffff0000u) : __uint_as_float(gw[j] << 16);
       const float u = e ? __uint_as_float(uw[j] & 0xffff0000u) : __uint_as_float(uw[j] << 16);
-      const float dh = e ? __uint_as_float(dw[j] & 0xffff0000u) : __uint_as_float(dw[j] << 16);
+      const float dh = dv[2 * j + e];
       const float sg = 1.0f / (1.0f + expf(-g));
       du[e] = dh * g * sg;
       dg[e] = dh * u * sg * (1.0f + g * (1.0f - sg));
@@ -250,15 +285,39 @@ __global__ __launch_bounds__(256) void split_f32_kernel(const float *src, size_t
   }
 }
 
-__global__ __launch_bounds__(256) void sum_partials_kernel(const float *part, int n_part, size_t n, float *out) {
-  const size_t stride = (size_t)gridDim.x * 256 * 4;
-  for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += stride) {   // n % 4 == 0
-    float4 a = *(const float4 *)(part + i);
-    for (int s = 1; s < n_part; ++s) {
-      const float4 b = *(const float4 *)(part + (size_t)s * n + i);
+// G and U of four hidden units per thread.
+__global__ __launch_bounds__(256) void swiglu_fwd_kernel(const SwigluRows g0, const SwigluRows g1, int F) {
+  const bool second = (int)blockIdx.x >= g0.rows;
+  const SwigluRows &G = second ? g1 : g0;
+  const size_t r = second ? blockIdx.x - g0.rows : blockIdx.x;
+  const int k = 4 * (blockIdx.y * 256 + threadIdx.x);
+  if (k >= F) return;
+  const float4 g4 = ld4_parts(G.gu_in, r * 2 * F + k), u4 = ld4_parts(G.gu_in, r * 2 * F + F + k);
+  const float g[4] = {g4.x, g4.y, g4.z, g4.w}, u[4] = {u4.x, u4.y, u4.z, u4.w};
+  float h[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) h[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
+  st4_split(G.hi, G.lo, r * F + k, h);
+  if (G.gu) {
+    *(uint2 *)(G.gu + r * 2 * F + k) = make_uint2(cvt_pk_bf16(g[0], g[1]), cvt_pk_bf16(g[2], g[3]));
+    *(uint2 *)(G.gu + r * 2 * F + F + k) = make_uint2(cvt_pk_bf16(u[0], u[1]), cvt_pk_bf16(u[2], u[3]));
+  }
+}
+
+template <bool OBF>
+__global__ __launch_bounds__(256) void sum_parts_kernel(const SumRange s0, const SumRange s1, const SumRange s2) {
+  const size_t n = s0.n + s1.n + s2.n, stride = (size_t)gridDim.x * 1024;
+  for (size_t t = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; t < n; t += stride) {      // all lengths multiples of 4
+    const int w = t < s0.n ? 0 : (t < s0.n + s1.n ? 1 : 2);
+    const SumRange &S = w == 0 ? s0 : (w == 1 ? s1 : s2);
+    const size_t i = t - (w == 0 ? 0 : (w == 1 ? s0.n : s0.n + s1.n));
+    float4 a = ld4_parts(S.parts, i);
+    if (S.resid) {
+      const float4 b = *(const float4 *)(S.resid + i);
       a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
     }
-    *(float4 *)(out + i) = a;
+    if constexpr (OBF) *(uint2 *)((bf16_t *)S.out + i) = make_uint2(cvt_pk_bf16(a.x, a.y), cvt_pk_bf16(a.z, a.w));
+    else *(float4 *)((float *)S.out + i) = a;
   }
 }
 
@@ -269,19 +328,23 @@ __global__ __launch_bounds__(256) void fill_f32_kernel(float *dst, size_t n, flo
 
 }  // namespace
 
-hipError_t launch_rmsnorm_fwd(const void *x, bool x_bf16, const int32_t *row_idx, const void *g, bool g_bf16, int rows,
-                              int d, float eps, bf16_t *hi, bf16_t *lo, float *rstd, hipStream_t st, bool frag) {
-  if (rows <= 0) return hipSuccess;
-  dim3 grid(rows), blk(256);
-  if (x_bf16 && g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<true, true>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd, frag ? 1 : 0);
-  else if (!x_bf16 && g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<false, true>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd, frag ? 1 : 0);
-  else if (!x_bf16 && !g_bf16) hipLaunchKernelGGL((rmsnorm_fwd_kernel<false, false>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd, frag ? 1 : 0);
-  else hipLaunchKernelGGL((rmsnorm_fwd_kernel<true, false>), grid, blk, 0, st, x, row_idx, g, d, eps, hi, lo, rstd, frag ? 1 : 0);
+hipError_t launch_rmsnorm_fwd(const NormRows *groups, int n_groups, const void *g, bool g_bf16, int d, float eps, hipStream_t st) {
+  if (n_groups < 1 || n_groups > 2 || d > 8192) return hipErrorInvalidValue;
+  NormRows g0 = groups[0], g1 = {};
+  if (n_groups > 1) g1 = groups[1];
+  if (g0.rows < 0 || g1.rows < 0) return hipErrorInvalidValue;
+  if (g0.rows + g1.rows == 0) return hipSuccess;
+  const dim3 grid(g0.rows + g1.rows), blk(256);
+  const int gb = g_bf16 ? 1 : 0;
+  if (d <= 1024) hipLaunchKernelGGL(rmsnorm_fwd_kernel<1>, grid, blk, 0, st, g0, g1, g, gb, d, eps);
+  else if (d <= 2048) hipLaunchKernelGGL(rmsnorm_fwd_kernel<2>, grid, blk, 0, st, g0, g1, g, gb, d, eps);
+  else if (d <= 4096) hipLaunchKernelGGL(rmsnorm_fwd_kernel<4>, grid, blk, 0, st, g0, g1, g, gb, d, eps);
+  else hipLaunchKernelGGL(rmsnorm_fwd_kernel<8>, grid, blk, 0, st, g0, g1, g, gb, d, eps);
   return hipGetLastError();
 }
 
 template <bool XBF, bool GBF>
-static void rmsnorm_bwd_nv(int nv, dim3 grid, hipStream_t st, const float *dy, const void *x, const int32_t *row_idx, const void *g,
+static void rmsnorm_bwd_nv(int nv, dim3 grid, hipStream_t st, const Parts &dy, const void *x, const int32_t *row_idx, const void *g,
                            const float *rstd, const float *resid, int rows, int d, float *dx_out, bf16_t *dx_bf,
                            float *dg_partial, int dense_out) {
   const dim3 blk(256);
@@ -291,7 +354,7 @@ static void rmsnorm_bwd_nv(int nv, dim3 grid, hipStream_t st, const float *dy, c
   else hipLaunchKernelGGL((rmsnorm_bwd_kernel<XBF, GBF, RB_MAXV>), grid, blk, 0, st, dy, x, row_idx, g, rstd, resid, rows, d, dx_out, dx_bf, dg_partial, dense_out);
 }
 
-hipError_t launch_rmsnorm_bwd(const float *dy, const void *x, bool x_bf16, const int32_t *row_idx, const void *g,
+hipError_t launch_rmsnorm_bwd(const Parts &dy, const void *x, bool x_bf16, const int32_t *row_idx, const void *g,
                               bool g_bf16, const float *rstd, const float *resid, int rows, int d, float *dx_out,
                               bf16_t *dx_bf, float *dg_partial, int n_part, hipStream_t st, int dense_out) {
   if (rows <= 0 || n_part <= 0) return hipSuccess;
@@ -319,16 +382,16 @@ hipError_t launch_colsum(const float *part, int n_part, int d, float *scratch, f
   return hipGetLastError();
 }
 
-hipError_t launch_rope_split(const float *qkv, const int32_t *positions, const double *inv_freq, int rows, int Hq,
-                             int Hkv, int hd, bf16_t *q_hi, bf16_t *k_hi, bf16_t *v_hi, bf16_t *q_lo, bf16_t *k_lo,
-                             bf16_t *v_lo, const int32_t *slot_mapping, void *cache_k, void *cache_v, bool cache_bf16,
-                             long long num_slots, int block_size, hipStream_t st) {
-  if (rows <= 0) return hipSuccess;
-  if (hd > 128) return hipErrorInvalidValue;
-  if (cache_bf16)
-    hipLaunchKernelGGL((rope_split_kernel<true>), dim3(rows), dim3(256), 0, st, qkv, positions, inv_freq, Hq, Hkv, hd, q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, slot_mapping, cache_k, cache_v, num_slots, block_size);
-  else
-    hipLaunchKernelGGL((rope_split_kernel<false>), dim3(rows), dim3(256), 0, st, qkv, positions, inv_freq, Hq, Hkv, hd, q_hi, k_hi, v_hi, q_lo, k_lo, v_lo, slot_mapping, cache_k, cache_v, num_slots, block_size);
+hipError_t launch_rope_split(const RopeRows *groups, int n_groups, const double *inv_freq, int Hq, int Hkv, int hd, void *cache_k,
+                             void *cache_v, bool cache_bf16, long long num_slots, int block_size, hipStream_t st) {
+  if (n_groups < 1 || n_groups > 2 || hd > 128 || hd % 8) return hipErrorInvalidValue;
+  RopeRows g0 = groups[0], g1 = {};
+  if (n_groups > 1) g1 = groups[1];
+  if (g0.rows < 0 || g1.rows < 0) return hipErrorInvalidValue;
+  const unsigned rows = (unsigned)(g0.rows + g1.rows);
+  if (rows == 0) return hipSuccess;
+  if (cache_bf16) hipLaunchKernelGGL((rope_split_kernel<true>), dim3(rows), dim3(256), 0, st, g0, g1, inv_freq, Hq, Hkv, hd, cache_k, cache_v, num_slots, block_size);
+  else hipLaunchKernelGGL((rope_split_kernel<false>), dim3(rows), dim3(256), 0, st, g0, g1, inv_freq, Hq, Hkv, hd, cache_k, cache_v, num_slots, block_size);
   return hipGetLastError();
 }
 
@@ -339,10 +402,20 @@ hipError_t launch_rope_table(const int32_t *positions, const double *inv_freq, i
   return hipGetLastError();
 }
 
-hipError_t launch_swiglu_bwd(const bf16_t *dhm, const bf16_t *gu, int rows, int F, bf16_t *dgu, hipStream_t st) {
+hipError_t launch_swiglu_bwd(const bf16_t *dhm, const Parts &parts, const bf16_t *gu, int rows, int F, bf16_t *dgu, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   if (F % 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(swiglu_bwd_kernel, dim3(rows, cdiv(F, 2048)), dim3(256), 0, st, dhm, gu, F, dgu);
+  hipLaunchKernelGGL(swiglu_bwd_kernel, dim3(rows, cdiv(F, 2048)), dim3(256), 0, st, dhm, parts, gu, F, dgu);
+  return hipGetLastError();
+}
+
+hipError_t launch_swiglu_fwd(const SwigluRows *groups, int n_groups, int F, hipStream_t st) {
+  if (n_groups < 1 || n_groups > 2 || F % 4) return hipErrorInvalidValue;
+  SwigluRows g0 = groups[0], g1 = {};
+  if (n_groups > 1) g1 = groups[1];
+  if (g0.rows < 0 || g1.rows < 0) return hipErrorInvalidValue;
+  if (g0.rows + g1.rows == 0) return hipSuccess;
+  hipLaunchKernelGGL(swiglu_fwd_kernel, dim3(g0.rows + g1.rows, cdiv(F, 1024)), dim3(256), 0, st, g0, g1, F);
   return hipGetLastError();
 }
 
@@ -385,10 +458,19 @@ hipError_t launch_fill_f32(float *dst, size_t n, float v, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_sum_partials(const float *part, int n_part, size_t n, float *out, hipStream_t st) {
+hipError_t launch_sum_parts(const SumRange *ranges, int n_ranges, bool out_bf16, hipStream_t st) {
+  if (n_ranges < 1 || n_ranges > 3) return hipErrorInvalidValue;
+  SumRange s[3] = {};
+  size_t n = 0;
+  for (int i = 0; i < n_ranges; ++i) {
+    s[i] = ranges[i];
+    n += s[i].n;
+    if (s[i].n % 4) return hipErrorInvalidValue;
+  }
   if (n == 0) return hipSuccess;
-  if (n % 4) return hipErrorInvalidValue;
   const size_t want = (n / 4 + 255) / 256;
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)(want < 4096 ? want : 4096)), dim3(256), 0, st, part, n_part, n, out);
+  const dim3 grid((unsigned)(want < 4096 ? want : 4096));
+  if (out_bf16) hipLaunchKernelGGL(sum_parts_kernel<true>, grid, dim3(256), 0, st, s[0], s[1], s[2]);
+  else hipLaunchKernelGGL(sum_parts_kernel<false>, grid, dim3(256), 0, st, s[0], s[1], s[2]);
   return hipGetLastError();
 }

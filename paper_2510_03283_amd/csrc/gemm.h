@@ -19,6 +19,7 @@ struct GemmMGroup {
   const void *resid;    // first residual row of the group (may be null)
   int M;                // rows in the group
   int npass;            // 1: A0*B0   2: + A1*B0   3: + A0*B1
+  long long c_split_stride;   // elements between the partial results of two k slices (k_splits > 1)
   // SwiGLU mode only: c receives hm = silu(G) * U as bf16 [M, F]; c_lo (nullable) its second bf16
   // term; c_gu (nullable) G and U as bf16 [M, 2F] (G in columns [0,F), U in [F,2F)).
   void *c_lo;
@@ -56,8 +57,10 @@ struct GemmParams {
   // multiplies 32 gate columns and the 32 up columns of the same hidden units, and the epilogue
   // writes silu(G) * U instead of G and U (ldc = F).
   int swiglu;
-  int k_splits;     // > 1: grid.y slices of the k range; slice z writes fp32 partial sums at C + z * c_split_stride
-  long long c_split_stride;   // elements
+  // k slices of the tiles of every row group, 1 = none (0 counts as 1).  More than one (four-wave kernel, fp32 output, no
+  // residual - see gemm_pick_splits): slice z writes its partial sums at c + z * c_split_stride of the group, for a
+  // consumer that adds them in order.
+  int k_splits[3];
   int mt_start[4];  // filled by gemm_launch
   int nt_start[4];
   int tile_m, tile_n;   // filled by gemm_launch: the block tile its cost model chose
@@ -69,10 +72,13 @@ struct GemmParams {
   int force_w4;     // 1: the 256x256 four-wave kernel whatever the cost model says (rejected if the problem does not fit it)
 };
 
-// Number of k slices worth using for a single-group, single-segment problem (1 = none): small
-// outputs with a long reduction leave most CUs idle otherwise.  Priced with the launcher's tile
-// cost model plus the traffic of writing and summing the partial results.
-int gemm_suggest_k_splits(int M, int N, int K);
+// Whether cutting the reduction of a product into slices pays.  base: the product as it would be launched otherwise
+// (with its fused epilogue, bf16 output or residual); plain: the same product with plain fp32 output, as the slices
+// would write it for a consumer that adds them (c and ldc as for one slice; only sizes are read).  part_floats: room for
+// the partial results; extra_us: what the consumer costs beyond the consumer of `base` (a launch).  On true k_splits
+// holds the slices of every row group.  Products that leave CUs idle or whose last round of tiles is nearly empty
+// gain; priced with product_us in gemm.hip plus the traffic of the partial results.
+bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &plain, size_t part_floats, double extra_us, int k_splits[3]);
 
 // Whether gemm_launch would run this problem on the four-wave kernel (its cost model picks the 256x256 tile, or
 // force_w4 is set, and the problem fits the kernel).  Forms that only that kernel has are launched after asking.

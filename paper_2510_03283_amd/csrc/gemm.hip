@@ -265,12 +265,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(const Gemm
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  // split-K: grid.y slices the k tiles; slice z writes its partial sums at C + z * c_split_stride
-  const int nk_all = (K + BKT - 1) / BKT;
-  const int nk_per = (nk_all + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int kt0 = (int)blockIdx.y * nk_per;
-  const int nk = max(0, min(nk_per, nk_all - kt0));
-  const int n_it = nk * G.npass;
+  const int nk = (K + BKT - 1) / BKT, n_it = nk * G.npass;
   // operand bases of this block's row group / column segment (scalar registers), and every lane's
   // byte offsets inside a tile
   const char *const a_hi = (const char *)G.a[0], *const a_lo = (const char *)G.a[1];
@@ -305,7 +300,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(const Gemm
     if (it + P < n_it) {
       const int t = it + P;
       const int pass = t >= 2 * nk ? 2 : (t >= nk ? 1 : 0);
-      const int kt = kt0 + t - pass * nk, k0 = kt * BKT;
+      const int k0 = (t - pass * nk) * BKT;
       bf16_t *st = lds + st_req * STAGE;
       st_req = st_req == NST - 1 ? 0 : st_req + 1;
       if ((LA == 1 || LB == 1) && k0 + BKT > K) {
@@ -448,7 +443,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_dl_kernel(const Gemm
       const int col = n0 + wn * WTN + j * 32 + (lane & 31);
       const int rbase = m0 + wm * WTM + i * 32 + 4 * (lane >> 5);
       if (col >= N) continue;
-      const long long cc = S.c_col + col + (long long)blockIdx.y * p.c_split_stride;
+      const long long cc = S.c_col + col;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = rbase + 8 * (r >> 2) + (r & 3);
@@ -497,7 +492,7 @@ hipError_t launch_dl(GemmParams &p, hipStream_t stream) {
     attr_done.set();
   }
   p.tile_m = BM; p.tile_n = BN;
-  hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, LA, LB, BKT, NST>), dim3((unsigned)tiles, (unsigned)(p.k_splits > 1 ? p.k_splits : 1)), dim3(NTHR), lds, stream, p);
+  hipLaunchKernelGGL((gemm_bf16_dl_kernel<BM, BN, WGM, WGN, LA, LB, BKT, NST>), dim3((unsigned)tiles), dim3(NTHR), lds, stream, p);
   return hipGetLastError();
 }
 
@@ -513,7 +508,12 @@ hipError_t launch_w4(GemmParams &p, hipStream_t stream) {
     attr_done.set();
   }
   p.tile_m = 256; p.tile_n = 256;
-  hipLaunchKernelGGL((gemm_bf16_w4_kernel<LA, LB>), dim3((unsigned)tiles, (unsigned)(p.k_splits > 1 ? p.k_splits : 1)), dim3(256), lds, stream, p);
+  int blocks = 0;
+  for (int g = 0; g < p.n_mg; ++g) {
+    p.k_splits[g] = std::max(1, p.k_splits[g]);
+    blocks += (p.mt_start[g + 1] - p.mt_start[g]) * (tiles / p.mt_start[p.n_mg]) * p.k_splits[g];
+  }
+  hipLaunchKernelGGL((gemm_bf16_w4_kernel<LA, LB>), dim3((unsigned)blocks), dim3(256), lds, stream, p);
   return hipGetLastError();
 }
 
@@ -529,18 +529,17 @@ bool aligned16(const void *q) { return ((uintptr_t)q & 15) == 0; }
 // ratios (0.92, 0.83) and 1 - 6 % worse on either side.
 template <int BM, int BN>
 double tile_cost(const GemmParams &p, int slots, double slot_share, double eff) {
-  const int ks = p.k_splits > 1 ? p.k_splits : 1;
   int nt = 0;
   for (int s = 0; s < p.n_ns; ++s) nt += cdiv(p.ns[s].N, BN);
   // The dispatcher hands the next block to whichever slot is free, in block-id order (row groups one
   // after the other, multi-pass groups first).  Time in passes of one tile: free_at[t] slots fall free at t.
   double w = 0;
-  for (int g = 0; g < p.n_mg; ++g) w += (double)cdiv(p.mg[g].M, BM) * nt * p.mg[g].npass * ks;
+  for (int g = 0; g < p.n_mg; ++g) w += (double)cdiv(p.mg[g].M, BM) * nt * p.mg[g].npass;
   std::vector<int> free_at((size_t)(w / slots) + 8, 0);
   free_at[0] = slots;
   size_t t = 0, end = 0;
   for (int g = 0; g < p.n_mg; ++g) {
-    long long n = (long long)cdiv(p.mg[g].M, BM) * nt * ks;
+    long long n = (long long)cdiv(p.mg[g].M, BM) * nt;
     const size_t c = (size_t)p.mg[g].npass;
     while (n > 0) {
       if (free_at[t] == 0) { ++t; continue; }
@@ -568,15 +567,61 @@ bool has_rope(const GemmParams &p) {
   return false;
 }
 
+bool is_split(const GemmParams &p) {
+  for (int g = 0; g < p.n_mg; ++g)
+    if (p.k_splits[g] > 1) return true;
+  return false;
+}
+
 template <int LA, int LB>
 bool uses_w4(const GemmParams &p) {
   return (p.force_w4 || choose_tile(p) == 1) && w4_fits<LA, LB>(p);
 }
 
+// Length in microseconds of a schedule of equal blocks per row group on `slots` slots, in block-id order.
+double makespan(int slots, int n_mg, const long long *n, const double *d) {
+  struct Free { double t; long long k; };
+  std::vector<Free> f{{0.0, slots}};                     // slots by the time they fall free, ascending
+  double end = 0.0;
+  for (int g = 0; g < n_mg; ++g) {
+    long long left = n[g];
+    while (left > 0) {
+      const long long k = std::min(left, f.front().k);
+      const double t = f.front().t + d[g];
+      f.front().k -= k;
+      if (f.front().k == 0) f.erase(f.begin());
+      auto it = f.begin();
+      while (it != f.end() && it->t < t) ++it;
+      if (it != f.end() && it->t == t) it->k += k;
+      else f.insert(it, {t, k});
+      left -= k;
+      end = std::max(end, t);
+    }
+  }
+  return end;
+}
+
+// Estimated time of a product, microseconds.  A k tile takes a block of the four-wave kernel 1.07 us while most CUs are
+// idle and 1.37 us when all are busy, a block of the 192x256 tile 1.45 us, of the 128x128 tile 0.68 us alone on its CU and
+// 1.15 us beside a second one; starting and storing a tile adds 6 - 8 us (measured over 15 shapes from 128 x 4096 x
+// 4096 to 3108 x 4096 x 11008, 2329 x 2048 x 2048 .. 5632; within 15 %).  tile as in choose_tile.
+double product_us(const GemmParams &p, int tile, const int *ks) {
+  const int bm = tile == 1 ? 256 : (tile == 2 ? 192 : 128), bn = tile == 0 ? 128 : 256;
+  long long nt = 0, n[3] = {0, 0, 0}, blocks = 0;
+  for (int s = 0; s < p.n_ns; ++s) nt += cdiv(p.ns[s].N, bn);
+  for (int g = 0; g < p.n_mg; ++g) blocks += n[g] = (long long)cdiv(p.mg[g].M, bm) * nt * (ks ? ks[g] : 1);
+  double d[3] = {0, 0, 0};
+  for (int g = 0; g < p.n_mg; ++g) {
+    const double it = std::ceil((double)cdiv(p.K, BK) * p.mg[g].npass / (ks ? ks[g] : 1));
+    d[g] = tile == 1 ? it * (1.07 + 0.3 * std::min(1.0, blocks / 256.0)) + 8 : (tile == 2 ? it * 1.45 + 8 : it * (blocks <= 256 ? 0.68 : 1.15) + 6);
+  }
+  return makespan(tile == 0 ? 512 : 256, p.n_mg, n, d);
+}
+
 template <int LA, int LB>
 hipError_t launch_layout(GemmParams &p, hipStream_t stream, const char **why) {
-  if (p.force_w4 || p.swiglu_bwd || has_rope(p)) {      // forms that only the four-wave kernel has
-    if (!uses_w4<LA, LB>(p)) { *why = "gemm: the problem does not run on the four-wave kernel"; return hipErrorInvalidValue; }
+  if (p.force_w4 || p.swiglu_bwd || has_rope(p) || is_split(p)) {      // forms that only the four-wave kernel has
+    if (is_split(p) ? !w4_fits<LA, LB>(p) : !uses_w4<LA, LB>(p)) { *why = "gemm: the problem does not run on the four-wave kernel"; return hipErrorInvalidValue; }
     return launch_w4<LA, LB>(p, stream);
   }
   const int tile = choose_tile(p);
@@ -596,7 +641,14 @@ hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const 
   *why = nullptr;
   if (p.n_mg < 1 || p.n_mg > 3 || p.n_ns < 1 || p.n_ns > 3) { *why = "gemm: group count"; return hipErrorInvalidValue; }
   if (p.K <= 0) { *why = "gemm: K <= 0"; return hipErrorInvalidValue; }
-  if (p.k_splits > 1 && (p.resid_kind || p.out_bf16 || p.c_split_stride <= 0)) { *why = "gemm: split-K needs fp32 output without residual"; return hipErrorInvalidValue; }
+  if (is_split(p)) {
+    bool ok = !p.resid_kind && !p.out_bf16 && !p.swiglu && !p.swiglu_bwd && !has_rope(p);
+    for (int g = 0; g < p.n_mg; ++g) {
+      const int it = cdiv(p.K, BK) * p.mg[g].npass, ks = std::max(1, p.k_splits[g]);
+      ok = ok && (ks == 1 || (p.mg[g].c_split_stride > 0 && cdiv(it, ks) * (ks - 1) < it));      // no empty slice
+    }
+    if (!ok) { *why = "gemm: k slices need plain fp32 output without residual and k tiles for every slice"; return hipErrorInvalidValue; }
+  }
   if ((LA == 0 || LB == 0) && p.K % BK) { *why = "gemm: K of a k-contiguous operand must be a multiple of 64"; return hipErrorInvalidValue; }
   if (p.lda % 8 || p.ldb % 8) { *why = "gemm: leading dimension not a multiple of 8"; return hipErrorInvalidValue; }
   if (p.lda <= 0 || p.ldb <= 0 || p.lda >= (1 << 22) || p.ldb >= (1 << 22)) { *why = "gemm: leading dimension out of range"; return hipErrorInvalidValue; }
@@ -618,18 +670,18 @@ hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const 
   }
   if (p.out_bf16 && p.ldc % 2) { *why = "gemm: bf16 output needs an even leading dimension"; return hipErrorInvalidValue; }
   if (p.swiglu) {
-    if (LA != 0 || LB != 0 || p.n_ns != 2 || p.ns[0].N != p.ns[1].N || p.ns[0].N % 2 || p.k_splits > 1 || p.resid_kind || p.n_kseg > 1 || p.ldc % 2) {
+    if (LA != 0 || LB != 0 || p.n_ns != 2 || p.ns[0].N != p.ns[1].N || p.ns[0].N % 2 || p.resid_kind || p.n_kseg > 1 || p.ldc % 2) {
       *why = "gemm: SwiGLU mode needs the NT form, two equal column segments and a plain bf16 output";
       return hipErrorInvalidValue;
     }
   }
   if (has_rope(p)) {
-    bool ok = LA == 0 && LB == 0 && !p.swiglu && !p.swiglu_bwd && !p.out_bf16 && !p.resid_kind && p.k_splits <= 1 && p.n_kseg <= 1 && p.rope_cs;
+    bool ok = LA == 0 && LB == 0 && !p.swiglu && !p.swiglu_bwd && !p.out_bf16 && !p.resid_kind && p.n_kseg <= 1 && p.rope_cs;
     for (int s = 0; s < p.n_ns; ++s) ok = ok && p.ns[s].N % 128 == 0 && p.ns[s].rope_hi;
     if (!ok) { *why = "gemm: rotary mode needs the NT form, plain fp32 output for the other rows, segments of whole 128-wide heads and an angle table"; return hipErrorInvalidValue; }
   }
   if (p.swiglu_bwd) {
-    if (LA != 0 || LB != 1 || p.n_ns != 1 || p.ns[0].c_col != 0 || p.ns[0].N % 2 || !p.out_bf16 || p.resid_kind || p.k_splits > 1 || p.swiglu ||
+    if (LA != 0 || LB != 1 || p.n_ns != 1 || p.ns[0].c_col != 0 || p.ns[0].N % 2 || !p.out_bf16 || p.resid_kind || p.swiglu ||
         p.ldc != 2ll * p.ns[0].N) {
       *why = "gemm: SwiGLU backward mode needs the NN form, one column segment, bf16 output [M, 2N] and no residual";
       return hipErrorInvalidValue;
@@ -661,25 +713,38 @@ bool gemm_uses_four_wave(int LA, int LB, const GemmParams &p) {
   return false;
 }
 
-int gemm_suggest_k_splits(int M, int N, int K) {
-  const int nk = cdiv(K, BK);
-  if (nk < 32) return 1;
-  GemmParams p;
-  memset(&p, 0, sizeof(p));
-  p.n_mg = p.n_ns = 1;
-  p.mg[0].M = M; p.mg[0].npass = 1;
-  p.ns[0].N = N;
-  // seconds: a CU does about 3.5 TFLOP/s on a 256x256 tile; partial sums move at about 3 TB/s
-  double best = 0;
-  int best_ks = 1;
-  for (int ks = 1; ks <= 8; ++ks) {
-    if (nk / ks < 16) break;
-    p.k_splits = ks;
-    const double c = std::min(std::min(tile_cost<256, 256>(p, 256, 1.0, 1.0), tile_cost<192, 256>(p, 256, 1.0, 0.92)),
-                              tile_cost<128, 128>(p, 512, 2.0, 0.83));
-    double t = c * 2.0 * ((double)K / ks) / 3.5e12;
-    if (ks > 1) t += 4e-6 + (double)(ks + 1) * M * N * 4.0 / 3e12;
-    if (ks == 1 || t < best * 0.95) { best = t; best_ks = ks; }
+bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &plain, size_t part_floats, double extra_us, int k_splits[3]) {
+  for (int g = 0; g < 3; ++g) k_splits[g] = 1;
+  const bool fits = LA == 0 ? (LB == 0 ? w4_fits<0, 0>(plain) : w4_fits<0, 1>(plain)) : w4_fits<1, 1>(plain);
+  long long nt = 0, units = 0, rows = 0;
+  for (int s = 0; s < plain.n_ns; ++s) nt += cdiv(plain.ns[s].N, 256);
+  for (int g = 0; g < plain.n_mg; ++g) { units += cdiv(plain.mg[g].M, 256) * nt * plain.mg[g].npass; rows += plain.mg[g].M; }
+  if (!fits || units >= 5 * 256) return false;           // five rounds and more: the last one is short beside the rest
+  const bool round_trip = !(base.out_bf16 || base.swiglu || base.swiglu_bwd || has_rope(base));   // fp32 result written and read back anyway
+  const double t0 = product_us(base, choose_tile(base), nullptr);
+  double best = 0.93 * t0;
+  bool found = false;
+  static const int cand[] = {2, 3, 4, 5, 6, 8, 12, 16};
+  for (int c : cand) {
+    // slices of about equal length: row groups with fewer passes are cut into fewer
+    int ks[3] = {1, 1, 1}, most = 1;
+    double floats = 0;
+    bool ok = true;
+    for (int g = 0; g < plain.n_mg; ++g) most = std::max(most, plain.mg[g].npass);
+    for (int g = 0; g < plain.n_mg; ++g) {
+      const int it = cdiv(plain.K, BK) * plain.mg[g].npass;
+      ks[g] = std::max(1, (c * plain.mg[g].npass + most / 2) / most);
+      ok = ok && it / ks[g] >= 4 && cdiv(it, ks[g]) * (ks[g] - 1) < it;
+      floats += (double)ks[g] * plain.mg[g].M * plain.ldc;
+    }
+    if (!ok || floats > (double)part_floats) continue;
+    // every partial result is written and read once: 5 TB/s
+    const double t = product_us(plain, 1, ks) + extra_us + (floats - (round_trip ? 1.0 : 0.0) * rows * plain.ldc) * 8.0 / 5e6;
+    if (t < best) {
+      best = t;
+      found = true;
+      for (int g = 0; g < 3; ++g) k_splits[g] = ks[g];
+    }
   }
-  return best_ks;
+  return found;
 }

@@ -43,12 +43,12 @@ typedef __attribute__((address_space(3))) char lds_char_t;
 // captured variables become selections between their addresses and keep all of them in private memory.
 struct W4Cur { uint32_t a0, a1, b0, b1, u0, u1, b_bytes, oa, ob; };
 template <int LA, int LB>
-__device__ __forceinline__ W4Cur w4_tile_src(int tt, int nk, int kt0, int m0, int n0, int N, int K, long long lda, long long ldb,
+__device__ __forceinline__ W4Cur w4_tile_src(int tt, int nk, int m0, int n0, int N, int K, long long lda, long long ldb,
                                              const void *a_hi, const void *a_lo, const void *b_hi, const void *b_lo, const void *u_hi, const void *u_lo,
                                              int swiglu, int n_kseg, int ks_s1, int ks_s2, const void *ks_b0, const void *ks_b1, const void *ks_b2) {
   constexpr int BKT = 64;
   const int pass = tt >= 2 * nk ? 2 : (tt >= nk ? 1 : 0);
-  const int k0 = (kt0 + tt - pass * nk) * BKT;
+  const int k0 = (tt - pass * nk) * BKT;
   W4Cur r;
   const uint64_t ab = (uint64_t)(pass == 1 ? a_lo : a_hi);
   r.a0 = (uint32_t)ab;
@@ -106,23 +106,27 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   lds_char_t *const lbase = (lds_char_t *)(lds_void_t *)smem_raw;
 
-  // block -> tile: the mapping of gemm_bf16_dl_kernel
+  // block -> tile and k slice: the mapping of gemm_bf16_dl_kernel over the tiles; a tile of row group g takes k_splits[g]
+  // blocks in a row
   const int n_ns_eff = p.swiglu ? 1 : p.n_ns;
   const int total_nt = p.nt_start[n_ns_eff];
-  int g = 0, first_blk = 0;
-  while (g + 1 < p.n_mg && (int)blockIdx.x >= first_blk + (p.mt_start[g + 1] - p.mt_start[g]) * total_nt) {
+  int g = 0, first_blk = 0, vb = (int)blockIdx.x;
+  while (g + 1 < p.n_mg && vb >= (p.mt_start[g + 1] - p.mt_start[g]) * total_nt * p.k_splits[g]) {
+    vb -= (p.mt_start[g + 1] - p.mt_start[g]) * total_nt * p.k_splits[g];
     first_blk += (p.mt_start[g + 1] - p.mt_start[g]) * total_nt;
     ++g;
   }
+  const int ks = p.k_splits[g], slice = vb % ks;
+  vb = first_blk + vb / ks;
   const int mtc = p.mt_start[g + 1] - p.mt_start[g], T = mtc * total_nt;
   int v = 0;
   {
-    const int x = blockIdx.x & 7;
+    const int x = vb & 7;
     for (int y = 0; y < x; ++y) {
       const int fy = (y - first_blk) & 7;
       v += fy < T ? (T - 1 - fy) / 8 + 1 : 0;
     }
-    v += ((int)blockIdx.x - first_blk - ((x - first_blk) & 7)) >> 3;
+    v += (vb - first_blk - ((x - first_blk) & 7)) >> 3;
   }
   const int band = p.mg[g].npass >= 2 ? GROUP_M_MULTI : GROUP_M;
   const int grp_sz = band * total_nt;
@@ -147,11 +151,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int nk_all = (K + BKT - 1) / BKT;
-  const int nk_per = (nk_all + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int kt0 = (int)blockIdx.y * nk_per;
-  const int nk = max(0, min(nk_per, nk_all - kt0));
-  const int n_it = nk * G.npass;
+  // k tiles tt0 .. tt0 + n_it - 1 of the tile's passes, one after the other (the launcher gives every slice some)
+  const int nk = (K + BKT - 1) / BKT, nk_slice = (nk * G.npass + ks - 1) / ks;
+  const int tt0 = slice * nk_slice, n_it = min(nk_slice, nk * G.npass - tt0);
   const long long lda = p.lda, ldb = p.ldb;
   const int n_kseg = p.n_kseg;
   const int ks_s1 = p.kseg_start[1], ks_s2 = p.kseg_start[2];
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   const void *const u_hi = swiglu ? p.ns[1].b[0] : b_hi, *const u_lo = swiglu && G.npass >= 3 ? p.ns[1].b[1] : u_hi;
   using Src = W4Src;
   auto tile_cur = [&](int tt) W4_INL -> W4Cur {
-    return w4_tile_src<LA, LB>(tt, nk, kt0, m0, n0, N, K, lda, ldb, a_hi, a_lo, b_hi, b_lo, u_hi, u_lo, swiglu, n_kseg, ks_s1, ks_s2, ks_b0, ks_b1, ks_b2);
+    return w4_tile_src<LA, LB>(tt, nk, m0, n0, N, K, lda, ldb, a_hi, a_lo, b_hi, b_lo, u_hi, u_lo, swiglu, n_kseg, ks_s1, ks_s2, ks_b0, ks_b1, ks_b2);
   };
   auto tile_src = [&](int tt) W4_INL -> Src { return w4_resources(tile_cur(tt), a_bytes); };
   // a tile that continues the k run of the one before it lies stepA / stepB bytes further on
@@ -265,34 +267,25 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fra[kk & 1][i]), __builtin_bit_cast(bf16x8_t, frb[kk & 1][j]), acc[i][j], 0, 0, 0);
   };
 
-  if (n_it <= 0) {
-    // an empty k slice of a split reduction (fp32 partial sums, no residual): its tile is zeros.  Kept apart
-    // from the main path so that the accumulators are not a phi around the loop.
-    float *const zp = (float *)G.c + (long long)blockIdx.y * p.c_split_stride + S.c_col;
-    for (int e = threadIdx.x; e < BM * BN; e += NTHR) {
-      const int row = m0 + e / BN, col = n0 + e % BN;
-      if (row < M && col < N) zp[(long long)row * p.ldc + col] = 0.f;
-    }
-    return;
-  }
   const int n_run = max(n_it, 3);      // tile times: at least one turn of the loop and one tile behind it
+  const int rq_last = tt0 + n_it - 1;
   int rq_tt;      // the tile requested last, and where it comes from
   W4Cur rq;
   {
     // prologue: tile 0 -> set 1 -> stage 0; tile 1 -> set 0; tile 2 -> set 1.  Tiles past the last repeat
     // the last one (their data is never multiplied): the loop's wait counts assume every request is issued.
     {
-      const Src s0 = tile_src(0);
+      const Src s0 = tile_src(tt0);
       static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(1), X, s0); });
       W4_SB;
-      const Src s1 = w4_resources(tile_cur(min(1, n_it - 1)), a_bytes, n_it < 2);
+      const Src s1 = w4_resources(tile_cur(tt0 + min(1, n_it - 1)), a_bytes, n_it < 2);
       static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(0), X, s1); });
       W4_SB;
       wait_vmcnt<2 * NL>();      // tile 0 is in
       W4_SB;
       static_for<0, 2 * NL>([&](auto X) W4_INL { stage_write(W4_IC(1), X, W4_IC(0)); });
       W4_SB;
-      rq_tt = min(2, n_it - 1);
+      rq_tt = tt0 + min(2, n_it - 1);
       rq = tile_cur(rq_tt);
       const Src s2 = w4_resources(rq, a_bytes, n_it < 3);
       static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(1), X, s2); });
@@ -311,10 +304,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       // the next request: tile t + 3, or the last tile again.  Only a change of pass or of k segment takes
       // the full computation.
       bool dead = false;
-      if (!tail && rq_tt >= n_it - 1) dead = true;
-      if (!tail && rq_tt < n_it - 1) {
+      if (!tail && rq_tt >= rq_last) dead = true;
+      if (!tail && rq_tt < rq_last) {
         ++rq_tt;
-        const int kq = (kt0 + rq_tt) * BKT;      // (k segments exclude passes)
+        const int kq = rq_tt * BKT;      // (k segments exclude passes)
         if (rq_tt == nk || rq_tt == 2 * nk || (n_kseg > 1 && (kq == ks_s1 || kq == ks_s2))) {
           rq = tile_cur(rq_tt);
         } else {
@@ -578,7 +571,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     }
     return;
   }
-  const long long c_col0 = c_col + (long long)blockIdx.y * p.c_split_stride;
+  const long long c_col0 = c_col + slice * G.c_split_stride;
   if (p.swiglu_bwd) {
     if constexpr (LA == 0 && LB == 1) {
       // SwiGLU backward in the epilogue of dHm = dY Wd: the tile of dHm never leaves the registers.  With G and U of

@@ -4,44 +4,82 @@
 #pragma once
 #include "common.h"
 
+// The fp32 result of a product that may have come in k slices: value i = sum over s < n of p[s * stride + i], added in
+// order.  n = 1: an ordinary buffer.
+struct Parts {
+  const float *p;
+  int n;
+  size_t stride;
+};
+
 // ---- elementwise.hip -------------------------------------------------------------------------
-// Row-wise RMSNorm: out = x * rsqrt(mean(x^2) + eps) * g.  x is fp32 or bf16 [*, d] (row r reads
-// input row row_idx[r] when row_idx is non-null), g is fp32 or bf16 [d].  rstd (nullable) gets
-// the row scale.
-hipError_t launch_rmsnorm_fwd(const void *x, bool x_bf16, const int32_t *row_idx, const void *g, bool g_bf16,
-                              int rows, int d, float eps, bf16_t *hi, bf16_t *lo, float *rstd, hipStream_t st, bool frag = false);
-// frag: hi in fragment order (common.h), d % 32 == 0, no lo.
+// Row-wise RMSNorm of one or two groups of rows in one launch: out = v * rsqrt(mean(v^2) + eps) * g.
+//   v = x                 (x: fp32 or bf16 [*, d]; row r reads row row_idx[r] when row_idx is non-null)
+//   v = parts + x         when parts.p is set: x is the residual, v is also written to v_out (fp32)
+// hi (and lo, nullable): bf16 terms of the result, row-major or (frag) in fragment order (common.h; d % 32 == 0, no lo).
+// rstd (nullable) gets the row scale.  g: fp32 or bf16 [d].
+struct NormRows {
+  const void *x;
+  bool x_bf16;
+  const int32_t *row_idx;
+  Parts parts;
+  float *v_out;
+  bf16_t *hi, *lo;
+  float *rstd;
+  int rows;
+  bool frag;
+};
+hipError_t launch_rmsnorm_fwd(const NormRows *groups, int n_groups, const void *g, bool g_bf16, int d, float eps, hipStream_t st);
 // RMSNorm backward.  dx_out[out_row] = resid[r] + rstd*(dy*g) - x*rstd^3*mean((dy*g)*x), where
 // out_row = row_idx ? row_idx[r] : r and x is read at the same row; resid (nullable) fp32.
 // dg_partial [n_part, d] receives per-block partial sums of dy*x*rstd (reduce with
 // launch_colsum).  dx_bf (nullable) gets a bf16 copy of dx_out rows (same row mapping).
 // dense_out != 0: output row r is written at row r (dx_out may then be dy itself) while x is still
 // read at row_idx[r].
-hipError_t launch_rmsnorm_bwd(const float *dy, const void *x, bool x_bf16, const int32_t *row_idx, const void *g,
+hipError_t launch_rmsnorm_bwd(const Parts &dy, const void *x, bool x_bf16, const int32_t *row_idx, const void *g,
                               bool g_bf16, const float *rstd, const float *resid, int rows, int d,
                               float *dx_out, bf16_t *dx_bf, float *dg_partial, int n_part, hipStream_t st,
                               int dense_out = 0);
 // out[j] (+)= sum over the n_part rows of part[:, j]; scratch: COLSUM_SLICES * d floats.
 constexpr int COLSUM_SLICES = 32;
 hipError_t launch_colsum(const float *part, int n_part, int d, float *scratch, float *out, int accumulate, hipStream_t st);
-// Rotary embedding of q and k inside qkv fp32 [rows, (Hq+2Hkv)*hd], split into head-major bf16
-// outputs q [rows, Hq*hd], k, v [rows, Hkv*hd]; optionally scatter k, v (rounded to the cache
-// type) into the paged cache at slot_mapping (null = no cache write).
-hipError_t launch_rope_split(const float *qkv, const int32_t *positions, const double *inv_freq, int rows, int Hq,
-                             int Hkv, int hd, bf16_t *q_hi, bf16_t *k_hi, bf16_t *v_hi, bf16_t *q_lo, bf16_t *k_lo,
-                             bf16_t *v_lo, const int32_t *slot_mapping, void *cache_k, void *cache_v, bool cache_bf16,
-                             long long num_slots, int block_size, hipStream_t st);
+// Rotary embedding of q and k inside qkv [rows, (Hq+2Hkv)*hd], split into head-major bf16 q [rows, Hq*hd] and
+// k, v [rows, Hkv*hd] (hi, optional lo), and, when slot_mapping is set, the append of k and v (cache element type) to
+// the paged cache at slot_mapping; one or two groups of rows in one launch.
+struct RopeRows {
+  Parts qkv;
+  const int32_t *positions, *slot_mapping;
+  bf16_t *q_hi, *k_hi, *v_hi, *q_lo, *k_lo, *v_lo;
+  int rows;
+};
+hipError_t launch_rope_split(const RopeRows *groups, int n_groups, const double *inv_freq, int Hq, int Hkv, int hd, void *cache_k,
+                             void *cache_v, bool cache_bf16, long long num_slots, int block_size, hipStream_t st);
 // cs[r, i] = (cos, sin) of positions[r] * inv_freq[i], i < hd/2 (angle formed and reduced in fp64): the
 // per-row rotary table the attention backward rotates dq and dk back with.
 hipError_t launch_rope_table(const int32_t *positions, const double *inv_freq, int rows, int hd, float2 *cs, hipStream_t st);
 // dU = dhm*silu(G), dG = dhm*U*sig(G)*(1+G*(1-sig(G))) -> dgu bf16 [rows, 2F].
-// gu bf16 [rows, 2F] (G = columns [0,F), U = [F,2F)) as the gate/up GEMM left it.  F % 8 == 0.
-hipError_t launch_swiglu_bwd(const bf16_t *dhm, const bf16_t *gu, int rows, int F, bf16_t *dgu, hipStream_t st);
+// gu bf16 [rows, 2F] (G = columns [0,F), U = [F,2F)) as the gate/up product left it; dhm bf16 [rows, F], or (null) parts.
+// F % 8 == 0.
+hipError_t launch_swiglu_bwd(const bf16_t *dhm, const Parts &parts, const bf16_t *gu, int rows, int F, bf16_t *dgu, hipStream_t st);
+// hm = silu(G) * U from G | U = gu_in [rows, 2F]: bf16 [rows, F] in one or (lo non-null) two terms, and G | U as bf16
+// [rows, 2F] when gu is non-null; one or two groups of rows.
+struct SwigluRows {
+  Parts gu_in;
+  bf16_t *hi, *lo, *gu;
+  int rows;
+};
+hipError_t launch_swiglu_fwd(const SwigluRows *groups, int n_groups, int F, hipStream_t st);
 // fp32 -> (hi, lo) bf16, n elements; lo nullable.
 hipError_t launch_split_f32(const float *src, size_t n, bf16_t *hi, bf16_t *lo, hipStream_t st);
 hipError_t launch_fill_f32(float *dst, size_t n, float v, hipStream_t st);
-// out[i] = sum_s part[s * n + i], n % 4 == 0 (partial sums of a split-K GEMM, fixed order).
-hipError_t launch_sum_partials(const float *part, int n_part, size_t n, float *out, hipStream_t st);
+// out[i] = parts (+ resid[i], fp32), n % 4 == 0, as fp32 or bf16; one to three ranges in one launch.
+struct SumRange {
+  Parts parts;
+  const float *resid;
+  void *out;
+  size_t n;
+};
+hipError_t launch_sum_parts(const SumRange *ranges, int n_ranges, bool out_bf16, hipStream_t st);
 
 // ---- gemm_skinny.hip --------------------------------------------------------------------------
 // C[m, n] = sum_k A[m, k] W[n, k] for at most SKINNY_MAX_ROWS rows, W bf16 [N, K] read once; see the file for the
@@ -84,9 +122,9 @@ hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t s
 hipError_t launch_lora_pack(const void *const *src, const int *rows, const int *cols, const int *r0, const int *c0, int n_src,
                             bool src_bf16, int dst_rows, int dst_cols, float scale, bf16_t *hi, bf16_t *lo, hipStream_t st);
 // (hi, lo) = two-term bf16 form of scale * src.
-hipError_t launch_scale_split(const float *src, size_t n, float scale, bf16_t *hi, bf16_t *lo, hipStream_t st);
+hipError_t launch_scale_split(const Parts &src, size_t n, float scale, bf16_t *hi, bf16_t *lo, hipStream_t st);
 // dst[rows, cols] (+)= scale * the window of src (row pitch src_ld) that starts at (r0, c0).
-hipError_t launch_extract(const float *src, int src_ld, int r0, int c0, int rows, int cols, float scale, float *dst, int accumulate, hipStream_t st);
+hipError_t launch_extract(const Parts &src, int src_ld, int r0, int c0, int rows, int cols, float scale, float *dst, int accumulate, hipStream_t st);
 
 // ---- loop.hip ---------------------------------------------------------------------------------
 // out[r] = arg max_j logits[r, j] (lowest index on ties), fp32 logits [rows, V].

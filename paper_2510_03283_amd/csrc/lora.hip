@@ -34,24 +34,30 @@ __global__ __launch_bounds__(256) void lora_pack_kernel(PackSrc s0, PackSrc s1, 
   }
 }
 
-__global__ __launch_bounds__(256) void scale_split_kernel(const float *__restrict__ src, size_t n, float scale,
+__device__ __forceinline__ float ld_parts(const Parts &s, size_t i) {
+  float v = s.p[i];
+  for (int k = 1; k < s.n; ++k) v += s.p[(size_t)k * s.stride + i];
+  return v;
+}
+
+__global__ __launch_bounds__(256) void scale_split_kernel(const Parts src, size_t n, float scale,
                                                           bf16_t *__restrict__ hi, bf16_t *__restrict__ lo) {
   const size_t stride = (size_t)gridDim.x * 256;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
     bf16_t h, l;
-    split_bf(src[i] * scale, h, l);
+    split_bf(ld_parts(src, i) * scale, h, l);
     hi[i] = h;
     if (lo) lo[i] = l;
   }
 }
 
 // dst[rows, cols] (+)= src[(r0 + i) * src_ld + c0 + j]
-__global__ __launch_bounds__(256) void extract_kernel(const float *__restrict__ src, int src_ld, int r0, int c0, int rows, int cols,
+__global__ __launch_bounds__(256) void extract_kernel(const Parts src, int src_ld, int r0, int c0, int rows, int cols,
                                                       float scale, float *__restrict__ dst, int accumulate) {
   const size_t n = (size_t)rows * cols, stride = (size_t)gridDim.x * 256;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
     const int r = (int)(i / cols), c = (int)(i % cols);
-    const float v = scale * src[(size_t)(r0 + r) * src_ld + c0 + c];
+    const float v = scale * ld_parts(src, (size_t)(r0 + r) * src_ld + c0 + c);
     dst[i] = accumulate ? dst[i] + v : v;
   }
 }
@@ -74,13 +80,13 @@ hipError_t launch_lora_pack(const void *const *src, const int *rows, const int *
   return hipGetLastError();
 }
 
-hipError_t launch_scale_split(const float *src, size_t n, float scale, bf16_t *hi, bf16_t *lo, hipStream_t st) {
+hipError_t launch_scale_split(const Parts &src, size_t n, float scale, bf16_t *hi, bf16_t *lo, hipStream_t st) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(scale_split_kernel, dim3(grid_for(n)), dim3(256), 0, st, src, n, scale, hi, lo);
   return hipGetLastError();
 }
 
-hipError_t launch_extract(const float *src, int src_ld, int r0, int c0, int rows, int cols, float scale, float *dst, int accumulate, hipStream_t st) {
+hipError_t launch_extract(const Parts &src, int src_ld, int r0, int c0, int rows, int cols, float scale, float *dst, int accumulate, hipStream_t st) {
   if (rows <= 0 || cols <= 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(extract_kernel, dim3(grid_for((size_t)rows * cols)), dim3(256), 0, st, src, src_ld, r0, c0, rows, cols, scale, dst, accumulate);
   return hipGetLastError();
