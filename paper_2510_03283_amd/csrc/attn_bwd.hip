@@ -68,10 +68,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16_t *__res
                                                           const float2 *__restrict__ cs, bf16_t *__restrict__ dqkv,
                                                           const int32_t *__restrict__ excl_lo,
                                                           const int32_t *__restrict__ excl_hi) {
-  constexpr int NKK = HD / 16, NOT = HD / 32;
+  constexpr int NKK = HD / 16, NOT = HD / 32, RK = HD == 128 ? 2 : 4;      // RK: operands read at a time
   using T = Tile<TB, HD, 256>;
   constexpr int STAGE = 2 * T::ELEMS;       // K tile, V tile
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
   bf16_t *lds = (bf16_t *)smem_raw;         // [2][STAGE]
   // blocks are dealt to the XCDs round-robin: block x takes head (x % Hkv) * group + x / Hkv, so the query heads
   // of one kv head (and all their row tiles) run on one XCD and its K and V stay in that XCD's L2
@@ -79,17 +79,18 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16_t *__res
   const int r0 = seg[s] - row_base, L = seg[s + 1] - seg[s];
   const int q0 = (gridDim.z - 1 - blockIdx.z) * 128;
   if (q0 >= L) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, j = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, j = lane & 31;
   const int qw0 = q0 + wave * 32, qi = qw0 + j;
   const size_t qld = (size_t)Hq * HD, kld = (size_t)Hkv * HD;
   const bf16_t *kbase = k + (size_t)r0 * kld + (size_t)kvh * HD, *vbase = v + (size_t)r0 * kld + (size_t)kvh * HD;
   const int kend = min(L, q0 + 128);
   const int ntiles = (kend + TB - 1) / TB;
   const int xlo = excl_lo ? excl_lo[s] : L, xhi = excl_lo ? excl_hi[s] : L;   // queries >= xhi skip keys xlo .. xhi-1
+  const uint32_t lane_off = T::lane_offset(kld);
   auto issue_tile = [&](int it) {
     bf16_t *S = lds + (it & 1) * STAGE;
-    T::issue(kbase, kld, it * TB, L, S);
-    T::issue(vbase, kld, it * TB, L, S + T::ELEMS);
+    T::issue(kbase, kld, it * TB, L, lane_off, S);
+    T::issue(vbase, kld, it * TB, L, lane_off, S + T::ELEMS);
   };
   issue_tile(0);
 
@@ -122,10 +123,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16_t *__res
     if (g == 0) dvec[(size_t)(r0 + qi) * Hq + h] = dv_;
   }
   // MFMA row j reads tile row swap23(j): register r = 8*mm + e then holds key 16*mm + 8*g + e
-  const typename T::FragK fk = T::frag_k_init(swap23(j));
-  typename T::FragT ft[NOT];
-#pragma unroll
-  for (int t = 0; t < NOT; ++t) ft[t] = T::frag_t_init(32 * t, lane);
+  const uint32_t fk = T::frag_k_lane(swap23(j), g);
+  const typename T::FragT ft = T::frag_t_init(lane);
   f32x16_t acc[NOT];
 #pragma unroll
   for (int t = 0; t < NOT; ++t)
@@ -139,40 +138,45 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16_t *__res
     const int kb = it * TB;
     if (kb > qw0 + 31) continue;
     if (qw0 >= xhi && kb >= xlo && kb + TB <= xhi) continue;
-    const bf16_t *Ks = lds + (it & 1) * STAGE, *Vs = Ks + T::ELEMS;
-    const bool need_mask = kb + TB - 1 > qw0 || kb + TB > L || (qw0 + 31 >= xhi && kb < xhi && kb + TB > xlo);
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
+    const uint32_t Ks = T::lds_addr(lds + (it & 1) * STAGE), Vs = Ks + T::ELEMS * 2;
+    static_for<0, 2>([&](auto ST) __attribute__((always_inline)) {
+      constexpr int st = decltype(ST)::value, off = st * 32 * HD * 2;
       f32x16_t sa, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
+      static_for<0, NKK / RK>([&](auto KH) __attribute__((always_inline)) {
+        constexpr int kk0 = RK * decltype(KH)::value;
+        bf16x8_t a[RK], b[RK];
+        T::template read_k<RK, kk0, off>(Ks, fk, a);
 #pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) {
-        const bf16x8_t a = T::frag_k(Ks + st * 32 * HD, fk, kk, g);
-        sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], sa, 0, 0, 0);
-        const bf16x8_t b = T::frag_k(Vs + st * 32 * HD, fk, kk, g);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, dof[kk], dp, 0, 0, 0);
-      }
+        for (int i = 0; i < RK; ++i) sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], qf[kk0 + i], sa, 0, 0, 0);
+        T::template read_k<RK, kk0, off>(Vs, fk, b);
+#pragma unroll
+        for (int i = 0; i < RK; ++i) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[i], dof[kk0 + i], dp, 0, 0, 0);
+      });
       float ds[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float p = __builtin_amdgcn_exp2f(fmaf(sa[r], sc, -lse2));
-        if (need_mask) {
-          const int key = kb + st * 32 + 16 * (r >> 3) + 8 * g + (r & 7);
-          if (!(key <= qi && key < L) || (qi >= xhi && key >= xlo && key < xhi)) p = 0.f;
-        }
-        ds[r] = p * (dp[r] - dv_) * rs;
-      }
+      for (int r = 0; r < 16; ++r) ds[r] = __builtin_amdgcn_exp2f(fmaf(sa[r], sc, -lse2)) * (dp[r] - dv_) * rs;
+      // (the key of register r minus that of this lane's first register is a constant)
+      if (kb + TB - 1 > qw0 || kb + TB > L) {
+        const int last = min(qi, L - 1) - kb - 8 * g;
 #pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        const bf16x8_t dsf = pack8(ds + 8 * mm);
-#pragma unroll
-        for (int t = 0; t < NOT; ++t) {
-          const bf16x8_t a = T::frag_t(Ks, ft[t], 2 * st + mm);
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dsf, acc[t], 0, 0, 0);
-        }
+        for (int r = 0; r < 16; ++r) ds[r] = st * 32 + 16 * (r >> 3) + (r & 7) > last ? 0.f : ds[r];
       }
-    }
+      if (qw0 + 31 >= xhi && kb < xhi && kb + TB > xlo) {
+        const int lo = xlo - kb - 8 * g, n_ex = qi >= xhi ? xhi - xlo : 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ds[r] = (uint32_t)(st * 32 + 16 * (r >> 3) + (r & 7) - lo) < (uint32_t)n_ex ? 0.f : ds[r];
+      }
+      const bf16x8_t dsf[2] = {pack8(ds), pack8(ds + 8)};
+#pragma unroll
+      for (int t = 0; t < NOT; ++t) {
+        bf16x8_t a[2];
+        T::template read_t<2, 2 * st>(Ks, ft, t, a);
+#pragma unroll
+        for (int mm = 0; mm < 2; ++mm) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mm], dsf[mm], acc[t], 0, 0, 0);
+      }
+    });
   }
   if (qi < L)
     store_grad_row<HD>(acc, cs + (size_t)(r0 + qi) * (HD / 2), g, dqkv + (size_t)(r0 + qi) * (qld + 2 * kld) + (size_t)h * HD);
@@ -180,33 +184,34 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16_t *__res
 
 // ------------------------------------------------------------------ dK, dV
 template <int HD>
-__global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkdv_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+__global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                             const bf16_t *__restrict__ v, const bf16_t *__restrict__ d_o,
                                                             const float *__restrict__ lse, const float *__restrict__ dvec,
                                                             const int32_t *__restrict__ seg, int row_base, int Hq,
                                                             int Hkv, const float2 *__restrict__ cs, bf16_t *__restrict__ dqkv,
                                                             const int32_t *__restrict__ excl_lo, const int32_t *__restrict__ excl_hi) {
-  constexpr int NKK = HD / 16, NOT = HD / 32;
+  constexpr int NKK = HD / 16, NOT = HD / 32, RK = HD == 128 ? 2 : 4;      // RK: operands read at a time
   using T = Tile<TB, HD, 256>;
   constexpr int STAGE = 2 * T::ELEMS + 4 * TB;    // Q tile, dO tile, lse[TB] and D[TB] as fp32 (2 bf16 slots each)
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
   bf16_t *lds = (bf16_t *)smem_raw;               // [2][STAGE]
   const int kvh = blockIdx.x, s = blockIdx.y, grp = Hq / Hkv;
   const int r0 = seg[s] - row_base, L = seg[s + 1] - seg[s];
   const int k0 = blockIdx.z * 128;
   if (k0 >= L) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, j = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, j = lane & 31;
   const int kw0 = k0 + wave * 32, ki = kw0 + j;      // this lane's key
   const size_t qld = (size_t)Hq * HD, kld = (size_t)Hkv * HD;
   const int xlo = excl_lo ? excl_lo[s] : L, xhi = excl_lo ? excl_hi[s] : L;   // queries >= xhi skip keys xlo .. xhi-1
   const int nqt = (L - k0 + TB - 1) / TB;            // query tiles per head (k0 is a multiple of TB)
   const int niter = grp * nqt;
+  const uint32_t lane_off = T::lane_offset(qld);
   auto issue_tile = [&](int it) {
     const int gi = it / nqt, qb = k0 + (it % nqt) * TB;
     const int h = kvh * grp + gi;
     bf16_t *S = lds + (it & 1) * STAGE;
-    T::issue(q + (size_t)r0 * qld + (size_t)h * HD, qld, qb, L, S);
-    T::issue(d_o + (size_t)r0 * qld + (size_t)h * HD, qld, qb, L, S + T::ELEMS);
+    T::issue(q + (size_t)r0 * qld + (size_t)h * HD, qld, qb, L, lane_off, S);
+    T::issue(d_o + (size_t)r0 * qld + (size_t)h * HD, qld, qb, L, lane_off, S + T::ELEMS);
     if (wave < 2) {                                  // one 4-byte element per lane: lane's value lands at base + 4*lane
       const int qq = qb + lane;
       const float *src = wave ? dvec : lse;
@@ -230,10 +235,8 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkdv_kernel(co
   }
   const float sc = 1.4426950408889634f / sqrtf((float)HD), rs = 1.0f / sqrtf((float)HD);
   // MFMA row j reads tile row swap23(j): register r = 8*mm + e then holds query 16*mm + 8*g + e
-  const typename T::FragK fk = T::frag_k_init(swap23(j));
-  typename T::FragT ft[NOT];
-#pragma unroll
-  for (int t = 0; t < NOT; ++t) ft[t] = T::frag_t_init(32 * t, lane);
+  const uint32_t fk = T::frag_k_lane(swap23(j), g);
+  const typename T::FragT ft = T::frag_t_init(lane);
   f32x16_t dka[NOT], dva[NOT];
 #pragma unroll
   for (int t = 0; t < NOT; ++t)
@@ -247,53 +250,83 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkdv_kernel(co
     const int qb = k0 + (it % nqt) * TB;
     if (qb + TB - 1 < kw0) continue;                 // every query of the tile precedes this wave's keys
     if (kw0 >= xlo && kw0 + 32 <= xhi && qb >= xhi) continue;   // ... or none of them may see these keys
-    const bf16_t *Qs = lds + (it & 1) * STAGE, *Os = Qs + T::ELEMS;
-    const float *lse_s = (const float *)(Os + T::ELEMS), *d_s = lse_s + TB;
-    const bool need_mask = qb < kw0 + 31 || qb + TB > L || kw0 + 32 > L || (kw0 + 31 >= xlo && kw0 < xhi && qb + TB > xhi);
+    const bf16_t *const stage = lds + (it & 1) * STAGE;
+    const uint32_t Qs = T::lds_addr(stage), Os = Qs + T::ELEMS * 2;
+    const float *lse_s = (const float *)(stage + 2 * T::ELEMS), *d_s = lse_s + TB;
+    static_for<0, 2>([&](auto ST) __attribute__((always_inline)) {
+      constexpr int st = decltype(ST)::value, off = st * 32 * HD * 2;
+      // P = exp(S - lse), then dV before dP: S and P's operand form are gone when the registers of dP are needed
+      f32x16_t sa;
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      f32x16_t sa, dp;
+      for (int r = 0; r < 16; ++r) sa[r] = 0.f;
+      static_for<0, NKK / RK>([&](auto KH) __attribute__((always_inline)) {
+        constexpr int kk0 = RK * decltype(KH)::value;
+        bf16x8_t a[RK];
+        T::template read_k<RK, kk0, off>(Qs, fk, a);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) {
-        const bf16x8_t a = T::frag_k(Qs + st * 32 * HD, fk, kk, g);
-        sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[kk], sa, 0, 0, 0);
-        const bf16x8_t b = T::frag_k(Os + st * 32 * HD, fk, kk, g);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, vf[kk], dp, 0, 0, 0);
-      }
-      float pv[16], ds[16];
+        for (int i = 0; i < RK; ++i) sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], kf[kk0 + i], sa, 0, 0, 0);
+      });
+      float pv[16];
 #pragma unroll
       for (int mm = 0; mm < 2; ++mm) {
         const int qo = st * 32 + 16 * mm + 8 * g;    // first of the 8 queries in registers 8*mm .. 8*mm+7
         const float4 la = *(const float4 *)(lse_s + qo), lb = *(const float4 *)(lse_s + qo + 4);
-        const float4 da = *(const float4 *)(d_s + qo), db = *(const float4 *)(d_s + qo + 4);
         const float ll[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
-        const float dd[8] = {da.x, da.y, da.z, da.w, db.x, db.y, db.z, db.w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int r = 8 * mm + e;
-          float p = __builtin_amdgcn_exp2f(fmaf(sa[r], sc, -1.4426950408889634f * ll[e]));
-          if (need_mask) {
-            const int qq = qb + qo + e;
-            if (!(qq >= ki && qq < L && ki < L) || (qq >= xhi && ki >= xlo && ki < xhi)) p = 0.f;
-          }
-          pv[r] = p;
-          ds[r] = p * (dp[r] - dd[e]) * rs;
+        for (int e = 0; e < 8; ++e) pv[8 * mm + e] = __builtin_amdgcn_exp2f(fmaf(sa[8 * mm + e], sc, -1.4426950408889634f * ll[e]));
+      }
+      // queries that do not see this lane's key: before it, past the sequence, behind the excluded rectangle.  (The
+      // query of register r minus that of this lane's first register is a constant.)
+      if (qb < kw0 + 31 || qb + TB > L || kw0 + 32 > L) {
+        const int first = ki < L ? ki - qb - 8 * g : TB, n_q = L - qb - 8 * g;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int c = st * 32 + 16 * (r >> 3) + (r & 7);
+          pv[r] = ((c < first) | (c >= n_q)) ? 0.f : pv[r];
         }
       }
+      if (kw0 + 31 >= xlo && kw0 < xhi && qb + TB > xhi) {
+        const int hi = ki >= xlo && ki < xhi ? xhi - qb - 8 * g : 2 * TB;
 #pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        const bf16x8_t pf = pack8(pv + 8 * mm), dsf = pack8(ds + 8 * mm);
+        for (int r = 0; r < 16; ++r) pv[r] = st * 32 + 16 * (r >> 3) + (r & 7) >= hi ? 0.f : pv[r];
+      }
+      {
+        const bf16x8_t pf[2] = {pack8(pv), pack8(pv + 8)};
 #pragma unroll
         for (int t = 0; t < NOT; ++t) {
-          const bf16x8_t a = T::frag_t(Os, ft[t], 2 * st + mm);
-          dva[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf, dva[t], 0, 0, 0);
-          const bf16x8_t b = T::frag_t(Qs, ft[t], 2 * st + mm);
-          dka[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, dsf, dka[t], 0, 0, 0);
+          bf16x8_t a[2];
+          T::template read_t<2, 2 * st>(Os, ft, t, a);
+#pragma unroll
+          for (int mm = 0; mm < 2; ++mm) dva[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mm], pf[mm], dva[t], 0, 0, 0);
         }
       }
-    }
+      f32x16_t dp;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dp[r] = 0.f;
+      static_for<0, NKK / RK>([&](auto KH) __attribute__((always_inline)) {
+        constexpr int kk0 = RK * decltype(KH)::value;
+        bf16x8_t b[RK];
+        T::template read_k<RK, kk0, off>(Os, fk, b);
+#pragma unroll
+        for (int i = 0; i < RK; ++i) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[i], vf[kk0 + i], dp, 0, 0, 0);
+      });
+#pragma unroll
+      for (int mm = 0; mm < 2; ++mm) {
+        const int qo = st * 32 + 16 * mm + 8 * g;
+        const float4 da = *(const float4 *)(d_s + qo), db = *(const float4 *)(d_s + qo + 4);
+        const float dd[8] = {da.x, da.y, da.z, da.w, db.x, db.y, db.z, db.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pv[8 * mm + e] *= (dp[8 * mm + e] - dd[e]) * rs;
+      }
+      const bf16x8_t dsf[2] = {pack8(pv), pack8(pv + 8)};
+#pragma unroll
+      for (int t = 0; t < NOT; ++t) {
+        bf16x8_t b[2];
+        T::template read_t<2, 2 * st>(Qs, ft, t, b);
+#pragma unroll
+        for (int mm = 0; mm < 2; ++mm) dka[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[mm], dsf[mm], dka[t], 0, 0, 0);
+      }
+    });
   }
   if (ki < L) {
     bf16_t *row = dqkv + (size_t)(r0 + ki) * (qld + 2 * kld) + qld + (size_t)kvh * HD;     // dk of this kv head; dv sits kld further

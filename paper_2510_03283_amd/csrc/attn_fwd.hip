@@ -43,9 +43,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
   constexpr int QB = 32 * NW;
   constexpr int NKK = HD / 16;     // MFMA k-steps over the head dimension
   constexpr int NOT = HD / 32;     // 32-row tiles of O^T
+  constexpr int RK = HD == 128 && SPLIT ? 2 : 4;   // K operands read at a time (what 256 registers leave room for)
   using T = Tile<KB, HD, 64 * NW>;
   constexpr int STAGE = 2 * NT * T::ELEMS;         // K (hi, lo), V (hi, lo)
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+  extern __shared__ __align__(1024) unsigned char smem_raw[];
   bf16_t *lds = (bf16_t *)smem_raw;                // [2][STAGE]
 
   // blocks are dealt to the XCDs round-robin: block x takes head (x % Hkv) * group + x / Hkv, so the query heads
@@ -54,7 +55,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
   const int r0 = seg[s] - row_base, L = seg[s + 1] - seg[s];
   const int q0 = (gridDim.z - 1 - blockIdx.z) * QB;      // long tiles first
   if (q0 >= L) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, j = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, j = lane & 31;
   const int qw0 = q0 + wave * 32;                        // first query of this wave
   const int qi = qw0 + j;                                // this lane's query (may be >= L: computed, not stored)
   const size_t qld = (size_t)Hq * HD, kld = (size_t)Hkv * HD;
@@ -69,20 +70,26 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
   // optional excluded rectangle: queries >= xhi do not see keys xlo .. xhi-1 (a preference pair stored
   // as prompt | chosen | rejected: the rejected response skips the chosen one)
   const int xlo = excl_lo ? excl_lo[s] : L, xhi = excl_lo ? excl_hi[s] : L;
+  const uint32_t lane_off = T::lane_offset(kld);
+  int32_t blk[PAGED ? T::NI : 1];                        // PAGED: block ids of the rows this lane loads of the next tile
+  auto next_entries = [&](int it) {
+    if constexpr (PAGED) T::paged_entries(pg.block_tables + (size_t)s * pg.max_blocks, pg.bshift, it * KB, nkeys, blk);
+  };
   auto issue_tile = [&](int it) {
     bf16_t *S = lds + (it & 1) * STAGE;
     if constexpr (PAGED) {
-      const int32_t *bt = pg.block_tables + (size_t)s * pg.max_blocks;
-      T::issue_paged(pg.cache_k, bt, pg.bshift, Hkv, kvh, pg.num_blocks, it * KB, nkeys, S);
-      T::issue_paged(pg.cache_v, bt, pg.bshift, Hkv, kvh, pg.num_blocks, it * KB, nkeys, S + T::ELEMS);
+      T::issue_paged(pg.cache_k, blk, pg.bshift, Hkv, kvh, pg.num_blocks, it * KB, S);
+      T::issue_paged(pg.cache_v, blk, pg.bshift, Hkv, kvh, pg.num_blocks, it * KB, S + T::ELEMS);
+      next_entries(it + 1);
     } else {
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        T::issue(kbase[t], kld, it * KB, L, S + t * T::ELEMS);
-        T::issue(vbase[t], kld, it * KB, L, S + (NT + t) * T::ELEMS);
+        T::issue(kbase[t], kld, it * KB, L, lane_off, S + t * T::ELEMS);
+        T::issue(vbase[t], kld, it * KB, L, lane_off, S + (NT + t) * T::ELEMS);
       }
     }
   };
+  next_entries(0);
   issue_tile(0);
 
   // Q fragments (B operand of S^T): 8 consecutive head-dim elements per k-step, kept in registers
@@ -101,10 +108,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
 
   // lane's K row inside a 32-key sub-tile: MFMA row j reads tile row swap23(j), so that register
   // r = 8*mm + e of S^T holds key 16*mm + 8*g + e
-  const typename T::FragK fk = T::frag_k_init(swap23(j));
-  typename T::FragT fv[NOT];
-#pragma unroll
-  for (int t = 0; t < NOT; ++t) fv[t] = T::frag_t_init(32 * t, lane);
+  const uint32_t fk = T::frag_k_lane(swap23(j), g);
+  const typename T::FragT fv = T::frag_t_init(lane);
 
   f32x16_t oacc[NOT];
 #pragma unroll
@@ -121,34 +126,47 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
     const int kb = it * KB;
     if (kb > pfx + qw0 + 31) continue;                   // every key of the tile is in this wave's future
     if (qw0 >= xhi && kb >= xlo && kb + KB <= xhi) continue;   // ... or inside the rectangle this wave must not see
-    const bf16_t *Kh = lds + (it & 1) * STAGE, *Kl = Kh + T::ELEMS, *Vh = Kh + NT * T::ELEMS, *Vl = Vh + T::ELEMS;
+    const uint32_t Kh = T::lds_addr(lds + (it & 1) * STAGE), Kl = Kh + T::ELEMS * 2, Vh = Kh + NT * T::ELEMS * 2, Vl = Vh + T::ELEMS * 2;
 
     // ---- S^T = K Q^T for the two 32-key sub-tiles; lane owns query j, register r owns a key
     f32x16_t sacc[2];
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
+    for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sacc[st][r] = 0.f;
+    static_for<0, 2>([&](auto ST) __attribute__((always_inline)) {
+      static_for<0, NKK / RK>([&](auto KH) __attribute__((always_inline)) {
+        constexpr int st = decltype(ST)::value, kk0 = RK * decltype(KH)::value, off = st * 32 * HD * 2;
+        bf16x8_t a[RK];
+        T::template read_k<RK, kk0, off>(Kh, fk, a);
 #pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) {
-        const bf16x8_t a = T::frag_k(Kh + st * 32 * HD, fk, kk, g);
-        sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[0][kk], sacc[st], 0, 0, 0);
-        if constexpr (SPLIT) {
-          sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[1][kk], sacc[st], 0, 0, 0);
-          const bf16x8_t al = T::frag_k(Kl + st * 32 * HD, fk, kk, g);
-          sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, qf[0][kk], sacc[st], 0, 0, 0);
+        for (int i = 0; i < RK; ++i) {
+          sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], qf[0][kk0 + i], sacc[st], 0, 0, 0);
+          if constexpr (SPLIT) sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], qf[1][kk0 + i], sacc[st], 0, 0, 0);
         }
-      }
-    }
-    // ---- mask (only tiles that touch the diagonal or the end of the sequence), online soft-max
-    if (kb + KB - 1 > pfx + qw0 || kb + KB > nkeys || (qw0 + 31 >= xhi && kb < xhi && kb + KB > xlo)) {
+        if constexpr (SPLIT) {
+          bf16x8_t al[RK];
+          T::template read_k<RK, kk0, off>(Kl, fk, al);
+#pragma unroll
+          for (int i = 0; i < RK; ++i) sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], qf[0][kk0 + i], sacc[st], 0, 0, 0);
+        }
+      });
+    });
+    // ---- mask (only tiles that touch the diagonal or the end of the sequence), online soft-max.  Key of register
+    // (st, r) minus that of this lane's first register is a constant: one comparison each.
+    if (kb + KB - 1 > pfx + qw0 || kb + KB > nkeys) {
+      const int last = min(pfx + qi, nkeys - 1) - kb - 8 * g;
 #pragma unroll
       for (int st = 0; st < 2; ++st)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = kb + st * 32 + 16 * (r >> 3) + 8 * g + (r & 7);
-          if (!(key <= pfx + qi && key < nkeys) || (qi >= xhi && key >= xlo && key < xhi)) sacc[st][r] = -INFINITY;
-        }
+        for (int r = 0; r < 16; ++r) sacc[st][r] = st * 32 + 16 * (r >> 3) + (r & 7) > last ? -INFINITY : sacc[st][r];
+    }
+    if (qw0 + 31 >= xhi && kb < xhi && kb + KB > xlo) {
+      const int lo = xlo - kb - 8 * g, n_ex = qi >= xhi ? xhi - xlo : 0;
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sacc[st][r] = (uint32_t)(st * 32 + 16 * (r >> 3) + (r & 7) - lo) < (uint32_t)n_ex ? -INFINITY : sacc[st][r];
     }
     float mx = sacc[0][0];
 #pragma unroll
@@ -179,24 +197,31 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
         if constexpr (SPLIT) pf[1][st][mm] = as_bf8(make_uint4(wl[0], wl[1], wl[2], wl[3]));
       }
     l_run = l_run * alpha + ps;
-    // ---- O^T = alpha O^T + V^T P^T
+    // ---- O^T = alpha O^T + V^T P^T (alpha is 1 for every query of the wave in most tiles)
+    if (__any(alpha != 1.0f)) {
 #pragma unroll
-    for (int t = 0; t < NOT; ++t) {
+      for (int t = 0; t < NOT; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[t][r] *= alpha;
-#pragma unroll
-      for (int st = 0; st < 2; ++st)
-#pragma unroll
-        for (int mm = 0; mm < 2; ++mm) {
-          const bf16x8_t a = T::frag_t(Vh, fv[t], 2 * st + mm);
-          oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[0][st][mm], oacc[t], 0, 0, 0);
-          if constexpr (SPLIT) {
-            oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[1][st][mm], oacc[t], 0, 0, 0);
-            const bf16x8_t al = T::frag_t(Vl, fv[t], 2 * st + mm);
-            oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, pf[0][st][mm], oacc[t], 0, 0, 0);
-          }
-        }
+        for (int r = 0; r < 16; ++r) oacc[t][r] *= alpha;
     }
+#pragma unroll
+    for (int t = 0; t < NOT; ++t)
+      static_for<0, 4 / RK>([&](auto KH) __attribute__((always_inline)) {
+        constexpr int k0 = RK * decltype(KH)::value;      // operand i of P: keys 16 (k0 + i) .. + 15
+        bf16x8_t a[RK];
+        T::template read_t<RK, k0>(Vh, fv, t, a);
+#pragma unroll
+        for (int i = 0; i < RK; ++i) {
+          oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], pf[0][(k0 + i) >> 1][(k0 + i) & 1], oacc[t], 0, 0, 0);
+          if constexpr (SPLIT) oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], pf[1][(k0 + i) >> 1][(k0 + i) & 1], oacc[t], 0, 0, 0);
+        }
+        if constexpr (SPLIT) {
+          bf16x8_t al[RK];
+          T::template read_t<RK, k0>(Vl, fv, t, al);
+#pragma unroll
+          for (int i = 0; i < RK; ++i) oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], pf[0][(k0 + i) >> 1][(k0 + i) & 1], oacc[t], 0, 0, 0);
+        }
+      });
   }
 
   // ---- normalise and store: lane owns query qi, rows 32t + 8(r/4) + 4g + r%4 of O^T

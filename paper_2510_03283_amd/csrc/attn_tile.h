@@ -14,7 +14,17 @@
 #pragma once
 #include "common.h"
 
+#include <type_traits>
+
 namespace attn {
+
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
 
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(8))) short s16x8_t;
@@ -49,25 +59,37 @@ struct Tile {
   }
 
   // Rows row0 .. row0+ROWS-1 of src (row pitch ld elements; src points at row 0, column 0 of the
-  // head); rows >= row_end read zeros.
-  static __device__ __forceinline__ void issue(const bf16_t *src, size_t ld, int row0, int row_end, bf16_t *S) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // head); rows >= row_end read zeros.  The loads go through a buffer resource that spans the tile's existing rows (its
+  // range check is the zero fill): beyond lane_offset, kept from tile to tile, an address costs no vector arithmetic.
+  static constexpr int RSTEP = NTHR / CPR;           // rows between two loads of a lane
+  static_assert(RSTEP % 16 == 0, "the swizzle of a lane's rows must not change from load to load");
+  static __device__ __forceinline__ uint32_t lane_offset(size_t ld) {
+    const int lr = threadIdx.x / CPR, c = (threadIdx.x % CPR) ^ swz(lr);
+    return (uint32_t)(lr * ld * 2) + c * 16;
+  }
+  static __device__ __forceinline__ void issue(const bf16_t *src, size_t ld, int row0, int row_end, uint32_t lane_off, bf16_t *S) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rows = min(row_end - row0, ROWS);
+    const auto q = __builtin_amdgcn_make_buffer_rsrc((void *)(src + (size_t)row0 * ld), 0, (int)(((rows - 1) * ld + HD) * 2), 0x00020000);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int q = wave + (NTHR / 64) * i;
-      const int chunk = q * 64 + lane;
-      const int lr = chunk / CPR, c = (chunk % CPR) ^ swz(lr);
-      const int gr = row0 + lr;
-      const bf16_t *p = gr < row_end ? src + (size_t)gr * ld + c * 8 : (const bf16_t *)&zero16;
-      __builtin_amdgcn_global_load_lds((gbl_void_t *)p, (lds_void_t *)(S + q * 512), 16, 0, 0);
-    }
+    for (int i = 0; i < NI; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(q, (lds_void_t *)(S + (wave + (NTHR / 64) * i) * 512), 16, (int)lane_off, (int)(i * RSTEP * ld * 2), 0, 0);
   }
 
   // Same tile, but row p (a token position of one request) is fetched from a paged cache
   // [blocks, Hkv, B, HD]: block id from the request's block table, B = 1 << bshift.  Positions at or
-  // beyond row_end, and block ids outside [0, num_blocks), read zeros.
-  static __device__ __forceinline__ void issue_paged(const bf16_t *cache, const int32_t *bt, int bshift, int Hkv, int kvh,
-                                                     long long num_blocks, int row0, int row_end, bf16_t *S) {
+  // beyond row_end, and block ids outside [0, num_blocks), read zeros.  The entries of this lane's rows are read
+  // (paged_entries) a tile time ahead of the loads that need them.
+  static __device__ __forceinline__ void paged_entries(const int32_t *bt, int bshift, int row0, int row_end, int32_t (&blk)[NI]) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int pos = row0 + ((wave + (NTHR / 64) * i) * 64 + lane) / CPR;
+      blk[i] = pos < row_end ? bt[pos >> bshift] : -1;
+    }
+  }
+  static __device__ __forceinline__ void issue_paged(const bf16_t *cache, const int32_t (&blk)[NI], int bshift, int Hkv, int kvh,
+                                                     long long num_blocks, int row0, bf16_t *S) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -75,39 +97,93 @@ struct Tile {
       const int chunk = q * 64 + lane;
       const int lr = chunk / CPR, c = (chunk % CPR) ^ swz(lr);
       const int pos = row0 + lr;
-      const bf16_t *p = (const bf16_t *)&zero16;
-      if (pos < row_end) {
-        const long long blk = bt[pos >> bshift];
-        if (blk >= 0 && blk < num_blocks)
-          p = cache + ((((size_t)blk * Hkv + kvh) << bshift) + (pos & ((1 << bshift) - 1))) * HD + c * 8;
-      }
+      const bf16_t *p = blk[i] >= 0 && blk[i] < num_blocks
+                            ? cache + ((((size_t)blk[i] * Hkv + kvh) << bshift) + (pos & ((1 << bshift) - 1))) * HD + c * 8
+                            : (const bf16_t *)&zero16;
       __builtin_amdgcn_global_load_lds((gbl_void_t *)p, (lds_void_t *)(S + q * 512), 16, 0, 0);
     }
   }
 
-  struct FragK { int base, sw; };
-  static __device__ __forceinline__ FragK frag_k_init(int row) { return FragK{row * HD, swz(row)}; }
-  // head-dim elements kk*16 + 8*half .. +7 of the row
-  static __device__ __forceinline__ bf16x8_t frag_k(const bf16_t *S, const FragK &f, int kk, int half) {
-    return *(const bf16x8_t *)(S + f.base + (((2 * kk + half) ^ f.sw) << 3));
+  // Operands are read by blocks of asm that end with their wait.  Written with the builtin, a transposing read makes the
+  // compiler wait for every direct global->LDS load in flight first (it does not know that they fill the other
+  // stage), so the prefetch of the next tile ends where the current one is multiplied; plain reads it hands out one
+  // or two at a time between the products.  Addresses are LDS byte addresses.
+  static __device__ __forceinline__ uint32_t lds_addr(const bf16_t *S) { return (uint32_t)(uintptr_t)(lds_void_t *)S; }
+  // chunk (2 kk + half) ^ sw of the row sits at lane address ^ 32 kk: 2 kk has no bit in common with half, a row starts at
+  // a multiple of its CPR chunks and a tile at a multiple of 256 bytes.  (The flip is applied behind the addition of the
+  // tile: flipped lane addresses are invariants that the compiler would keep in a register each.)
+  static __device__ __forceinline__ uint32_t frag_k_lane(int row, int half) { return (uint32_t)(row * HD * 2 + ((half ^ swz(row)) << 4)); }
+  // head-dim elements (KK0 + i) * 16 + 8 * half .. +7, i < N (2 or 4), of the row, OFF bytes into the tile
+  template <int N, int KK0, int OFF>
+  static __device__ __forceinline__ void read_k(uint32_t tile, uint32_t lane, bf16x8_t (&f)[N]) {
+    static_assert(N == 2 || N == 4, "two or four operands");
+    __builtin_amdgcn_sched_barrier(0);      // (hoisted over the products in front of them, the reads only take registers)
+    const uint32_t a0 = (tile + lane) ^ (32 * KK0), a1 = a0 ^ 32, a2 = a0 ^ 64, a3 = a1 ^ 64;
+    if constexpr (N == 4)
+      asm volatile("ds_read_b128 %0, %4 offset:%8\n\t"
+                   "ds_read_b128 %1, %5 offset:%8\n\t"
+                   "ds_read_b128 %2, %6 offset:%8\n\t"
+                   "ds_read_b128 %3, %7 offset:%8\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[N - 2]), "=&v"(f[N - 1])
+                   : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "i"(OFF)
+                   : "memory");
+    else
+      asm volatile("ds_read_b128 %0, %2 offset:%4\n\t"
+                   "ds_read_b128 %1, %3 offset:%4\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : "=&v"(f[0]), "=&v"(f[1])
+                   : "v"(a0), "v"(a1), "i"(OFF)
+                   : "memory");
   }
 
-  struct FragT { int a0, a1; };
-  // operand row = head-dim index r0 + lane%32 (r0 multiple of 32)
-  static __device__ __forceinline__ FragT frag_t_init(int r0, int lane) {
+  // operand row = head-dim index 32 t + lane%32.  Tile t reads chunk 4 t + (0..3), whose bits do not overlap, so its
+  // addresses are those of t = 0 with 64 t flipped.
+  struct FragT { uint32_t a0, a1; };
+  static __device__ __forceinline__ FragT frag_t_init(int lane) {
     const int grp = lane >> 4, j = lane & 15;
     const int row = 8 * (grp >> 1) + (j >> 2);                       // + 16*kk (+4 for the second read)
-    const int c = (r0 >> 3) + 2 * (grp & 1) + ((j & 3) >> 1);
+    const int c = 2 * (grp & 1) + ((j & 3) >> 1);
     FragT f;
-    f.a0 = row * HD + ((c ^ swz(row)) << 3) + 4 * (j & 1);
-    f.a1 = (row + 4) * HD + ((c ^ swz(row + 4)) << 3) + 4 * (j & 1);
+    f.a0 = (row * HD + ((c ^ swz(row)) << 3) + 4 * (j & 1)) * 2;
+    f.a1 = ((row + 4) * HD + ((c ^ swz(row + 4)) << 3) + 4 * (j & 1)) * 2;
     return f;
   }
-  static __device__ __forceinline__ bf16x8_t frag_t(const bf16_t *S, const FragT &f, int kk) {
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(S + f.a0 + kk * 16 * HD));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(S + f.a1 + kk * 16 * HD));
-    const s16x8_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8_t, v);
+  // the N (2 or 4) operands of tile rows 16 (KK0 + i) .. + 15, i < N
+  template <int N, int KK0>
+  static __device__ __forceinline__ void read_t(uint32_t tile, const FragT &f, int t, bf16x8_t (&out)[N]) {
+    typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    constexpr int RS = 16 * HD * 2;      // bytes of 16 rows
+    const uint32_t a0 = (tile + KK0 * RS + f.a0) ^ (64 * t), a1 = (tile + KK0 * RS + f.a1) ^ (64 * t);
+    u32x2 l[N], h[N];
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (N == 4) {
+      asm volatile("ds_read_b64_tr_b16 %0, %8\n\t"
+                   "ds_read_b64_tr_b16 %1, %9\n\t"
+                   "ds_read_b64_tr_b16 %2, %8 offset:%10\n\t"
+                   "ds_read_b64_tr_b16 %3, %9 offset:%10\n\t"
+                   "ds_read_b64_tr_b16 %4, %8 offset:%11\n\t"
+                   "ds_read_b64_tr_b16 %5, %9 offset:%11\n\t"
+                   "ds_read_b64_tr_b16 %6, %8 offset:%12\n\t"
+                   "ds_read_b64_tr_b16 %7, %9 offset:%12\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : "=&v"(l[0]), "=&v"(h[0]), "=&v"(l[1]), "=&v"(h[1]), "=&v"(l[2]), "=&v"(h[2]), "=&v"(l[3]), "=&v"(h[3])
+                   : "v"(a0), "v"(a1), "i"(RS), "i"(2 * RS), "i"(3 * RS)
+                   : "memory");
+    } else {
+      static_assert(N == 2, "two or four operands");
+      asm volatile("ds_read_b64_tr_b16 %0, %4\n\t"
+                   "ds_read_b64_tr_b16 %1, %5\n\t"
+                   "ds_read_b64_tr_b16 %2, %4 offset:%6\n\t"
+                   "ds_read_b64_tr_b16 %3, %5 offset:%6\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : "=&v"(l[0]), "=&v"(h[0]), "=&v"(l[1]), "=&v"(h[1])
+                   : "v"(a0), "v"(a1), "i"(RS)
+                   : "memory");
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) out[i] = __builtin_bit_cast(bf16x8_t, u32x4{l[i][0], l[i][1], h[i][0], h[i][1]});
   }
 };
 
