@@ -42,29 +42,61 @@ struct AdamW {
   }
 };
 
-// Four elements per thread with 16-byte accesses (HBM-bound: 26-30 bytes per element); the last
-// n % 4 elements are done one by one by the first threads.
-template <bool PBF16>
+// HBM-bound: 26 - 30 bytes per element.  A block owns ADAM_U x 4 KB adjacent bytes of every fp32 stream and a thread asks for
+// all its operands before the first is used; the last n % 4 elements are done one by one by the first threads.  (A loop over 8192
+// blocks, one group of four per turn: 966 us for 131 M elements with an fp32 master copy, 263 us for 45 M; now 668 and 231 us,
+// 5.9 TB/s.)
+constexpr int ADAM_U = 2;
+typedef float f32x4_s __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2_s __attribute__((ext_vector_type(2)));
+
+template <bool NT, typename T>
+__device__ __forceinline__ T ld_stream(const T *p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, typename T>
+__device__ __forceinline__ void st_stream(T v, T *p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+template <bool PBF16, bool NT>
 __global__ __launch_bounds__(256) void adamw_kernel(void *__restrict__ param, float *__restrict__ master, const float *__restrict__ grad,
                                                     float *__restrict__ m, float *__restrict__ v, size_t n, const AdamW a) {
-  const size_t n4 = n / 4, stride = (size_t)gridDim.x * 256;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
-    const float4 g = ((const float4 *)grad)[i];
-    float4 mi = ((float4 *)m)[i], vi = ((float4 *)v)[i], p;
-    if (master) p = ((const float4 *)master)[i];
-    else if constexpr (PBF16) {
-      const uint2 r = ((const uint2 *)param)[i];
-      p = make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u), __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
-    } else p = ((const float4 *)param)[i];
-    p.x = a.step(g.x, mi.x, vi.x, p.x);
-    p.y = a.step(g.y, mi.y, vi.y, p.y);
-    p.z = a.step(g.z, mi.z, vi.z, p.z);
-    p.w = a.step(g.w, mi.w, vi.w, p.w);
-    ((float4 *)m)[i] = mi;
-    ((float4 *)v)[i] = vi;
-    if (master) ((float4 *)master)[i] = p;
-    if constexpr (PBF16) ((uint2 *)param)[i] = make_uint2(pack2(f2bf(p.x), f2bf(p.y)), pack2(f2bf(p.z), f2bf(p.w)));
-    else ((float4 *)param)[i] = p;
+  const size_t n4 = n / 4, stride = (size_t)gridDim.x * 256 * ADAM_U;
+  for (size_t base = (size_t)blockIdx.x * 256 * ADAM_U + threadIdx.x; base < n4; base += stride) {
+    f32x4_s g[ADAM_U], mi[ADAM_U], vi[ADAM_U], p[ADAM_U];
+#pragma unroll
+    for (int u = 0; u < ADAM_U; ++u) {
+      const size_t i = base + u * 256;
+      if (i >= n4) continue;
+      g[u] = ld_stream<NT>((const f32x4_s *)grad + i);
+      mi[u] = ld_stream<NT>((const f32x4_s *)m + i);
+      vi[u] = ld_stream<NT>((const f32x4_s *)v + i);
+      if (master) p[u] = ld_stream<NT>((const f32x4_s *)master + i);
+      else if constexpr (PBF16) {
+        const u32x2_s r = ld_stream<NT>((const u32x2_s *)param + i);
+        p[u] = f32x4_s{__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u), __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u)};
+      } else p[u] = ld_stream<NT>((const f32x4_s *)param + i);
+    }
+#pragma unroll
+    for (int u = 0; u < ADAM_U; ++u) {
+      const size_t i = base + u * 256;
+      if (i >= n4) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float mj = mi[u][j], vj = vi[u][j];
+        p[u][j] = a.step(g[u][j], mj, vj, p[u][j]);
+        mi[u][j] = mj;
+        vi[u][j] = vj;
+      }
+      st_stream<NT>(mi[u], (f32x4_s *)m + i);
+      st_stream<NT>(vi[u], (f32x4_s *)v + i);
+      if (master) st_stream<NT>(p[u], (f32x4_s *)master + i);
+      if constexpr (PBF16) st_stream<NT>(u32x2_s{pack2(f2bf(p[u].x), f2bf(p[u].y)), pack2(f2bf(p[u].z), f2bf(p[u].w))}, (u32x2_s *)param + i);
+      else st_stream<NT>(p[u], (f32x4_s *)param + i);
+    }
   }
   const size_t i = n4 * 4 + (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) {
@@ -88,12 +120,15 @@ hipError_t launch_argmax_rows(const float *logits, int rows, int V, int32_t *out
 hipError_t launch_adamw(void *param, bool param_bf16, float *master, const float *grad, float *m, float *v, size_t n, float lr,
                         float b1, float b2, float eps, float wd, float c1, float c2, hipStream_t st) {
   if (n == 0) return hipSuccess;
-  const size_t want = (n / 4 + 255) / 256 + 1;
-  const unsigned blocks = (unsigned)(want < 8192 ? want : 8192);
+  const size_t want = (n / 4 + 256 * ADAM_U - 1) / (256 * ADAM_U) + 1;
+  const unsigned blocks = (unsigned)(want < (1u << 20) ? want : (1u << 20));
   const AdamW a{lr, b1, b2, eps, wd, c1, c2};
   const uintptr_t al = (uintptr_t)param | (uintptr_t)master | (uintptr_t)grad | (uintptr_t)m | (uintptr_t)v;
   if (al & 15) return hipErrorInvalidValue;       // 16-byte accesses
-  if (param_bf16) hipLaunchKernelGGL(adamw_kernel<true>, dim3(blocks), dim3(256), 0, st, param, master, grad, m, v, n, a);
-  else hipLaunchKernelGGL(adamw_kernel<false>, dim3(blocks), dim3(256), 0, st, param, master, grad, m, v, n, a);
+  // Streams of more than four times the 256 MB last-level cache are read and written past it: 131 M elements 734 -> 668 us, 45 M
+  // 247 -> 231; 17 M elements are better off cached where the step is repeated (67 against 85 us).
+  const bool nt = n * 28 > ((size_t)1 << 30);
+  auto *k = param_bf16 ? (nt ? adamw_kernel<true, true> : adamw_kernel<true, false>) : (nt ? adamw_kernel<false, true> : adamw_kernel<false, false>);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, param, master, grad, m, v, n, a);
   return hipGetLastError();
 }

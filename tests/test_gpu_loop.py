@@ -89,3 +89,32 @@ def test_adamw_steps(torch_mod, bf):
             B.mace_adamw_step(h, param, master, m, m, v, lr, b1, b2, eps, wd, 0)
     finally:
         B.mace_destroy(h)
+
+
+@pytest.mark.parametrize("bf,n", [(True, 1), (False, 3), (True, 2047), (True, 2053), (False, 4096 + 6), (True, 38_400_007), (False, 38_400_001)])
+def test_adamw_block_edges(torch_mod, bf, n):
+    """Sizes around a block's 2048 elements, with and without a tail, and past the size from which the streams bypass the
+    caches; with an fp32 master copy for bf16 parameters.  Bar as above: a few fp32 roundings of each term."""
+    import torch
+    from paper_2510_03283_amd import binding as B
+    h = B.mace_create(256, 4, 4, 64, 704, 2048, 1e-6, 1e4, B.MACE_BF16 if bf else B.MACE_F32)
+    try:
+        gen = torch.Generator(device="cuda").manual_seed(n)
+        master = 0.02 * torch.randn(n, generator=gen, device="cuda")
+        param = master.to(torch.bfloat16) if bf else master
+        g = 1e-3 * torch.randn(n, generator=gen, device="cuda")
+        m = 1e-3 * torch.randn(n, generator=gen, device="cuda"); v = 1e-6 * torch.rand(n, generator=gen, device="cuda")
+        lr, b1, b2, eps, wd, t = 1e-3, 0.9, 0.95, 1e-8, 0.1, 5
+        m64 = b1 * m.double() + (1 - b1) * g.double()
+        v64 = b2 * v.double() + (1 - b2) * g.double() ** 2
+        p64 = master.double()
+        p64 = p64 - lr * ((m64 / (1 - b1 ** t)) / ((v64 / (1 - b2 ** t)).sqrt() + eps) + wd * p64)
+        B.mace_adamw_step(h, param, master if bf else None, g, m, v, lr, b1, b2, eps, wd, t)
+        torch.cuda.synchronize()
+        assert (m.double() - m64).abs().max() <= 1e-6 * m64.abs().max()
+        assert (v.double() - v64).abs().max() <= 1e-6 * v64.abs().max()
+        assert (master.double() - p64).abs().max() <= 2e-6 * p64.abs().max() + 1e-9
+        if bf:
+            assert torch.equal(param, master.to(torch.bfloat16))
+    finally:
+        B.mace_destroy(h)
