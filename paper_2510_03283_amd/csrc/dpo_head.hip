@@ -171,40 +171,46 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(float *__restrict__ u, 
   }
 }
 
-// Single block.  Sequence sums in fp64 (fixed order, deterministic), then the pair terms:
+// Single block of 16 waves; a wave takes the pairs w, w + 16, ...  (Latency-bound: with the whole block on one sequence at a
+// time, every sequence cost nine barriers: 64 sequences of 512 rows 122 -> 23 us, 8 of 160 14.8 -> 7.0 us.)  Sequence sums in fp64 in a fixed order
+// (deterministic), then the pair terms:
 // z = beta((logp+ - ref+) - (logp- - ref-)), loss = softplus(-z), dloss_mean/dlogp+ = (sigmoid(z)-1) beta / n_pairs.
-__global__ __launch_bounds__(256) void dpo_pairs_kernel(const float *__restrict__ logp_t, const int32_t *ft_seq_offsets,
-                                                        const int32_t *prompt_lens, int n_seq, const float *ref_logp,
-                                                        float beta, float *logp_out, float *loss_per_pair,
-                                                        float *loss_mean, float *clpd, int32_t *win, float *dlogp) {
-  __shared__ double part[256];
-  __shared__ double seqsum[2];
-  __shared__ double total;
-  const int n_pairs = n_seq / 2;
-  if (threadIdx.x == 0) total = 0.0;
-  int base = 0;
-  for (int pr = 0; pr < n_pairs; ++pr) {
-    for (int q = 0; q < 2; ++q) {
-      const int s = 2 * pr + q;
-      const int n = (ft_seq_offsets[s + 1] - ft_seq_offsets[s]) - prompt_lens[s];
-      double a = 0.0;
-      for (int i = threadIdx.x; i < n; i += 256) a += (double)logp_t[base + i];
-      part[threadIdx.x] = a;
-      __syncthreads();
-      for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
-        __syncthreads();
-      }
-      if (threadIdx.x == 0) seqsum[q] = part[0];
-      __syncthreads();
-      base += n;
-    }
-    if (threadIdx.x == 0) {
-      const double lp = seqsum[0], lm = seqsum[1];
-      const double z = (double)beta * ((lp - (double)ref_logp[2 * pr]) - (lm - (double)ref_logp[2 * pr + 1]));
-      const double loss = fmax(-z, 0.0) + log1p(exp(-fabs(z)));
-      const double sig = 1.0 / (1.0 + exp(-z));
-      const double c = (sig - 1.0) * (double)beta / (double)n_pairs;
+// loss_mean adds the pair losses per wave and then over the waves, in fp64.  Sequence s starts at log-probability
+// ft_seq_offsets[s] - ft_seq_offsets[0] - sum of the prompts before it: each wave carries that sum along.
+constexpr int DPO_WAVES = 16;
+__device__ __forceinline__ double wave_sum_f64(double x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+
+__global__ __launch_bounds__(64 * DPO_WAVES) void dpo_pairs_kernel(const float *__restrict__ logp_t, const int32_t *ft_seq_offsets,
+                                                                   const int32_t *prompt_lens, int n_seq, const float *ref_logp,
+                                                                   float beta, float *logp_out, float *loss_per_pair,
+                                                                   float *loss_mean, float *clpd, int32_t *win, float *dlogp) {
+  __shared__ double total[DPO_WAVES];
+  const int n_pairs = n_seq / 2, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double mine = 0.0;
+  int seen = 0, prompts = 0;                     // prompts = rows of the prompts of sequences 0 .. seen - 1 (this lane's share)
+  for (int pr = w; pr < n_pairs; pr += DPO_WAVES) {
+    for (int s = seen + lane; s < 2 * pr; s += 64) prompts += prompt_lens[s];
+    seen = 2 * pr;
+    int before = prompts;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    const int o0 = ft_seq_offsets[2 * pr], o1 = ft_seq_offsets[2 * pr + 1], o2 = ft_seq_offsets[2 * pr + 2];
+    const int base = o0 - ft_seq_offsets[0] - before, na = o1 - o0 - prompt_lens[2 * pr], nb = o2 - o1 - prompt_lens[2 * pr + 1];
+    double lp = 0.0, lm = 0.0;
+    for (int i = lane; i < na; i += 64) lp += (double)logp_t[base + i];
+    for (int i = lane; i < nb; i += 64) lm += (double)logp_t[base + na + i];
+    lp = wave_sum_f64(lp);
+    lm = wave_sum_f64(lm);
+    const double z = (double)beta * ((lp - (double)ref_logp[2 * pr]) - (lm - (double)ref_logp[2 * pr + 1]));
+    const double loss = fmax(-z, 0.0) + log1p(exp(-fabs(z)));
+    const double sig = 1.0 / (1.0 + exp(-z));
+    const double c = (sig - 1.0) * (double)beta / (double)n_pairs;
+    mine += loss;
+    if (lane == 0) {
       logp_out[2 * pr] = (float)lp;
       logp_out[2 * pr + 1] = (float)lm;
       loss_per_pair[pr] = (float)loss;
@@ -212,11 +218,15 @@ __global__ __launch_bounds__(256) void dpo_pairs_kernel(const float *__restrict_
       if (win) win[pr] = (lp - lm) > 0.0 ? 1 : 0;
       dlogp[2 * pr] = (float)c;
       dlogp[2 * pr + 1] = (float)(-c);
-      total += loss;
     }
-    __syncthreads();
   }
-  if (threadIdx.x == 0) *loss_mean = n_pairs > 0 ? (float)(total / (double)n_pairs) : 0.f;
+  if (lane == 0) total[w] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int i = 0; i < DPO_WAVES; ++i) t += total[i];
+    *loss_mean = n_pairs > 0 ? (float)(t / (double)n_pairs) : 0.f;
+  }
 }
 
 }  // namespace
@@ -254,7 +264,7 @@ hipError_t launch_scale_rows(float *u, const bf16_t *n_hi, bf16_t *n_c, const in
 hipError_t launch_dpo_pairs(const float *logp_t, const int32_t *ft_seq_offsets, const int32_t *prompt_lens, int n_seq,
                             const float *ref_logp, float beta, float *logp_out, float *loss_per_pair, float *loss_mean,
                             float *clpd, int32_t *win, float *dlogp, hipStream_t st) {
-  hipLaunchKernelGGL(dpo_pairs_kernel, dim3(1), dim3(256), 0, st, logp_t, ft_seq_offsets, prompt_lens, n_seq, ref_logp, beta, logp_out, loss_per_pair, loss_mean, clpd, win, dlogp);
+  hipLaunchKernelGGL(dpo_pairs_kernel, dim3(1), dim3(64 * DPO_WAVES), 0, st, logp_t, ft_seq_offsets, prompt_lens, n_seq, ref_logp, beta, logp_out, loss_per_pair, loss_mean, clpd, win, dlogp);
   return hipGetLastError();
 }
 
