@@ -198,9 +198,9 @@ Saved plan_saved(const Dims &D, size_t Tf, Bump &s) {
   return S;
 }
 
-// Room for the partial results of products whose reduction is cut into slices (gemm_pick_splits).  One pool per stream
-// of a call: a partial result is read by the launch behind its product and gone.  What a product of these rows can ask
-// for, at most 256 MB.
+// Room for the partial results of products whose reduction is cut into slices (gemm_pick_splits): what a product of
+// these rows can ask for, at most 256 MB.  Two of them in a call, one for the caller's stream and one for the side stream
+// (room_for).
 struct PartPool {
   float *base;
   size_t floats;
@@ -427,7 +427,15 @@ int run_gemm(mace_ctx *h, int LA, int LB, GemmParams &p, hipStream_t st, const c
   }
   return MACE_OK;
 }
-int max_splits(const int *ks) { return std::max(ks[0], std::max(ks[1], ks[2])); }
+// Where a product on stream s puts its slices.  Two launches on different streams of a call are unordered from the fork to
+// the join, so they must not meet in one pool: `side` belongs to the side stream from the first fork to the join, and
+// outside that span (nothing in flight there, a later fork waits for what was issued here) to the caller's stream.  In
+// between a product of the caller's stream takes what the not yet consumed partial results `live` leave of `main`.
+PartPool room_for(const mace_ctx *h, hipStream_t s, const PartPool &main, const PartPool &side, const Parts &live = {}) {
+  if ((h->side && s == h->side) || h->n_fork == 0) return side;
+  const size_t used = live.p == main.base ? (size_t)live.n * live.stride : 0;
+  return PartPool{main.base + used, main.floats - used};
+}
 // A product with its reduction cut into slices where that pays: `plain` is `base` with fp32 output, no residual and no fused
 // epilogue.  On true it has been issued and out[g] holds the partial results of row group g (plain's ldc); otherwise nothing
 // has been issued and the caller launches `base`.  extra_us: what the consumer of the parts costs beyond that of `base`.
@@ -455,7 +463,9 @@ int run_gemm_parts(mace_ctx *h, int LA, int LB, const GemmParams &base, const Ge
 // by themselves, and a second resident GEMM only splits the CUs and the L2 between two working
 // sets (measured: 2.5 - 3 % slower at 12 K and 64 K rows of a 7B-class layer, 2 % faster at 1.5 K
 // and 3.5 K rows).
-int run_gemm_side(mace_ctx *h, int LA, int LB, GemmParams &p, const PartPool &pool, hipStream_t st, const char *where) {
+// live: partial results in `main` that a launch behind this one still reads.
+int run_gemm_side(mace_ctx *h, int LA, int LB, GemmParams &p, const PartPool &main, const PartPool &side, const Parts &live, hipStream_t st,
+                  const char *where) {
   long long M = 0, N = 0;
   for (int g = 0; g < p.n_mg; ++g) M += p.mg[g].M;
   for (int s = 0; s < p.n_ns; ++s) N += p.ns[s].N;
@@ -465,7 +475,7 @@ int run_gemm_side(mace_ctx *h, int LA, int LB, GemmParams &p, const PartPool &po
   bool done = false;
   GemmParams plain = p;
   plain.resid_kind = 0;
-  int rc = run_gemm_parts(h, LA, LB, p, plain, pool, 5.0, s2, where, part, done);
+  int rc = run_gemm_parts(h, LA, LB, p, plain, room_for(h, s2, main, side, live), 5.0, s2, where, part, done);
   if (done && rc == MACE_OK) {
     SumRange r[3];
     for (int g = 0; g < p.n_mg; ++g) r[g] = SumRange{part[g], p.resid_kind ? (const float *)p.mg[g].resid : nullptr, p.mg[g].c, part[g].stride};
@@ -1081,7 +1091,7 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(p, F.a_i, nullptr, L.t_qkv, nullptr, I.Ti, 1);
     gp_seg(p, L.aqkv_hi, L.aqkv_lo, 3 * LR, 0);
     Parts t_i, t_f;
-    TRY(run_adapter_product(h, p, I.Tf, I.Ti, 3 * LR, L.t_qkv, F.side_pool, s2, "lora t_qkv gemm", t_f, t_i));
+    TRY(run_adapter_product(h, p, I.Tf, I.Ti, 3 * LR, L.t_qkv, room_for(h, s2, F.pool, F.side_pool), s2, "lora t_qkv gemm", t_f, t_i));
     prof_mark(h, s2, T_MISC);
     HIP_TRY(launch_scale_split(t_i, (size_t)I.Ti * 3 * LR, lora->scale, L.tq_hi, nullptr, s2), "lora t_qkv split");
     HIP_TRY(launch_scale_split(t_f, (size_t)I.Tf * 3 * LR, lora->scale, S.tq, L.tq_lo, s2), "lora t_qkv split ft");
@@ -1153,7 +1163,7 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(p, F.o_i, nullptr, L.t_o, nullptr, I.Ti, 1);
     gp_seg(p, L.ao_hi, L.ao_lo, LR, 0);
     Parts t_i, t_f;
-    TRY(run_adapter_product(h, p, I.Tf, I.Ti, LR, L.t_o, F.side_pool, s2, "lora t_o gemm", t_f, t_i));
+    TRY(run_adapter_product(h, p, I.Tf, I.Ti, LR, L.t_o, room_for(h, s2, F.pool, F.side_pool), s2, "lora t_o gemm", t_f, t_i));
     prof_mark(h, s2, T_MISC);
     HIP_TRY(launch_scale_split(t_i, (size_t)I.Ti * LR, lora->scale, L.to_hi, nullptr, s2), "lora t_o split");
     HIP_TRY(launch_scale_split(t_f, (size_t)I.Tf * LR, lora->scale, S.to, L.to_lo, s2), "lora t_o split ft");
@@ -1350,7 +1360,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     p.resid_kind = acc;
     gp_group(p, B.dy_bf, nullptr, grads->w_down, grads->w_down, D.d, 1);
     gp_seg(p, S.hm, nullptr, D.F, 0);
-    TRY(run_gemm_side(h, 1, 1, p, B.side_pool, st, "dWd gemm"));
+    TRY(run_gemm_side(h, 1, 1, p, B.pool, B.side_pool, {}, st, "dWd gemm"));
   }
   // db = dG Wg + dU Wu ; dWg = dG^T b ; dWu = dU^T b
   Parts db = {B.db, 1, 0};
@@ -1374,7 +1384,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     if (grads->w_gate) gp_group(p, B.dgu, nullptr, grads->w_gate, grads->w_gate, D.F, 1);
     if (grads->w_up) gp_group(p, B.dgu + D.F, nullptr, grads->w_up, grads->w_up, D.F, 1);
     gp_seg(p, S.b, nullptr, D.d, 0);
-    TRY(run_gemm_side(h, 1, 1, p, B.side_pool, st, "dWg/dWu gemm"));
+    TRY(run_gemm_side(h, 1, 1, p, B.pool, B.side_pool, db, st, "dWg/dWu gemm"));
   }
   // RMSNorm (MLP) backward: dx1 = dy + ...
   prof_mark(h, st, T_RMSNORM);
@@ -1389,7 +1399,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     p.out_bf16 = 1;
     gp_group(p, B.dx1_bf, nullptr, L.dto, nullptr, Tf, 1);
     gp_seg(p, L.bo_hi, nullptr, LR, 0);
-    TRY(run_gemm_bf16_parts(h, p, B.side_pool, s2, "lora dt_o gemm"));
+    TRY(run_gemm_bf16_parts(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dt_o gemm"));
     if (s2 != st) prof_mark(h, s2, -1);
   }
   {
@@ -1415,7 +1425,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     p.resid_kind = acc;
     gp_group(p, B.dx1_bf, nullptr, grads->wo, grads->wo, D.d, 1);
     gp_seg(p, S.o, nullptr, D.qd, 0);
-    TRY(run_gemm_side(h, 1, 1, p, B.side_pool, st, "dWo gemm"));
+    TRY(run_gemm_side(h, 1, 1, p, B.pool, B.side_pool, {}, st, "dWo gemm"));
   }
   if (lora) {
     HIP_TRY(side_join(h, st), "join side stream");
@@ -1432,7 +1442,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       gp_group(p, B.dx1_bf, nullptr, L.dbo, nullptr, D.d, 1);
       gp_seg(p, S.to, nullptr, LR, 0);
       Parts gr;
-      TRY(run_adapter_grad(h, p, B.side_pool, s2, "lora dB_o gemm", gr));
+      TRY(run_adapter_grad(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dB_o gemm", gr));
       prof_mark(h, s2, T_MISC);
       HIP_TRY(launch_extract(gr, LR, 0, 0, D.d, lora->rank, 1.0f, lgrads->b_o, acc, s2), "lora dB_o");
       if (s2 != st) prof_mark(h, s2, -1);
@@ -1443,7 +1453,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       gp_group(p, L.dto, nullptr, L.dao, nullptr, LR, 1);
       gp_seg(p, S.o, nullptr, D.qd, 0);
       Parts gr;
-      TRY(run_adapter_grad(h, p, B.side_pool, s2, "lora dA_o gemm", gr));
+      TRY(run_adapter_grad(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dA_o gemm", gr));
       prof_mark(h, s2, T_MISC);
       HIP_TRY(launch_extract(gr, D.qd, 0, 0, lora->rank, D.qd, 1.0f, lgrads->a_o, acc, s2), "lora dA_o");
       if (s2 != st) prof_mark(h, s2, -1);
@@ -1469,7 +1479,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       p.out_bf16 = 1;
       gp_group(p, B.dqkv, nullptr, L.dtq, nullptr, Tf, 1);
       gp_seg(p, L.bblk_hi, nullptr, 3 * LR, 0);
-      TRY(run_gemm_bf16_parts(h, p, B.side_pool, s2, "lora dt_qkv gemm"));
+      TRY(run_gemm_bf16_parts(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dt_qkv gemm"));
       if (s2 != st) prof_mark(h, s2, -1);
     }
     {
@@ -1501,7 +1511,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
         gp_group(p, B.dqkv, nullptr, L.dbblk, nullptr, D.nqkv, 1);
         gp_seg(p, S.tq, nullptr, 3 * LR, 0);
         Parts gr;
-        TRY(run_adapter_grad(h, p, B.side_pool, s2, "lora dB_qkv gemm", gr));
+        TRY(run_adapter_grad(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dB_qkv gemm", gr));
         float *dst[3] = {lgrads->b_q, lgrads->b_k, lgrads->b_v};
         const int r0[3] = {0, D.qd, D.qd + D.kd}, nr[3] = {D.qd, D.kd, D.kd};
         for (int i = 0; i < 3; ++i)
@@ -1517,7 +1527,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
         gp_group(p, L.dtq, nullptr, L.daqkv, nullptr, 3 * LR, 1);
         gp_seg(p, S.a, nullptr, D.d, 0);
         Parts gr;
-        TRY(run_adapter_grad(h, p, B.side_pool, s2, "lora dA_qkv gemm", gr));
+        TRY(run_adapter_grad(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dA_qkv gemm", gr));
         float *dst[3] = {lgrads->a_q, lgrads->a_k, lgrads->a_v};
         for (int i = 0; i < 3; ++i)
           if (dst[i]) {
@@ -1534,7 +1544,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       if (grads->wk) gp_group(p, as[1], nullptr, grads->wk, grads->wk, D.kd, 1);
       if (grads->wv) gp_group(p, as[2], nullptr, grads->wv, grads->wv, D.kd, 1);
       gp_seg(p, S.a, nullptr, D.d, 0);
-      TRY(run_gemm_side(h, 1, 1, p, B.side_pool, st, "dWqkv gemm"));
+      TRY(run_gemm_side(h, 1, 1, p, B.pool, B.side_pool, da, st, "dWqkv gemm"));
     }
   }
   // RMSNorm (attention) backward: dx = dx1 + ...
@@ -1678,7 +1688,7 @@ static int dpo_impl(mace_handle_t h, const float *h_ft, const void *g_final, con
     p.resid_kind = acc;
     gp_group(p, P.dl, nullptr, dw_lm, dw_lm, D.V, 1);
     gp_seg(p, n_c, nullptr, D.d, 0);
-    TRY(run_gemm_side(h, 1, 1, p, PartPool{}, st, "dE gemm"));
+    TRY(run_gemm_side(h, 1, 1, p, {}, {}, {}, st, "dE gemm"));
   }
   if (dh_ft || dg_final) {
     const int n_part = Ri < DG_PARTS ? Ri : DG_PARTS;

@@ -1,0 +1,131 @@
+"""Launch decisions, stream order and buffer extents of the library on a machine without a GPU: its host code is linked
+against a HIP runtime that only records (launch_recorder.cpp), and the recorded launches are checked here."""
+import json
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2510_03283_amd")
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    from paper_2510_03283_amd import build
+    objs = [os.path.join(build.BUILD_DIR, s[:-4] + ".o") for s in build.sources()]
+    if not all(os.path.exists(o) for o in objs):
+        build.build_library()
+    d = tmp_path_factory.mktemp("recorder")
+    obj, exe = str(d / "recorder.o"), str(d / "recorder")
+    subprocess.run([build.HIPCC, "-x", "hip", "--offload-host-only", "-fPIE", "-std=c++17", "-O1", "-I", build.CSRC, "-c",
+                    os.path.join(ROOT, "tests", "launch_recorder.cpp"), "-o", obj], check=True)
+    subprocess.run(["g++", obj, *objs, "-o", exe], check=True)
+
+    def run(call, **opts):
+        args = [f"{k}={','.join(map(str, v)) if isinstance(v, (list, tuple)) else v}" for k, v in opts.items()]
+        out = subprocess.run([exe, call, *args], capture_output=True, text=True, check=True).stdout
+        return [json.loads(l) for l in out.splitlines()]
+
+    return run
+
+
+def status(rec):
+    return next(r for r in rec if r["op"] == "return")
+
+
+def plan(rec):
+    return [r for r in rec if r["op"] == "plan"]
+
+
+def slice_lifetimes(rec):
+    """Every range of partial results: the launch that writes it, the launches that read it, and for each launch
+    the number of launches of either stream it is known to follow (from stream order, event records and waits)."""
+    n_done = [0, 0]                                   # launches issued per stream
+    sees = [[0, 0], [0, 0]]                           # sees[s][t]: launches of t that whatever comes next on s follows
+    events, live, out = {}, {}, []
+    for i, r in enumerate(rec):
+        if r["op"] == "record":
+            s = r["stream"]
+            events[r["event"]] = [n_done[t] if t == s else sees[s][t] for t in (0, 1)]
+        elif r["op"] == "wait":
+            s = r["stream"]
+            sees[s] = [max(a, b) for a, b in zip(sees[s], events[r["event"]])]
+        elif r["op"] == "launch":
+            s = r["stream"]
+            n_done[s] += 1
+            sees[s][s] = n_done[s] - 1
+            me = dict(i=i, kernel=r["kernel"], stream=s, at=n_done[s], follows=list(sees[s]))
+            for kind, *rng in r["ranges"]:
+                if kind == "parts_out":
+                    life = dict(begin=rng[0], end=rng[0] + rng[1], writer=me, readers=[])
+                    out.append(life)
+                    live[tuple(rng)] = life
+                elif kind == "parts_in":
+                    assert tuple(rng) in live, f"launch {i} reads slices nobody wrote"
+                    live[tuple(rng)]["readers"].append(me)
+    return out
+
+
+def check_slices(rec):
+    def before(a, b):
+        return b["follows"][a["stream"]] >= a["at"]
+    lives = slice_lifetimes(rec)
+    for n, x in enumerate(lives):
+        assert x["readers"], f"slices of launch {x['writer']['i']} are never read"
+        for r in x["readers"]:
+            assert before(x["writer"], r), f"launch {r['i']} reads the slices of {x['writer']['i']} without an order between them"
+        for y in lives[n + 1:]:
+            if x["begin"] < y["end"] and y["begin"] < x["end"]:
+                for a in [x["writer"], *x["readers"]]:
+                    assert before(a, y["writer"]), (f"launch {y['writer']['i']} (stream {y['writer']['stream']}) overwrites slices of launch "
+                                                    f"{x['writer']['i']} (stream {x['writer']['stream']}) that launch {a['i']} may still use")
+    return lives
+
+
+# Weight-gradient products are split between the caller's stream and the side stream by their sizes; where attention
+# or the MLP is narrower than the model, both streams get some of them.
+BWD = [
+    dict(d=4096, hq=16, hkv=8, hd=128, F=1024, ft=[4096] * 4),
+    dict(d=4096, hq=16, hkv=16, hd=128, F=512, ft=[4096] * 4),
+    dict(d=2048, hq=16, hkv=16, hd=128, F=512, ft=[4096] * 8),
+    dict(d=2560, hq=16, hkv=8, hd=128, F=9728, ft=[1640] * 8),
+    dict(d=3584, hq=28, hkv=28, hd=64, F=9472, ft=[1200] * 8),
+    dict(d=3072, hq=16, hkv=16, hd=128, F=8192, ft=[1600] * 8),
+    dict(d=2048, hq=8, hkv=4, hd=128, F=5632, ft=[2048] * 8),
+    dict(d=2048, hq=32, hkv=4, hd=64, F=5632, ft=[2048] * 8),
+    dict(d=4096, hq=32, hkv=32, hd=128, F=11008, ft=[768] * 4),
+]
+
+
+@pytest.mark.parametrize("single_stream", [0, 1])
+@pytest.mark.parametrize("lora", [0, 16])
+@pytest.mark.parametrize("shape", BWD, ids=lambda s: f"d{s['d']}_q{s['hq'] * s['hd']}_F{s['F']}_{sum(s['ft'])}")
+def test_slices_of_the_backward_do_not_meet(recorder, shape, lora, single_stream):
+    rec = recorder("bwd", lora=lora, single_stream=single_stream, **shape)
+    assert status(rec)["status"] == 0
+    check_slices(rec)
+
+
+def test_slices_of_the_backward_do_not_meet_over_a_range_of_shapes(recorder):
+    both = 0
+    for d in (1024, 2048, 4096):
+        for qd in (512, 1024, 2048, 4096):
+            for F in (512, 1024, 2816, 8192):
+                for rows in (700, 2100, 9000, 17000, 33000):
+                    rec = recorder("bwd", d=d, hq=qd // 128, hkv=qd // 128 // (2 if qd >= 256 else 1), hd=128, F=F, ft=[rows // 4 + i for i in range(4)], accumulate=1)
+                    assert status(rec)["status"] == 0
+                    both += len({x["writer"]["stream"] for x in check_slices(rec)}) == 2
+    assert both > 20                                  # slices on both streams of one call do occur
+
+
+@pytest.mark.parametrize("lora", [0, 16])
+@pytest.mark.parametrize("single_stream", [0, 1])
+def test_slices_of_the_forward_do_not_meet(recorder, lora, single_stream):
+    n = 0
+    for d, hq, hkv, F in ((1024, 8, 2, 2816), (2048, 8, 4, 5632), (4096, 32, 8, 11008)):
+        for prefill, ft in (([300, 77], []), ([300], [500, 420]), ([], [700, 650]), ([1500] * 2, [900] * 4)):
+            rec = recorder("fwd", d=d, hq=hq, hkv=hkv, hd=128, F=F, prefill=prefill, decode=[100, 40], ft=ft, lora=lora, single_stream=single_stream)
+            assert status(rec)["status"] == 0
+            n += len(check_slices(rec))
+    assert n > 0
