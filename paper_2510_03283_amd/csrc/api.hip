@@ -764,7 +764,9 @@ static bool skinny_fits(const Dims &D, long long rows) {
 }
 static int run_skinny(mace_ctx *h, const SkinnyParams &p, int asrc, int epi, double flops, hipStream_t st, const char *where) {
   prof_mark(h, st, T_GEMM_NT, flops);
-  HIP_TRY(launch_skinny(p, asrc, epi, st), where);
+  const char *why = nullptr;
+  const hipError_t e = launch_skinny(p, asrc, epi, st, &why);
+  if (e != hipSuccess) return fail(why ? MACE_BAD_SHAPE : MACE_HIP_ERROR, std::string(where) + ": " + (why ? why : hipGetErrorString(e)));
   if (h->plan.size() < 256) {
     mace_gemm_plan_t r;
     memset(&r, 0, sizeof(r));

@@ -350,8 +350,14 @@ hipError_t sk_rows(const SkinnyParams &p, hipStream_t st) {
 // groups of columns a fp32-output product of N columns is cut into
 int skinny_parts(int N) { return N / 16 < SK_HALF_BELOW ? N / 8 : N / 16; }
 
-hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t st) {
+hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t st, const char **why) {
+  *why = nullptr;
   if (p.M <= 0) return hipSuccess;
+  for (int i = 0; i < (epi == SK_E_QKV ? 3 : (epi == SK_E_SWIGLU ? 2 : 1)); ++i)
+    if (!p.w[i] || ((uintptr_t)p.w[i] & 15)) {      // 16-byte pieces go straight to LDS
+      *why = "gemm: weights must be 16-byte aligned";
+      return hipErrorInvalidValue;
+    }
   // 32-bit byte offsets into the weights; whole chunks of k, whole groups of weight rows
   if (p.M > SKINNY_MAX_ROWS || p.K % SK_KC || p.K <= 0 || p.N % 16 || (long long)p.N * p.K * 2 >= (1ll << 32)) return hipErrorInvalidValue;
   if (epi == SK_E_QKV) {

@@ -129,3 +129,22 @@ def test_slices_of_the_forward_do_not_meet(recorder, lora, single_stream):
             assert status(rec)["status"] == 0
             n += len(check_slices(rec))
     assert n > 0
+
+
+MACE_BAD_SHAPE = -2
+
+
+@pytest.mark.parametrize("rows", [1, 16, 33, 64, 65])
+@pytest.mark.parametrize("weight", ["wq", "wk", "wv", "wo", "w_gate", "w_up", "w_down"])
+def test_misaligned_weights_are_refused(recorder, rows, weight):
+    """A weight matrix that is not 16-byte aligned is refused on every path, the weight-streaming one for few rows included."""
+    assert status(recorder("fwd", decode=[5] * rows))["status"] == 0
+    r = status(recorder("fwd", decode=[5] * rows, misalign=weight))
+    assert r["status"] == MACE_BAD_SHAPE, r
+
+
+@pytest.mark.parametrize("rows", [1, 16, 33, 64, 65])
+def test_misaligned_head_is_refused(recorder, rows):
+    assert status(recorder("logits", decode=[5] * rows, n=rows))["status"] == 0
+    r = status(recorder("logits", decode=[5] * rows, n=rows, misalign="w_lm"))
+    assert r["status"] == MACE_BAD_SHAPE, r
