@@ -168,7 +168,7 @@ __global__ __launch_bounds__(SK_THR) void skinny_kernel(const SkinnyParams p) {
   // Row scales from the partial sums of squares: SK_THR / rows threads share a row.  Requested before the ring is
   // filled and added while its first chunks are in flight (added behind the loop, row by row, it cost a 22016 x 4096
   // product of 64 rows 15 us of 70).
-  constexpr int TPR = SK_THR / (MT * 16);
+  constexpr int TPR = SK_THR / (MT == 3 ? 64 : MT * 16);
   if constexpr (SCALE) {
     const int m = (int)threadIdx.x / TPR;
     float v = 0.f;
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(SK_THR) void skinny_kernel(const SkinnyParams p) {
     }
 #pragma unroll
     for (int o = 1; o < TPR; o <<= 1) v += __shfl_xor(v, o, 64);
-    if (threadIdx.x % TPR == 0) ssq[0][m] = v;
+    if (threadIdx.x % TPR == 0 && m < MT * 16) ssq[0][m] = v;
   }
   {
     // a wave's chunks are SK_WAVES apart
@@ -340,6 +340,7 @@ hipError_t sk_rows(const SkinnyParams &p, hipStream_t st) {
   if (p.M <= 16) return sk_pick<ASRC, EPI, 1>(p, st);
   if constexpr (ASRC == SK_A_FRAG) {
     if (p.M <= 32) return sk_pick<ASRC, EPI, 2>(p, st);
+    if (p.M <= 48) return sk_pick<ASRC, EPI, 3>(p, st);      // never more tiles than the rows fill: the others are not allocated
     return sk_pick<ASRC, EPI, 4>(p, st);
   }
   return hipErrorInvalidValue;

@@ -2,6 +2,7 @@
 against a HIP runtime that only records (launch_recorder.cpp), and the recorded launches are checked here."""
 import json
 import os
+import re
 import subprocess
 
 import pytest
@@ -148,3 +149,35 @@ def test_misaligned_head_is_refused(recorder, rows):
     assert status(recorder("logits", decode=[5] * rows, n=rows))["status"] == 0
     r = status(recorder("logits", decode=[5] * rows, n=rows, misalign="w_lm"))
     assert r["status"] == MACE_BAD_SHAPE, r
+
+
+def skinny_reads(rec):
+    """Weight-streaming launches whose activations come in 16-row tiles: (pointer, bytes read, rows)."""
+    out = []
+    for r in rec:
+        if r["op"] == "launch" and "skinny_kernelI" in r["kernel"]:
+            mt, _, _, _, asrc, _ = re.search(r"skinny_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)ELi(\d+)ELi(\d+)E", r["kernel"]).groups()
+            if int(asrc) == 0:
+                _, a, m, _, k = r["ranges"][0]
+                out.append((a, int(mt) * 16 * k * 2, m))
+    return out
+
+
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 31, 32, 33, 40, 47, 48, 49, 63, 64])
+def test_few_row_products_read_inside_their_buffers(recorder, rows):
+    # forward: the activation buffers hold whole 16-row tiles and lie one behind the other
+    d, F = 1024, 2816
+    rec = recorder("fwd", d=d, F=F, decode=[5] * rows)
+    reads = skinny_reads(rec)
+    assert len(reads) == (4 if rows > 16 else 3)
+    for (_, n, m), k in zip(reads, [d] * (len(reads) - 1) + [F]):
+        assert n == -(-m // 16) * 16 * k * 2, f"{m} rows of {k} values: {n} bytes read"
+    # logits: the smallest workspace the call accepts
+    lo, hi = 256, 1 << 24
+    while lo < hi:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if status(recorder("logits", d=d, decode=[5] * rows, n=rows, work=mid))["status"] == 0 else (mid + 1, hi)
+    rec = recorder("logits", d=d, decode=[5] * rows, n=rows, work=lo)
+    work = next(r for r in rec if r["op"] == "work")
+    (a, n, _), = skinny_reads(rec)
+    assert work["ptr"] <= a and a + n <= work["ptr"] + lo, f"{rows} rows read {a + n - work['ptr'] - lo} bytes past a workspace of {lo}"
