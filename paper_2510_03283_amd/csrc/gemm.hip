@@ -698,7 +698,10 @@ hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const 
   }
   // multi-pass row groups first (stable): their tiles take longest and should start first
   for (int i = 1; i < p.n_mg; ++i)
-    for (int j = i; j > 0 && p.mg[j].npass > p.mg[j - 1].npass; --j) std::swap(p.mg[j], p.mg[j - 1]);
+    for (int j = i; j > 0 && p.mg[j].npass > p.mg[j - 1].npass; --j) {
+      std::swap(p.mg[j], p.mg[j - 1]);
+      std::swap(p.k_splits[j], p.k_splits[j - 1]);
+    }
   if (LA == 0 && LB == 0) return launch_layout<0, 0>(p, stream, why);
   if (LA == 0 && LB == 1) return launch_layout<0, 1>(p, stream, why);
   if (LA == 1 && LB == 1) return launch_layout<1, 1>(p, stream, why);

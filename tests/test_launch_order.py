@@ -181,3 +181,12 @@ def test_few_row_products_read_inside_their_buffers(recorder, rows):
     work = next(r for r in rec if r["op"] == "work")
     (a, n, _), = skinny_reads(rec)
     assert work["ptr"] <= a and a + n <= work["ptr"] + lo, f"{rows} rows read {a + n - work['ptr'] - lo} bytes past a workspace of {lo}"
+
+
+@pytest.mark.parametrize("groups", [[(300, 1, 2), (500, 2, 4)], [(256, 1, 1), (300, 2, 3), (700, 3, 5)], [(500, 2, 4), (300, 1, 2)]])
+def test_slices_follow_their_row_group(recorder, groups):
+    """The launcher starts row groups of more passes first; the slices of a group have to move with it."""
+    r = status(recorder("gemm", groups=[v for g in groups for v in g], N=2048, K=4096))
+    assert r["status"] == 0, r
+    assert [g[1] for g in r["groups"]] == sorted((g[1] for g in groups), reverse=True)
+    assert {tuple(g) for g in r["groups"]} == set(groups)
