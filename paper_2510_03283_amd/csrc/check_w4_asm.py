@@ -23,12 +23,10 @@ def check(name, lines):
     if not loads:
         return False, f"{name}: no buffer loads found"
     labels = {m.group(1): i for i, l in enumerate(code) for m in [re.match(r'^(\.LBB\d+_\d+):', l)] if m}
+    first_store = next((i for i, l in enumerate(code) if 'global_store' in l), len(code))
     barriers = [i for i, l in enumerate(code) if 's_barrier' in l]
-    if len(barriers) < 5:
-        return False, f"{name}: expected 5 barriers (prologue, two loop phases, two tail phases) first, found {len(barriers)}"
-    # what lies behind the tail phases (partial tiles, epilogue) begins with the wait states in front of the first
-    # accumulator read; its own loads are the compiler's
-    first_store = next((i for i, l in enumerate(code) if 'global_store' in l or (i > barriers[4] and 's_nop 15' in l)), len(code))
+    if len(barriers) != 5:
+        return False, f"{name}: expected 5 barriers (prologue, two loop phases, two tail phases), found {len(barriers)}"
     # the main loop: the backward branch behind the third barrier, up to the block it reaches
     back = [(i, labels[m.group(1)]) for i, l in enumerate(code) for m in [re.search(r's_c?branch\S*\s+(\.LBB\d+_\d+)', l)]
             if m and m.group(1) in labels and labels[m.group(1)] <= i and barriers[2] < i < barriers[3]]

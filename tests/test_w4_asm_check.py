@@ -76,6 +76,14 @@ def test_load_behind_the_loop():
     assert not ok and "loads issued behind the loop" in msg
 
 
+@pytest.mark.parametrize("extra", ["\ts_barrier", "\ts_barrier\n\ts_nop 15\n\tbuffer_load_dwordx4 v[4:7], v20, s[0:3], s9 offen"])
+def test_barrier_behind_the_loop(extra):
+    """The kernel has five barriers; with another one the positions the checks hang on may be others than meant, and
+    what follows it must not go unchecked."""
+    ok, msg = _checker().check("k", "\n".join(_kernel()).replace("\tglobal_store", extra + "\n\tglobal_store").split("\n"))
+    assert not ok and "expected 5 barriers" in msg
+
+
 def test_generated_code_of_the_built_library_passes():
     asm = os.path.join(ROOT, "paper_2510_03283_amd", "_build", "gemm-hip-amdgcn-amd-amdhsa-gfx950.s")
     if not os.path.exists(asm):
