@@ -63,30 +63,42 @@ __host__ __device__ __forceinline__ size_t frag_index(int m, int k, int K) {
   return ((size_t)(m >> 4) * (K >> 5) + (k >> 5)) * 512 + (size_t)((((k >> 3) & 3) * 16 + (m & 15)) * 8 + (k & 7));
 }
 
-// (cos, sin) of a rotary angle >= 0, given in fp64.  Quadrant reduction with a two-term pi/2 (the product k * pi/2 is
+// (cos, sin) of a rotary angle >= 0, both in fp64.  Quadrant reduction with a two-term pi/2 (the product k * pi/2 is
 // exact to about 2^-106 relative, so any int32 position keeps full accuracy), then the Taylor polynomials on
-// |x| <= pi/4 (remainder below 4e-13): the fp32 results are those of a correctly rounded fp64 evaluation.  About 30
-// fp64 instructions and no private memory, where the general library routine brings its large-argument tables.
-__device__ __forceinline__ float2 rope_angle(double ang) {
+// |x| <= pi/4, whose remainders (x^19 / 19!, x^18 / 18!) are below 1e-17: the error is that of the fp64 arithmetic, at most
+// 3e-16, so the fp32 results are the correctly rounded ones except where the true value lies that close to the middle of
+// two fp32 numbers.  About 35 fp64 instructions and no private memory, where the general library routine brings its
+// large-argument tables.
+__host__ __device__ __forceinline__ void rope_sincos(double ang, double &sn, double &cs) {
   const double k = rint(ang * 0.63661977236758134308);          // 2 / pi
   double x = fma(-k, 1.57079632679489661923, ang);
   x = fma(-k, 6.123233995736766e-17, x);                        // pi/2 - double(pi/2)
   const double z = x * x;
-  double s = fma(z, 1.0 / 6227020800.0, -1.0 / 39916800.0);
+  double s = fma(z, 1.0 / 355687428096000.0, -1.0 / 1307674368000.0);
+  s = fma(z, s, 1.0 / 6227020800.0);
+  s = fma(z, s, -1.0 / 39916800.0);
   s = fma(z, s, 1.0 / 362880.0);
   s = fma(z, s, -1.0 / 5040.0);
   s = fma(z, s, 1.0 / 120.0);
   s = fma(z, s, -1.0 / 6.0);
   s = fma(z * x, s, x);
-  double c = fma(z, 1.0 / 479001600.0, -1.0 / 3628800.0);
+  double c = fma(z, 1.0 / 20922789888000.0, -1.0 / 87178291200.0);
+  c = fma(z, c, 1.0 / 479001600.0);
+  c = fma(z, c, -1.0 / 3628800.0);
   c = fma(z, c, 1.0 / 40320.0);
   c = fma(z, c, -1.0 / 720.0);
   c = fma(z, c, 1.0 / 24.0);
   c = fma(z, c, -0.5);
   c = fma(z, c, 1.0);
   const int q = (int)((long long)k & 3);
-  const float fs = (float)(q & 1 ? c : s), fc = (float)(q & 1 ? s : c);
-  return make_float2(q == 1 || q == 2 ? -fc : fc, q >= 2 ? -fs : fs);
+  const double a = q & 1 ? c : s, b = q & 1 ? s : c;
+  sn = q >= 2 ? -a : a;
+  cs = q == 1 || q == 2 ? -b : b;
+}
+__device__ __forceinline__ float2 rope_angle(double ang) {
+  double s, c;
+  rope_sincos(ang, s, c);
+  return make_float2((float)c, (float)s);
 }
 
 __device__ __forceinline__ float wave_sum(float v) {

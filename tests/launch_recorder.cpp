@@ -4,7 +4,7 @@
 // pointers are made-up addresses; nothing here reads or writes through them.
 //
 // usage: launch_recorder <call> key=value ...      (see main)
-#include <cstdarg>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -159,6 +159,17 @@ static int raw_gemm() {
   return 0;
 }
 
+// rope_sincos of every angle positions[i] * 1e4^(-2 j / 128), all digits
+static int rope() {
+  for (int pos : list("positions"))
+    for (int j = 0; j < 64; ++j) {
+      double s, c;
+      rope_sincos((double)pos * std::pow(1e4, -2.0 * j / 128), s, c);
+      printf("{\"op\": \"rope\", \"angle\": %.17g, \"sin\": %.17g, \"cos\": %.17g}\n", (double)pos * std::pow(1e4, -2.0 * j / 128), s, c);
+    }
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const std::string call = argc > 1 ? argv[1] : "";
   for (int i = 2; i < argc; ++i) {
@@ -168,6 +179,7 @@ int main(int argc, char **argv) {
   }
   (void)stream_id(nullptr);
   if (call == "gemm") return raw_gemm();
+  if (call == "rope") return rope();
   mace_model_t m = {(int32_t)num("d", 1024), (int32_t)num("hq", 8), (int32_t)num("hkv", 8), (int32_t)num("hd", 128), (int32_t)num("F", 2816), (int32_t)num("V", 4096),
                     1e-6f, 1e4f, num("bf16", 1) ? MACE_BF16 : MACE_F32};
   mace_handle_t h;

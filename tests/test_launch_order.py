@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -190,3 +191,30 @@ def test_slices_follow_their_row_group(recorder, groups):
     assert r["status"] == 0, r
     assert [g[1] for g in r["groups"]] == sorted((g[1] for g in groups), reverse=True)
     assert {tuple(g) for g in r["groups"]} == set(groups)
+
+
+# pi / 2 in three pieces of at most 32 bits and a rest (Machin's formula in integers)
+PI_HALF = [3373259426 * 2.0 ** -31, 140128397 * 2.0 ** -61, 206333480 * 2.0 ** -91, 2.9038559739793605e-28]
+
+
+def test_rotary_angles_have_fp64_accuracy(recorder):
+    """The rotary sine and cosine against 80-bit results: three roundings of values up to 1 (the reduced angle, the
+    polynomial, its last step) leave at most 3 * 2^-53; the result near a zero is as accurate as the reduced angle."""
+    positions = [0, 1, 2, 3, 7, 100, 1023, 2047, 4095, 8191, 16383, 32768, 131071, 1 << 20, (1 << 24) + 1, (1 << 31) - 1] + list(range(5, 6000, 13))
+    assert np.finfo(np.longdouble).eps < 2e-19
+    rec = recorder("rope", positions=positions)
+    assert len(rec) == 64 * len(positions)
+    ang = np.array([r["angle"] for r in rec])
+    k = np.rint(ang * (2 / np.pi)).astype(np.longdouble)
+    # k has at most 31 bits: its product with a piece is exact in 64 bits of mantissa
+    x = ang.astype(np.longdouble)
+    for piece in PI_HALF:
+        x = x - k * np.longdouble(piece)
+    s, c = np.sin(x), np.cos(x)
+    q = k.astype(np.int64) & 3
+    sn = np.choose(q, [s, c, -s, -c])
+    cs = np.choose(q, [c, -s, -c, s])
+    for got, want in (([r["sin"] for r in rec], sn), ([r["cos"] for r in rec], cs)):
+        err = np.abs(np.array(got).astype(np.longdouble) - want)
+        print("largest error", float(err.max()))
+        assert float(err.max()) <= 3 * 2.0 ** -53
