@@ -765,13 +765,14 @@ static bool skinny_fits(const Dims &D, long long rows) {
 static int run_skinny(mace_ctx *h, const SkinnyParams &p, int asrc, int epi, double flops, hipStream_t st, const char *where) {
   prof_mark(h, st, T_GEMM_NT, flops);
   const char *why = nullptr;
-  const hipError_t e = launch_skinny(p, asrc, epi, st, &why);
+  int tile[2] = {0, 0};
+  const hipError_t e = launch_skinny(p, asrc, epi, st, &why, tile);
   if (e != hipSuccess) return fail(why ? MACE_BAD_SHAPE : MACE_HIP_ERROR, std::string(where) + ": " + (why ? why : hipGetErrorString(e)));
   if (h->plan.size() < 256) {
     mace_gemm_plan_t r;
     memset(&r, 0, sizeof(r));
     snprintf(r.name, sizeof(r.name), "%s", where);
-    r.tile_m = p.M; r.tile_n = 16; r.k_splits = 1;
+    r.tile_m = tile[0]; r.tile_n = tile[1]; r.k_splits = 1;
     r.m = p.M; r.n = epi == SK_E_SWIGLU ? 2ll * p.N : p.N; r.k = p.K;
     h->plan.push_back(r);
   }

@@ -314,7 +314,9 @@ __global__ __launch_bounds__(SK_THR) void skinny_kernel(const SkinnyParams p) {
 }
 
 template <int MT, int NC, int D, bool HALF, int ASRC, int EPI>
-hipError_t sk_launch(const SkinnyParams &p, int groups, hipStream_t st) {
+hipError_t sk_launch(const SkinnyParams &p, int groups, hipStream_t st, int tile[2]) {
+  tile[0] = MT * 16;
+  tile[1] = NC * (HALF ? 8 : 16);
   hipLaunchKernelGGL((skinny_kernel<MT, NC, D, HALF, ASRC, EPI>), dim3(groups / NC), dim3(SK_THR), 0, st, p);
   return hipGetLastError();
 }
@@ -325,23 +327,23 @@ hipError_t sk_launch(const SkinnyParams &p, int groups, hipStream_t st) {
 // A short reduction of at most 16 rows prefers two (32000 x 2048 at one row: 25 / 23 / 26 us).  One group otherwise;
 // 8-row groups where 16-row groups would leave CUs without a block (2048 x 5632 at one row: 6.5 -> 5.8 us).
 template <int ASRC, int EPI, int MT>
-hipError_t sk_pick(const SkinnyParams &p, hipStream_t st) {
+hipError_t sk_pick(const SkinnyParams &p, hipStream_t st, int tile[2]) {
   const int groups = EPI == SK_E_SWIGLU ? p.N / 8 : p.N / 16;
-  if (MT == 1 && p.K <= 2048 && groups >= 1024 && groups % 2 == 0) return sk_launch<MT, 2, 2, false, ASRC, EPI>(p, groups, st);
-  if (groups >= 640 && groups % 4 == 0) return sk_launch<MT, 4, 2, false, ASRC, EPI>(p, groups, st);
+  if (MT == 1 && p.K <= 2048 && groups >= 1024 && groups % 2 == 0) return sk_launch<MT, 2, 2, false, ASRC, EPI>(p, groups, st, tile);
+  if (groups >= 640 && groups % 4 == 0) return sk_launch<MT, 4, 2, false, ASRC, EPI>(p, groups, st, tile);
   if constexpr (EPI == SK_E_F32) {
-    if (groups < SK_HALF_BELOW) return sk_launch<MT, 1, 3, true, ASRC, EPI>(p, 2 * groups, st);
+    if (groups < SK_HALF_BELOW) return sk_launch<MT, 1, 3, true, ASRC, EPI>(p, 2 * groups, st, tile);
   }
-  return sk_launch<MT, 1, 3, false, ASRC, EPI>(p, groups, st);
+  return sk_launch<MT, 1, 3, false, ASRC, EPI>(p, groups, st, tile);
 }
 
 template <int ASRC, int EPI>
-hipError_t sk_rows(const SkinnyParams &p, hipStream_t st) {
-  if (p.M <= 16) return sk_pick<ASRC, EPI, 1>(p, st);
+hipError_t sk_rows(const SkinnyParams &p, hipStream_t st, int tile[2]) {
+  if (p.M <= 16) return sk_pick<ASRC, EPI, 1>(p, st, tile);
   if constexpr (ASRC == SK_A_FRAG) {
-    if (p.M <= 32) return sk_pick<ASRC, EPI, 2>(p, st);
-    if (p.M <= 48) return sk_pick<ASRC, EPI, 3>(p, st);      // never more tiles than the rows fill: the others are not allocated
-    return sk_pick<ASRC, EPI, 4>(p, st);
+    if (p.M <= 32) return sk_pick<ASRC, EPI, 2>(p, st, tile);
+    if (p.M <= 48) return sk_pick<ASRC, EPI, 3>(p, st, tile);      // never more tiles than the rows fill: the others are not allocated
+    return sk_pick<ASRC, EPI, 4>(p, st, tile);
   }
   return hipErrorInvalidValue;
 }
@@ -351,7 +353,7 @@ hipError_t sk_rows(const SkinnyParams &p, hipStream_t st) {
 // groups of columns a fp32-output product of N columns is cut into
 int skinny_parts(int N) { return N / 16 < SK_HALF_BELOW ? N / 8 : N / 16; }
 
-hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t st, const char **why) {
+hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t st, const char **why, int tile[2]) {
   *why = nullptr;
   if (p.M <= 0) return hipSuccess;
   for (int i = 0; i < (epi == SK_E_QKV ? 3 : (epi == SK_E_SWIGLU ? 2 : 1)); ++i)
@@ -362,12 +364,12 @@ hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t s
   // 32-bit byte offsets into the weights; whole chunks of k, whole groups of weight rows
   if (p.M > SKINNY_MAX_ROWS || p.K % SK_KC || p.K <= 0 || p.N % 16 || (long long)p.N * p.K * 2 >= (1ll << 32)) return hipErrorInvalidValue;
   if (epi == SK_E_QKV) {
-    if (asrc == SK_A_FRAG) return sk_rows<SK_A_FRAG, SK_E_QKV>(p, st);
-    if (asrc == SK_A_NORM_BF16) return sk_rows<SK_A_NORM_BF16, SK_E_QKV>(p, st);
+    if (asrc == SK_A_FRAG) return sk_rows<SK_A_FRAG, SK_E_QKV>(p, st, tile);
+    if (asrc == SK_A_NORM_BF16) return sk_rows<SK_A_NORM_BF16, SK_E_QKV>(p, st, tile);
   } else if (epi == SK_E_SWIGLU) {
-    if (asrc == SK_A_FRAG) return sk_rows<SK_A_FRAG, SK_E_SWIGLU>(p, st);
+    if (asrc == SK_A_FRAG) return sk_rows<SK_A_FRAG, SK_E_SWIGLU>(p, st, tile);
   } else if (epi == SK_E_F32) {
-    if (asrc == SK_A_FRAG) return sk_rows<SK_A_FRAG, SK_E_F32>(p, st);
+    if (asrc == SK_A_FRAG) return sk_rows<SK_A_FRAG, SK_E_F32>(p, st, tile);
   }
   return hipErrorInvalidValue;
 }

@@ -114,8 +114,8 @@ struct SkinnyParams {
   long long num_slots;
 };
 int skinny_parts(int N);
-// A non-null *why is set on a rejected problem.
-hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t st, const char **why);
+// A non-null *why is set on a rejected problem; tile: rows and weight rows (of all matrices) of a block.
+hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t st, const char **why, int tile[2]);
 
 // ---- lora.hip ---------------------------------------------------------------------------------
 // dst[dst_rows, dst_cols] as bf16 (hi, nullable lo) = zeros with up to three source matrices

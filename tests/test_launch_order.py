@@ -184,6 +184,17 @@ def test_few_row_products_read_inside_their_buffers(recorder, rows):
     assert work["ptr"] <= a and a + n <= work["ptr"] + lo, f"{rows} rows read {a + n - work['ptr'] - lo} bytes past a workspace of {lo}"
 
 
+@pytest.mark.parametrize("d,hq,hkv,F,V", [(1024, 8, 8, 2816, 4096), (2048, 32, 8, 5632, 32000), (4096, 32, 32, 11008, 32000)])
+@pytest.mark.parametrize("rows", [1, 17, 33, 64])
+def test_plan_records_the_tiles_of_few_row_products(recorder, rows, d, hq, hkv, F, V):
+    opts = dict(d=d, hq=hq, hkv=hkv, hd=d // hq, F=F, V=V, decode=[5] * rows)
+    for rec in (recorder("fwd", **opts), recorder("logits", n=rows, **opts)):
+        grids = [r["grid"][0] for r in rec if r["op"] == "launch" and "skinny_kernelI" in r["kernel"]]
+        assert len(grids) == len(plan(rec)) > 0
+        for g, r in zip(grids, plan(rec)):
+            assert r["tile"] == [-(-rows // 16) * 16, r["n"] // g], (r, g)
+
+
 @pytest.mark.parametrize("groups", [[(300, 1, 2), (500, 2, 4)], [(256, 1, 1), (300, 2, 3), (700, 3, 5)], [(500, 2, 4), (300, 1, 2)]])
 def test_slices_follow_their_row_group(recorder, groups):
     """The launcher starts row groups of more passes first; the slices of a group have to move with it."""
