@@ -1668,7 +1668,7 @@ static int dpo_impl(mace_handle_t h, const float *h_ft, const void *g_final, con
     }
   }
   prof_mark(h, st, T_MISC);
-  HIP_TRY(launch_dpo_pairs(P.logp_t, shared ? P.vseq_off : ft_seq_offsets, shared ? P.vprompt : prompt_lens, n_seq, ref_logp, beta, logp_out, loss_per_pair, loss_mean, clpd_out, win_out, P.dlogp, st), "dpo pairs");
+  HIP_TRY(launch_dpo_pairs(P.logp_t, shared ? P.vseq_off : ft_seq_offsets, shared ? P.vprompt : prompt_lens, n_seq, Ri, ref_logp, beta, logp_out, loss_per_pair, loss_mean, clpd_out, win_out, P.dlogp, st), "dpo pairs");
   if (!want_grad) { prof_mark(h, st, -1); return MACE_OK; }
   if (dh_ft) { prof_mark(h, st, T_MISC); HIP_TRY(launch_fill_f32(dh_ft, (size_t)Tf * D.d, 0.f, st), "zero dh");
   }

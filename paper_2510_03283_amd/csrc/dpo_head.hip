@@ -171,9 +171,12 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(float *__restrict__ u, 
   }
 }
 
-// Single block of 16 waves; a wave takes the pairs w, w + 16, ...  (Latency-bound: with the whole block on one sequence at a
-// time, every sequence cost nine barriers: 64 sequences of 512 rows 122 -> 23 us, 8 of 160 14.8 -> 7.0 us.)  Sequence sums in fp64 in a fixed order
-// (deterministic), then the pair terms:
+// Single block of 16 waves; `share` (a power of two) of them take a pair, and with share = 1 wave w the pairs w, w + 16, ...
+// The kernel is bound by latency: with the whole block on one sequence at a time every sequence costs nine barriers, with one
+// wave to a pair a long response is a chain of loads, and sharing a pair costs a barrier.  Whole block / one wave to
+// a pair / now, us: 64 sequences of 512 rows 105 / 17.3 / 12.9, 8 of 160 11.7 / 4.3 / 5.1, 8 of 2048 26.4 / 20.2 / 9.1, 2 of 2048
+// 8.9 / 18.6 / 6.1, 2 of 8192 20.5 / 65 / 7.3.
+// Sequence sums in fp64 in a fixed order (deterministic), then the pair terms:
 // z = beta((logp+ - ref+) - (logp- - ref-)), loss = softplus(-z), dloss_mean/dlogp+ = (sigmoid(z)-1) beta / n_pairs.
 // loss_mean adds the pair losses per wave and then over the waves, in fp64.  Sequence s starts at log-probability
 // ft_seq_offsets[s] - ft_seq_offsets[0] - sum of the prompts before it: each wave carries that sum along.
@@ -187,24 +190,12 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
 __global__ __launch_bounds__(64 * DPO_WAVES) void dpo_pairs_kernel(const float *__restrict__ logp_t, const int32_t *ft_seq_offsets,
                                                                    const int32_t *prompt_lens, int n_seq, const float *ref_logp,
                                                                    float beta, float *logp_out, float *loss_per_pair,
-                                                                   float *loss_mean, float *clpd, int32_t *win, float *dlogp) {
-  __shared__ double total[DPO_WAVES];
+                                                                   float *loss_mean, float *clpd, int32_t *win, float *dlogp, int share) {
+  __shared__ double total[DPO_WAVES], part[DPO_WAVES][2];
   const int n_pairs = n_seq / 2, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int sub = w & (share - 1), step = 64 * share;
   double mine = 0.0;
-  int seen = 0, prompts = 0;                     // prompts = rows of the prompts of sequences 0 .. seen - 1 (this lane's share)
-  for (int pr = w; pr < n_pairs; pr += DPO_WAVES) {
-    for (int s = seen + lane; s < 2 * pr; s += 64) prompts += prompt_lens[s];
-    seen = 2 * pr;
-    int before = prompts;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
-    const int o0 = ft_seq_offsets[2 * pr], o1 = ft_seq_offsets[2 * pr + 1], o2 = ft_seq_offsets[2 * pr + 2];
-    const int base = o0 - ft_seq_offsets[0] - before, na = o1 - o0 - prompt_lens[2 * pr], nb = o2 - o1 - prompt_lens[2 * pr + 1];
-    double lp = 0.0, lm = 0.0;
-    for (int i = lane; i < na; i += 64) lp += (double)logp_t[base + i];
-    for (int i = lane; i < nb; i += 64) lm += (double)logp_t[base + na + i];
-    lp = wave_sum_f64(lp);
-    lm = wave_sum_f64(lm);
+  auto finish = [&](int pr, double lp, double lm) {
     const double z = (double)beta * ((lp - (double)ref_logp[2 * pr]) - (lm - (double)ref_logp[2 * pr + 1]));
     const double loss = fmax(-z, 0.0) + log1p(exp(-fabs(z)));
     const double sig = 1.0 / (1.0 + exp(-z));
@@ -218,6 +209,37 @@ __global__ __launch_bounds__(64 * DPO_WAVES) void dpo_pairs_kernel(const float *
       if (win) win[pr] = (lp - lm) > 0.0 ? 1 : 0;
       dlogp[2 * pr] = (float)c;
       dlogp[2 * pr + 1] = (float)(-c);
+    }
+  };
+  int seen = 0, prompts = 0;                     // prompts = rows of the prompts of sequences 0 .. seen - 1 (this lane's share)
+  for (int pr = w / share; pr < n_pairs; pr += DPO_WAVES / share) {      // (share > 1: at most one turn)
+    for (int s = seen + lane; s < 2 * pr; s += 64) prompts += prompt_lens[s];
+    seen = 2 * pr;
+    int before = prompts;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    const int o0 = ft_seq_offsets[2 * pr], o1 = ft_seq_offsets[2 * pr + 1], o2 = ft_seq_offsets[2 * pr + 2];
+    const int base = o0 - ft_seq_offsets[0] - before, na = o1 - o0 - prompt_lens[2 * pr], nb = o2 - o1 - prompt_lens[2 * pr + 1];
+    double lp = 0.0, lm = 0.0;
+#pragma unroll 4
+    for (int i = 64 * sub + lane; i < na; i += step) lp += (double)logp_t[base + i];
+#pragma unroll 4
+    for (int i = 64 * sub + lane; i < nb; i += step) lm += (double)logp_t[base + na + i];
+    lp = wave_sum_f64(lp);
+    lm = wave_sum_f64(lm);
+    if (share == 1) {
+      finish(pr, lp, lm);
+    } else if (lane == 0) {
+      part[w][0] = lp;
+      part[w][1] = lm;
+    }
+  }
+  if (share > 1) {
+    __syncthreads();
+    if (sub == 0 && w / share < n_pairs) {
+      double lp = 0.0, lm = 0.0;
+      for (int i = 0; i < share; ++i) { lp += part[w + i][0]; lm += part[w + i][1]; }
+      finish(w / share, lp, lm);
     }
   }
   if (lane == 0) total[w] = mine;
@@ -262,9 +284,13 @@ hipError_t launch_scale_rows(float *u, const bf16_t *n_hi, bf16_t *n_c, const in
 }
 
 hipError_t launch_dpo_pairs(const float *logp_t, const int32_t *ft_seq_offsets, const int32_t *prompt_lens, int n_seq,
-                            const float *ref_logp, float beta, float *logp_out, float *loss_per_pair, float *loss_mean,
+                            int rows, const float *ref_logp, float beta, float *logp_out, float *loss_per_pair, float *loss_mean,
                             float *clpd, int32_t *win, float *dlogp, hipStream_t st) {
-  hipLaunchKernelGGL(dpo_pairs_kernel, dim3(1), dim3(64 * DPO_WAVES), 0, st, logp_t, ft_seq_offsets, prompt_lens, n_seq, ref_logp, beta, logp_out, loss_per_pair, loss_mean, clpd, win, dlogp);
+  // waves of a pair: all that the pairs leave, and at least four turns of a wave over a response of mean length (8 of 160
+  // rows: 5.1 us with one wave to a pair, 5.6 with four)
+  int share = DPO_WAVES;
+  while (share > 1 && (share * (n_seq / 2) > DPO_WAVES || 4 * 64 * share > rows / n_seq)) share >>= 1;
+  hipLaunchKernelGGL(dpo_pairs_kernel, dim3(1), dim3(64 * DPO_WAVES), 0, st, logp_t, ft_seq_offsets, prompt_lens, n_seq, ref_logp, beta, logp_out, loss_per_pair, loss_mean, clpd, win, dlogp, share);
   return hipGetLastError();
 }
 

@@ -211,7 +211,7 @@ hipError_t launch_logp_correct(const bf16_t *n_lo, const float *u, int rows, int
 // c = dlogp[seq_id[r]]:  u[r, :] *= c (u nullable);  n_c[r, :] = bf16(c * n_hi[r, :]) (n_c nullable)
 hipError_t launch_scale_rows(float *u, const bf16_t *n_hi, bf16_t *n_c, const int32_t *seq_id, const float *dlogp, int rows, int d,
                              hipStream_t st);
-// Per-sequence sums, pair losses, metrics and dloss_mean/dlogp per sequence.
+// Per-sequence sums, pair losses, metrics and dloss_mean/dlogp per sequence; rows: loss rows of all sequences.
 hipError_t launch_dpo_pairs(const float *logp_t, const int32_t *ft_seq_offsets, const int32_t *prompt_lens, int n_seq,
-                            const float *ref_logp, float beta, float *logp_out, float *loss_per_pair, float *loss_mean,
+                            int rows, const float *ref_logp, float beta, float *logp_out, float *loss_per_pair, float *loss_mean,
                             float *clpd, int32_t *win, float *dlogp, hipStream_t st);
