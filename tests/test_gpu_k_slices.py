@@ -40,3 +40,58 @@ def test_sliced_products(torch_mod, name):
     finally:
         it.close()
     check_iteration(torch_mod, wl, f"slices {name}")
+
+
+@pytest.mark.parametrize("single_stream", [0, 1])
+def test_sliced_weight_gradients_are_accumulated(torch_mod, single_stream):
+    """All four weight-gradient products of a layer in slices, on the side stream and on the caller's: the sum of the slices
+    is added to what the gradient held (in place), and alone it is the oracle's gradient."""
+    from helpers import rel_fro_err, run_oracle
+    from paper_2510_03283_amd import binding as B
+    from paper_2510_03283_amd.harness import DeviceIteration
+    torch = torch_mod
+    wl = custom_workload("slices_acc", synth.ModelDims(512, 4, 2, 128, 1408, 2048), prefill=[], decode=[], n_pairs=2, prompt=400, resp=(350, 450), seed=4200)
+    ref = run_oracle(wl)
+    it = DeviceIteration(wl, options={B.MACE_OPT_SINGLE_STREAM: 1} if single_stream else None)
+    try:
+        plans = it.step_with_plans()
+        torch.cuda.synchronize()
+        once = {k: v.clone() for k, v in it.grads.items()}
+        for k, v in once.items():
+            e = rel_fro_err(v.cpu().numpy(), ref["grads"][k])
+            print(f"d{k}: {e:.2e}", flush=True)
+            assert e <= 2e-2, (k, e)
+        gen = torch.Generator(device="cuda").manual_seed(7)
+        before = {k: torch.randn(v.shape, generator=gen, device="cuda") * v.std() for k, v in once.items()}
+        for k, v in it.grads.items():
+            v.copy_(before[k])
+        B.mace_hybrid_layer_bwd(it.h, it.w_struct, it.batch, it.x, it.dh, it.saved, it.dx, it.g_struct, 1, it.ws)
+        for p in (plans["bwd"], B.mace_launch_plan(it.h)):
+            cut = {(r["name"], r["on_side_stream"]) for r in p if r["layout"] == 2 and r["k_splits"] > 1}
+            assert cut == {(n, 1 - single_stream) for n in ("dWd gemm", "dWg/dWu gemm", "dWo gemm", "dWqkv gemm")}, cut
+        torch.cuda.synchronize()
+        for k, v in it.grads.items():      # one fp32 addition more than the gradient alone
+            assert torch.allclose(v, before[k] + once[k], rtol=3e-7, atol=3e-7 * float(once[k].std())), k
+    finally:
+        it.close()
+
+
+def test_sliced_adapter_products(torch_mod):
+    """Adapter products in slices, read by the scaling split and the gradient extraction; the vocabulary reduction of the
+    head in slices beside them."""
+    from paper_2510_03283_amd.harness import DeviceIteration
+    dims = synth.ModelDims(2048, 4, 4, 128, 512, 4096)
+    wl = custom_workload("slices_lora", dims, prefill=[130], decode=[5, 300], n_pairs=2, prompt=170, resp=(90, 130), seed=4300)
+    spec = synth.ConfigSpec("slices_lora", 4300, dims, None, None, None, None, 2, 170, None, (90, 130))
+    lora = synth.make_lora(spec, rank=16, scale=2.0)
+    it = DeviceIteration(wl, lora=lora)
+    try:
+        plans = it.step_with_plans()
+        torch_mod.cuda.synchronize()
+        sliced = {r["name"]: r["k_splits"] for p in plans.values() for r in p if r["k_splits"] > 1}
+        print(f"slices: {sliced}", flush=True)
+        expect = {f"lora {n} gemm" for n in ("t_qkv", "t_o", "dt_o", "dt_qkv", "dB_o", "dA_o", "dB_qkv", "dA_qkv")} | {"dn gemm"}
+        assert expect <= set(sliced), expect - set(sliced)
+    finally:
+        it.close()
+    check_iteration(torch_mod, wl, "sliced adapters", lora=lora)

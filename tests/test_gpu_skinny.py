@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hq,hkv,hd", [(8, 2, 64), (4, 4, 128)])
 @pytest.mark.parametrize("rows", [3, 16, 17, 32, 33, 48, 63, 64, 65])
 def test_few_rows(torch_mod, hq, hkv, hd, rows):
-    # K of 320 and 704 leaves waves without a chunk, d_ff / 8 is odd; contexts on and off block edges
+    # K of 320 leaves waves without a chunk, K of 704 gives three of them a second one; contexts on and off block edges
     dims = synth.ModelDims(320, hq, hkv, hd, 704, 4096, io_bf16=True)
     n_dec = 3 if rows < 16 else 7
     wl = custom_workload("skinny", dims, prefill=() if rows == n_dec else (rows - n_dec,),
@@ -25,6 +25,46 @@ def test_few_rows(torch_mod, hq, hkv, hd, rows):
 
 @pytest.mark.parametrize("n_decode", [1, 2, 32])
 def test_edge_decode_rows(torch_mod, n_decode):
-    """The edge configuration's decode requests alone (two and one row group per block, 8-row groups)."""
+    """The edge configuration's decode requests alone (QKV one row group per block, gate / up four, the others 8-row groups)."""
     wl = synth.make_workload("edge", n_prefill=0, n_decode=n_decode, n_pairs=0)
     check_iteration(torch_mod, wl, f"edge decode {n_decode}")
+
+
+# The row groups of a block (sk_pick in csrc/gemm_skinny.hip) change with the number of weight rows: model, rows and the
+# (rows, weight rows) tile that every product of the batch has to run with.
+FOUR = (320, 64, 8, 128, 5120, 10240)            # 640 groups: four to a block
+TWO = (320, 64, 32, 128, 8192, 16384)            # 1024 groups, K <= 2048: two to a block up to 16 rows, else four
+WIDE = (3072, 4, 4, 64, 704, 4096)               # 192 groups: whole 16-row groups in the output and down products
+GROUPS = [(FOUR, rows, (64, 8, 64, 8, 64)) for rows in (1, 16, 17, 33, 48, 64)]
+GROUPS += [(TWO, rows, (32, 8, 32, 8, 32)) for rows in (2, 16)] + [(TWO, 20, (64, 8, 64, 8, 64))]
+GROUPS += [(WIDE, rows, (16, 16, 16, 16, 16)) for rows in (1, 17, 40, 64)]
+GROUPS += [((320, 128, 16, 64, 704, 4096), rows, (64, 8, 16, 8, 16)) for rows in (5, 20)]      # 64-wide heads, 640 groups
+
+
+@pytest.mark.parametrize("dims,rows,cols", GROUPS, ids=lambda v: "_".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_row_groups_per_block(torch_mod, dims, rows, cols):
+    import numpy as np
+    from helpers import max_abs_norm_err, run_oracle
+    from oracle import mace_oracle as O
+    from paper_2510_03283_amd import binding as B
+    from paper_2510_03283_amd.harness import DeviceIteration
+    n_dec = min(rows, 5)
+    wl = custom_workload("row_groups", synth.ModelDims(*dims), prefill=() if rows == n_dec else (rows - n_dec,), decode=(33, 0, 15, 300, 16)[:n_dec],
+                         n_pairs=0, prompt=3, resp=(2, 9), seed=500 + rows)
+    check_iteration(torch_mod, wl, f"{dims} rows {rows}")
+    ref = run_oracle(wl)
+    it = DeviceIteration(wl)
+    try:
+        it.forward()
+        plan = B.mace_launch_plan(it.h)
+        logits = torch_mod.empty((rows, dims[5]), dtype=torch_mod.float32, device="cuda")
+        B.mace_next_token_logits(it.h, it.y, None, rows, it.gf, it.E, logits, None, it.ws)
+        plan += B.mace_launch_plan(it.h)
+        assert [r["tile"] for r in plan] == [(-(-rows // 16) * 16, c) for c in cols], [(r["name"], r["tile"]) for r in plan]
+        torch_mod.cuda.synchronize()
+        want, _ = O.next_token_logits(wl.dims, wl.weights, ref["y"])
+        e = max_abs_norm_err(logits.cpu().numpy(), want)
+        print(f"logits of {rows} rows: {e:.2e}", flush=True)
+        assert np.all(np.isfinite(logits.cpu().numpy())) and e <= 1e-2
+    finally:
+        it.close()
