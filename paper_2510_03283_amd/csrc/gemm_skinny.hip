@@ -1,4 +1,4 @@
-// Weight-streaming products of a few activation rows: C[m, n] = sum_k A[m, k] W[n, k], m < 128, W bf16 [N, K].
+// Weight-streaming products of a few activation rows: C[m, n] = sum_k A[m, k] W[n, k], at most 64 rows m, W bf16 [N, K].
 //
 // With a handful of rows a product reads its weights once and does almost nothing else, so it is bound by the
 // weight stream, not by the matrix cores.  The tiles of the large kernels put such a problem on N / 128 blocks that
@@ -131,18 +131,41 @@ __global__ __launch_bounds__(SK_THR) void skinny_kernel(const SkinnyParams p) {
   for (int h = 0; h < 2; ++h) faddr[h] = ring0 + frow * 128 + (((4 * h + g) ^ ((frow >> 1) & 7)) << 4);
   auto mult = [&](Acts &s, int slot) __attribute__((always_inline)) {
     sk_u32x4_t w[2][NC];
-    // (the reads name the last activations requested: the compiler waits for those, hence for the weights)
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int cg = 0; cg < NC; ++cg)
-        asm volatile("ds_read_b128 %0, %1" : "=v"(w[h][cg]) : "v"(faddr[h] + (uint32_t)(slot * SLOT + cg * (WR * 128))), "v"(s.a[1][MT - 1]));
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int cg = 0; cg < NC; ++cg)
-        if (h == 0 && cg == 0) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[h][cg]));
-        else asm volatile("" : "+v"(w[h][cg]));
+    // The reads name the last activations requested: the compiler waits for those, hence for the weights.  One block
+    // of asm that ends with its wait: the compiler takes the outputs as written when it ends.
+    const uint32_t w0 = faddr[0] + (uint32_t)(slot * SLOT), w1 = faddr[1] + (uint32_t)(slot * SLOT);
+    if constexpr (NC == 1)
+      asm volatile("ds_read_b128 %0, %2\n\t"
+                   "ds_read_b128 %1, %3\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : "=&v"(w[0][0]), "=&v"(w[1][0])
+                   : "v"(w0), "v"(w1), "v"(s.a[1][MT - 1])
+                   : "memory");
+    else if constexpr (NC == 2)
+      asm volatile("ds_read_b128 %0, %4\n\t"
+                   "ds_read_b128 %1, %4 offset:%6\n\t"
+                   "ds_read_b128 %2, %5\n\t"
+                   "ds_read_b128 %3, %5 offset:%6\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : "=&v"(w[0][0]), "=&v"(w[0][NC - 1]), "=&v"(w[1][0]), "=&v"(w[1][NC - 1])
+                   : "v"(w0), "v"(w1), "i"(WR * 128), "v"(s.a[1][MT - 1])
+                   : "memory");
+    else {
+      static_assert(NC == 4, "one, two or four groups");
+      asm volatile("ds_read_b128 %0, %8\n\t"
+                   "ds_read_b128 %1, %8 offset:%10\n\t"
+                   "ds_read_b128 %2, %8 offset:%11\n\t"
+                   "ds_read_b128 %3, %8 offset:%12\n\t"
+                   "ds_read_b128 %4, %9\n\t"
+                   "ds_read_b128 %5, %9 offset:%10\n\t"
+                   "ds_read_b128 %6, %9 offset:%11\n\t"
+                   "ds_read_b128 %7, %9 offset:%12\n\t"
+                   "s_waitcnt lgkmcnt(0)"
+                   : "=&v"(w[0][0]), "=&v"(w[0][1 % NC]), "=&v"(w[0][2 % NC]), "=&v"(w[0][3 % NC]), "=&v"(w[1][0]), "=&v"(w[1][1 % NC]),
+                     "=&v"(w[1][2 % NC]), "=&v"(w[1][3 % NC])
+                   : "v"(w0), "v"(w1), "i"(WR * 128), "i"(2 * WR * 128), "i"(3 * WR * 128), "v"(s.a[1][MT - 1])
+                   : "memory");
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int h = 0; h < 2; ++h)

@@ -3,6 +3,7 @@ assembly: the kernel counts its own memory waits, so the checker has to notice a
 its load is still in flight, a scratch access inside the loop and a load issued behind the loop."""
 import importlib.util
 import os
+import re
 
 import pytest
 
@@ -89,3 +90,14 @@ def test_generated_code_of_the_built_library_passes():
     if not os.path.exists(asm):
         pytest.skip("library not built in this tree")
     assert _checker().main(asm) == 0
+
+
+@pytest.mark.parametrize("source", sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".h")) and f not in ("gemm.hip", "gemm_w4.h")))
+def test_reads_in_asm_end_with_their_wait(source):
+    """The compiler takes the outputs of a block of asm as written when the block ends, and may copy or overwrite them
+    there; a read still in flight has to be waited for inside.  (The two sources left out count their waits.)"""
+    text = open(os.path.join(CSRC, source)).read()
+    blocks = [re.findall(r'"((?:[^"\\]|\\.)*)"', b.split("\" :")[0] + '"') for b in re.findall(r"\basm\b[^;]*;", text)]
+    for b in ("".join(parts) for parts in blocks):
+        if re.search(r"ds_read|buffer_load|global_load|flat_load", b):
+            assert "s_waitcnt" in b[max(b.rfind("ds_read"), b.rfind("_load")):], b
