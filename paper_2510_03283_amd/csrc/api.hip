@@ -585,7 +585,11 @@ int mace_create(mace_handle_t *out, const mace_model_t *model) {
   c->inv_freq = nullptr;
   const int half = m.head_dim / 2;
   std::vector<double> f(half);
-  for (int i = 0; i < half; ++i) f[i] = std::pow((double)m.rope_theta, -2.0 * i / m.head_dim);
+  for (int i = 0; i < half; ++i) {
+    f[i] = std::pow((double)m.rope_theta, -2.0 * i / m.head_dim);
+    // whole turns per position (a base far below 1) change no angle; without them every angle stays in the range of rope_sincos
+    if (f[i] > 524288.0) f[i] = (double)fmodl((long double)f[i], 6.283185307179586476925286766559L);
+  }
   hipError_t e = hipMalloc((void **)&c->inv_freq, half * sizeof(double));
   if (e == hipSuccess) e = hipMemcpy(c->inv_freq, f.data(), half * sizeof(double), hipMemcpyHostToDevice);
   if (e != hipSuccess) {

@@ -63,7 +63,7 @@ __host__ __device__ __forceinline__ size_t frag_index(int m, int k, int K) {
   return ((size_t)(m >> 4) * (K >> 5) + (k >> 5)) * 512 + (size_t)((((k >> 3) & 3) * 16 + (m & 15)) * 8 + (k & 7));
 }
 
-// (cos, sin) of a rotary angle >= 0, both in fp64.  Quadrant reduction with a two-term pi/2 (the product k * pi/2 is
+// (cos, sin) of a rotary angle 0 .. 2^50 (positions are below 2^31, frequencies at most 2^19), both in fp64.  Quadrant reduction with a two-term pi/2 (the product k * pi/2 is
 // exact to about 2^-106 relative, so any int32 position keeps full accuracy), then the Taylor polynomials on
 // |x| <= pi/4, whose remainders (x^19 / 19!, x^18 / 18!) are below 1e-17: the error is that of the fp64 arithmetic, at most
 // 3e-16, so the fp32 results are the correctly rounded ones except where the true value lies that close to the middle of

@@ -96,7 +96,12 @@ hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipMalloc(void **p, size_t n) { *p = fake(n); return hipSuccess; }
 hipError_t hipFree(void *) { return hipSuccess; }
-hipError_t hipMemcpy(void *, const void *, size_t, hipMemcpyKind) { return hipSuccess; }
+static bool g_uploads;      // print the fp64 arrays that are copied to the device
+hipError_t hipMemcpy(void *, const void *src, size_t n, hipMemcpyKind) {
+  if (g_uploads)
+    for (size_t i = 0; i < n / 8; ++i) printf("{\"op\": \"upload\", \"value\": %.17g}\n", ((const double *)src)[i]);
+  return hipSuccess;
+}
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
@@ -181,9 +186,11 @@ int main(int argc, char **argv) {
   if (call == "gemm") return raw_gemm();
   if (call == "rope") return rope();
   mace_model_t m = {(int32_t)num("d", 1024), (int32_t)num("hq", 8), (int32_t)num("hkv", 8), (int32_t)num("hd", 128), (int32_t)num("F", 2816), (int32_t)num("V", 4096),
-                    1e-6f, 1e4f, num("bf16", 1) ? MACE_BF16 : MACE_F32};
+                    1e-6f, g_opt.count("theta") ? (float)atof(g_opt["theta"].c_str()) : 1e4f, num("bf16", 1) ? MACE_BF16 : MACE_F32};
   mace_handle_t h;
+  g_uploads = call == "create";
   if (mace_create(&h, &m) != MACE_OK) { fprintf(stderr, "%s\n", mace_last_error()); return 3; }
+  if (g_uploads) return 0;
   if (num("single_stream", 0)) mace_set_option(h, MACE_OPT_SINGLE_STREAM, 1);
 
   // batch: prefill=lengths decode=contexts ft=lengths

@@ -229,3 +229,22 @@ def test_rotary_angles_have_fp64_accuracy(recorder):
         err = np.abs(np.array(got).astype(np.longdouble) - want)
         print("largest error", float(err.max()))
         assert float(err.max()) <= 3 * 2.0 ** -53
+
+
+@pytest.mark.parametrize("theta", [1e6, 1e4, 1.0, 1e-3, 1e-9, 1e-30, 1e-44])
+def test_rotary_frequencies_stay_in_the_range_of_the_angles(recorder, theta):
+    """Frequencies of bases down to the smallest mace_create accepts.  Up to 2^19 they are theta^(-2 i / hd); above (where
+    the angle of a late position would leave the range of rope_sincos) whole turns are left out, to 64 bits of 2 pi."""
+    f = np.array([r["value"] for r in recorder("create", theta=theta)])
+    want = np.float64(np.float32(theta)) ** (-2.0 * np.arange(64) / 128)
+    assert len(f) == 64 and f.max() <= 2.0 ** 19 and f.min() >= 0
+    small = want <= 2.0 ** 19
+    np.testing.assert_allclose(f[small], want[small], rtol=1e-15)      # (two libraries' pow, an ulp or two)
+    if theta >= 1:
+        assert small.all()
+    two_pi = 4 * np.sum(np.array(PI_HALF, np.longdouble))
+    turns = want[~small].astype(np.longdouble) / two_pi
+    near = turns < 2.0 ** 40                                       # (whole turns of larger ones are below the last bit of theta's power)
+    angle = (turns[near] - np.floor(turns[near])) * two_pi
+    diff = np.abs(f[~small][near].astype(np.longdouble) - angle)
+    assert np.all(np.minimum(diff, two_pi - diff) <= want[~small][near] * 2.0 ** -50)
