@@ -154,7 +154,9 @@ size_t mace_fwd_saved_bytes(mace_handle_t h, int32_t n_ft_tokens);
 /* Bytes of scratch the forward, backward and DPO calls need for a batch of these sizes
  * (n_tokens total rows, n_ft_tokens fine-tune rows, n_decode requests with at most
  * max_context cached tokens, n_loss_rows response tokens).  One workspace of this size serves
- * all three calls of an iteration; its contents need not survive between calls. */
+ * all three calls of an iteration; its contents need not survive between calls.  Up to 512 MB of it is
+ * room for partial results of products whose reduction is cut into slices, reserved by row count and
+ * model size alone. */
 size_t mace_workspace_bytes(mace_handle_t h, int32_t n_tokens, int32_t n_ft_tokens, int32_t n_decode,
                             int32_t max_context, int32_t n_loss_rows);
 

@@ -2,15 +2,15 @@
 // head, bf16, in their memory layout [row][HD], filled by direct global->LDS loads.
 //
 // The same tile serves two kinds of MFMA operand:
-//  * frag_k: 8 consecutive head-dim elements of one tile row per lane (reduction over the head
+//  * read_k: 8 consecutive head-dim elements of one tile row per lane (reduction over the head
 //    dimension), one 16-byte LDS read;
-//  * frag_t: for head-dim index r0 + lane%32, the 8 tile rows kk*16 + 8*(lane/32) .. +7
+//  * read_t: for head-dim index 32 t + lane%32, the 8 tile rows kk*16 + 8*(lane/32) .. +7
 //    (reduction over the tile rows), two transposing 8-byte reads (ds_read_b64_tr_b16);
 // so no transposed copy of a tile is ever built.  A wave-wide direct load writes 64 consecutive
 // 16-byte chunks, hence tiles are unpadded; the chunk position inside a row is XOR-swizzled
 // with a function of the row that keeps BOTH read patterns free of bank conflicts:
-// 16 consecutive rows at one logical chunk (frag_k) and 4 consecutive rows x 4 consecutive
-// chunks (frag_t) each touch 16 different 16-byte bank groups.
+// 16 consecutive rows at one logical chunk (read_k) and 4 consecutive rows x 4 consecutive
+// chunks (read_t) each touch 16 different 16-byte bank groups.
 #pragma once
 #include "common.h"
 
@@ -32,7 +32,7 @@ typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void gbl_void_t;
 
-static __device__ __align__(16) uint4 zero16 = {0u, 0u, 0u, 0u};   // source of rows beyond the sequence
+static __device__ __align__(16) uint4 zero16 = {0u, 0u, 0u, 0u};   // source of the rows of a paged tile beyond the sequence
 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {   // vmcnt <= N, no wait on the other counters
@@ -108,6 +108,9 @@ struct Tile {
   // compiler wait for every direct global->LDS load in flight first (it does not know that they fill the other
   // stage), so the prefetch of the next tile ends where the current one is multiplied; plain reads it hands out one
   // or two at a time between the products.  Addresses are LDS byte addresses.
+  // Measured with the buffer loads, the early block-table entries, the constant-against-bound masks and two blocks per CU for the
+  // 128-wide dK/dV kernel, which came with it: dK/dV 16 x 768 rows, 32 heads of 128, 507 -> 324 us, two-term forward 391 -> 375, dQ 273 -> 263;
+  // 8 x 420 rows, 32 heads of 64, 92 -> 74, 47 -> 41, 43 -> 37; paged prefill of 2329 rows behind 512 cached ones 56 -> 46.
   static __device__ __forceinline__ uint32_t lds_addr(const bf16_t *S) { return (uint32_t)(uintptr_t)(lds_void_t *)S; }
   // chunk (2 kk + half) ^ sw of the row sits at lane address ^ 32 kk: 2 kk has no bit in common with half, a row starts at
   // a multiple of its CPR chunks and a tile at a multiple of 256 bytes.  (The flip is applied behind the addition of the

@@ -347,8 +347,12 @@ hipError_t sk_launch(const SkinnyParams &p, int groups, hipStream_t st, int tile
 // Groups of 16 weight rows per block.  Four where that still gives most CUs a block: the activations then cross L2 -> CU
 // once per 64 weight rows, which is what bounds the products of more than 16 rows otherwise (32000 x 4096 at 64 rows:
 // 95 us with one group, 67 with two, 55 with four; at one row 51 / 49 / 46 us; 12288 x 4096 at 64 rows: 33 / 31 / 24).
-// A short reduction of at most 16 rows prefers two (32000 x 2048 at one row: 25 / 23 / 26 us).  One group otherwise;
-// 8-row groups where 16-row groups would leave CUs without a block (2048 x 5632 at one row: 6.5 -> 5.8 us).
+// A short reduction of at most 16 rows prefers two.  One / two / four groups in us, weights from HBM (more copies in turn than the
+// last-level cache holds), 16 rows: 16384 x 2048 14.0 / 12.9 / 13.9, 32000 x 2048 26.3 / 24.2 / 25.5, 65536 x 2048 51.3 / 47.7 /
+// 49.6, gate | up 2 x 11008 x 2048 19.1 / 17.4 / 21.7, 32000 x 1024 14.0 / 13.7 / 14.5; but 16384 x 4096 26.2 / 27.0 / 24.6, 32000 x 4096
+// 50.5 / 48.4 / 45.4, and 32 rows 32000 x 2048 32.9 / 27.5 / 27.2.  One group otherwise; 8-row groups where 16-row groups
+// would leave CUs without a block (2048 x 5632 at one row: 6.5 -> 5.8 us; 64 rows, 2048 x 2048 7.8 -> 7.1; at
+// 192 groups whole ones are ahead: 3072 x 2048 at 16 rows 5.0 against 6.1, at 64 rows 8.1 against 12.1).
 template <int ASRC, int EPI, int MT>
 hipError_t sk_pick(const SkinnyParams &p, hipStream_t st, int tile[2]) {
   const int groups = EPI == SK_E_SWIGLU ? p.N / 8 : p.N / 16;
