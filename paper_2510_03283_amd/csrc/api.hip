@@ -397,7 +397,7 @@ struct LogitWs {
 };
 LogitWs plan_logits(const Dims &D, size_t n, Bump &w) {
   LogitWs P;
-  P.n_hi = w.take<bf16_t>((n <= SKINNY_MAX_ROWS ? align_up(n, 16) : n) * D.d);      // whole tiles of the fragment order
+  P.n_hi = w.take<bf16_t>((D.bf && n <= SKINNY_MAX_ROWS ? align_up(n, 16) : n) * D.d);      // few-row path: whole tiles of the fragment order
   P.e_hi = D.bf ? nullptr : w.take<bf16_t>((size_t)D.V * D.d);
   return P;
 }

@@ -184,6 +184,15 @@ def test_few_row_products_read_inside_their_buffers(recorder, rows):
     assert work["ptr"] <= a and a + n <= work["ptr"] + lo, f"{rows} rows read {a + n - work['ptr'] - lo} bytes past a workspace of {lo}"
 
 
+@pytest.mark.parametrize("rows", [1, 17, 63])
+def test_fp32_logits_need_no_more_scratch_than_their_rows(recorder, rows):
+    """fp32 models never take the few-row products, so their scratch holds the rows themselves and the head's bf16 form."""
+    d, V = 1024, 4096
+    work = -(-rows * d * 2 // 256) * 256 + V * d * 2
+    rec = recorder("logits", d=d, V=V, bf16=0, decode=[5] * rows, n=rows, work=work)
+    assert status(rec)["status"] == 0 and not skinny_reads(rec)
+
+
 @pytest.mark.parametrize("d,hq,hkv,F,V", [(1024, 8, 8, 2816, 4096), (2048, 32, 8, 5632, 32000), (4096, 32, 32, 11008, 32000)])
 @pytest.mark.parametrize("rows", [1, 17, 33, 64])
 def test_plan_records_the_tiles_of_few_row_products(recorder, rows, d, hq, hkv, F, V):
