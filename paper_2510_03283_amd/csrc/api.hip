@@ -30,6 +30,7 @@ struct mace_ctx {
   hipStream_t side = nullptr;
   hipEvent_t ev_fork[N_FORK_EVENTS] = {}, ev_join = nullptr;
   int n_fork = 0;          // forks issued in the current call
+  bool in_span = false;    // between the first fork and the join (with MACE_OPT_SINGLE_STREAM: where they would be)
   bool head_two_pass = false;   // MACE_OPT_HEAD_TWO_PASS: every logit of the DPO head from two-term activations
   bool single_stream = false;   // MACE_OPT_SINGLE_STREAM
   int decode_chunk = 0;         // MACE_OPT_DECODE_CHUNK
@@ -72,6 +73,7 @@ void prof_mark(mace_ctx *h, hipStream_t st, int tag, double flops = 0.0, double 
 // Side stream on which work may start once everything issued so far on `st` is done; returns `st`
 // itself when the context has no side stream.
 hipStream_t side_fork(mace_ctx *h, hipStream_t st) {
+  h->in_span = true;
   if (!h->side || h->single_stream || h->n_fork >= N_FORK_EVENTS) return st;
   hipEvent_t ev = h->ev_fork[h->n_fork];
   if (hipEventRecord(ev, st) != hipSuccess || hipStreamWaitEvent(h->side, ev, 0) != hipSuccess) return st;
@@ -80,6 +82,7 @@ hipStream_t side_fork(mace_ctx *h, hipStream_t st) {
 }
 // Makes `st` wait for everything issued on the side stream in this call.
 hipError_t side_join(mace_ctx *h, hipStream_t st) {
+  h->in_span = false;
   if (!h->side || h->n_fork == 0) return hipSuccess;
   h->n_fork = 0;
   hipError_t e = hipEventRecord(h->ev_join, h->side);
@@ -430,9 +433,11 @@ int run_gemm(mace_ctx *h, int LA, int LB, GemmParams &p, hipStream_t st, const c
 // Where a product on stream s puts its slices.  Two launches on different streams of a call are unordered from the fork to
 // the join, so they must not meet in one pool: `side` belongs to the side stream from the first fork to the join, and
 // outside that span (nothing in flight there, a later fork waits for what was issued here) to the caller's stream.  In
-// between a product of the caller's stream takes what the not yet consumed partial results `live` leave of `main`.
-PartPool room_for(const mace_ctx *h, hipStream_t s, const PartPool &main, const PartPool &side, const Parts &live = {}) {
-  if ((h->side && s == h->side) || h->n_fork == 0) return side;
+// between a product of the caller's stream takes what the not yet consumed partial results `live` leave of `main`.  The room
+// decides how many slices there are, so MACE_OPT_SINGLE_STREAM, which has to give the same bits, shares the pools out
+// as the two streams would (for_side: the product is one for the side stream).
+PartPool room_for(const mace_ctx *h, hipStream_t s, bool for_side, const PartPool &main, const PartPool &side, const Parts &live = {}) {
+  if (!h->in_span || (for_side && (h->single_stream || s == h->side))) return side;
   const size_t used = live.p == main.base ? (size_t)live.n * live.stride : 0;
   return PartPool{main.base + used, main.floats - used};
 }
@@ -475,7 +480,7 @@ int run_gemm_side(mace_ctx *h, int LA, int LB, GemmParams &p, const PartPool &ma
   bool done = false;
   GemmParams plain = p;
   plain.resid_kind = 0;
-  int rc = run_gemm_parts(h, LA, LB, p, plain, room_for(h, s2, main, side, live), 5.0, s2, where, part, done);
+  int rc = run_gemm_parts(h, LA, LB, p, plain, room_for(h, s2, main_chain_small, main, side, live), 5.0, s2, where, part, done);
   if (done && rc == MACE_OK) {
     SumRange r[3];
     for (int g = 0; g < p.n_mg; ++g) r[g] = SumRange{part[g], p.resid_kind ? (const float *)p.mg[g].resid : nullptr, p.mg[g].c, part[g].stride};
@@ -1098,7 +1103,7 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(p, F.a_i, nullptr, L.t_qkv, nullptr, I.Ti, 1);
     gp_seg(p, L.aqkv_hi, L.aqkv_lo, 3 * LR, 0);
     Parts t_i, t_f;
-    TRY(run_adapter_product(h, p, I.Tf, I.Ti, 3 * LR, L.t_qkv, room_for(h, s2, F.pool, F.side_pool), s2, "lora t_qkv gemm", t_f, t_i));
+    TRY(run_adapter_product(h, p, I.Tf, I.Ti, 3 * LR, L.t_qkv, room_for(h, s2, true, F.pool, F.side_pool), s2, "lora t_qkv gemm", t_f, t_i));
     prof_mark(h, s2, T_MISC);
     HIP_TRY(launch_scale_split(t_i, (size_t)I.Ti * 3 * LR, lora->scale, L.tq_hi, nullptr, s2), "lora t_qkv split");
     HIP_TRY(launch_scale_split(t_f, (size_t)I.Tf * 3 * LR, lora->scale, S.tq, L.tq_lo, s2), "lora t_qkv split ft");
@@ -1170,7 +1175,7 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_group(p, F.o_i, nullptr, L.t_o, nullptr, I.Ti, 1);
     gp_seg(p, L.ao_hi, L.ao_lo, LR, 0);
     Parts t_i, t_f;
-    TRY(run_adapter_product(h, p, I.Tf, I.Ti, LR, L.t_o, room_for(h, s2, F.pool, F.side_pool), s2, "lora t_o gemm", t_f, t_i));
+    TRY(run_adapter_product(h, p, I.Tf, I.Ti, LR, L.t_o, room_for(h, s2, true, F.pool, F.side_pool), s2, "lora t_o gemm", t_f, t_i));
     prof_mark(h, s2, T_MISC);
     HIP_TRY(launch_scale_split(t_i, (size_t)I.Ti * LR, lora->scale, L.to_hi, nullptr, s2), "lora t_o split");
     HIP_TRY(launch_scale_split(t_f, (size_t)I.Tf * LR, lora->scale, S.to, L.to_lo, s2), "lora t_o split ft");
@@ -1406,7 +1411,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     p.out_bf16 = 1;
     gp_group(p, B.dx1_bf, nullptr, L.dto, nullptr, Tf, 1);
     gp_seg(p, L.bo_hi, nullptr, LR, 0);
-    TRY(run_gemm_bf16_parts(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dt_o gemm"));
+    TRY(run_gemm_bf16_parts(h, p, room_for(h, s2, true, B.pool, B.side_pool), s2, "lora dt_o gemm"));
     if (s2 != st) prof_mark(h, s2, -1);
   }
   {
@@ -1449,7 +1454,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       gp_group(p, B.dx1_bf, nullptr, L.dbo, nullptr, D.d, 1);
       gp_seg(p, S.to, nullptr, LR, 0);
       Parts gr;
-      TRY(run_adapter_grad(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dB_o gemm", gr));
+      TRY(run_adapter_grad(h, p, room_for(h, s2, true, B.pool, B.side_pool), s2, "lora dB_o gemm", gr));
       prof_mark(h, s2, T_MISC);
       HIP_TRY(launch_extract(gr, LR, 0, 0, D.d, lora->rank, 1.0f, lgrads->b_o, acc, s2), "lora dB_o");
       if (s2 != st) prof_mark(h, s2, -1);
@@ -1460,7 +1465,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       gp_group(p, L.dto, nullptr, L.dao, nullptr, LR, 1);
       gp_seg(p, S.o, nullptr, D.qd, 0);
       Parts gr;
-      TRY(run_adapter_grad(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dA_o gemm", gr));
+      TRY(run_adapter_grad(h, p, room_for(h, s2, true, B.pool, B.side_pool), s2, "lora dA_o gemm", gr));
       prof_mark(h, s2, T_MISC);
       HIP_TRY(launch_extract(gr, D.qd, 0, 0, lora->rank, D.qd, 1.0f, lgrads->a_o, acc, s2), "lora dA_o");
       if (s2 != st) prof_mark(h, s2, -1);
@@ -1486,7 +1491,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
       p.out_bf16 = 1;
       gp_group(p, B.dqkv, nullptr, L.dtq, nullptr, Tf, 1);
       gp_seg(p, L.bblk_hi, nullptr, 3 * LR, 0);
-      TRY(run_gemm_bf16_parts(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dt_qkv gemm"));
+      TRY(run_gemm_bf16_parts(h, p, room_for(h, s2, true, B.pool, B.side_pool), s2, "lora dt_qkv gemm"));
       if (s2 != st) prof_mark(h, s2, -1);
     }
     {
@@ -1518,7 +1523,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
         gp_group(p, B.dqkv, nullptr, L.dbblk, nullptr, D.nqkv, 1);
         gp_seg(p, S.tq, nullptr, 3 * LR, 0);
         Parts gr;
-        TRY(run_adapter_grad(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dB_qkv gemm", gr));
+        TRY(run_adapter_grad(h, p, room_for(h, s2, true, B.pool, B.side_pool), s2, "lora dB_qkv gemm", gr));
         float *dst[3] = {lgrads->b_q, lgrads->b_k, lgrads->b_v};
         const int r0[3] = {0, D.qd, D.qd + D.kd}, nr[3] = {D.qd, D.kd, D.kd};
         for (int i = 0; i < 3; ++i)
@@ -1534,7 +1539,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
         gp_group(p, L.dtq, nullptr, L.daqkv, nullptr, 3 * LR, 1);
         gp_seg(p, S.a, nullptr, D.d, 0);
         Parts gr;
-        TRY(run_adapter_grad(h, p, room_for(h, s2, B.pool, B.side_pool), s2, "lora dA_qkv gemm", gr));
+        TRY(run_adapter_grad(h, p, room_for(h, s2, true, B.pool, B.side_pool), s2, "lora dA_qkv gemm", gr));
         float *dst[3] = {lgrads->a_q, lgrads->a_k, lgrads->a_v};
         for (int i = 0; i < 3; ++i)
           if (dst[i]) {

@@ -1,10 +1,9 @@
 """Weight gradients of one backward whose cut products are spread over both streams (attention or MLP narrower than the
-model, many rows): the two-stream run against the single-stream run of the same inputs.  The operands are the same
-bf16 values; only the number of slices of an fp32 sum over 16384 rows may differ, an error of about
-sqrt(16384) * 2^-24 = 8e-6 on each side.  Slices that overwrite each other's partial results change it by whole addends."""
+model, many rows): the two-stream run against the single-stream run of the same inputs, which has to give the same bits.
+Slices that overwrite each other's partial results change a gradient by whole addends."""
+import numpy as np
 import pytest
 
-from helpers import rel_fro_err
 from paper_2510_03283_amd import synth
 from test_gpu_parity import custom_workload
 
@@ -33,6 +32,4 @@ def test_slices_on_both_streams(torch_mod, hq, hkv, F):
         finally:
             it.close()
     for k in got[0]:
-        e = rel_fro_err(got[0][k], got[1][k])
-        print(f"{k}: {e:.2e}", flush=True)
-        assert e <= 2e-5, (k, e)
+        assert np.array_equal(got[0][k], got[1][k]), k

@@ -122,6 +122,20 @@ def test_slices_of_the_backward_do_not_meet_over_a_range_of_shapes(recorder):
 
 
 @pytest.mark.parametrize("lora", [0, 16])
+@pytest.mark.parametrize("shape", BWD + [dict(d=3584, hq=16, hkv=4, hd=128, F=2816, ft=[1412] * 8)],
+                         ids=lambda s: f"d{s['d']}_q{s['hq'] * s['hd']}_F{s['F']}_{sum(s['ft'])}")
+def test_one_stream_cuts_the_same_slices(recorder, shape, lora):
+    """MACE_OPT_SINGLE_STREAM promises the same bits, so every product has the same tile and the same number of slices."""
+    plans = []
+    for single_stream in (0, 1):
+        rec = recorder("bwd", lora=lora, single_stream=single_stream, **shape)
+        assert status(rec)["status"] == 0
+        check_slices(rec)
+        plans.append([(r["name"], r["tile"], r["k_splits"]) for r in plan(rec)])
+    assert plans[0] == plans[1]
+
+
+@pytest.mark.parametrize("lora", [0, 16])
 @pytest.mark.parametrize("single_stream", [0, 1])
 def test_slices_of_the_forward_do_not_meet(recorder, lora, single_stream):
     n = 0
