@@ -23,10 +23,11 @@ def check(name, lines):
     if not loads:
         return False, f"{name}: no buffer loads found"
     labels = {m.group(1): i for i, l in enumerate(code) for m in [re.match(r'^(\.LBB\d+_\d+):', l)] if m}
-    first_store = next((i for i, l in enumerate(code) if 'global_store' in l), len(code))
     barriers = [i for i, l in enumerate(code) if 's_barrier' in l]
     if len(barriers) != 5:
         return False, f"{name}: expected 5 barriers (prologue, two loop phases, two tail phases), found {len(barriers)}"
+    # the epilogue, whose loads and stores the compiler knows: behind the wait states that end the main loop's part
+    first_store = next((i for i, l in enumerate(code) if i > barriers[-1] and ('global_store' in l or re.search(r's_nop 15\s*$', l))), len(code))
     # the main loop: the backward branch behind the third barrier, up to the block it reaches
     back = [(i, labels[m.group(1)]) for i, l in enumerate(code) for m in [re.search(r's_c?branch\S*\s+(\.LBB\d+_\d+)', l)]
             if m and m.group(1) in labels and labels[m.group(1)] <= i and barriers[2] < i < barriers[3]]

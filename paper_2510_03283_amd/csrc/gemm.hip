@@ -500,7 +500,8 @@ template <int LA, int LB>
 hipError_t launch_w4(GemmParams &p, hipStream_t stream) {
   const int tiles = count_tiles<256, 256>(p);
   if (tiles == 0) return hipSuccess;
-  constexpr size_t lds = (size_t)2 * (256 + 256) * BK * sizeof(bf16_t);
+  constexpr size_t lds = w4_lds_bytes<LA, LB>();
+  static_assert(lds <= 160 * 1024, "LDS budget of a gfx950 CU");
   static DeviceOnce attr_done;
   if (!attr_done.test()) {
     hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_w4_kernel<LA, LB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

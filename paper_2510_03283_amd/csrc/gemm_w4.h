@@ -1,5 +1,5 @@
 // 256x256x64 block tile on FOUR waves (2 x 2, wave tile 128x128), included by gemm.hip inside its
-// anonymous namespace (it uses DirectStage's tile layouts and swizzles).
+// anonymous namespace.
 //
 // One wave per SIMD owns all 512 registers of a lane: 256 accumulator registers (AGPRs) and 256
 // VGPRs, of which 128 are two register sets that stage operand tiles on their way global -> VGPR
@@ -7,9 +7,14 @@
 // fragment reads per MFMA, the tiles reach LDS through 16-byte ds_writes (a quarter of the LDS time of
 // a direct global->LDS load) and every global load has two tile times to land.  Nothing covers a
 // stall of the only wave of a SIMD, so the loop is written as an explicit schedule: one fragment
-// read or one "move" (wait for a staged register, ds_write it, request the same register again for
+// read, or one half of a "move" (wait for a staged register and ds_write it; request the same register again for
 // the tile three ahead) behind single MFMAs, one barrier per k tile, and the first fragments of the
 // next tile read behind that barrier under the last MFMAs of the current one.
+//
+// The MFMAs are the 16x16x32 form.  What bounds the loop on real data is power: with 32x32x16 MFMAs the pipes were
+// busy 0.72 - 0.81 of the cycles at a clock of 1.6 GHz.  A loop of nothing but MFMAs on random operands runs at
+// 1.83 PFLOP/s with 32x32x16 and at 2.06 with 16x16x32, with the fragment reads of this kernel 1.73 and 1.95 (on zeros
+// all of them 2.46): the 16x16 form moves half the accumulator bits per flop, which costs less than its doubled operand reads.
 //
 // Operand loads are buffer loads whose resource spans the operand from its first to its last
 // element: a load beyond the end returns zeros, which is the whole edge handling (rows past M or N
@@ -85,6 +90,44 @@ __device__ __forceinline__ W4Src w4_resources(const W4Cur c, uint32_t a_bytes, b
   return r;
 }
 
+// How an operand tile lies in LDS, for 256 threads and 16x16x32 fragments (8 consecutive k of one row per lane).
+// Every address is one lane part plus constants.
+// LAYOUT 0 (k contiguous): [row][64 k], 16-byte chunk kc of a row at position kc ^ ((row / 2) % 8).
+// LAYOUT 1 (rows contiguous): [k][256 rows] with a pitch of 544 bytes and 128 more behind every eighth k.  A fragment
+// comes from two transposing reads, whose lanes take 8 bytes of four k and, in the next 16 lanes, of the four k
+// eight further on: 32 bytes each at eight different places of the 256 bytes of all banks.  (A swizzle would have to mix lane bits
+// into the bits that select the fragment, i.e. take an address register per fragment.)
+template <int LAYOUT>
+struct W4Tile {
+  static constexpr int BYTES = LAYOUT == 0 ? 256 * 128 : 8 * 4480;
+  static constexpr int LOAD_STEP = LAYOUT == 0 ? 4096 : 4480;      // LDS bytes from one load of a thread to its next (of 8)
+  static constexpr int LOAD_ROWS = LAYOUT == 0 ? 32 : 8;           // ... and rows of the matrix in memory
+  static constexpr int NFA = LAYOUT == 0 ? 2 : 1;                  // lane addresses of fragments (LAYOUT 0: one per k step)
+  static constexpr int RPF = LAYOUT == 0 ? 1 : 2;                  // LDS reads per fragment
+  // byte offset in memory and in LDS of a thread's first load
+  static __device__ __forceinline__ uint32_t global_offset(int thread, long long ld) {
+    if constexpr (LAYOUT == 0) {
+      const int lr = thread >> 3, kc = (thread & 7) ^ ((lr >> 1) & 7);
+      return (uint32_t)((lr * ld + kc * 8) * 2);
+    } else {
+      return (uint32_t)(((thread >> 5) * ld + (thread & 31) * 8) * 2);
+    }
+  }
+  static __device__ __forceinline__ uint32_t lds_offset(int thread) {
+    return LAYOUT == 0 ? (uint32_t)thread * 16u : (uint32_t)((thread >> 5) * 544 + (thread & 31) * 16);
+  }
+  // fragment f of k step kk starts at frag_lane(w0, lane, kk) + frag_const(kk, f); w0: the wave's first row
+  static __device__ __forceinline__ uint32_t frag_lane(int w0, int lane, int kk) {
+    const int q = lane >> 4, j = lane & 15;
+    if constexpr (LAYOUT == 0) return (uint32_t)((w0 + j) * 128 + (((4 * kk + q) ^ (j >> 1)) * 16));
+    else return (uint32_t)((8 * q + (j >> 2)) * 544 + q * 128 + (w0 + 4 * (j & 3)) * 2);
+  }
+  static constexpr int frag_const(int kk, int f) { return LAYOUT == 0 ? f * 2048 : kk * (32 * 544 + 4 * 128) + f * 32; }
+  static constexpr int FRAG_HALF = 4 * 544;                        // LAYOUT 1: from the first four k of a fragment to the others
+};
+template <int LA, int LB>
+constexpr size_t w4_lds_bytes() { return 2 * ((size_t)W4Tile<LA>::BYTES + W4Tile<LB>::BYTES); }
+
 // An accumulator element for the epilogue, read where it lives.  The accumulators stay in AGPRs from the loop to
 // the end of the kernel; handed over as plain values, the register allocator copies whole 16-register blocks into
 // VGPRs at the end of the loop for all epilogue variants at once, spills what does not fit and reloads a block
@@ -95,13 +138,17 @@ __device__ __forceinline__ float w4_acc_rd(float a) {
   return v;
 }
 
+// (asm: with the builtin the register allocator gives some of the 64 accumulators two homes and moves them around the loop)
+__device__ __forceinline__ void w4_mfma(f32x4_t &c, const u32x4_t b, const u32x4_t a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b), "v"(a));
+}
+
 template <int LA, int LB>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
-  constexpr int BM = 256, BN = 256, BKT = 64, NTHR = 256, WGN = 2, WTM = 128, WTN = 128, TM = 4, TN = 4;
-  using SA = DirectStage<BM, LA, BKT, 512>;    // tile layout, swizzle and fragment addressing
-  using SB = DirectStage<BN, LB, BKT, 512>;
+  constexpr int BM = 256, BN = 256, BKT = 64, NTHR = 256, WGN = 2, WTM = 128, WTN = 128, TM = 8, TN = 8;      // TM x TN blocks of 16x16
+  using SA = W4Tile<LA>;
+  using SB = W4Tile<LB>;
   constexpr int NL = BM * BKT / 8 / NTHR;      // 16-byte loads per lane and operand tile (8)
-  constexpr int OPB = BM * BKT * 2;            // bytes of one operand tile (32 KB)
   // LDS: A stage 0 | A stage 1 | B stage 0 | B stage 1
   extern __shared__ __align__(16) unsigned char smem_raw[];
   lds_char_t *const lbase = (lds_char_t *)(lds_void_t *)smem_raw;
@@ -143,13 +190,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
 
-  f32x16_t acc[TM][TN];
+  // Block (i, j): the B fragment is the first operand, so register r of a lane holds row 16 i + lane % 16 and column
+  // 16 j + 4 (lane / 16) + r - four neighbouring columns, which leave as one 16-byte store.
+  f32x4_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
   // k tiles tt0 .. tt0 + n_it - 1 of the tile's passes, one after the other (the launcher gives every slice some)
   const int nk = (K + BKT - 1) / BKT, nk_slice = (nk * G.npass + ks - 1) / ks;
@@ -171,106 +220,99 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   // a tile that continues the k run of the one before it lies stepA / stepB bytes further on
   const uint32_t stepA = (uint32_t)(LA == 0 ? BKT * 2 : BKT * lda * 2), stepB = (uint32_t)(LB == 0 ? BKT * 2 : BKT * ldb * 2);
 
-  // Byte offset of this lane's first load inside an operand tile; load x of a tile fetches the chunk
-  // 256 x further on, which is strA (strB) bytes away in memory and keeps the swizzle phase.
-  static_assert(256 % SA::CPR == 0 && 256 % SB::CPR == 0 && (256 / SA::CPR) % 4 == 0 && (256 / SB::CPR) % 4 == 0,
-                "a step of 256 chunks must keep the swizzle phase");
-  uint32_t offA, offB;
-  {
-    const int chunk = wave * 64 + lane;
-    {
-      const int lr = chunk / SA::CPR, pos = chunk % SA::CPR;
-      if constexpr (LA == 0) {
-        offA = (uint32_t)(((long long)lr * lda + (pos ^ ((lr / SA::RPB) % SA::CPR)) * 8) * 2);
-      } else {
-        const int c = SA::POW2 ? pos ^ ((lr & 3) << 2) : (pos + SA::CPR - 4 * (lr & 3)) % SA::CPR;
-        offA = (uint32_t)(((long long)lr * lda + 8 * c) * 2);
-      }
-    }
-    {
-      const int lr = chunk / SB::CPR, pos = chunk % SB::CPR;
-      if constexpr (LB == 0) {
-        offB = (uint32_t)(((long long)lr * ldb + (pos ^ ((lr / SB::RPB) % SB::CPR)) * 8) * 2);
-      } else {
-        const int c = SB::POW2 ? pos ^ ((lr & 3) << 2) : (pos + SB::CPR - 4 * (lr & 3)) % SB::CPR;
-        offB = (uint32_t)(((long long)lr * ldb + 8 * c) * 2);
-      }
-    }
-  }
-  const uint32_t strA = (uint32_t)(256 / SA::CPR * lda * 2), strB = (uint32_t)(256 / SB::CPR * ldb * 2);
-  // k-contiguous B: loads 2u and 2u+1 are 32 rows apart, except in SwiGLU mode, where they fetch the gate and
-  // the up rows of the same 32 hidden units out of two matrices
-  const uint32_t strB_pair = swiglu ? strB : 2 * strB, strB_odd = swiglu ? 0u : strB;
-  typename SA::FragAddr fa = SA::template frag_addr<TM>(wm * WTM, lane);
-  typename SB::FragAddr fb = SB::template frag_addr<TN>(wn * WTN, lane);
-  // The B stages start 64 KB into LDS, beyond the 16-bit offset field of an LDS instruction.  Their lane
-  // addresses carry the 64 KB and are made opaque, so that stage and fragment offsets stay immediates (seen
-  // as "lane part + constant" the compiler folds all constants into one and keeps a register per sum).
+  // Byte offset of this lane's first load inside an operand tile; load x of a tile lies x * strA (strB) bytes further on.
+  const uint32_t offA = SA::global_offset((int)threadIdx.x, lda), offB = SB::global_offset((int)threadIdx.x, ldb);
+  const uint32_t strA = (uint32_t)(SA::LOAD_ROWS * lda * 2), strB = (uint32_t)(SB::LOAD_ROWS * ldb * 2);
+  // SwiGLU mode: the 128 columns of a wave are 64 gate columns and the 64 up columns of the same hidden units, so loads
+  // 4 w .. 4 w + 3 of a tile fetch 64 gate and 64 up rows (32 a load) out of two matrices
+  const uint32_t strB_w = swiglu ? 2 * strB : 4 * strB, strB_u = swiglu ? 0u : 2 * strB;
+  uint32_t fa[2], fb[2];
 #pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    fb.v[x] += 2 * OPB;
-    asm volatile("" : "+v"(fb.v[x]));
+  for (int x = 0; x < 2; ++x) {
+    fa[x] = SA::frag_lane(wm * WTM, lane, x < SA::NFA ? x : 0);
+    fb[x] = SB::frag_lane(wn * WTN, lane, x < SB::NFA ? x : 0) + 2 * SA::BYTES;
+    // The B stages start 64 KB into LDS or further on, beyond the 16-bit offset field of an LDS instruction.  Their lane
+    // addresses carry that and are made opaque, so that stage and fragment offsets stay immediates (seen
+    // as "lane part + constant" the compiler folds all constants into one and keeps a register per sum).
+    asm volatile("" : "+v"(fa[x]));
+    asm volatile("" : "+v"(fb[x]));
   }
-  const uint32_t wofs = (uint32_t)(wave * 1024 + lane * 16);     // load x of a tile sits at wofs + x * 4096
-  uint32_t wofs_b = wofs + 2 * OPB;
+  uint32_t wofs = SA::lds_offset((int)threadIdx.x), wofs_b = SB::lds_offset((int)threadIdx.x) + 2 * SA::BYTES;
+  asm volatile("" : "+v"(wofs));
   asm volatile("" : "+v"(wofs_b));
 
   u32x4_t ra[2][NL], rb[2][NL];        // register sets: tile t waits in set (t + 1) & 1
-  u32x4_t fra[2][TM], frb[2][TN];      // fragments, double-buffered over k steps
+  u32x4_t fra[TM], frb[TN];            // fragments of the current k step; a half of them is replaced as soon as it has been used
 
   auto bload = [&](u32x4_t &dst, const u32x4_t &rs, uint32_t voff, uint32_t soff) W4_INL {
     asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(dst) : "v"(voff), "s"(rs), "s"(soff));
   };
-  // load x (0..7: A, 8..15: B) of the tile described by `src`.  SwiGLU mode: the B tile interleaves 32 gate
-  // rows and the 32 up rows of the same hidden units; a load covers 8 rows of one of the two.
+  // load x (0..7: A, 8..15: B) of the tile described by `src`
   auto request = [&](auto SET, auto X, const Src &src) W4_INL {
     constexpr int set = decltype(SET)::value, x = decltype(X)::value;
     if constexpr (x < NL) {
       bload(ra[set][x], src.qa, offA, src.oa + x * strA);
     } else {
       constexpr int y = x - NL;
-      if constexpr (LB == 0) bload(rb[set][y], (y & 1) ? src.qu : src.qb, offB, src.ob + (y >> 1) * strB_pair + (y & 1) * strB_odd);
+      if constexpr (LB == 0) bload(rb[set][y], (y & 2) ? src.qu : src.qb, offB, src.ob + (y >> 2) * strB_w + ((y >> 1) & 1) * strB_u + (y & 1) * strB);
       else bload(rb[set][y], src.qb, offB, src.ob + y * strB);
     }
   };
   auto stage_write = [&](auto SET, auto X, auto ST) W4_INL {
     constexpr int set = decltype(SET)::value, x = decltype(X)::value, st = decltype(ST)::value;
-    if constexpr (x < NL) *(lds_u32x4_t *)(lbase + wofs + st * OPB + x * 4096) = ra[set][x];
-    else *(lds_u32x4_t *)(lbase + wofs_b + st * OPB + (x - NL) * 4096) = rb[set][x - NL];
+    if constexpr (x < NL) *(lds_u32x4_t *)(lbase + wofs + st * SA::BYTES + x * SA::LOAD_STEP) = ra[set][x];
+    else *(lds_u32x4_t *)(lbase + wofs_b + st * SB::BYTES + (x - NL) * SB::LOAD_STEP) = rb[set][x - NL];
   };
-  // fragment f (0..3: A rows, 4..7: B columns) of k step kk out of stage st into fragment buffer nb
-  auto read1 = [&](auto ST, auto KK, auto NB, auto FF) W4_INL {
-    constexpr int st = decltype(ST)::value, kk = decltype(KK)::value, nb = decltype(NB)::value, f = decltype(FF)::value;
-    if constexpr (f < TM) {
-      if constexpr (LA == 0) {
-        fra[nb][f] = *(lds_u32x4_t *)(lbase + fa.v[kk] + st * OPB + f * 32 * BKT * 2);
-      } else {
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(lbase + fa.v[f] + st * OPB + kk * 16 * BM * 2));
-        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(lbase + fa.v[f] + st * OPB + kk * 16 * BM * 2 + 4 * BM * 2));
-        const u32x2_t l2 = __builtin_bit_cast(u32x2_t, lo), h2 = __builtin_bit_cast(u32x2_t, hi);
-        fra[nb][f] = u32x4_t{l2[0], l2[1], h2[0], h2[1]};
-      }
+  // fragment f of half HF of an operand (OP 0: A, 1: B) for k step kk out of stage st
+  auto frag = [&](auto TL, uint32_t base, auto O) W4_INL -> u32x4_t {
+    using T = decltype(TL);
+    constexpr int o = decltype(O)::value;
+    if constexpr (T::RPF == 1) {
+      return *(lds_u32x4_t *)(lbase + base + o);
     } else {
-      constexpr int j = f - TM;
-      if constexpr (LB == 0) {
-        frb[nb][j] = *(lds_u32x4_t *)(lbase + fb.v[kk] + st * OPB + j * 32 * BKT * 2);
-      } else {
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(lbase + fb.v[j] + st * OPB + kk * 16 * BN * 2));
-        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(lbase + fb.v[j] + st * OPB + kk * 16 * BN * 2 + 4 * BN * 2));
-        const u32x2_t l2 = __builtin_bit_cast(u32x2_t, lo), h2 = __builtin_bit_cast(u32x2_t, hi);
-        frb[nb][j] = u32x4_t{l2[0], l2[1], h2[0], h2[1]};
-      }
+      const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(lbase + base + o));
+      const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(lbase + base + o + T::FRAG_HALF));
+      const u32x2_t l2 = __builtin_bit_cast(u32x2_t, lo), h2 = __builtin_bit_cast(u32x2_t, hi);
+      return u32x4_t{l2[0], l2[1], h2[0], h2[1]};
     }
   };
-  auto mfma1 = [&](auto KK, auto Q) W4_INL {
-    constexpr int kk = decltype(KK)::value, q = decltype(Q)::value, i = q / TN, j = q % TN;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fra[kk & 1][i]), __builtin_bit_cast(bf16x8_t, frb[kk & 1][j]), acc[i][j], 0, 0, 0);
+  auto read1 = [&](auto OP, auto ST, auto KK, auto HF, auto FF) W4_INL {
+    constexpr int op = decltype(OP)::value, st = decltype(ST)::value, kk = decltype(KK)::value, f = 4 * decltype(HF)::value + decltype(FF)::value;
+    if constexpr (op == 0) fra[f] = frag(SA{}, fa[SA::NFA == 2 ? kk : 0], W4_IC(st * SA::BYTES + SA::frag_const(kk, f)));
+    else frb[f] = frag(SB{}, fb[SB::NFA == 2 ? kk : 0], W4_IC(st * SB::BYTES + SB::frag_const(kk, f)));
+  };
+  auto mfma1 = [&](auto I, auto J) W4_INL {
+    constexpr int i = decltype(I)::value, j = decltype(J)::value;
+    w4_mfma(acc[i][j], frb[j], fra[i]);
   };
 
   const int n_run = max(n_it, 3);      // tile times: at least one turn of the loop and one tile behind it
   const int rq_last = tt0 + n_it - 1;
-  int rq_tt;      // the tile requested last, and where it comes from
-  W4Cur rq;
+  // The request cursor: the tile requested last, where it comes from, and how many tiles may follow it by a step of stepA /
+  // stepB alone, without a change of pass or k segment.  Past the last tile the requests, which then only keep the
+  // count of loads in flight constant, get empty resources: zeros, without going to memory.
+  int rq_tt, rq_left;
+  Src rq;
+  auto run_length = [&](int tt) W4_INL -> int {
+    const int pass_end = tt >= 2 * nk ? 3 * nk : (tt >= nk ? 2 * nk : nk);
+    int e = min(pass_end, rq_last + 1);
+    if (n_kseg > 1) {      // (k segments exclude passes)
+      if (tt * BKT < ks_s1) e = min(e, ks_s1 / BKT);
+      else if (tt * BKT < ks_s2) e = min(e, ks_s2 / BKT);
+    }
+    return (int)w4_sgpr((uint32_t)(e - 1 - tt));
+  };
+  auto advance = [&]() W4_INL {
+    rq.oa += stepA;
+    rq.ob += stepB;
+    if (__builtin_expect(--rq_left < 0, 0)) {
+      rq_tt = min(rq_tt, rq_last) + 1;
+      const bool dead = rq_tt > rq_last;
+      rq = w4_resources(tile_cur(min(rq_tt, rq_last)), a_bytes, dead);
+      rq_left = dead ? 0x7fffffff : run_length(rq_tt);
+      rq_tt = dead ? rq_tt : rq_tt + rq_left;      // the last tile of the run
+    }
+  };
   {
     // prologue: tile 0 -> set 1 -> stage 0; tile 1 -> set 0; tile 2 -> set 1.  Tiles past the last repeat
     // the last one (their data is never multiplied): the loop's wait counts assume every request is issued.
@@ -286,75 +328,70 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       static_for<0, 2 * NL>([&](auto X) W4_INL { stage_write(W4_IC(1), X, W4_IC(0)); });
       W4_SB;
       rq_tt = tt0 + min(2, n_it - 1);
-      rq = tile_cur(rq_tt);
-      const Src s2 = w4_resources(rq, a_bytes, n_it < 3);
-      static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(1), X, s2); });
+      rq = w4_resources(tile_cur(rq_tt), a_bytes, n_it < 3);
+      rq_left = n_it < 3 ? 0x7fffffff : run_length(rq_tt);
+      rq_tt += n_it < 3 ? 0 : rq_left;
+      static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(1), X, rq); });
+      W4_SB;
+      advance();
       W4_SB;
       __syncthreads();
-      static_for<0, TM + TN>([&](auto F) W4_INL { read1(W4_IC(0), W4_IC(0), W4_IC(0), F); });
+      static_for<0, 4>([&](auto F) W4_INL { read1(W4_IC(0), W4_IC(0), W4_IC(0), W4_IC(0), F); });
+      static_for<0, 4>([&](auto F) W4_INL { read1(W4_IC(1), W4_IC(0), W4_IC(0), W4_IC(0), F); });
       W4_SB;
     }
     // Tile time t (phase ph = t & 1): multiply tile t out of stage ph; move tile t+1 from register set ph
     // into stage ph^1 (free since the barrier of tile time t-1), re-requesting each register right after
-    // its ds_write for tile t+3; barrier behind the first MFMA of the last k step; the first fragments of
+    // its ds_write for tile t+3; barrier in the seventh of eight quarters; the first fragments of
     // tile t+1 behind the barrier.
     auto phase = [&](auto PH, auto TAIL, int t) W4_INL {
       constexpr int ph = decltype(PH)::value;
       constexpr bool tail = decltype(TAIL)::value;
-      // the next request: tile t + 3, or the last tile again.  Only a change of pass or of k segment takes
-      // the full computation.
-      bool dead = false;
-      if (!tail && rq_tt >= rq_last) dead = true;
-      if (!tail && rq_tt < rq_last) {
-        ++rq_tt;
-        const int kq = rq_tt * BKT;      // (k segments exclude passes)
-        if (rq_tt == nk || rq_tt == 2 * nk || (n_kseg > 1 && (kq == ks_s1 || kq == ks_s2))) {
-          rq = tile_cur(rq_tt);
-        } else {
-          rq.oa += stepA;
-          rq.ob += stepB;
-        }
-      }
-      const Src src = w4_resources(rq, a_bytes, dead);
       // (the tiles behind the loop request nothing: what they would request lies past the last tile, and a
       // load still in flight when control leaves this code could land in a register that holds something else
       // by then; the last of them moves nothing either)
-      auto move = [&](auto X) W4_INL {
+      auto move_write = [&](auto X) W4_INL {
         if constexpr (!tail) {
           wait_vmcnt<4 * NL - 1>();      // the load that filled this register is followed by 31 younger ones
           W4_SB;
         }
         if constexpr (!(tail && ph == 1)) stage_write(W4_IC(ph), X, W4_IC(ph ^ 1));
-        if constexpr (!tail) {
-          W4_SB;
-          request(W4_IC(ph), X, src);
-        }
       };
-      // k steps 0..2: behind fourteen of the sixteen MFMAs either one fragment read of the next step or one move,
-      // the two kinds interleaved (r m r r m r - r m r m r m r m -; 16 moves over the three steps).  Measured
-      // against other orders on one box: all eight reads first and the six moves behind them is 1 - 4 % slower on
-      // every shape, moves first 1 - 4 % slower still.  (One heavy instruction behind every MFMA - all ds_writes
-      // first, the requests behind them, the last eight in k step 3 - is 1 - 2 % faster than reads-then-moves on
-      // long reductions and makes the first k tiles of every output tile slower.)
-      static_for<0, 3>([&](auto KK) W4_INL {
-        constexpr int kk = decltype(KK)::value;
+      auto move_request = [&](auto X) W4_INL {
+        if constexpr (!tail) request(W4_IC(ph), X, rq);
+      };
+      // Eight quarters of sixteen MFMAs: a quarter multiplies one half of the A fragments (AH) with one half of the B
+      // fragments (BH), in an order in which consecutive quarters share a half and each half is replaced in the quarter
+      // behind its last use (RO: operand, RH: half, RK: k step; the last two out of the next tile).  A quarter walks the half that came
+      // last in its outer loop (OUTER_B), so a fragment has about sixteen MFMAs from its read to its first use.
+      // Inside a quarter every other row runs backwards, so that consecutive MFMAs always share an operand (1.5 % of an MFMA-only loop
+      // on random operands; power again).
+      // What follows an MFMA: RD a fragment read, MW / MR the write and the request of a move; 16 moves over the first six quarters.
+      // An MFMA takes 16 cycles and an instruction of the one wave four, so a third instruction behind one is late: write and request
+      // behind one MFMA cost 2 - 3 %, the moves spread over the whole quarter 1 - 2 %.  (16384 x 4096 x 4096: 1.34 us a k tile on
+      // random operands with all of it, 1.32 without the output stores, 1.15 without the loads, 1.24 without the ds_writes, 1.06 without
+      // both, 1.21 without the fragment reads; with 32x32x16 MFMAs 1.49.)
+      static_for<0, 8>([&](auto PP) W4_INL {
+        constexpr int pp = decltype(PP)::value;
+        constexpr int AH[8] = {0, 0, 1, 1, 0, 0, 1, 1}, BH[8] = {0, 1, 1, 0, 1, 0, 0, 1};
+        constexpr int RO[8] = {1, 0, 0, 1, 1, 0, 0, 1}, RH[8] = {1, 1, 0, 1, 0, 1, 0, 0}, RK[8] = {0, 0, 1, 1, 1, 1, 0, 0};
+        constexpr bool OUTER_B[8] = {true, true, false, false, true, true, false, false};
+        constexpr int M0[8] = {0, 3, 6, 9, 12, 14, 16, 16}, MN[8] = {3, 3, 3, 3, 2, 2, 0, 0};      // first move and how many
         static_for<0, 16>([&](auto Q) W4_INL {
-          constexpr int q = decltype(Q)::value;
-          mfma1(KK, Q);
-          // what follows MFMA q of a k step: fragment RD[q] of the next step, or move MV[q] of this step's six
-          constexpr int RD[16] = {0, -1, 1, 2, -1, 3, -1, 4, -1, 5, -1, 6, -1, 7, -1, -1};
-          constexpr int MV[16] = {-1, 0, -1, -1, 1, -1, -1, -1, 2, -1, 3, -1, 4, -1, 5, -1};
-          if constexpr (RD[q] >= 0) { read1(W4_IC(ph), W4_IC(kk + 1), W4_IC((kk + 1) & 1), W4_IC(RD[q])); W4_SB; }
-          if constexpr (MV[q] >= 0 && kk * 6 + MV[q] < 2 * NL) { W4_SB; move(W4_IC(kk * 6 + MV[q])); W4_SB; }
+          constexpr int q = decltype(Q)::value, o = q >> 2, n = o & 1 ? 3 - (q & 3) : q & 3;
+          mfma1(W4_IC(4 * AH[pp] + (OUTER_B[pp] ? n : o)), W4_IC(4 * BH[pp] + (OUTER_B[pp] ? o : n)));
+          W4_SB;
+          constexpr int RD[16] = {0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, 3, -1, -1, -1};
+          constexpr int RD6[16] = {-1, -1, -1, -1, -1, -1, -1, -1, 0, -1, 1, -1, 2, -1, 3, -1};      // behind the barrier
+          constexpr int MW[16] = {-1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1, -1};
+          constexpr int MR[16] = {-1, -1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1};
+          constexpr int rd = pp == 6 ? RD6[q] : RD[q];
+          if constexpr (!tail && pp == 6 && q == 2) { advance(); W4_SB; }
+          if constexpr (pp == 6 && q == 6) { __syncthreads(); W4_SB; }
+          if constexpr (rd >= 0) { read1(W4_IC(RO[pp]), W4_IC(pp >= 6 ? ph ^ 1 : ph), W4_IC(RK[pp]), W4_IC(RH[pp]), W4_IC(rd)); W4_SB; }
+          if constexpr (MW[q] >= 0 && MW[q] < MN[pp]) { move_write(W4_IC(M0[pp] + MW[q])); W4_SB; }
+          if constexpr (MR[q] >= 0 && MR[q] < MN[pp]) { move_request(W4_IC(M0[pp] + MR[q])); W4_SB; }
         });
-      });
-      mfma1(W4_IC(3), W4_IC(0)); W4_SB;
-      __syncthreads();
-      W4_SB;
-      static_for<1, 16>([&](auto Q) W4_INL {
-        constexpr int q = decltype(Q)::value;
-        if constexpr (q <= 8) read1(W4_IC(ph ^ 1), W4_IC(0), W4_IC(0), W4_IC(q - 1));
-        mfma1(W4_IC(3), Q); W4_SB;
       });
       // The compiler does not know which registers have a load in flight, and where control leaves the loop it
       // may copy or spill what is live there.  So the loop's last iteration ends with a wait for all loads (the
@@ -380,15 +417,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     if (t + 1 < n_run) phase(W4_IC(1), std::true_type{}, t + 1);
   }
 
-  // Epilogue.  Accumulator register r of block (i, j) holds row 8 (r / 4) + 4 (lane / 32) + r % 4 and column
-  // lane % 32 of the 32x32 block.  Every access is a buffer instruction on a view of the wave's part of the
+  // Epilogue.  Register r of block (i, j) holds row 16 i + lane % 16 and column 16 j + 4 (lane / 16) + r of the wave's
+  // 128x128.  Every access is a buffer instruction on a view of the wave's part of the
   // matrix (from its first row and column on, as many bytes as its existing rows take): the address is
-  // "view + uniform row offset + lane offset".  The row offset is one scalar that walks down the rows (from one
-  // register to the next the row index grows by 1, 1, 1, 5; by 2, 6 where registers are handled in pairs), the
+  // "view + uniform row offset + lane offset".  The row offset is one scalar that walks down 16 rows at a time, the
   // lane offset one register per column block, and that is all the address arithmetic there is.  Edges need no
   // code: an access to a row past the last is out of the view's range, which the hardware drops (a load
-  // returns zero), a lane whose column does not exist carries an offset beyond any view, and an output that was
+  // returns zero), a lane whose columns do not exist carries an offset beyond any view, and an output that was
   // not asked for is an empty view.
+  // fp32: the four columns of a lane are one 16-byte access, 64 bytes of 16 rows per instruction.  bf16: the words of two
+  // neighbouring blocks go through v_permlane16_swap, which gives every lane eight neighbouring columns: 16 bytes again.
+  // Column counts that do not divide by that (the NT form only) take narrow accesses at the same places (WIDE = 0).
+  // Against 32x32 blocks, whose lanes own columns of single rows: a quarter of the store instructions, no pair swaps.
   // (no lambda below may name p, G or S: captured by reference the kernel arguments are copied to private memory)
   // (the reads of the accumulators are asm, which the compiler's hazard handling does not look into: the wait
   // states between the last MFMA and the first read of its result are given here)
@@ -399,98 +439,100 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   const void *const Rp = G.resid;
   const int c_col = S.c_col;
   const long long ldc = p.ldc, ldr = p.ldr;
-  const bool odd = lane & 1;
   const int row_u = m0 + wm * WTM;                                  // the wave's first row
   const int rows_v = max(0, min(WTM, M - row_u));                   // how many of its rows exist
-  const int lrow = 4 * (lane >> 5), lcol = lane & 31;
+  const int lrow = lane & 15, lq = lane >> 4, lcol = 4 * lq;        // a lane's row and first column in a block
+  const int pcol = 16 * (lq & 1) + 8 * (lq >> 1);                   // its first column in a pair of blocks behind the swap
   constexpr uint32_t OUT = 0x80000000u;                             // lane offset of a column that does not exist
   auto view = [](const void *base, long long bytes) W4_INL {
     return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000);
   };
-  // (stores carry the non-temporal hint: the outputs are not read again by this launch, and kept out of the way of
-  // the operand panels in L2 the two-pass shapes run 1.7 % faster; one-pass shapes do not change)
+  // Stores of the forms that move most beside the tile itself - residuals, the four outputs of a fine-tune row's SwiGLU -
+  // carry the non-temporal hint, which keeps them out of the way of the operand panels in L2: two passes over 16384 x 4096 x 4096
+  // with fp32 / bf16 residual 820 / 806 -> 810 / 800 us, SwiGLU of 16384 x 11008 x 4096 4252 -> 4187.  Plain
+  // fp32 and bf16 outputs lose by it (half lines leave L2 before their other half has come): 16384 x 4096 x 1024 137 -> 149 and 119 -> 124 us.
   auto store32 = [](uint32_t w, __amdgpu_buffer_rsrc_t q, uint32_t voff, uint32_t soff) W4_INL {
-    __builtin_amdgcn_raw_buffer_store_b32(w, q, (int)voff, (int)soff, 2);
+    __builtin_amdgcn_raw_buffer_store_b32(w, q, (int)voff, (int)soff, 0);
   };
-  auto swap_pair = [&](float mine_r, float mine_r1) W4_INL -> float {     // the partner's value for the row this lane stores
-    const float send = odd ? mine_r : mine_r1;
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0xB1, 0xF, 0xF, true));
+  auto store128 = [](auto NT, u32x4_t w, __amdgpu_buffer_rsrc_t q, uint32_t voff, uint32_t soff) W4_INL {
+    __builtin_amdgcn_raw_buffer_store_b128(w, q, (int)voff, (int)soff, decltype(NT)::value ? 2 : 0);
+  };
+  // The bf16 words of two neighbouring blocks (x: even, y: odd; columns +0, +1 and +2, +3 of the lane's four).  vw: lane offset
+  // of the pair form; vn, left: of the lane's first column in the even block, and how many columns exist from there on.
+  auto store_pair = [&](auto WIDE, auto NT, uint32_t x0, uint32_t x1, uint32_t y0, uint32_t y1, __amdgpu_buffer_rsrc_t q, uint32_t vw, uint32_t vn, int left, uint32_t soff) W4_INL {
+    if constexpr (decltype(WIDE)::value != 0) {
+      const u32x2_t a = __builtin_amdgcn_permlane16_swap(x0, y0, false, false), b = __builtin_amdgcn_permlane16_swap(x1, y1, false, false);
+      store128(NT, u32x4_t{a[0], b[0], a[1], b[1]}, q, vw, soff);
+    } else {
+      store32(x0, q, left > 0 ? vn : OUT, soff);
+      store32(x1, q, left > 2 ? vn + 4u : OUT, soff);
+      store32(y0, q, left > 16 ? vn + 32u : OUT, soff);
+      store32(y1, q, left > 18 ? vn + 36u : OUT, soff);
+    }
   };
   if (swiglu) {
     if constexpr (LA == 0 && LB == 0) {
-      // column blocks (0, 1) and (2, 3) of a wave are G and U of the same 32 hidden units
+      // column blocks j and j + 4 (j < 4) of a wave are G and U of the same 16 hidden units
       const int F = N;
       bf16_t *const hi = (bf16_t *)Cp, *const lo = (bf16_t *)G.c_lo, *const gu = (bf16_t *)G.c_gu;
       const int f_u = n0 + wn * (WTN / 2);
-      // Stores of full 128-byte lines.  After the pair swap a lane holds the packed pair (fc, fc + 1) of row
-      // (row + odd) for each of the wave's two unit blocks (jj = 0, 1), in the row half lane / 32 selects.  One
-      // v_permlane32_swap of the two blocks' words gives {lower lanes: block 0, upper lanes: block 1} of
-      // row half 0 in one register and the same of row half 1 in the other: a store then covers 64 units
-      // (128 bytes) of two rows instead of 32 units of four.
-      const int col_l = lane - (odd ? 1 : 0);                      // lane part of the unit index (blocks are 32 apart)
-      const int row_l = odd ? 1 : 0;                               // lane part of the row
-      const bool okc = f_u + col_l < F;
-      // lane offsets for row half 0 and (four rows on) row half 1; U lies F units behind G
-      uint32_t vh[2], vg[2], vu[2];
+      uint32_t vh[2], vg[2], vu[2];      // lane offsets by pair of blocks; U lies F units behind G
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        vh[hh] = okc ? (uint32_t)((int)((row_l + 4 * hh) * ldc) + col_l) * 2u : OUT;
-        vg[hh] = okc ? (uint32_t)((row_l + 4 * hh) * 2 * F + col_l) * 2u : OUT;
-        vu[hh] = okc ? vg[hh] + (uint32_t)F * 2u : OUT;
+      for (int jp = 0; jp < 2; ++jp) {
+        const bool ok = f_u + jp * 32 + pcol < F;
+        vh[jp] = ok ? (uint32_t)((int)(lrow * ldc) + jp * 32 + pcol) * 2u : OUT;
+        vg[jp] = ok ? (uint32_t)(lrow * 2 * F + jp * 32 + pcol) * 2u : OUT;
+        vu[jp] = ok ? vg[jp] + (uint32_t)F * 2u : OUT;
       }
+      const uint32_t nh = (uint32_t)((int)(lrow * ldc) + lcol) * 2u, ng = (uint32_t)(lrow * 2 * F + lcol) * 2u, nu = ng + (uint32_t)F * 2u;
       const auto qh = view(hi + (long long)row_u * ldc + f_u, rows_v * ldc * 2);
       const auto ql = view(lo + (long long)row_u * ldc + f_u, lo ? rows_v * ldc * 2 : 0);
       const auto qg = view(gu + (long long)row_u * 2 * F + f_u, gu ? (long long)rows_v * F * 4 : 0);
       // (row strides go through w4_sgpr: a stride that shares a subexpression with a lane offset is otherwise
       // computed in vector registers, and a vector register as the scalar offset of a buffer instruction
       // becomes a loop over its distinct values)
-      const uint32_t h2r = w4_sgpr((uint32_t)(ldc * 4)), h6r = w4_sgpr((uint32_t)(ldc * 12)), g2r = w4_sgpr((uint32_t)F * 8u), g6r = w4_sgpr((uint32_t)F * 24u);      // 2 and 6 rows
+      const uint32_t h16 = w4_sgpr((uint32_t)(ldc * 32)), g16 = w4_sgpr((uint32_t)F * 64u);      // 16 rows
       // KIND 0: only hm (inference rows); 1: hm in two terms and G, U kept (fine-tune rows)
-      auto emit = [&](auto KIND) W4_INL {
+      auto emit = [&](auto KIND, auto WIDE) W4_INL {
         constexpr int kind = decltype(KIND)::value;
         uint32_t sh = 0, sg = 0;      // row offsets in hm (both terms) and in G|U
         static_for<0, TM>([&](auto I) W4_INL {
           constexpr int i = decltype(I)::value;
-          static_for<0, 8>([&](auto R2) W4_INL {
-            constexpr int r = 2 * decltype(R2)::value;
-            uint32_t wh[2], wl[2], wg[2], wu[2];
-            static_for<0, 2>([&](auto JJ) W4_INL {
-              constexpr int jj = decltype(JJ)::value;
-              const float g2[2] = {w4_acc_rd(acc[i][2 * jj][r]), w4_acc_rd(acc[i][2 * jj][r + 1])};
-              const float u2[2] = {w4_acc_rd(acc[i][2 * jj + 1][r]), w4_acc_rd(acc[i][2 * jj + 1][r + 1])};
+          static_for<0, 2>([&](auto JP) W4_INL {
+            constexpr int jp = decltype(JP)::value;
+            uint32_t wh[4], wl[4], wg[4], wu[4];
+            static_for<0, 4>([&](auto W) W4_INL {      // word w: columns 2 (w % 2), + 1 of block 2 jp + w / 2
+              constexpr int w = decltype(W)::value, j = 2 * jp + w / 2, r = 2 * (w % 2);
+              const float g2[2] = {w4_acc_rd(acc[i][j][r]), w4_acc_rd(acc[i][j][r + 1])};
+              const float u2[2] = {w4_acc_rd(acc[i][j + 4][r]), w4_acc_rd(acc[i][j + 4][r + 1])};
               float h2[2];
 #pragma unroll
               for (int e = 0; e < 2; ++e) h2[e] = g2[e] * __builtin_amdgcn_rcpf(1.0f + __expf(-g2[e])) * u2[e];
-              const float hp = swap_pair(h2[0], h2[1]);
-              split_pk_bf16(odd ? hp : h2[0], odd ? h2[1] : hp, wh[jj], wl[jj]);
+              split_pk_bf16(h2[0], h2[1], wh[w], wl[w]);
               if constexpr (kind != 0) {
-                const float gp = swap_pair(g2[0], g2[1]), up = swap_pair(u2[0], u2[1]);
-                wg[jj] = cvt_pk_bf16(odd ? gp : g2[0], odd ? g2[1] : gp);
-                wu[jj] = cvt_pk_bf16(odd ? up : u2[0], odd ? u2[1] : up);
+                wg[w] = cvt_pk_bf16(g2[0], g2[1]);
+                wu[w] = cvt_pk_bf16(u2[0], u2[1]);
               }
             });
-            // row halves: words [0] belong to rows (row + row_l), words [1] to the rows four further on
-            const u32x2_t s_h = __builtin_amdgcn_permlane32_swap(wh[0], wh[1], false, false);
-            static_for<0, 2>([&](auto H) W4_INL { store32(s_h[decltype(H)::value], qh, vh[decltype(H)::value], sh); });
+            const int left = F - f_u - jp * 32 - lcol;
+            store_pair(WIDE, KIND, wh[0], wh[1], wh[2], wh[3], qh, vh[jp], nh + jp * 64u, left, sh);
             if constexpr (kind != 0) {
-              const u32x2_t s_l = __builtin_amdgcn_permlane32_swap(wl[0], wl[1], false, false);
-              const u32x2_t s_g = __builtin_amdgcn_permlane32_swap(wg[0], wg[1], false, false);
-              const u32x2_t s_u = __builtin_amdgcn_permlane32_swap(wu[0], wu[1], false, false);
-              static_for<0, 2>([&](auto H) W4_INL {
-                constexpr int hh = decltype(H)::value;
-                store32(s_l[hh], ql, vh[hh], sh);
-                store32(s_g[hh], qg, vg[hh], sg);
-                store32(s_u[hh], qg, vu[hh], sg);
-              });
+              store_pair(WIDE, KIND, wl[0], wl[1], wl[2], wl[3], ql, vh[jp], nh + jp * 64u, left, sh);
+              store_pair(WIDE, KIND, wg[0], wg[1], wg[2], wg[3], qg, vg[jp], ng + jp * 64u, left, sg);
+              store_pair(WIDE, KIND, wu[0], wu[1], wu[2], wu[3], qg, vu[jp], nu + jp * 64u, left, sg);
             }
-            sh += (r & 2) ? h6r : h2r;
-            sg += (r & 2) ? g6r : g2r;
           });
+          sh += h16;
+          sg += g16;
           W4_SB;
         });
       };
-      if (!lo && !gu) emit(W4_IC(0));
-      else emit(W4_IC(1));
+      if (F % 8 == 0) {
+        if (!lo && !gu) emit(W4_IC(0), W4_IC(1));
+        else emit(W4_IC(1), W4_IC(1));
+      } else {
+        emit(W4_IC(1), W4_IC(0));
+      }
     }
     return;
   }
@@ -498,73 +540,60 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   if (G.rope) {
     if constexpr (LA == 0 && LB == 0) {
       // Rotary embedding and operand split in the epilogue of the QKV product: the wave's 128 columns are one head
-      // (head dimension 128), so element i of the head sits in column blocks 0, 1 and its partner i + 64 in the
-      // same register of blocks 2, 3.  (cos, sin) of (row, i) come from the group's table; the rotated (Q, K) or
-      // plain (V) values leave as two bf16 terms through the pair and half swaps of the packed bf16 stores.
+      // (head dimension 128), so element i of the head sits in column blocks 0 .. 3 and its partner i + 64 in the
+      // same register of blocks 4 .. 7.  (cos, sin) of (row, i) come from the group's table; the rotated (Q, K) or
+      // plain (V) values leave as two bf16 terms (segments are whole heads, so the pair form always fits).
       const int rot = S.rope_rot;
       bf16_t *const ohi = (bf16_t *)S.rope_hi, *const olo = (bf16_t *)S.rope_lo;
-      const int col_l = lane - (odd ? 1 : 0), row_l = odd ? 1 : 0;
-      uint32_t vo[2][2];      // lane offsets of the stores by row half and block pair (output rows are N wide)
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-        for (int jp = 0; jp < 2; ++jp)
-          vo[hh][jp] = col_u + jp * 64 + col_l < N ? (uint32_t)((row_l + 4 * hh) * N + col_l + jp * 64) * 2u : OUT;
-      const uint32_t vt[2] = {(uint32_t)(lrow * 64 + lcol) * 8u, (uint32_t)(lrow * 64 + 32 + lcol) * 8u};      // table, blocks 0 and 1
+      const bool ok = col_u < N;
+      const uint32_t vo = ok ? (uint32_t)(lrow * N + pcol) * 2u : OUT;      // output rows are N wide; 64 bytes per pair of blocks
+      const uint32_t vt = (uint32_t)(lrow * 64 + lcol) * 8u;                // table; 128 bytes per block
       const auto qh = view(ohi + (long long)row_u * N + col_u, (long long)rows_v * N * 2);
       const auto ql = view(olo + (long long)row_u * N + col_u, olo ? (long long)rows_v * N * 2 : 0);
       const auto qt = view(p.rope_cs + (long long)row_u * 128, (long long)rows_v * 512);
-      const uint32_t o2r = w4_sgpr((uint32_t)N * 4u), o6r = w4_sgpr((uint32_t)N * 12u);      // 2 and 6 output rows
+      const uint32_t o16 = w4_sgpr((uint32_t)N * 32u);      // 16 output rows
       uint32_t so = 0, st = 0;      // row offsets of the outputs and of the table
-      static_for<0, TM>([&](auto I) W4_INL {
-        constexpr int i = decltype(I)::value;
-        u32x2_t cs[16][2];      // the table entries of the block row's 16 registers, requested together
-        {
-          uint32_t q = st;
-          static_for<0, 16>([&](auto R) W4_INL {
-            constexpr int r = decltype(R)::value;
-            static_for<0, 2>([&](auto J) W4_INL { cs[r][decltype(J)::value] = __builtin_amdgcn_raw_buffer_load_b64(qt, (int)vt[decltype(J)::value], (int)q, 0); });
-            q += (r & 3) == 3 ? 2560u : 512u;
-          });
-          st += 32u * 512u;
-        }
-        W4_SB;
-        static_for<0, 8>([&](auto R2) W4_INL {
-          constexpr int r2 = decltype(R2)::value, r = 2 * r2;
-          float v[TN][2];
-          static_for<0, TN>([&](auto J) W4_INL {
-            constexpr int j = decltype(J)::value;
-            v[j][0] = w4_acc_rd(acc[i][j][r]);
-            v[j][1] = w4_acc_rd(acc[i][j][r + 1]);
-          });
-          if (rot) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int e = 0; e < 2; ++e) {
-                const float c = __uint_as_float(cs[r + e][j][0]), sn = __uint_as_float(cs[r + e][j][1]);
-                const float a = v[j][e], b = v[j + 2][e];
-                v[j][e] = a * c - b * sn;
-                v[j + 2][e] = b * c + a * sn;
-              }
-          }
-          uint32_t wh[TN], wl[TN];
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const float vx = swap_pair(v[j][0], v[j][1]);
-            split_pk_bf16(odd ? vx : v[j][0], odd ? v[j][1] : vx, wh[j], wl[j]);
-          }
-          static_for<0, 2>([&](auto JP) W4_INL {
-            constexpr int jp = decltype(JP)::value;
-            const u32x2_t s_h = __builtin_amdgcn_permlane32_swap(wh[2 * jp], wh[2 * jp + 1], false, false);
-            const u32x2_t s_l = __builtin_amdgcn_permlane32_swap(wl[2 * jp], wl[2 * jp + 1], false, false);
-            static_for<0, 2>([&](auto H) W4_INL {
-              constexpr int hh = decltype(H)::value;
-              store32(s_h[hh], qh, vo[hh][jp], so);
-              store32(s_l[hh], ql, vo[hh][jp], so);
+      static_for<0, TM / 2>([&](auto IH) W4_INL {
+        u32x4_t cs[2][4][2];      // the table entries of 32 rows, requested together: (cos, sin) of columns +0, +1 and +2, +3
+        static_for<0, 2>([&](auto II) W4_INL {
+          static_for<0, 4>([&](auto J) W4_INL {
+            static_for<0, 2>([&](auto E) W4_INL {
+              constexpr int ii = decltype(II)::value, j = decltype(J)::value, e = decltype(E)::value;
+              cs[ii][j][e] = __builtin_amdgcn_raw_buffer_load_b128(qt, (int)(vt + j * 128u + e * 16u), (int)(st + ii * 8192u), 0);
             });
           });
-          so += (r2 & 1) ? o6r : o2r;
+        });
+        st += 2u * 8192u;
+        W4_SB;
+        static_for<0, 2>([&](auto II) W4_INL {
+          constexpr int ii = decltype(II)::value, i = 2 * decltype(IH)::value + ii;
+          static_for<0, 2>([&](auto JP) W4_INL {
+            constexpr int jp = decltype(JP)::value;
+            uint32_t wh[2][4], wl[2][4];      // first half of the head, second half
+            static_for<0, 4>([&](auto W) W4_INL {
+              constexpr int w = decltype(W)::value, j = 2 * jp + w / 2, e = w % 2, r = 2 * e;
+              float v[2] = {w4_acc_rd(acc[i][j][r]), w4_acc_rd(acc[i][j][r + 1])};
+              float u[2] = {w4_acc_rd(acc[i][j + 4][r]), w4_acc_rd(acc[i][j + 4][r + 1])};
+              if (rot) {
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                  const float c = __uint_as_float(cs[ii][j][e][2 * x]), sn = __uint_as_float(cs[ii][j][e][2 * x + 1]);
+                  const float a = v[x], b = u[x];
+                  v[x] = a * c - b * sn;
+                  u[x] = b * c + a * sn;
+                }
+              }
+              split_pk_bf16(v[0], v[1], wh[0][w], wl[0][w]);
+              split_pk_bf16(u[0], u[1], wh[1][w], wl[1][w]);
+            });
+            static_for<0, 2>([&](auto H) W4_INL {
+              constexpr int hh = decltype(H)::value;
+              const uint32_t o = vo + (hh * 128u + jp * 64u);
+              store_pair(W4_IC(1), W4_IC(0), wh[hh][0], wh[hh][1], wh[hh][2], wh[hh][3], qh, o, 0u, 0, so);
+              store_pair(W4_IC(1), W4_IC(0), wl[hh][0], wl[hh][1], wl[hh][2], wl[hh][3], ql, o, 0u, 0, so);
+            });
+          });
+          so += o16;
         });
         W4_SB;
       });
@@ -576,75 +605,67 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     if constexpr (LA == 0 && LB == 1) {
       // SwiGLU backward in the epilogue of dHm = dY Wd: the tile of dHm never leaves the registers.  With G and U of
       // the forward (bf16 [M, 2F], G | U) it becomes dG = dHm U s (1 + G (1 - s)) and dU = dHm G s, s = sigmoid(G),
-      // written as bf16 [M, 2F] (dG | dU) - the same layout, so G, U, dG and dU of an element pair share one lane
-      // offset (U and dU lie F columns further on).  The pair and half swaps of the packed bf16 stores are done on
-      // the fp32 values, so that a lane computes on the two neighbouring columns it loads and stores as one word.
+      // written as bf16 [M, 2F] (dG | dU) - the same layout, so G, U, dG and dU share one lane
+      // offset (U and dU lie F columns further on).  The swap of the pair form is done on
+      // the fp32 values, so that a lane computes on the eight columns it loads and stores (F is a multiple of 8).
       const int F = N;
-      const int col_l = lane - (odd ? 1 : 0), row_l = odd ? 1 : 0;
-      uint32_t vg[2][TN / 2], vu[2][TN / 2];      // lane offsets by row half and block pair, G / dG and U / dU
+      uint32_t vg[4], vu[4];      // lane offsets by pair of blocks, G / dG and U / dU
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-        for (int jp = 0; jp < TN / 2; ++jp) {
-          const bool ok = col_u + jp * 64 + col_l < F;
-          vg[hh][jp] = ok ? (uint32_t)((row_l + 4 * hh) * 2 * F + col_l + jp * 64) * 2u : OUT;
-          vu[hh][jp] = ok ? vg[hh][jp] + (uint32_t)F * 2u : OUT;
-        }
+      for (int jp = 0; jp < 4; ++jp) {
+        const bool ok = col_u + jp * 32 + pcol < F;
+        vg[jp] = ok ? (uint32_t)(lrow * 2 * F + jp * 32 + pcol) * 2u : OUT;
+        vu[jp] = ok ? vg[jp] + (uint32_t)F * 2u : OUT;
+      }
       const auto qo = view((bf16_t *)Cp + (long long)row_u * 2 * F + col_u, (long long)rows_v * F * 4);
       const auto qi = view((const bf16_t *)G.c_gu + (long long)row_u * 2 * F + col_u, (long long)rows_v * F * 4);
-      const uint32_t s2r = w4_sgpr((uint32_t)F * 8u), s6r = w4_sgpr((uint32_t)F * 24u);      // 2 and 6 rows
+      const uint32_t s16 = w4_sgpr((uint32_t)F * 64u);      // 16 rows
       uint32_t sc = 0;
-      static_for<0, TM>([&](auto I) W4_INL {
-        constexpr int i = decltype(I)::value;
-        // G and U of the 32 rows of block row i are requested together (nothing else covers the latency)
-        uint32_t gw[8][TN / 2][2], uw[8][TN / 2][2];
+      static_for<0, TM / 4>([&](auto IH) W4_INL {
+        // G and U of 64 rows are requested together (nothing else covers the latency)
+        u32x4_t gw[4][4], uw[4][4];
         {
           uint32_t q = sc;
-          static_for<0, 8>([&](auto R2) W4_INL {
-            constexpr int r2 = decltype(R2)::value;
-            static_for<0, TN / 2>([&](auto JP) W4_INL {
-              static_for<0, 2>([&](auto H) W4_INL {
-                constexpr int jp = decltype(JP)::value, hh = decltype(H)::value;
-                gw[r2][jp][hh] = __builtin_amdgcn_raw_buffer_load_b32(qi, (int)vg[hh][jp], (int)q, 0);
-                uw[r2][jp][hh] = __builtin_amdgcn_raw_buffer_load_b32(qi, (int)vu[hh][jp], (int)q, 0);
-              });
+          static_for<0, 4>([&](auto II) W4_INL {
+            static_for<0, 4>([&](auto JP) W4_INL {
+              constexpr int ii = decltype(II)::value, jp = decltype(JP)::value;
+              gw[ii][jp] = __builtin_amdgcn_raw_buffer_load_b128(qi, (int)vg[jp], (int)q, 0);
+              uw[ii][jp] = __builtin_amdgcn_raw_buffer_load_b128(qi, (int)vu[jp], (int)q, 0);
             });
-            q += (r2 & 1) ? s6r : s2r;
+            q += s16;
           });
         }
         W4_SB;
-        static_for<0, 8>([&](auto R2) W4_INL {
-          constexpr int r2 = decltype(R2)::value, r = 2 * r2;
-          static_for<0, TN / 2>([&](auto JP) W4_INL {
+        static_for<0, 4>([&](auto II) W4_INL {
+          constexpr int ii = decltype(II)::value, i = 4 * decltype(IH)::value + ii;
+          static_for<0, 4>([&](auto JP) W4_INL {
             constexpr int jp = decltype(JP)::value;
-            float x0[2], x1[2];      // the lane's column pair of dHm, by block of the pair
-            static_for<0, 2>([&](auto JB) W4_INL {
-              constexpr int jb = decltype(JB)::value, j = 2 * jp + jb;
-              const float va = w4_acc_rd(acc[i][j][r]), vb = w4_acc_rd(acc[i][j][r + 1]);
-              const float vx = swap_pair(va, vb);
-              x0[jb] = odd ? vx : va;
-              x1[jb] = odd ? vb : vx;
+            float dh[8];
+            static_for<0, 4>([&](auto R) W4_INL {
+              constexpr int r = decltype(R)::value;
+              const u32x2_t t = __builtin_amdgcn_permlane16_swap(__float_as_uint(w4_acc_rd(acc[i][2 * jp][r])), __float_as_uint(w4_acc_rd(acc[i][2 * jp + 1][r])), false, false);
+              dh[r] = __uint_as_float(t[0]);
+              dh[r + 4] = __uint_as_float(t[1]);
             });
-            const u32x2_t t0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0[0]), __float_as_uint(x0[1]), false, false);
-            const u32x2_t t1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(x1[0]), __float_as_uint(x1[1]), false, false);
-            static_for<0, 2>([&](auto H) W4_INL {
-              constexpr int hh = decltype(H)::value;
-              const float dh[2] = {__uint_as_float(t0[hh]), __uint_as_float(t1[hh])};
-              const uint32_t g2 = gw[r2][jp][hh], u2 = uw[r2][jp][hh];
+            u32x4_t og, ou;
+            static_for<0, 4>([&](auto W) W4_INL {
+              constexpr int w = decltype(W)::value;
+              const uint32_t g2 = gw[ii][jp][w], u2 = uw[ii][jp][w];
               float dg[2], du[2];
 #pragma unroll
               for (int e = 0; e < 2; ++e) {
                 const float g = e ? __uint_as_float(g2 & 0xffff0000u) : __uint_as_float(g2 << 16);
                 const float u = e ? __uint_as_float(u2 & 0xffff0000u) : __uint_as_float(u2 << 16);
                 const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-g));
-                du[e] = dh[e] * g * sg;
-                dg[e] = dh[e] * u * sg * (1.0f + g * (1.0f - sg));
+                du[e] = dh[2 * w + e] * g * sg;
+                dg[e] = dh[2 * w + e] * u * sg * (1.0f + g * (1.0f - sg));
               }
-              store32(cvt_pk_bf16(dg[0], dg[1]), qo, vg[hh][jp], sc);
-              store32(cvt_pk_bf16(du[0], du[1]), qo, vu[hh][jp], sc);
+              og[w] = cvt_pk_bf16(dg[0], dg[1]);
+              ou[w] = cvt_pk_bf16(du[0], du[1]);
             });
+            store128(W4_IC(0), og, qo, vg[jp], sc);
+            store128(W4_IC(0), ou, qo, vu[jp], sc);
           });
-          sc += (r2 & 1) ? s6r : s2r;
+          sc += s16;
         });
         W4_SB;
       });
@@ -652,93 +673,121 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     return;
   }
   if (obf) {
-    // packed bf16 (even column count and offset, no residual): neighbouring lanes (columns c, c+1) swap one
-    // value of a register pair (rows r, r+1); the even lane then holds columns (c, c+1) of row r, the odd lane
-    // columns (c-1, c) of row r+1.  The words of two neighbouring column blocks go through v_permlane32_swap
-    // (see the SwiGLU stores): a store covers 64 columns (128 bytes) of two rows.
-    const int col_l = lane - (odd ? 1 : 0), row_l = odd ? 1 : 0;
-    uint32_t vp[2][TN / 2];      // lane offsets by row half and block pair
+    // packed bf16 (even column count and offset, no residual)
+    uint32_t vp[TN / 2];      // lane offsets by pair of blocks
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-      for (int jp = 0; jp < TN / 2; ++jp)
-        vp[hh][jp] = col_u + jp * 64 + col_l < N ? (uint32_t)((int)((row_l + 4 * hh) * ldc) + col_l + jp * 64) * 2u : OUT;
+    for (int jp = 0; jp < TN / 2; ++jp) vp[jp] = col_u + jp * 32 + pcol < N ? (uint32_t)((int)(lrow * ldc) + jp * 32 + pcol) * 2u : OUT;
+    const uint32_t vn = (uint32_t)((int)(lrow * ldc) + lcol) * 2u;
     const auto qc = view((bf16_t *)Cp + (long long)row_u * ldc + c_col + col_u, rows_v * ldc * 2);
-    const uint32_t p2r = w4_sgpr((uint32_t)(ldc * 4)), p6r = w4_sgpr((uint32_t)(ldc * 12));      // 2 and 6 rows
-    uint32_t sc = 0;
-    static_for<0, TM>([&](auto I) W4_INL {
-      static_for<0, 8>([&](auto R2) W4_INL {
-        constexpr int i = decltype(I)::value, r = 2 * decltype(R2)::value;
+    const uint32_t p16 = w4_sgpr((uint32_t)(ldc * 32));      // 16 rows
+    auto emit = [&](auto WIDE) W4_INL {
+      uint32_t sc = 0;
+      static_for<0, TM>([&](auto I) W4_INL {
+        constexpr int i = decltype(I)::value;
         static_for<0, TN / 2>([&](auto JP) W4_INL {
           constexpr int jp = decltype(JP)::value;
-          uint32_t w[2];
-          static_for<0, 2>([&](auto JB) W4_INL {
-            constexpr int jb = decltype(JB)::value, j = 2 * jp + jb;
-            const float va = w4_acc_rd(acc[i][j][r]), vb = w4_acc_rd(acc[i][j][r + 1]);
-            const float vx = swap_pair(va, vb);
-            w[jb] = cvt_pk_bf16(odd ? vx : va, odd ? vb : vx);
+          uint32_t w[4];
+          static_for<0, 4>([&](auto W) W4_INL {
+            constexpr int x = decltype(W)::value, j = 2 * jp + x / 2, r = 2 * (x % 2);
+            w[x] = cvt_pk_bf16(w4_acc_rd(acc[i][j][r]), w4_acc_rd(acc[i][j][r + 1]));
           });
-          const u32x2_t sw = __builtin_amdgcn_permlane32_swap(w[0], w[1], false, false);
-          static_for<0, 2>([&](auto H) W4_INL { store32(sw[decltype(H)::value], qc, vp[decltype(H)::value][jp], sc); });
+          store_pair(WIDE, W4_IC(0), w[0], w[1], w[2], w[3], qc, vp[jp], vn + jp * 64u, N - col_u - jp * 32 - lcol, sc);
         });
-        sc += (r & 2) ? p6r : p2r;
+        sc += p16;
+        W4_SB;
       });
-      W4_SB;
-    });
+    };
+    if constexpr (LB == 1) {
+      emit(W4_IC(1));
+    } else {
+      if (N % 8 == 0) emit(W4_IC(1));
+      else emit(W4_IC(0));
+    }
     return;
   }
   // fp32 output; RES 0: no residual, 1: + fp32 residual (projections onto an fp32 stream, weight gradients that
-  // accumulate), 2: + bf16 residual.  The residuals of eight blocks are requested together before the first is
+  // accumulate), 2: + bf16 residual.  The residuals of 64 rows are requested together before the first is
   // added: with one wave per SIMD nothing else covers the latency of a request.
-  auto emit = [&](auto RES) W4_INL {
+  auto emit = [&](auto RES, auto WIDE) W4_INL {
     constexpr int res = decltype(RES)::value, rsz = res == 2 ? 2 : 4;
+    constexpr bool wide = decltype(WIDE)::value != 0;
     uint32_t vc[TN], vr[TN];      // lane offsets by column block, in C and in the residual
+    int left[TN];                 // how many columns exist from the lane's first one on
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const bool ok = col_u + j * 32 + lcol < N;
-      vc[j] = ok ? (uint32_t)((int)(lrow * ldc) + lcol + j * 32) * 4u : OUT;
-      vr[j] = ok ? (uint32_t)((int)(lrow * ldr) + lcol + j * 32) * (uint32_t)rsz : OUT;
+      left[j] = N - col_u - j * 16 - lcol;
+      vc[j] = left[j] > 0 ? (uint32_t)((int)(lrow * ldc) + lcol + j * 16) * 4u : OUT;
+      vr[j] = left[j] > 0 ? (uint32_t)((int)(lrow * ldr) + lcol + j * 16) * (uint32_t)rsz : OUT;
     }
     const auto qc = view((char *)Cp + ((long long)row_u * ldc + c_col0 + col_u) * 4, rows_v * ldc * 4);
     const auto qr = view((const char *)Rp + ((long long)row_u * ldr + c_col0 + col_u) * rsz, res ? rows_v * ldr * rsz : 0);
-    const uint32_t c1 = w4_sgpr((uint32_t)(ldc * 4)), c5 = w4_sgpr((uint32_t)(ldc * 20)), c64 = w4_sgpr((uint32_t)(ldc * 256));
-    const uint32_t r1 = w4_sgpr((uint32_t)(ldr * rsz)), r5 = w4_sgpr((uint32_t)(ldr * (5 * rsz))), r64 = w4_sgpr((uint32_t)(ldr * (64 * rsz)));
-    uint32_t sc = 0, sr = 0;      // row offsets of the current 64-row half
-    static_for<0, TM / 2>([&](auto IH) W4_INL {
-      constexpr int ih = decltype(IH)::value;
-      float rv[2][16][TN];
+    const uint32_t c16 = w4_sgpr((uint32_t)(ldc * 64)), r16 = w4_sgpr((uint32_t)(ldr * (16 * rsz)));      // 16 rows
+    uint32_t sc = 0, sr = 0;
+    static_for<0, TM / 4>([&](auto IH) W4_INL {
+      u32x4_t rv[4][TN];
       if constexpr (res != 0) {
-        static_for<0, TN>([&](auto J) W4_INL {
-          constexpr int j = decltype(J)::value;
-          uint32_t q = sr;
-          static_for<0, 32>([&](auto IR) W4_INL {
-            constexpr int ii = decltype(IR)::value / 16, r = decltype(IR)::value % 16;
-            if constexpr (res == 1) rv[ii][r][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(qr, (int)vr[j], (int)q, 0));
-            else rv[ii][r][j] = bf2f(__builtin_amdgcn_raw_buffer_load_b16(qr, (int)vr[j], (int)q, 0));
-            q += (r & 3) == 3 ? r5 : r1;
+        static_for<0, 4>([&](auto II) W4_INL {
+          static_for<0, TN>([&](auto J) W4_INL {
+            constexpr int ii = decltype(II)::value, j = decltype(J)::value;
+            if constexpr (wide && res == 1) {
+              rv[ii][j] = __builtin_amdgcn_raw_buffer_load_b128(qr, (int)vr[j], (int)sr, 0);
+            } else if constexpr (wide) {
+              const u32x2_t t = __builtin_amdgcn_raw_buffer_load_b64(qr, (int)vr[j], (int)sr, 0);
+              rv[ii][j] = u32x4_t{t[0], t[1], 0u, 0u};      // widened when it is added
+            } else {
+              static_for<0, 4>([&](auto E) W4_INL {
+                constexpr int e = decltype(E)::value;
+                const int o = left[j] > e ? (int)(vr[j] + e * rsz) : (int)OUT;
+                if constexpr (res == 1) rv[ii][j][e] = __builtin_amdgcn_raw_buffer_load_b32(qr, o, (int)sr, 0);
+                else rv[ii][j][e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(qr, o, (int)sr, 0) << 16;
+              });
+            }
           });
+          sr += r16;
         });
-        sr += r64;
         W4_SB;
       }
-      static_for<0, TN>([&](auto J) W4_INL {
-        constexpr int j = decltype(J)::value;
-        uint32_t q = sc;
-        static_for<0, 32>([&](auto IR) W4_INL {
-          constexpr int ii = decltype(IR)::value / 16, r = decltype(IR)::value % 16, i = 2 * ih + ii;
-          float v = w4_acc_rd(acc[i][j][r]);
-          if constexpr (res != 0) v += rv[ii][r][j];
-          store32(__builtin_bit_cast(uint32_t, v), qc, vc[j], q);
-          q += (r & 3) == 3 ? c5 : c1;
+      static_for<0, 4>([&](auto II) W4_INL {
+        constexpr int ii = decltype(II)::value, i = 4 * decltype(IH)::value + ii;
+        static_for<0, TN>([&](auto J) W4_INL {
+          constexpr int j = decltype(J)::value;
+          u32x4_t v;
+          static_for<0, 4>([&](auto E) W4_INL {
+            constexpr int e = decltype(E)::value;
+            float f = w4_acc_rd(acc[i][j][e]);
+            if constexpr (res == 2 && wide) f += __uint_as_float(e % 2 ? rv[ii][j][e / 2] & 0xffff0000u : rv[ii][j][e / 2] << 16);
+            else if constexpr (res != 0) f += __uint_as_float(rv[ii][j][e]);
+            v[e] = __float_as_uint(f);
+          });
+          if constexpr (wide) {
+            store128(RES, v, qc, vc[j], sc);
+          } else {
+            static_for<0, 4>([&](auto E) W4_INL {
+              constexpr int e = decltype(E)::value;
+              store32(v[e], qc, left[j] > e ? vc[j] + e * 4u : OUT, sc);
+            });
+          }
         });
+        sc += c16;
         W4_SB;
       });
-      sc += c64;
     });
   };
-  if (rk == 0) emit(W4_IC(0));
-  else if (rk == 1) emit(W4_IC(1));
-  else emit(W4_IC(2));
+  // (rows of a bf16 residual that start on odd elements have no aligned 8-byte pieces; 16-byte accesses to fp32 rows need
+  // no more than the 4 bytes every float has)
+  const bool wide = LB == 1 || N % 4 == 0, wide_r = wide && rk == 2 && ldr % 2 == 0 && (((uintptr_t)Rp + 2 * c_col0) & 3) == 0;
+  if (rk == 0) {
+    if constexpr (LB == 1) emit(W4_IC(0), W4_IC(1));
+    else if (wide) emit(W4_IC(0), W4_IC(1));
+    else emit(W4_IC(0), W4_IC(0));
+  } else if (rk == 1) {
+    if constexpr (LB == 1) emit(W4_IC(1), W4_IC(1));
+    else if (wide) emit(W4_IC(1), W4_IC(1));
+    else emit(W4_IC(1), W4_IC(0));
+  } else {
+    if (wide_r) emit(W4_IC(2), W4_IC(1));
+    else emit(W4_IC(2), W4_IC(0));
+  }
 }
 
 // Operand views must fit the 32-bit byte offsets of a buffer load, and 128 rows of an output or residual the

@@ -200,3 +200,45 @@ def test_rejects_what_the_four_wave_kernel_cannot_do(torch_mod, handle):
         binding.mace_gemm_bf16(handle, 0, 0, 64, 64, 64, a, b, c, resid=r, ldc=66, kernel=1)
     binding.mace_gemm_bf16(handle, 0, 0, 64, 64, 64, a, b, c, resid=r, ldc=66, kernel=0)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("N,resid,ldr", [(331, None, 0), (333, "f32", 335), (334, "bf16", 341), (332, "bf16", 341), (336, "bf16", 342), (1, "f32", 3)])
+def test_column_counts_and_residual_rows_without_whole_vectors(torch_mod, handle, N, resid, ldr):
+    """The four-wave kernel stores and adds four columns at once where the column count (and the rows of a bf16 residual) allow
+    it, single ones elsewhere: odd column counts, residual rows that start on odd elements, outputs that start on odd rows."""
+    torch = torch_mod
+    from paper_2510_03283_amd import binding
+    M, K = 300, 192
+    rng = np.random.default_rng(N)
+    a, b, A, B = operands(torch, rng, 0, 0, M, N, K)
+    ref, r = A @ B.T, None
+    if resid:
+        r = torch.from_numpy(rng.uniform(-20, 20, (M + 2, ldr)).astype(np.float32)).cuda()
+        r = r.to(torch.bfloat16) if resid == "bf16" else r
+        ref = ref + f64(r)[:M, :N]
+    for ldc in (N, N + 3):
+        c = out_buffer(torch, M + 5, ldc, torch.float32)
+        binding.mace_gemm_bf16(handle, 0, 0, M, N, K, a, b, c, resid=r, ldc=ldc, ldr=ldr or None, kernel=1)
+        torch.cuda.synchronize()
+        check_out(c, ref, M, N, 1e-5, f"{M}x{N}x{K} ldc {ldc} {resid} ldr {ldr}")
+
+
+@pytest.mark.parametrize("F", [330, 328, 4])
+def test_swiglu_unit_counts_without_whole_vectors(torch_mod, handle, F):
+    torch = torch_mod
+    from paper_2510_03283_amd import binding
+    M, K = 300, 192
+    rng = np.random.default_rng(F)
+    a = bf16_of(torch, rng.uniform(-1, 1, (M, K)))
+    wg, wu = (bf16_of(torch, rng.uniform(-1, 1, (F, K)) / 4) for _ in range(2))
+    G, U = f64(a) @ f64(wg).T, f64(a) @ f64(wu).T
+    ref = G / (1.0 + np.exp(-G)) * U
+    for keep in (False, True):
+        hm, lo = (out_buffer(torch, M + 5, F, torch.bfloat16) for _ in range(2))
+        gu = out_buffer(torch, M + 5, 2 * F, torch.bfloat16)
+        binding.mace_gemm_bf16(handle, 0, 0, M, F, K, a, wg, hm, b_up=wu, c_lo=lo if keep else None, c_gu=gu if keep else None, ldc=F, swiglu=True, kernel=1)
+        torch.cuda.synchronize()
+        check_out(hm, ref, M, F, 4e-3, f"hm, {F} units, keep {keep}")
+        if keep:
+            assert np.abs((f64(hm) + f64(lo))[:M] - ref).max() / np.abs(ref).max() <= 5e-5
+            check_out(gu, np.concatenate([G, U], axis=1), M, 2 * F, 4e-3, f"G | U, {F} units")
