@@ -18,16 +18,30 @@ def regs(tok):
     return out
 
 def check(name, lines):
+    """All main loops of a kernel: each with its prologue and tail has five barriers (the NT kernel has a second loop for two passes)."""
     code = [l.split(';')[0].rstrip() for l in lines]
-    loads = [i for i, l in enumerate(code) if 'buffer_load_dwordx4' in l]
+    barriers = [i for i, l in enumerate(code) if 's_barrier' in l]
+    if len(barriers) != 5 and not (len(barriers) == 10 and 'ILi0ELi0E' in name):
+        return False, f"{name}: expected 5 barriers (prologue, two loop phases, two tail phases) a loop, found {len(barriers)}"
+    ok, msgs, start = True, [], 0
+    for k in range(0, len(barriers), 5):
+        # a loop that is not the last ends with the jump over the next one
+        last = k + 5 == len(barriers)
+        end = len(code) if last else next((i for i, l in enumerate(code) if i > barriers[k + 4] and re.search(r's_branch\s', l)), len(code))
+        if not last and end > barriers[k + 5]:
+            return False, f"{name}: no end of the first loop found"
+        o, m = check_loop(name, code, barriers[k:k + 5], start, end)
+        ok, start = ok and o, end
+        msgs.append(m)
+    return ok, "\n".join(msgs)
+
+def check_loop(name, code, barriers, start, end):
+    loads = [i for i, l in enumerate(code) if start <= i < end and 'buffer_load_dwordx4' in l]
     if not loads:
         return False, f"{name}: no buffer loads found"
     labels = {m.group(1): i for i, l in enumerate(code) for m in [re.match(r'^(\.LBB\d+_\d+):', l)] if m}
-    barriers = [i for i, l in enumerate(code) if 's_barrier' in l]
-    if len(barriers) != 5:
-        return False, f"{name}: expected 5 barriers (prologue, two loop phases, two tail phases), found {len(barriers)}"
     # the epilogue, whose loads and stores the compiler knows: behind the wait states that end the main loop's part
-    first_store = next((i for i, l in enumerate(code) if i > barriers[-1] and ('global_store' in l or re.search(r's_nop 15\s*$', l))), len(code))
+    first_store = next((i for i, l in enumerate(code) if barriers[-1] < i < end and ('global_store' in l or re.search(r's_nop 15\s*$', l))), end)
     # the main loop: the backward branch behind the third barrier, up to the block it reaches
     back = [(i, labels[m.group(1)]) for i, l in enumerate(code) for m in [re.search(r's_c?branch\S*\s+(\.LBB\d+_\d+)', l)]
             if m and m.group(1) in labels and labels[m.group(1)] <= i and barriers[2] < i < barriers[3]]

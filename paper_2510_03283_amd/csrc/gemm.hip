@@ -645,7 +645,7 @@ hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const 
   if (is_split(p)) {
     bool ok = !p.resid_kind && !p.out_bf16 && !p.swiglu && !p.swiglu_bwd && !has_rope(p);
     for (int g = 0; g < p.n_mg; ++g) {
-      const int it = cdiv(p.K, BK) * p.mg[g].npass, ks = std::max(1, p.k_splits[g]);
+      const int it = w4_tile_steps(LA, LB, cdiv(p.K, BK), p.mg[g].npass), ks = std::max(1, p.k_splits[g]);
       ok = ok && (ks == 1 || (p.mg[g].c_split_stride > 0 && cdiv(it, ks) * (ks - 1) < it));      // no empty slice
     }
     if (!ok) { *why = "gemm: k slices need plain fp32 output without residual and k tiles for every slice"; return hipErrorInvalidValue; }
@@ -736,9 +736,9 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
     bool ok = true;
     for (int g = 0; g < plain.n_mg; ++g) most = std::max(most, plain.mg[g].npass);
     for (int g = 0; g < plain.n_mg; ++g) {
-      const int it = cdiv(plain.K, BK) * plain.mg[g].npass;
+      const int nk = cdiv(plain.K, BK), it = w4_tile_steps(LA, LB, nk, plain.mg[g].npass);
       ks[g] = std::max(1, (c * plain.mg[g].npass + most / 2) / most);
-      ok = ok && it / ks[g] >= 4 && cdiv(it, ks[g]) * (ks[g] - 1) < it;
+      ok = ok && nk * plain.mg[g].npass / ks[g] >= 4 && cdiv(it, ks[g]) * (ks[g] - 1) < it;
       floats += (double)ks[g] * plain.mg[g].M * plain.ldc;
     }
     if (!ok || floats > (double)part_floats) continue;

@@ -143,6 +143,10 @@ __device__ __forceinline__ void w4_mfma(f32x4_t &c, const u32x4_t b, const u32x4
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b), "v"(a));
 }
 
+// Steps of the reduction of an output tile, which slices are cut from: k tiles times passes, or - two passes of the NT form, which go through
+// every k tile together - k tiles.
+__host__ __device__ constexpr int w4_tile_steps(int LA, int LB, int nk, int npass) { return LA == 0 && LB == 0 && npass == 2 ? nk : nk * npass; }
+
 template <int LA, int LB>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   constexpr int BM = 256, BN = 256, BKT = 64, NTHR = 256, WGN = 2, WTM = 128, WTN = 128, TM = 8, TN = 8;      // TM x TN blocks of 16x16
@@ -201,8 +205,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
   // k tiles tt0 .. tt0 + n_it - 1 of the tile's passes, one after the other (the launcher gives every slice some)
-  const int nk = (K + BKT - 1) / BKT, nk_slice = (nk * G.npass + ks - 1) / ks;
-  const int tt0 = slice * nk_slice, n_it = min(nk_slice, nk * G.npass - tt0);
+  // (two passes that share their B tiles count as one: w4_tile_steps)
+  const int nk = (K + BKT - 1) / BKT, n_steps = w4_tile_steps(LA, LB, nk, G.npass), nk_slice = (n_steps + ks - 1) / ks;
+  const int tt0 = slice * nk_slice, n_it = min(nk_slice, n_steps - tt0);
   const long long lda = p.lda, ldb = p.ldb;
   const int n_kseg = p.n_kseg;
   const int ks_s1 = p.kseg_start[1], ks_s2 = p.kseg_start[2];
@@ -286,6 +291,168 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     w4_mfma(acc[i][j], frb[j], fra[i]);
   };
 
+  // One tile time.
+  // Eight quarters of sixteen MFMAs: a quarter multiplies one half of the A fragments (AH) with one half of the B
+  // fragments (BH), in an order in which consecutive quarters share a half and each half is replaced in the quarter
+  // behind its last use (RO: operand, RH: half, RK: k step; the last two out of the next tile).  A quarter walks the half that came
+  // last in its outer loop (OUTER_B), so a fragment has about sixteen MFMAs from its read to its first use.
+  // Inside a quarter every other row runs backwards, so that consecutive MFMAs always share an operand (1.5 % of an MFMA-only loop
+  // on random operands; power again).
+  // What follows an MFMA: RD a fragment read, MW / MR the write and the request of a move; the moves (PER_Q of the quarter) over the first six quarters.
+  // An MFMA takes 16 cycles and an instruction of the one wave four, so a third instruction behind one is late: write and request
+  // behind one MFMA cost 2 - 3 %, the moves spread over the whole quarter 1 - 2 %.  (16384 x 4096 x 4096: 1.34 us a k tile on
+  // random operands with all of it, 1.32 without the output stores, 1.15 without the loads, 1.24 without the ds_writes, 1.06 without
+  // both, 1.21 without the fragment reads; with 32x32x16 MFMAs 1.49.)
+  // read(operand, from the next tile, k step, half, fragment); write(move), request(move); mid: between two MFMAs of the seventh
+  // quarter, in front of the barrier; turn: right behind the barrier, before the first read from the next tile.
+  auto tile_time = [&](auto MOVES, auto read, auto write, auto request_, auto mid, auto turn) W4_INL {
+    static_for<0, 8>([&](auto PP) W4_INL {
+      constexpr int pp = decltype(PP)::value;
+      constexpr int AH[8] = {0, 0, 1, 1, 0, 0, 1, 1}, BH[8] = {0, 1, 1, 0, 1, 0, 0, 1};
+      constexpr int RO[8] = {1, 0, 0, 1, 1, 0, 0, 1}, RH[8] = {1, 1, 0, 1, 0, 1, 0, 0}, RK[8] = {0, 0, 1, 1, 1, 1, 0, 0};
+      constexpr bool OUTER_B[8] = {true, true, false, false, true, true, false, false};
+      constexpr int PER_Q16[8] = {3, 3, 3, 3, 2, 2, 0, 0}, M0_16[8] = {0, 3, 6, 9, 12, 14, 16, 16};      // moves of a quarter, and its first
+      constexpr bool m16 = decltype(MOVES)::value == 16;
+      static_assert(m16 || decltype(MOVES)::value == 12, "16 or 12 moves");
+      constexpr int per_q = m16 ? PER_Q16[pp] : (pp < 6 ? 2 : 0), m0_q = m16 ? M0_16[pp] : 2 * pp;
+      static_for<0, 16>([&](auto Q) W4_INL {
+        constexpr int q = decltype(Q)::value, o = q >> 2, n = o & 1 ? 3 - (q & 3) : q & 3;
+        mfma1(W4_IC(4 * AH[pp] + (OUTER_B[pp] ? n : o)), W4_IC(4 * BH[pp] + (OUTER_B[pp] ? o : n)));
+        W4_SB;
+        constexpr int RD[16] = {0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, 3, -1, -1, -1};
+        constexpr int RD6[16] = {-1, -1, -1, -1, -1, -1, -1, -1, 0, -1, 1, -1, 2, -1, 3, -1};      // behind the barrier
+        constexpr int MW[16] = {-1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1, -1};
+        constexpr int MR[16] = {-1, -1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1};
+        constexpr int rd = pp == 6 ? RD6[q] : RD[q];
+        if constexpr (pp == 6 && q == 2) { mid(); W4_SB; }
+        if constexpr (pp == 6 && q == 6) { __syncthreads(); W4_SB; turn(); W4_SB; }
+        if constexpr (rd >= 0) { read(W4_IC(RO[pp]), W4_IC(pp >= 6), W4_IC(RK[pp]), W4_IC(RH[pp]), W4_IC(rd)); W4_SB; }
+        if constexpr (MW[q] >= 0 && MW[q] < per_q) { write(W4_IC(m0_q + MW[q])); W4_SB; }
+        if constexpr (MR[q] >= 0 && MR[q] < per_q) { request_(W4_IC(m0_q + MR[q])); W4_SB; }
+      });
+    });
+  };
+
+  // Two passes over the same B (activations in two bf16 terms, NT form): both terms of a k tile are multiplied while its B tile
+  // is in LDS, so a tile time fetches and stages 12 instead of 16 pieces per thread.  LDS: A stage 0 holds the first term,
+  // A stage 1 the second, the B stages alternate by k tile.  Registers: ra[0] / ra[1] the two terms, rb[0] B; a register is requested
+  // again right behind its ds_write, a whole k tile (two tile times) before its data is due, and 24 moves make a turn, so
+  // 23 younger loads follow the one that is waited for.  16384 x 4096 with two passes over K = 1024 / 4096 / 11008:
+  // 217 / 759 / 2000 us one pass behind the other, 209 / 719 / 1888 so.
+  constexpr bool HAS_PAIR = LA == 0 && LB == 0;
+  const bool pair = HAS_PAIR && G.npass == 2;
+  if constexpr (HAS_PAIR) {
+    if (pair) {
+      const int n_run = max(n_it, 2);      // k tiles: at least one turn of the loop and one tile behind it
+      Src s0 = tile_src(tt0);
+      u32x4_t ql = s0.qa;
+      ql[0] = w4_sgpr((uint32_t)(uint64_t)a_lo);
+      ql[1] = w4_sgpr((uint32_t)((uint64_t)a_lo >> 32) & 0xffffu);
+      // byte offsets of the tiles requested next: first term and B; second term
+      uint32_t oa = s0.oa, ol = s0.oa, ob = s0.ob;
+      const uint32_t b_bytes = s0.qb[2];
+      // H, L: the terms of A; requests past the last tile get empty resources
+      auto rq_h = [&](auto X) W4_INL { bload(ra[0][decltype(X)::value], s0.qa, offA, oa + decltype(X)::value * strA); };
+      auto rq_l = [&](auto X) W4_INL { bload(ra[1][decltype(X)::value], ql, offA, ol + decltype(X)::value * strA); };
+      auto rq_b = [&](auto X) W4_INL {
+        constexpr int y = decltype(X)::value;
+        bload(rb[0][y], (y & 2) ? s0.qu : s0.qb, offB, ob + (y >> 2) * strB_w + ((y >> 1) & 1) * strB_u + (y & 1) * strB);
+      };
+      auto wr_h = [&](auto X) W4_INL { stage_write(W4_IC(0), X, W4_IC(0)); };
+      auto wr_l = [&](auto X) W4_INL { stage_write(W4_IC(1), X, W4_IC(1)); };
+      auto wr_b = [&](auto X) W4_INL { stage_write(W4_IC(0), W4_IC(NL + decltype(X)::value), W4_IC(0)); };      // (wofs_b turns with the B stages)
+      auto step_hb = [&](int tile) W4_INL {      // to this tile of the slice
+        oa += stepA;
+        ob += stepB;
+        const bool live = tile < n_it;
+        s0.qa[2] = live ? a_bytes : 0u;
+        s0.qb[2] = live ? b_bytes : 0u;
+        s0.qu[2] = live ? b_bytes : 0u;
+      };
+      // prologue: tile 0 of the first term and of B into LDS; the rest in the order in which the loop moves it
+      static_for<0, NL>(rq_h);
+      static_for<0, NL>(rq_b);
+      static_for<0, NL>(rq_l);
+      W4_SB;
+      step_hb(1);
+      ol += stepA;
+      ql[2] = 1 < n_it ? a_bytes : 0u;
+      W4_SB;
+      wait_vmcnt<NL>();
+      W4_SB;
+      static_for<0, NL>(wr_h);
+      static_for<0, NL>(wr_b);
+      W4_SB;
+      static_for<0, NL / 2>(rq_b);
+      static_for<0, NL>(rq_h);
+      static_for<NL / 2, NL>(rq_b);
+      W4_SB;
+      step_hb(2);
+      wofs_b ^= (uint32_t)SB::BYTES;      // (the B stages lie 64 and 96 KB into LDS)
+      __syncthreads();
+      static_for<0, 4>([&](auto F) W4_INL { read1(W4_IC(0), W4_IC(0), W4_IC(0), W4_IC(0), F); });
+      static_for<0, 4>([&](auto F) W4_INL { read1(W4_IC(1), W4_IC(0), W4_IC(0), W4_IC(0), F); });
+      W4_SB;
+      // Pass ph over k tile u: the other term's tile (ph 0: second term of u; 1: first term of u + 1) into the other A stage and half of B
+      // of tile u + 1 into the other B stage.
+      auto phase = [&](auto PH, auto TAIL, int u) W4_INL {
+        constexpr int ph = decltype(PH)::value;
+        constexpr bool tail = decltype(TAIL)::value;
+        auto write = [&](auto M) W4_INL {
+          constexpr int m = decltype(M)::value;
+          if constexpr (!tail) {
+            wait_vmcnt<3 * NL - 1>();
+            W4_SB;
+          }
+          if constexpr (tail && (ph == 1 || m >= NL)) return;
+          else if constexpr (m >= NL) wr_b(W4_IC(m - NL + ph * (NL / 2)));
+          else if constexpr (ph == 0) wr_l(M);
+          else wr_h(M);
+        };
+        auto request2 = [&](auto M) W4_INL {
+          constexpr int m = decltype(M)::value;
+          if constexpr (tail) return;
+          else if constexpr (m >= NL) rq_b(W4_IC(m - NL + ph * (NL / 2)));
+          else if constexpr (ph == 0) rq_l(M);
+          else rq_h(M);
+        };
+        tile_time(W4_IC(12),
+                  [&](auto OP, auto NEXT, auto KK, auto HF, auto FF) W4_INL {
+                    read1(OP, W4_IC(decltype(OP)::value == 0 ? (decltype(NEXT)::value ? ph ^ 1 : ph) : 0), KK, HF, FF);
+                  },
+                  write, request2,
+                  [&]() W4_INL {
+                    if constexpr (!tail && ph == 0) {
+                      ol += stepA;
+                      ql[2] = u + 2 < n_it ? a_bytes : 0u;
+                    }
+                    if constexpr (!tail && ph == 1) step_hb(u + 3);
+                  },
+                  [&]() W4_INL {
+                    if constexpr (ph == 1) {
+                      wofs_b ^= (uint32_t)SB::BYTES;
+#pragma unroll
+                      for (int x = 0; x < 2; ++x) fb[x] ^= (uint32_t)SB::BYTES;
+                    }
+                  });
+        if constexpr (!tail && ph == 1) {
+          if (u + 2 >= n_run) {      // as below: nothing is in flight behind the loop
+            wait_vmcnt<0>();
+            W4_SB;
+          }
+        }
+      };
+      int u = 0;
+      do {
+        phase(W4_IC(0), std::false_type{}, u);
+        phase(W4_IC(1), std::false_type{}, u);
+        ++u;
+      } while (u + 1 < n_run);
+      phase(W4_IC(0), std::true_type{}, u);
+      phase(W4_IC(1), std::true_type{}, u);
+    }
+  }
+  if (!pair) {
   const int n_run = max(n_it, 3);      // tile times: at least one turn of the loop and one tile behind it
   const int rq_last = tt0 + n_it - 1;
   // The request cursor: the tile requested last, where it comes from, and how many tiles may follow it by a step of stepA /
@@ -360,39 +527,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       auto move_request = [&](auto X) W4_INL {
         if constexpr (!tail) request(W4_IC(ph), X, rq);
       };
-      // Eight quarters of sixteen MFMAs: a quarter multiplies one half of the A fragments (AH) with one half of the B
-      // fragments (BH), in an order in which consecutive quarters share a half and each half is replaced in the quarter
-      // behind its last use (RO: operand, RH: half, RK: k step; the last two out of the next tile).  A quarter walks the half that came
-      // last in its outer loop (OUTER_B), so a fragment has about sixteen MFMAs from its read to its first use.
-      // Inside a quarter every other row runs backwards, so that consecutive MFMAs always share an operand (1.5 % of an MFMA-only loop
-      // on random operands; power again).
-      // What follows an MFMA: RD a fragment read, MW / MR the write and the request of a move; 16 moves over the first six quarters.
-      // An MFMA takes 16 cycles and an instruction of the one wave four, so a third instruction behind one is late: write and request
-      // behind one MFMA cost 2 - 3 %, the moves spread over the whole quarter 1 - 2 %.  (16384 x 4096 x 4096: 1.34 us a k tile on
-      // random operands with all of it, 1.32 without the output stores, 1.15 without the loads, 1.24 without the ds_writes, 1.06 without
-      // both, 1.21 without the fragment reads; with 32x32x16 MFMAs 1.49.)
-      static_for<0, 8>([&](auto PP) W4_INL {
-        constexpr int pp = decltype(PP)::value;
-        constexpr int AH[8] = {0, 0, 1, 1, 0, 0, 1, 1}, BH[8] = {0, 1, 1, 0, 1, 0, 0, 1};
-        constexpr int RO[8] = {1, 0, 0, 1, 1, 0, 0, 1}, RH[8] = {1, 1, 0, 1, 0, 1, 0, 0}, RK[8] = {0, 0, 1, 1, 1, 1, 0, 0};
-        constexpr bool OUTER_B[8] = {true, true, false, false, true, true, false, false};
-        constexpr int M0[8] = {0, 3, 6, 9, 12, 14, 16, 16}, MN[8] = {3, 3, 3, 3, 2, 2, 0, 0};      // first move and how many
-        static_for<0, 16>([&](auto Q) W4_INL {
-          constexpr int q = decltype(Q)::value, o = q >> 2, n = o & 1 ? 3 - (q & 3) : q & 3;
-          mfma1(W4_IC(4 * AH[pp] + (OUTER_B[pp] ? n : o)), W4_IC(4 * BH[pp] + (OUTER_B[pp] ? o : n)));
-          W4_SB;
-          constexpr int RD[16] = {0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, 3, -1, -1, -1};
-          constexpr int RD6[16] = {-1, -1, -1, -1, -1, -1, -1, -1, 0, -1, 1, -1, 2, -1, 3, -1};      // behind the barrier
-          constexpr int MW[16] = {-1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1, -1};
-          constexpr int MR[16] = {-1, -1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1};
-          constexpr int rd = pp == 6 ? RD6[q] : RD[q];
-          if constexpr (!tail && pp == 6 && q == 2) { advance(); W4_SB; }
-          if constexpr (pp == 6 && q == 6) { __syncthreads(); W4_SB; }
-          if constexpr (rd >= 0) { read1(W4_IC(RO[pp]), W4_IC(pp >= 6 ? ph ^ 1 : ph), W4_IC(RK[pp]), W4_IC(RH[pp]), W4_IC(rd)); W4_SB; }
-          if constexpr (MW[q] >= 0 && MW[q] < MN[pp]) { move_write(W4_IC(M0[pp] + MW[q])); W4_SB; }
-          if constexpr (MR[q] >= 0 && MR[q] < MN[pp]) { move_request(W4_IC(M0[pp] + MR[q])); W4_SB; }
-        });
-      });
+      tile_time(W4_IC(16),
+                [&](auto OP, auto NEXT, auto KK, auto HF, auto FF) W4_INL { read1(OP, W4_IC(decltype(NEXT)::value ? ph ^ 1 : ph), KK, HF, FF); },
+                move_write, move_request, [&]() W4_INL { if constexpr (!tail) advance(); }, []() W4_INL {});
       // The compiler does not know which registers have a load in flight, and where control leaves the loop it
       // may copy or spill what is live there.  So the loop's last iteration ends with a wait for all loads (the
       // pipeline runs empty once per output tile), and the code behind the loop issues none.
@@ -415,6 +552,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     } while (t + 2 < n_run);
     phase(W4_IC(0), std::true_type{}, t);
     if (t + 1 < n_run) phase(W4_IC(1), std::true_type{}, t + 1);
+  }
   }
 
   // Epilogue.  Register r of block (i, j) holds row 16 i + lane % 16 and column 16 j + 4 (lane / 16) + r of the wave's

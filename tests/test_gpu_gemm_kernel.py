@@ -242,3 +242,20 @@ def test_swiglu_unit_counts_without_whole_vectors(torch_mod, handle, F):
         if keep:
             assert np.abs((f64(hm) + f64(lo))[:M] - ref).max() / np.abs(ref).max() <= 5e-5
             check_out(gu, np.concatenate([G, U], axis=1), M, 2 * F, 4e-3, f"G | U, {F} units")
+
+
+@pytest.mark.parametrize("k_tiles", [1, 2, 3, 4, 7])
+def test_two_terms_over_short_reductions(torch_mod, handle, k_tiles):
+    """Both terms of the activations go through every k tile together (NT form): one k tile runs the padded loop, the others one to
+    six turns of it, the second term's own rows have to be the ones that are added."""
+    torch = torch_mod
+    from paper_2510_03283_amd import binding
+    M, N, K = 300, 264, 64 * k_tiles
+    rng = np.random.default_rng(900 + k_tiles)
+    a, b, A, B = operands(torch, rng, 0, 0, M, N, K)
+    a_lo = bf16_of(torch, rng.uniform(-1, 1, (M, K)))          # as large as the first term: a swapped or missing one shows
+    ref = (A + f64(a_lo)) @ B.T
+    c = out_buffer(torch, M + 5, N + 8, torch.float32)
+    binding.mace_gemm_bf16(handle, 0, 0, M, N, K, a, b, c, a_lo=a_lo, ldc=N + 8, kernel=1)
+    torch.cuda.synchronize()
+    check_out(c, ref, M, N, 1e-5, f"two terms, {k_tiles} k tiles")
