@@ -143,6 +143,11 @@ __device__ __forceinline__ void w4_mfma(f32x4_t &c, const u32x4_t b, const u32x4
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(b), "v"(a));
 }
 
+__device__ __forceinline__ void w4_clear(f32x4_t &c) {
+  c = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  asm volatile("" : "+a"(c));
+}
+
 // Steps of the reduction of an output tile, which slices are cut from: k tiles times passes, or - two passes of the NT form, which go through
 // every k tile together - k tiles.
 __host__ __device__ constexpr int w4_tile_steps(int LA, int LB, int nk, int npass) { return LA == 0 && LB == 0 && npass == 2 ? nk : nk * npass; }
@@ -156,6 +161,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   // LDS: A stage 0 | A stage 1 | B stage 0 | B stage 1
   extern __shared__ __align__(16) unsigned char smem_raw[];
   lds_char_t *const lbase = (lds_char_t *)(lds_void_t *)smem_raw;
+
+  // The arguments span nine lines of the scalar cache, and the mapping below walks them in a chain of dependent loads; asked
+  // for one line after the other the first block on a CU waits for each (1 us a launch, 3072 x 4096 x 1024: 33.2 -> 32.3 us).
+  asm volatile("" ::"s"(p.mg[0].M), "s"(p.mg[1].M), "s"(p.mg[2].M), "s"(p.ns[0].N), "s"(p.ns[1].N), "s"(p.ns[2].N), "s"(p.K), "s"(p.n_kseg), "s"(p.k_splits[2]), "s"(p.mt_start[3]),
+               "s"(p.nt_start[3]), "s"(p.swiglu_bwd));
 
   // block -> tile and k slice: the mapping of gemm_bf16_dl_kernel over the tiles; a tile of row group g takes k_splits[g]
   // blocks in a row
@@ -197,14 +207,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   // Block (i, j): the B fragment is the first operand, so register r of a lane holds row 16 i + lane % 16 and column
   // 16 j + 4 (lane / 16) + r - four neighbouring columns, which leave as one 16-byte store.
   f32x4_t acc[TM][TN];
+  // (called behind the first requests, whose latency covers it; pinned there, or it ends up behind the first barrier)
+  auto clear = [&]() W4_INL {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+      for (int j = 0; j < TN; ++j) w4_clear(acc[i][j]);
+  };
 
-  // k tiles tt0 .. tt0 + n_it - 1 of the tile's passes, one after the other (the launcher gives every slice some)
   // (two passes that share their B tiles count as one: w4_tile_steps)
   const int nk = (K + BKT - 1) / BKT, n_steps = w4_tile_steps(LA, LB, nk, G.npass), nk_slice = (n_steps + ks - 1) / ks;
   const int tt0 = slice * nk_slice, n_it = min(nk_slice, n_steps - tt0);
@@ -378,6 +388,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       ol += stepA;
       ql[2] = 1 < n_it ? a_bytes : 0u;
       W4_SB;
+      clear();
+      W4_SB;
       wait_vmcnt<NL>();
       W4_SB;
       static_for<0, NL>(wr_h);
@@ -489,6 +501,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       W4_SB;
       const Src s1 = w4_resources(tile_cur(tt0 + min(1, n_it - 1)), a_bytes, n_it < 2);
       static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(0), X, s1); });
+      W4_SB;
+      clear();
       W4_SB;
       wait_vmcnt<2 * NL>();      // tile 0 is in
       W4_SB;
