@@ -155,8 +155,8 @@ size_t weight_elems(const Dims &D, int i) {
   }
 }
 
-// Reserve (and for fp32 models fill) the split weights.  need_lo: the forward uses the lo term.
-int prepare_weights(const Dims &D, const mace_layer_w_t *w, Bump &ws, bool need_lo, bool run, hipStream_t st, WSplit &out) {
+// Reserve the split weights of fp32 models; `fill` (nullable) gets the ranges to split.  need_lo: the forward uses the lo term.
+void prepare_weights(const Dims &D, const mace_layer_w_t *w, Bump &ws, bool need_lo, WSplit &out, std::vector<SplitRange> *fill = nullptr) {
   const void *src[7] = {w ? w->wq : nullptr, w ? w->wk : nullptr, w ? w->wv : nullptr, w ? w->wo : nullptr,
                         w ? w->w_gate : nullptr, w ? w->w_up : nullptr, w ? w->w_down : nullptr};
   for (int i = 0; i < 7; ++i) {
@@ -168,10 +168,9 @@ int prepare_weights(const Dims &D, const mace_layer_w_t *w, Bump &ws, bool need_
       bf16_t *lo = need_lo ? ws.take<bf16_t>(weight_elems(D, i)) : nullptr;
       out.hi[i] = hi;
       out.lo[i] = lo;
-      if (run) HIP_TRY(launch_split_f32((const float *)src[i], weight_elems(D, i), hi, lo, st), "split weights");
+      if (fill) fill->push_back(SplitRange{(const float *)src[i], weight_elems(D, i), hi, lo});
     }
   }
-  return MACE_OK;
 }
 
 // ---------------------------------------------------------------- saved activations (ft rows)
@@ -336,26 +335,12 @@ int check_lora(const mace_lora_t *l) {
 // backward folds the adapter scale into them).
 int prepare_lora(const Dims &D, const mace_lora_t *l, const LoraWs &L, float b_scale, hipStream_t st) {
   const int r = l->rank;
-  {
-    const void *src[3] = {l->a_q, l->a_k, l->a_v};
-    const int rows[3] = {r, r, r}, cols[3] = {D.d, D.d, D.d}, r0[3] = {0, LR, 2 * LR}, c0[3] = {0, 0, 0};
-    HIP_TRY(launch_lora_pack(src, rows, cols, r0, c0, 3, D.bf, 3 * LR, D.d, 1.0f, L.aqkv_hi, L.aqkv_lo, st), "pack A_qkv");
-  }
-  {
-    const void *src[1] = {l->a_o};
-    const int rows[1] = {r}, cols[1] = {D.qd}, z[1] = {0};
-    HIP_TRY(launch_lora_pack(src, rows, cols, z, z, 1, D.bf, LR, D.qd, 1.0f, L.ao_hi, L.ao_lo, st), "pack A_o");
-  }
-  {
-    const void *src[3] = {l->b_q, l->b_k, l->b_v};
-    const int rows[3] = {D.qd, D.kd, D.kd}, cols[3] = {r, r, r}, r0[3] = {0, D.qd, D.qd + D.kd}, c0[3] = {0, LR, 2 * LR};
-    HIP_TRY(launch_lora_pack(src, rows, cols, r0, c0, 3, D.bf, D.nqkv, 3 * LR, b_scale, L.bblk_hi, L.bblk_lo, st), "pack B_qkv");
-  }
-  {
-    const void *src[1] = {l->b_o};
-    const int rows[1] = {D.d}, cols[1] = {r}, z[1] = {0};
-    HIP_TRY(launch_lora_pack(src, rows, cols, z, z, 1, D.bf, D.d, LR, b_scale, L.bo_hi, L.bo_lo, st), "pack B_o");
-  }
+  const PackDst dst[4] = {
+      {{{l->a_q, r, D.d, 0, 0}, {l->a_k, r, D.d, LR, 0}, {l->a_v, r, D.d, 2 * LR, 0}}, 3, 3 * LR, D.d, 1.0f, L.aqkv_hi, L.aqkv_lo},
+      {{{l->a_o, r, D.qd, 0, 0}}, 1, LR, D.qd, 1.0f, L.ao_hi, L.ao_lo},
+      {{{l->b_q, D.qd, r, 0, 0}, {l->b_k, D.kd, r, D.qd, LR}, {l->b_v, D.kd, r, D.qd + D.kd, 2 * LR}}, 3, D.nqkv, 3 * LR, b_scale, L.bblk_hi, L.bblk_lo},
+      {{{l->b_o, D.d, r, 0, 0}}, 1, D.d, LR, b_scale, L.bo_hi, L.bo_lo}};
+  HIP_TRY(launch_lora_pack(dst, 4, D.bf, st), "pack adapters");
   return MACE_OK;
 }
 
@@ -752,10 +737,10 @@ size_t mace_workspace_bytes(mace_handle_t h, int32_t n_tokens, int32_t n_ft_toke
   const Dims D(h->m);
   WSplit ws;
   Bump f(nullptr), b(nullptr), p(nullptr);
-  prepare_weights(D, nullptr, f, true, false, nullptr, ws);
+  prepare_weights(D, nullptr, f, true, ws);
   plan_fwd(D, (size_t)(n_tokens - n_ft_tokens), (size_t)n_ft_tokens, n_decode, max_context, h->decode_chunk, f);
   plan_lora(D, (size_t)n_tokens, false, f);
-  prepare_weights(D, nullptr, b, false, false, nullptr, ws);
+  prepare_weights(D, nullptr, b, false, ws);
   plan_bwd(D, (size_t)n_ft_tokens, b);
   plan_lora(D, (size_t)n_ft_tokens, true, b);
   plan_dpo(D, (size_t)n_loss_rows, 1u << 16, p);
@@ -798,7 +783,8 @@ static int next_token_logits_impl(mace_handle_t h, const float *y, const int32_t
   const bf16_t *e_hi = (const bf16_t *)w_lm;
   if (!D.bf) {
     prof_mark(h, st, T_MISC);
-    HIP_TRY(launch_split_f32((const float *)w_lm, (size_t)D.V * D.d, P.e_hi, nullptr, st), "split E");
+    const SplitRange r = {(const float *)w_lm, (size_t)D.V * D.d, P.e_hi, nullptr};
+    HIP_TRY(launch_split_f32(&r, 1, st), "split E");
     e_hi = P.e_hi;
   }
   const bool skinny = n <= SKINNY_MAX_ROWS && D.bf && (long long)D.V * D.d < (1ll << 31);
@@ -1065,14 +1051,16 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
   {
     Bump m(nullptr);
     WSplit tmp;
-    prepare_weights(D, w, m, true, false, st, tmp);
+    prepare_weights(D, w, m, true, tmp);
     plan_fwd(D, I.Ti, I.Tf, I.Td, I.max_ctx, h->decode_chunk, m);
     if (lora) plan_lora(D, (size_t)I.T, false, m);
     if (m.off > workspace_bytes) return fail(MACE_WORKSPACE_TOO_SMALL, "forward workspace too small");
   }
   SideGuard side_guard(h, st);      // waits for side-stream work an earlier failed call may have left; joins on every return
   Bump wsb(workspace), svb(saved);
-  TRY(prepare_weights(D, w, wsb, true, true, st, W));
+  std::vector<SplitRange> split;
+  prepare_weights(D, w, wsb, true, W, &split);
+  HIP_TRY(launch_split_f32(split.data(), (int)split.size(), st), "split weights");
   FwdWs F = plan_fwd(D, I.Ti, I.Tf, I.Td, I.max_ctx, h->decode_chunk, wsb);
   LoraWs L;
   if (lora) {
@@ -1317,7 +1305,7 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
   {
     Bump m(nullptr);
     WSplit tmp;
-    prepare_weights(D, w, m, false, false, st, tmp);
+    prepare_weights(D, w, m, false, tmp);
     plan_bwd(D, I.Tf, m);
     if (lora) plan_lora(D, (size_t)I.Tf, true, m);
     if (m.off > workspace_bytes) return fail(MACE_WORKSPACE_TOO_SMALL, "backward workspace too small");
@@ -1325,7 +1313,8 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
   SideGuard side_guard(h, st);
   Bump wsb(workspace), svb((void *)saved);
   WSplit W;
-  TRY(prepare_weights(D, w, wsb, false, true, st, W));
+  std::vector<SplitRange> split;
+  prepare_weights(D, w, wsb, false, W, &split);
   BwdWs B = plan_bwd(D, I.Tf, wsb);
   LoraWs L;
   if (lora) {
@@ -1340,7 +1329,8 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
   const int n_part = Tf < DG_PARTS ? Tf : DG_PARTS;
 
   prof_mark(h, st, T_MISC);
-  HIP_TRY(launch_split_f32(dy_ft, (size_t)Tf * D.d, B.dy_bf, nullptr, st), "cast dy");
+  split.push_back(SplitRange{dy_ft, (size_t)Tf * D.d, B.dy_bf, nullptr});
+  HIP_TRY(launch_split_f32(split.data(), (int)split.size(), st), "cast dy, split weights");
   // MLP: dHm = dY Wd ; SwiGLU backward ; dWd = dY^T Hm with the Hm the forward kept
   {
     // where the product runs on the four-wave kernel its epilogue does the SwiGLU backward (dHm stays in registers)
@@ -1626,7 +1616,8 @@ static int dpo_impl(mace_handle_t h, const float *h_ft, const void *g_final, con
   const bf16_t *e_hi = (const bf16_t *)w_lm, *e_lo = nullptr;
   if (!D.bf) {
     prof_mark(h, st, T_MISC);
-    HIP_TRY(launch_split_f32((const float *)w_lm, (size_t)D.V * D.d, P.e_hi, P.e_lo, st), "split head");
+    const SplitRange r = {(const float *)w_lm, (size_t)D.V * D.d, P.e_hi, P.e_lo};
+    HIP_TRY(launch_split_f32(&r, 1, st), "split head");
     e_hi = P.e_hi; e_lo = P.e_lo;
   }
   const int Ri = (int)R;

@@ -277,8 +277,16 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const bf16_t *__restric
 
 // HBM-bound: four elements per thread (16-byte loads, 8-byte stores) where the pointers allow it (n4 = n / 4, else 0), the
 // rest one by one.  65536 x 4096 to one bf16 term: 412 us with one element per turn (3.9 TB/s), 330 us now (4.9 TB/s).
-__global__ __launch_bounds__(256) void split_f32_kernel(const float *__restrict__ src, size_t n, size_t n4, bf16_t *__restrict__ hi, bf16_t *__restrict__ lo) {
-  const size_t stride = (size_t)gridDim.x * 256, t = (size_t)blockIdx.x * 256 + threadIdx.x;
+// One launch for all ranges of a call (a model in fp32 has seven weight matrices to split in front of every forward and
+// backward: 2.3 us each, and as much again between two launches).  A range takes the blocks first .. first + count - 1 of the grid.
+struct SplitJob { SplitRange r; size_t n4; unsigned first, count; };
+struct SplitJobs { SplitJob j[MAX_SPLIT_RANGES]; };
+__global__ __launch_bounds__(256) void split_f32_kernel(const SplitJobs jobs, int n_jobs) {
+  int k = 0;
+  while (k + 1 < n_jobs && blockIdx.x >= jobs.j[k + 1].first) ++k;
+  const float *__restrict__ src = jobs.j[k].r.src;
+  bf16_t *__restrict__ hi = jobs.j[k].r.hi, *__restrict__ lo = jobs.j[k].r.lo;
+  const size_t n = jobs.j[k].r.n, n4 = jobs.j[k].n4, stride = (size_t)jobs.j[k].count * 256, t = (size_t)(blockIdx.x - jobs.j[k].first) * 256 + threadIdx.x;
   for (size_t i = t; i < n4; i += stride) {
     float v[4];
     ld4<false>(src, 4 * i, v);
@@ -426,12 +434,22 @@ hipError_t launch_swiglu_fwd(const SwigluRows *groups, int n_groups, int F, hipS
   return hipGetLastError();
 }
 
-hipError_t launch_split_f32(const float *src, size_t n, bf16_t *hi, bf16_t *lo, hipStream_t st) {
+hipError_t launch_split_f32(const SplitRange *ranges, int n_ranges, hipStream_t st) {
+  if (n_ranges > MAX_SPLIT_RANGES) return hipErrorInvalidValue;
+  SplitJobs jobs = {};
+  int n = 0;
+  unsigned blocks = 0;
+  for (int i = 0; i < n_ranges; ++i) {
+    const SplitRange &r = ranges[i];
+    if (r.n == 0) continue;
+    const size_t n4 = ((uintptr_t)r.src & 15) || (((uintptr_t)r.hi | (uintptr_t)r.lo) & 7) ? 0 : r.n / 4;
+    const size_t want = ((n4 ? n4 + 3 : r.n) + 255) / 256;
+    const unsigned count = (unsigned)(want < 16384 ? want : 16384);
+    jobs.j[n++] = SplitJob{r, n4, blocks, count};
+    blocks += count;
+  }
   if (n == 0) return hipSuccess;
-  const size_t n4 = ((uintptr_t)src & 15) || (((uintptr_t)hi | (uintptr_t)lo) & 7) ? 0 : n / 4;
-  const size_t want = ((n4 ? n4 + 3 : n) + 255) / 256;
-  const unsigned blocks = (unsigned)(want < 16384 ? want : 16384);
-  hipLaunchKernelGGL(split_f32_kernel, dim3(blocks), dim3(256), 0, st, src, n, n4, hi, lo);
+  hipLaunchKernelGGL(split_f32_kernel, dim3(blocks), dim3(256), 0, st, jobs, n);
   return hipGetLastError();
 }
 

@@ -69,8 +69,14 @@ struct SwigluRows {
   int rows;
 };
 hipError_t launch_swiglu_fwd(const SwigluRows *groups, int n_groups, int F, hipStream_t st);
-// fp32 -> (hi, lo) bf16, n elements; lo nullable.
-hipError_t launch_split_f32(const float *src, size_t n, bf16_t *hi, bf16_t *lo, hipStream_t st);
+// fp32 -> (hi, lo) bf16, n elements (lo nullable), of up to MAX_SPLIT_RANGES ranges in one launch.
+struct SplitRange {
+  const float *src;
+  size_t n;
+  bf16_t *hi, *lo;
+};
+constexpr int MAX_SPLIT_RANGES = 8;
+hipError_t launch_split_f32(const SplitRange *ranges, int n_ranges, hipStream_t st);
 hipError_t launch_fill_f32(float *dst, size_t n, float v, hipStream_t st);
 // out[i] = parts (+ resid[i], fp32), n % 4 == 0, as fp32 or bf16; one to three ranges in one launch.
 struct SumRange {
@@ -123,9 +129,18 @@ hipError_t launch_skinny(const SkinnyParams &p, int asrc, int epi, hipStream_t s
 
 // ---- lora.hip ---------------------------------------------------------------------------------
 // dst[dst_rows, dst_cols] as bf16 (hi, nullable lo) = zeros with up to three source matrices
-// (fp32 or bf16, [rows, cols] row-major), multiplied by scale, placed at (r0, c0).
-hipError_t launch_lora_pack(const void *const *src, const int *rows, const int *cols, const int *r0, const int *c0, int n_src,
-                            bool src_bf16, int dst_rows, int dst_cols, float scale, bf16_t *hi, bf16_t *lo, hipStream_t st);
+// (fp32 or bf16, [rows, cols] row-major), multiplied by scale, placed at (r0, c0); up to four destinations in one launch.
+struct PackSrc {
+  const void *p;
+  int rows, cols, r0, c0;
+};
+struct PackDst {
+  PackSrc src[3];
+  int n_src, rows, cols;
+  float scale;
+  bf16_t *hi, *lo;
+};
+hipError_t launch_lora_pack(const PackDst *dst, int n_dst, bool src_bf16, hipStream_t st);
 // (hi, lo) = two-term bf16 form of scale * src.
 hipError_t launch_scale_split(const Parts &src, size_t n, float scale, bf16_t *hi, bf16_t *lo, hipStream_t st);
 // dst[rows, cols] (+)= scale * the window of src (row pitch src_ld) that starts at (r0, c0).

@@ -4,33 +4,29 @@
 // low-rank activations, and cutting the adapter gradients back out of the padded products.
 #include "kernels.h"
 
+#include <algorithm>
+
 namespace {
 
-struct PackSrc {
-  const void *p;     // [rows, cols] row-major, fp32 or bf16
-  int rows, cols;
-  int r0, c0;        // placement of element (0, 0) in the destination
-};
-
-// dst[dst_rows, dst_cols] (hi, optional lo) = zeros, except the windows covered by up to 3 sources.
+// Grid (elements, destination).
+struct PackDsts { PackDst d[4]; };
 template <bool BF16>
-__global__ __launch_bounds__(256) void lora_pack_kernel(PackSrc s0, PackSrc s1, PackSrc s2, int n_src, int dst_rows, int dst_cols, float scale,
-                                                        bf16_t *__restrict__ hi, bf16_t *__restrict__ lo) {
-  const size_t n = (size_t)dst_rows * dst_cols, stride = (size_t)gridDim.x * 256;
+__global__ __launch_bounds__(256) void lora_pack_kernel(const PackDsts all) {
+  const PackDst &D = all.d[blockIdx.y];
+  const size_t n = (size_t)D.rows * D.cols, stride = (size_t)gridDim.x * 256;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
-    const int r = (int)(i / dst_cols), c = (int)(i % dst_cols);
+    const int r = (int)(i / D.cols), c = (int)(i % D.cols);
     float v = 0.f;
-    const PackSrc *ss[3] = {&s0, &s1, &s2};
 #pragma unroll
     for (int k = 0; k < 3; ++k)
-      if (k < n_src) {
-        const int rr = r - ss[k]->r0, cc = c - ss[k]->c0;
-        if (rr >= 0 && rr < ss[k]->rows && cc >= 0 && cc < ss[k]->cols) v = ld_io<BF16>(ss[k]->p, (size_t)rr * ss[k]->cols + cc);
+      if (k < D.n_src) {
+        const int rr = r - D.src[k].r0, cc = c - D.src[k].c0;
+        if (rr >= 0 && rr < D.src[k].rows && cc >= 0 && cc < D.src[k].cols) v = ld_io<BF16>(D.src[k].p, (size_t)rr * D.src[k].cols + cc);
       }
     bf16_t h, l;
-    split_bf(v * scale, h, l);
-    hi[i] = h;
-    if (lo) lo[i] = l;
+    split_bf(v * D.scale, h, l);
+    D.hi[i] = h;
+    if (D.lo) D.lo[i] = l;
   }
 }
 
@@ -66,17 +62,22 @@ unsigned grid_for(size_t n) { return (unsigned)((n + 255) / 256 < 2048 ? (n + 25
 
 }  // namespace
 
-hipError_t launch_lora_pack(const void *const *src, const int *rows, const int *cols, const int *r0, const int *c0, int n_src,
-                            bool src_bf16, int dst_rows, int dst_cols, float scale, bf16_t *hi, bf16_t *lo, hipStream_t st) {
-  if (n_src < 1 || n_src > 3 || dst_rows <= 0 || dst_cols <= 0) return hipErrorInvalidValue;
-  PackSrc s[3] = {};
-  for (int k = 0; k < n_src; ++k) {
-    if (!src[k] || rows[k] <= 0 || cols[k] <= 0 || r0[k] < 0 || c0[k] < 0 || r0[k] + rows[k] > dst_rows || c0[k] + cols[k] > dst_cols) return hipErrorInvalidValue;
-    s[k] = PackSrc{src[k], rows[k], cols[k], r0[k], c0[k]};
+hipError_t launch_lora_pack(const PackDst *dst, int n_dst, bool src_bf16, hipStream_t st) {
+  if (n_dst < 1 || n_dst > 4) return hipErrorInvalidValue;
+  PackDsts all = {};
+  size_t most = 0;
+  for (int i = 0; i < n_dst; ++i) {
+    const PackDst &D = all.d[i] = dst[i];
+    if (D.n_src < 1 || D.n_src > 3 || D.rows <= 0 || D.cols <= 0) return hipErrorInvalidValue;
+    for (int k = 0; k < D.n_src; ++k) {
+      const PackSrc &s = D.src[k];
+      if (!s.p || s.rows <= 0 || s.cols <= 0 || s.r0 < 0 || s.c0 < 0 || s.r0 + s.rows > D.rows || s.c0 + s.cols > D.cols) return hipErrorInvalidValue;
+    }
+    most = std::max(most, (size_t)D.rows * D.cols);
   }
-  const size_t n = (size_t)dst_rows * dst_cols;
-  if (src_bf16) hipLaunchKernelGGL(lora_pack_kernel<true>, dim3(grid_for(n)), dim3(256), 0, st, s[0], s[1], s[2], n_src, dst_rows, dst_cols, scale, hi, lo);
-  else hipLaunchKernelGGL(lora_pack_kernel<false>, dim3(grid_for(n)), dim3(256), 0, st, s[0], s[1], s[2], n_src, dst_rows, dst_cols, scale, hi, lo);
+  const dim3 grid(grid_for(most), (unsigned)n_dst);
+  if (src_bf16) hipLaunchKernelGGL(lora_pack_kernel<true>, grid, dim3(256), 0, st, all);
+  else hipLaunchKernelGGL(lora_pack_kernel<false>, grid, dim3(256), 0, st, all);
   return hipGetLastError();
 }
 
