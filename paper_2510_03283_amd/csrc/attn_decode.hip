@@ -9,11 +9,12 @@
 // nontemporal loads (the cache is read once per iteration and should not displace the weights).
 #include "kernels.h"
 
+#include <algorithm>
 #include <cstdlib>
 
 namespace {
 
-constexpr int MIN_CHUNK = 512, MAX_CHUNK = 4096;   // tokens per block: a power of two in this range, chosen per launch
+constexpr int MIN_PINNED = 512, MAX_CHUNK = 4096;   // tokens per block: a power of two, 128 .. MAX_CHUNK chosen per launch, from MIN_PINNED on a caller's choice
 constexpr int UNR = 4;       // token loads in flight per lane for K and for V
 
 __device__ __forceinline__ float safe_scale(float m_old, float m_new) {
@@ -204,20 +205,55 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const bf16_t *__restri
   }
 }
 
+// Merges the splits of a (request, head): CG groups of HD threads take every CG-th split each, in one pass with its own soft-max
+// state, and are merged through LDS, in order.  The time is the latency of the loads, so a group has those of CU splits in flight.
+// (One group, first the maximum of all splits and then their sums: 8000 tokens in 32 splits 28 us with the kernel in front, in 63 splits 40;
+// now 8000 tokens 12.2 and 12.8.)
+constexpr int CG = 4, CU = 4;
 template <int HD>
-__global__ __launch_bounds__(HD) void attn_decode_combine_kernel(const float *__restrict__ partial,
-                                                                 const int32_t *__restrict__ ctx_lens, int Hq, int nsplit, int chunk,
-                                                                 bf16_t *__restrict__ out, float *__restrict__ norms, int frag_row0) {
-  const int req = blockIdx.x, h = blockIdx.y, e = threadIdx.x;
+__global__ __launch_bounds__(CG * HD) void attn_decode_combine_kernel(const float *__restrict__ partial,
+                                                                      const int32_t *__restrict__ ctx_lens, int Hq, int nsplit, int chunk,
+                                                                      bf16_t *__restrict__ out, float *__restrict__ norms, int frag_row0) {
+  __shared__ float sa[CG][HD], sml[CG][2];
+  const int req = blockIdx.x, h = blockIdx.y, e = threadIdx.x % HD, g = threadIdx.x / HD;
   const int ns = min(nsplit, (ctx_lens[req] + 1 + chunk - 1) / chunk);
   const float *src = partial + ((size_t)req * Hq + h) * nsplit * (HD + 2);
-  float mn = -INFINITY;
-  for (int s = 0; s < ns; ++s) mn = fmaxf(mn, src[s * (HD + 2) + HD]);
-  float lo = 0.f, ao = 0.f;
-  for (int s = 0; s < ns; ++s) {
-    const float a = safe_scale(src[s * (HD + 2) + HD], mn);
-    lo += src[s * (HD + 2) + HD + 1] * a;
-    ao += src[s * (HD + 2) + e] * a;
+  float m = -INFINITY, l = 0.f, a = 0.f;
+  for (int s0 = g; s0 < ns; s0 += CG * CU) {
+    float mv[CU], lv[CU], av[CU], mn = m;
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const int s = s0 + u * CG;
+      const float *p = src + (size_t)min(s, ns - 1) * (HD + 2);
+      mv[u] = s < ns ? p[HD] : -INFINITY;
+      lv[u] = p[HD + 1];
+      av[u] = p[e];
+    }
+#pragma unroll
+    for (int u = 0; u < CU; ++u) mn = fmaxf(mn, mv[u]);
+    const float al = safe_scale(m, mn);
+    l *= al;
+    a *= al;
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      const float w = safe_scale(mv[u], mn);
+      l += lv[u] * w;
+      a += av[u] * w;
+    }
+    m = mn;
+  }
+  sa[g][e] = a;
+  if (e == 0) { sml[g][0] = m; sml[g][1] = l; }
+  __syncthreads();
+  if (g) return;
+  float mn = sml[0][0], lo = 0.f, ao = 0.f;
+#pragma unroll
+  for (int k = 1; k < CG; ++k) mn = fmaxf(mn, sml[k][0]);
+#pragma unroll
+  for (int k = 0; k < CG; ++k) {
+    const float w = safe_scale(sml[k][0], mn);
+    lo += sml[k][1] * w;
+    ao += sa[k][e] * w;
   }
   const float v = lo > 0.f ? ao / lo : 0.f;
   out[frag_row0 >= 0 ? frag_index(frag_row0 + req, h * HD + e, Hq * HD) : ((size_t)req * Hq + h) * HD + e] = f2bf(v);
@@ -260,21 +296,33 @@ bool launch_grp(int grp, const bf16_t *q, const void *ck, const void *cv, long l
 
 // Tokens per block.  Long chunks mean fewer blocks that find nothing to do, fewer partial states to write
 // and merge and a longer stream per block (6.2 -> 6.6 TB/s from 512 to 2048 tokens on a 256-request,
-// 32-head batch) - as long as the grid still fills the chip several times over.  Shorter chunks than 512
-// tokens do not help small batches (32 requests x 8 kv heads of 4 query heads each: 41 us at 512, 49 us
-// at 128): with four query heads per kv head the per-token arithmetic, not the stream, sets the time.
+// 32-head batch) - as long as the grid still fills the chip several times over.  Where it does not, a block's own
+// chain of loads sets the time and short chunks win; at 128 tokens a wave has one or two turns of its loop.  us at 128 / 256 / 512 tokens, both
+// kernels, heads x kv heads x width 32 x 8 x 64: one request of 700 tokens 9.0 / 10.8 / 14.6, of 8000 12.8 / 12.2 / 16.3, 16 of 300 - 1200 15.1 / 16.7 / 20.9,
+// 32 of 256 - 2048 (4352 blocks of 128) 31.0 / 29.7 / 31.1, 64 of 500 - 2000 (4096 blocks of 256) 57.5 / 53.3 / 57.0; 32 x 32 x 128: one of 700 9.0 /
+// 11.3 / 17.4, 8 of 300 - 1200 21.5 / 24.8 / 36.3, 16 (5120 blocks of 128) 38.0 / 38.7 / 44.4, 32 of 256 - 2048 (9216 blocks of 256) 112.8 / 110.8 / 116.0,
+// 64 of 500 - 2000 (16384 blocks of 256) 223 / 218 / 216.
+constexpr long long MOST_128 = 4096, MOST_256 = 10240;      // blocks up to which 128 and 256 tokens are taken
 static int decode_chunk_tokens(int n_decode, int Hkv, int max_context, int chunk_tokens) {
-  if (chunk_tokens) return chunk_tokens >= MIN_CHUNK && chunk_tokens <= MAX_CHUNK && !(chunk_tokens & (chunk_tokens - 1)) ? chunk_tokens : -1;
-  int chunk = MIN_CHUNK;
-  while (chunk < MAX_CHUNK && (long long)Hkv * n_decode * cdiv(max_context + 1, 2 * chunk) >= 8192) chunk *= 2;
+  if (chunk_tokens) return chunk_tokens >= MIN_PINNED && chunk_tokens <= MAX_CHUNK && !(chunk_tokens & (chunk_tokens - 1)) ? chunk_tokens : -1;
+  const long long streams = (long long)Hkv * n_decode;
+  if (streams * cdiv(max_context + 1, 128) <= MOST_128) return 128;
+  if (streams * cdiv(max_context + 1, 256) <= MOST_256) return 256;
+  int chunk = 512;
+  while (chunk < MAX_CHUNK && streams * cdiv(max_context + 1, 2 * chunk) >= 8192) chunk *= 2;
   return chunk;
 }
 
 size_t decode_partial_floats(int n_decode, int Hq, int Hkv, int hd, int max_context, int chunk_tokens) {
   int chunk = decode_chunk_tokens(n_decode, Hkv, max_context, chunk_tokens);
-  if (chunk < 0) chunk = MIN_CHUNK;                                    // an invalid override is rejected at launch; size for the worst case
-  const size_t nsplit = (size_t)cdiv(max_context + 1, chunk);
-  return (size_t)n_decode * Hq * nsplit * (hd + 2);
+  if (chunk < 0) chunk = 512;                                          // an invalid override is rejected at launch; size for the worst case
+  const size_t streams = (size_t)n_decode * Hkv;
+  size_t blocks = streams * cdiv(max_context + 1, chunk);
+  if (!chunk_tokens) {      // room for every smaller batch too: one that takes shorter chunks has more blocks
+    blocks = std::max(blocks, std::min(streams * cdiv(max_context + 1, 128), (size_t)MOST_128));
+    blocks = std::max(blocks, std::min(streams * cdiv(max_context + 1, 256), (size_t)MOST_256));
+  }
+  return blocks * (Hq / Hkv) * (hd + 2);
 }
 
 hipError_t launch_attn_decode(const bf16_t *q, const void *cache_k, const void *cache_v, bool cache_bf16,
@@ -299,7 +347,7 @@ hipError_t launch_attn_decode(const bf16_t *q, const void *cache_k, const void *
   if (!ok) return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (hd == 64) hipLaunchKernelGGL((attn_decode_combine_kernel<64>), dim3(n_decode, Hq), dim3(64), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
-  else hipLaunchKernelGGL((attn_decode_combine_kernel<128>), dim3(n_decode, Hq), dim3(128), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
+  if (hd == 64) hipLaunchKernelGGL((attn_decode_combine_kernel<64>), dim3(n_decode, Hq), dim3(CG * 64), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
+  else hipLaunchKernelGGL((attn_decode_combine_kernel<128>), dim3(n_decode, Hq), dim3(CG * 128), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
   return hipGetLastError();
 }
