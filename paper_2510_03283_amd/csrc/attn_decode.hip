@@ -313,14 +313,19 @@ static int decode_chunk_tokens(int n_decode, int Hkv, int max_context, int chunk
   return chunk;
 }
 
+// Room for the partial states of this batch and of every smaller one (fewer requests, shorter contexts), which may take shorter chunks and have
+// more blocks: the rule takes a chunk below MAX_CHUNK only up to a number of blocks, and a batch has at most streams * cdiv(context, chunk) of
+// them.  512 to 2048 tokens are taken where twice the chunk makes fewer than 8192 blocks, so they make at most twice 8191 themselves.
 size_t decode_partial_floats(int n_decode, int Hq, int Hkv, int hd, int max_context, int chunk_tokens) {
-  int chunk = decode_chunk_tokens(n_decode, Hkv, max_context, chunk_tokens);
-  if (chunk < 0) chunk = 512;                                          // an invalid override is rejected at launch; size for the worst case
   const size_t streams = (size_t)n_decode * Hkv;
-  size_t blocks = streams * cdiv(max_context + 1, chunk);
-  if (!chunk_tokens) {      // room for every smaller batch too: one that takes shorter chunks has more blocks
-    blocks = std::max(blocks, std::min(streams * cdiv(max_context + 1, 128), (size_t)MOST_128));
-    blocks = std::max(blocks, std::min(streams * cdiv(max_context + 1, 256), (size_t)MOST_256));
+  auto blocks_of = [&](int chunk) { return streams * cdiv(max_context + 1, chunk); };
+  size_t blocks;
+  if (chunk_tokens) {
+    const int chunk = decode_chunk_tokens(n_decode, Hkv, max_context, chunk_tokens);
+    blocks = blocks_of(chunk < 0 ? 512 : chunk);                       // an invalid override is rejected at launch; size for the worst case
+  } else {
+    blocks = std::max({std::min(blocks_of(128), (size_t)MOST_128), std::min(blocks_of(256), (size_t)MOST_256), std::min(blocks_of(512), (size_t)2 * 8191),
+                       blocks_of(MAX_CHUNK)});
   }
   return blocks * (Hq / Hkv) * (hd + 2);
 }

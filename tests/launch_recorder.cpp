@@ -193,6 +193,15 @@ int main(int argc, char **argv) {
   if (g_uploads) return 0;
   if (num("single_stream", 0)) mace_set_option(h, MACE_OPT_SINGLE_STREAM, 1);
 
+  if (call == "workspace") {      // decode=counts contexts=lengths: the bytes of every pair, tokens=, ft_tokens= other rows
+    for (int n : list("decode"))
+      for (int c : list("contexts")) {
+        const int other = (int)num("tokens", 0), Tf = (int)num("ft_tokens", 0);
+        printf("{\"op\": \"workspace\", \"decode\": %d, \"context\": %d, \"bytes\": %zu}\n", n, c, mace_workspace_bytes(h, n + other + Tf, Tf, n, c, 0));
+      }
+    return 0;
+  }
+
   // batch: prefill=lengths decode=contexts ft=lengths
   const std::vector<int> pre = list("prefill"), ctx = list("decode"), ft = list("ft");
   std::vector<int32_t> seg{0}, lens(ctx.begin(), ctx.end());

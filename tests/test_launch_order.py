@@ -227,6 +227,33 @@ def test_slices_follow_their_row_group(recorder, groups):
     assert {tuple(g) for g in r["groups"]} == set(groups)
 
 
+DECODE_HEADS = [(4096, 32, 32, 128), (2048, 32, 8, 64), (1024, 8, 2, 128), (1024, 8, 1, 64)]
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd", DECODE_HEADS, ids=lambda v: str(v))
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_workspace_grows_with_requests_and_contexts(recorder, d, hq, hkv, hd, bf16):
+    """What is enough for a batch is enough for one with fewer requests or shorter contexts, whatever tokens a block either takes.  (The requests'
+    own rows only add: 66 rows and more, past the few-row products and their own scratch.)"""
+    ns = [1, 2, 7, 16, 17, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 200, 255, 256, 257, 400]
+    ctx = sorted({max(0, c + e) for c in (0, 128, 256, 384, 512, 640, 1024, 1536, 2048, 3072, 4096, 6144, 8192, 16384) for e in (-1, 0, 1)})
+    rec = recorder("workspace", d=d, hq=hq, hkv=hkv, hd=hd, F=256, V=256, bf16=bf16, decode=ns, contexts=ctx, tokens=66)
+    size = np.array([r["bytes"] for r in rec]).reshape(len(ns), len(ctx))
+    assert size.min() > 0
+    assert (np.diff(size, axis=0) >= 0).all() and (np.diff(size, axis=1) >= 0).all()
+
+
+@pytest.mark.parametrize("rows,longest", [(1100, 4095), (1600, 4095), (2048, 4095), (2048, 1023)])
+def test_shorter_contexts_fit_the_workspace_of_longer_ones(recorder, rows, longest):
+    """64 requests of a 7B-class layer beside others, with adapters: the forward plans its scratch by the longest context that is there,
+    the caller by the longest that may come."""
+    opts = dict(d=4096, hq=32, hkv=32, hd=128, F=11008, V=32000)
+    (size,) = recorder("workspace", decode=[64], contexts=[longest], tokens=rows - 64, **opts)
+    for ctx in (longest, longest * 3 // 4, longest // 2, longest // 4, 511, 255, 127, 0):
+        rec = recorder("fwd", prefill=[rows - 64], decode=[ctx] + [ctx // 2] * 63, lora=16, work=size["bytes"], **opts)
+        assert status(rec)["status"] == 0, (ctx, status(rec))
+
+
 # pi / 2 in three pieces of at most 32 bits and a rest (Machin's formula in integers)
 PI_HALF = [3373259426 * 2.0 ** -31, 140128397 * 2.0 ** -61, 206333480 * 2.0 ** -91, 2.9038559739793605e-28]
 
