@@ -226,8 +226,8 @@ __global__ __launch_bounds__(CG * HD) void attn_decode_combine_kernel(const floa
       const int s = s0 + u * CG;
       const float *p = src + (size_t)min(s, ns - 1) * (HD + 2);
       mv[u] = s < ns ? p[HD] : -INFINITY;
-      lv[u] = p[HD + 1];
-      av[u] = p[e];
+      lv[u] = s < ns ? p[HD + 1] : 0.f;      // (a sum can be infinite, and weight 0 does not remove it)
+      av[u] = s < ns ? p[e] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < CU; ++u) mn = fmaxf(mn, mv[u]);

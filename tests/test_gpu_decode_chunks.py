@@ -28,3 +28,24 @@ def test_batches_on_both_sides_of_the_rule(torch_mod, hq, hkv, hd):
         ctx = [(i * 197) % 2000 for i in range(n - 1)] + [2000]
         wl = custom_workload("rule", dims, prefill=[], decode=ctx, n_pairs=0, prompt=3, resp=(2, 9))
         check_iteration(torch_mod, wl, f"{n} requests Hq{hq} Hkv{hkv} hd{hd}")
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_an_infinite_value_stays_in_its_head(torch_mod, hd):
+    """An infinite cached value makes its own element infinite (the norm of its head shows it: an infinity, not a NaN), wherever among the
+    splits of its request it lies: alone, first, last, and in splits that fill the merge's turns to different degrees."""
+    import numpy as np
+    from paper_2510_03283_amd.harness import DeviceIteration
+    dims = synth.ModelDims(n_q_heads=2, n_kv_heads=2, head_dim=hd, **SMALL)
+    at = [(60, 30), (300, 10), (300, 290), (2100, 100), (2100, 2090), (1000, 500), (500, None)]      # context, position of the infinity
+    wl = custom_workload("infinite", dims, prefill=[], decode=[c for c, _ in at], n_pairs=0, prompt=3, resp=(2, 9))
+    for j, (_, p) in enumerate(at):
+        if p is not None:
+            wl.ctx_v[j][p, 1, 5] = np.inf
+    it = DeviceIteration(wl)
+    it.forward()
+    torch_mod.cuda.synchronize()
+    norms = it.head_norms.cpu().numpy()
+    it.close()
+    assert np.isfinite(norms[:, 0]).all(), norms
+    assert [bool(np.isinf(n)) for n in norms[:, 1]] == [p is not None for _, p in at] and not np.isnan(norms).any(), norms
