@@ -245,27 +245,27 @@ __global__ __launch_bounds__(CG * HD) void attn_decode_combine_kernel(const floa
   sa[g][e] = a;
   if (e == 0) { sml[g][0] = m; sml[g][1] = l; }
   __syncthreads();
-  if (g) return;
-  float mn = sml[0][0], lo = 0.f, ao = 0.f;
+  // (every thread stays to the end: there is a barrier in the norms)
+  float v = 0.f;
+  if (g == 0) {
+    float mn = sml[0][0], lo = 0.f, ao = 0.f;
 #pragma unroll
-  for (int k = 1; k < CG; ++k) mn = fmaxf(mn, sml[k][0]);
+    for (int k = 1; k < CG; ++k) mn = fmaxf(mn, sml[k][0]);
 #pragma unroll
-  for (int k = 0; k < CG; ++k) {
-    const float w = safe_scale(sml[k][0], mn);
-    lo += sml[k][1] * w;
-    ao += sa[k][e] * w;
-  }
-  const float v = lo > 0.f ? ao / lo : 0.f;
-  out[frag_row0 >= 0 ? frag_index(frag_row0 + req, h * HD + e, Hq * HD) : ((size_t)req * Hq + h) * HD + e] = f2bf(v);
-  if (norms) {                                   // L2 norm of the head's output vector (fp32 values)
-    __shared__ float red[2];
-    float s = wave_sum(v * v);
-    if constexpr (HD > 64) {
-      if ((e & 63) == 0) red[e >> 6] = s;
-      __syncthreads();
-      s = red[0] + red[1];
+    for (int k = 0; k < CG; ++k) {
+      const float w = safe_scale(sml[k][0], mn);
+      lo += sml[k][1] * w;
+      ao += sa[k][e] * w;
     }
-    if (e == 0) norms[(size_t)req * Hq + h] = sqrtf(s);
+    v = lo > 0.f ? ao / lo : 0.f;
+    out[frag_row0 >= 0 ? frag_index(frag_row0 + req, h * HD + e, Hq * HD) : ((size_t)req * Hq + h) * HD + e] = f2bf(v);
+  }
+  if (norms) {                                   // L2 norm of the head's output vector (fp32 values)
+    __shared__ float red[HD / 64];
+    const float s = wave_sum(v * v);
+    if (g == 0 && (e & 63) == 0) red[e >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) norms[(size_t)req * Hq + h] = sqrtf(HD > 64 ? red[0] + red[HD / 64 - 1] : red[0]);
   }
 }
 
