@@ -223,11 +223,19 @@ __global__ __launch_bounds__(CG * HD) void attn_decode_combine_kernel(const floa
     float mv[CU], lv[CU], av[CU], mn = m;
 #pragma unroll
     for (int u = 0; u < CU; ++u) {
-      const int s = s0 + u * CG;
-      const float *p = src + (size_t)min(s, ns - 1) * (HD + 2);
-      mv[u] = s < ns ? p[HD] : -INFINITY;
-      lv[u] = s < ns ? p[HD + 1] : 0.f;      // (a sum can be infinite, and weight 0 does not remove it)
-      av[u] = s < ns ? p[e] : 0.f;
+      const float *p = src + (size_t)min(s0 + u * CG, ns - 1) * (HD + 2);
+      mv[u] = p[HD];
+      lv[u] = p[HD + 1];
+      av[u] = p[e];
+    }
+    // slots past the end add nothing (a sum can be infinite, so weight 0 alone does not do it); behind the asm, or every load gets a branch of its own
+#pragma unroll
+    for (int u = 0; u < CU; ++u) {
+      asm volatile("" : "+v"(mv[u]), "+v"(lv[u]), "+v"(av[u]));
+      const bool ok = s0 + u * CG < ns;
+      mv[u] = ok ? mv[u] : -INFINITY;
+      lv[u] = ok ? lv[u] : 0.f;
+      av[u] = ok ? av[u] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < CU; ++u) mn = fmaxf(mn, mv[u]);
