@@ -208,9 +208,10 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const bf16_t *__restri
 // Merges the splits of a (request, head): CG groups of HD threads take every CG-th split each, in one pass with its own soft-max
 // state, and are merged through LDS, in order.  The time is the latency of the loads, so a group has those of CU splits in flight.
 // (One group, first the maximum of all splits and then their sums: 8000 tokens in 32 splits 28 us with the kernel in front, in 63 splits 40;
-// now 8000 tokens 12.2 and 12.8.)
-constexpr int CG = 4, CU = 4;
-template <int HD>
+// now 8000 tokens 12.2 and 12.8.)  Up to CU splits one group has all of them in flight, and idle groups would only fill the chip: 256 requests of 32 heads in
+// one or two splits 7.9 us with four groups, 4.8 with one.
+constexpr int CU = 4;
+template <int HD, int CG>
 __global__ __launch_bounds__(CG * HD) void attn_decode_combine_kernel(const float *__restrict__ partial,
                                                                       const int32_t *__restrict__ ctx_lens, int Hq, int nsplit, int chunk,
                                                                       bf16_t *__restrict__ out, float *__restrict__ norms, int frag_row0) {
@@ -250,30 +251,38 @@ __global__ __launch_bounds__(CG * HD) void attn_decode_combine_kernel(const floa
     }
     m = mn;
   }
-  sa[g][e] = a;
-  if (e == 0) { sml[g][0] = m; sml[g][1] = l; }
-  __syncthreads();
-  // (every thread stays to the end: there is a barrier in the norms)
-  float v = 0.f;
-  if (g == 0) {
-    float mn = sml[0][0], lo = 0.f, ao = 0.f;
-#pragma unroll
-    for (int k = 1; k < CG; ++k) mn = fmaxf(mn, sml[k][0]);
-#pragma unroll
-    for (int k = 0; k < CG; ++k) {
-      const float w = safe_scale(sml[k][0], mn);
-      lo += sml[k][1] * w;
-      ao += sa[k][e] * w;
-    }
-    v = lo > 0.f ? ao / lo : 0.f;
-    out[frag_row0 >= 0 ? frag_index(frag_row0 + req, h * HD + e, Hq * HD) : ((size_t)req * Hq + h) * HD + e] = f2bf(v);
-  }
-  if (norms) {                                   // L2 norm of the head's output vector (fp32 values)
-    __shared__ float red[HD / 64];
-    const float s = wave_sum(v * v);
-    if (g == 0 && (e & 63) == 0) red[e >> 6] = s;
+  if constexpr (CG > 1) {
+    sa[g][e] = a;
+    if (e == 0) { sml[g][0] = m; sml[g][1] = l; }
     __syncthreads();
-    if (threadIdx.x == 0) norms[(size_t)req * Hq + h] = sqrtf(HD > 64 ? red[0] + red[HD / 64 - 1] : red[0]);
+  }
+  // (every thread stays to the end: there is a barrier in the norms)
+  float n2 = 0.f;
+  if (g == 0) {
+    if constexpr (CG > 1) {
+      float mn = sml[0][0];
+#pragma unroll
+      for (int k = 1; k < CG; ++k) mn = fmaxf(mn, sml[k][0]);
+      l = a = 0.f;
+#pragma unroll
+      for (int k = 0; k < CG; ++k) {
+        const float w = safe_scale(sml[k][0], mn);
+        l += sml[k][1] * w;
+        a += sa[k][e] * w;
+      }
+    }
+    const float v = l > 0.f ? a / l : 0.f;
+    out[frag_row0 >= 0 ? frag_index(frag_row0 + req, h * HD + e, Hq * HD) : ((size_t)req * Hq + h) * HD + e] = f2bf(v);
+    if (norms) n2 = wave_sum(v * v);             // L2 norm of the head's output vector (fp32 values)
+  }
+  if (norms) {
+    if constexpr (HD > 64) {
+      __shared__ float red[HD / 64];
+      if (g == 0 && (e & 63) == 0) red[e >> 6] = n2;
+      __syncthreads();
+      n2 = red[0] + red[1];
+    }
+    if (threadIdx.x == 0) norms[(size_t)req * Hq + h] = sqrtf(n2);
   }
 }
 
@@ -360,7 +369,10 @@ hipError_t launch_attn_decode(const bf16_t *q, const void *cache_k, const void *
   if (!ok) return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (hd == 64) hipLaunchKernelGGL((attn_decode_combine_kernel<64>), dim3(n_decode, Hq), dim3(CG * 64), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
-  else hipLaunchKernelGGL((attn_decode_combine_kernel<128>), dim3(n_decode, Hq), dim3(CG * 128), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
+  auto combine = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(n_decode, Hq), dim3(threads), 0, st, partial, ctx_lens, Hq, nsplit, chunk, out, norms, frag_row0);
+  };
+  if (hd == 64) nsplit <= CU ? combine(attn_decode_combine_kernel<64, 1>, 64) : combine(attn_decode_combine_kernel<64, 4>, 256);
+  else nsplit <= CU ? combine(attn_decode_combine_kernel<128, 1>, 128) : combine(attn_decode_combine_kernel<128, 4>, 512);
   return hipGetLastError();
 }
