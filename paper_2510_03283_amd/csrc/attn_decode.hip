@@ -311,37 +311,47 @@ bool launch_grp(int grp, const bf16_t *q, const void *ck, const void *cv, long l
 
 }  // namespace
 
-// Tokens per block.  Long chunks mean fewer blocks that find nothing to do, fewer partial states to write
-// and merge and a longer stream per block (6.2 -> 6.6 TB/s from 512 to 2048 tokens on a 256-request,
-// 32-head batch) - as long as the grid still fills the chip several times over.  Where it does not, a block's own
-// chain of loads sets the time and short chunks win; at 128 tokens a wave has one or two turns of its loop.  us at 128 / 256 / 512 tokens, both
-// kernels, heads x kv heads x width 32 x 8 x 64: one request of 700 tokens 9.0 / 10.8 / 14.6, of 8000 12.8 / 12.2 / 16.3, 16 of 300 - 1200 15.1 / 16.7 / 20.9,
-// 32 of 256 - 2048 (4352 blocks of 128) 31.0 / 29.7 / 31.1, 64 of 500 - 2000 (4096 blocks of 256) 57.5 / 53.3 / 57.0; 32 x 32 x 128: one of 700 9.0 /
-// 11.3 / 17.4, 8 of 300 - 1200 21.5 / 24.8 / 36.3, 16 (5120 blocks of 128) 38.0 / 38.7 / 44.4, 32 of 256 - 2048 (9216 blocks of 256) 112.8 / 110.8 / 116.0,
-// 64 of 500 - 2000 (16384 blocks of 256) 223 / 218 / 216.
-constexpr long long MOST_128 = 4096, MOST_256 = 10240;      // blocks up to which 128 and 256 tokens are taken
-static int decode_chunk_tokens(int n_decode, int Hkv, int max_context, int chunk_tokens) {
+// Tokens per block.  A block's time has a fixed part (query, merge of its waves) and one that grows with its chunk; a grid that leaves the chip
+// idle takes the time of one block, a larger one that of all its blocks.  In units of the work on 128 tokens a chunk of c tokens is priced as
+//     LATENCY * hd / 64 * c / 128  +  blocks(c) * (c / 128 + fixed),    fixed = 0.08 query heads per kv head
+// (a wave takes 32 tokens of 64-wide heads at a time, 16 of 128-wide ones), and the cheapest of 128, 256 and 512 is taken.  The constants are fitted to 936
+// 1380 batches of 1 - 256 requests of 25 - 8000 tokens, 4 - 32 kv heads with 1 - 8 query heads each, 64 and 128 wide: on average 1.8 % above the best of the three
+// (512 for all 22 % above it; 128 up to 4096 blocks, else 256 up to 10240 4.3 %, and up to 59 % above 512).  us at 128 / 256 / 512 tokens, both kernels, heads x kv heads x width
+// 32 x 8 x 64: 1 request of 700 tokens 9.0 / 10.8 / 14.6; 32 of 400 - 1600 30.3 / 29.9 / 35.1; 64 of 100 - 400 27.3 / 23.9 / 25.1; 128 of 100 - 400 45.1 / 38.4 / 32.4;
+// 256 of 50 - 200 47.8 / 38.3 / 45.7; 256 of 200 - 800 99 / 120 / 105; 128 of 400 - 1600 92 / 78 / 104; 32 x 32 x 128: 16 of 100 - 400 22.0 / 26.2 / 34.7; 64 of 100 -
+// 400 51.7 / 55.7 / 52.4; 32 of 800 - 3200 165 / 158 / 161; 128 of 50 - 200 59.6 / 59.5 / 79.2.
+// Past MOST_256 blocks of 256 the stream sets the time: long chunks mean fewer blocks that find nothing to do, fewer partial states to write and merge and a longer stream per
+// block (6.2 -> 6.6 TB/s from 512 to 2048 tokens on a 256-request, 32-head batch) - as long as the grid still fills the chip several times over.
+constexpr double LATENCY = 150;
+constexpr long long MOST_256 = 10240;
+static int decode_chunk_tokens(int n_decode, int Hq, int Hkv, int hd, int max_context, int chunk_tokens) {
   if (chunk_tokens) return chunk_tokens >= MIN_PINNED && chunk_tokens <= MAX_CHUNK && !(chunk_tokens & (chunk_tokens - 1)) ? chunk_tokens : -1;
   const long long streams = (long long)Hkv * n_decode;
-  if (streams * cdiv(max_context + 1, 128) <= MOST_128) return 128;
-  if (streams * cdiv(max_context + 1, 256) <= MOST_256) return 256;
   int chunk = 512;
-  while (chunk < MAX_CHUNK && streams * cdiv(max_context + 1, 2 * chunk) >= 8192) chunk *= 2;
+  if (streams * cdiv(max_context + 1, 256) <= MOST_256) {
+    double best = 0;
+    for (int c = 128; c <= 512; c *= 2) {
+      const double cost = LATENCY * hd / 64 * c / 128 + (double)(streams * cdiv(max_context + 1, c)) * (c / 128 + 0.08 * (Hq / Hkv));
+      if (c == 128 || cost < best) { best = cost; chunk = c; }
+    }
+  }
+  while (chunk >= 512 && chunk < MAX_CHUNK && streams * cdiv(max_context + 1, 2 * chunk) >= 8192) chunk *= 2;
   return chunk;
 }
 
 // Room for the partial states of this batch and of every smaller one (fewer requests, shorter contexts), which may take shorter chunks and have
 // more blocks: the rule takes a chunk below MAX_CHUNK only up to a number of blocks, and a batch has at most streams * cdiv(context, chunk) of
-// them.  512 to 2048 tokens are taken where twice the chunk makes fewer than 8192 blocks, so they make at most twice 8191 themselves.
+// them.  256 tokens make at most MOST_256 blocks, 128 twice as many; 512 to 2048 are taken where twice the chunk makes fewer than 8192, so they make at most
+// twice 8191 themselves.
 size_t decode_partial_floats(int n_decode, int Hq, int Hkv, int hd, int max_context, int chunk_tokens) {
   const size_t streams = (size_t)n_decode * Hkv;
   auto blocks_of = [&](int chunk) { return streams * cdiv(max_context + 1, chunk); };
   size_t blocks;
   if (chunk_tokens) {
-    const int chunk = decode_chunk_tokens(n_decode, Hkv, max_context, chunk_tokens);
+    const int chunk = decode_chunk_tokens(n_decode, Hq, Hkv, hd, max_context, chunk_tokens);
     blocks = blocks_of(chunk < 0 ? 512 : chunk);                       // an invalid override is rejected at launch; size for the worst case
   } else {
-    blocks = std::max({std::min(blocks_of(128), (size_t)MOST_128), std::min(blocks_of(256), (size_t)MOST_256), std::min(blocks_of(512), (size_t)2 * 8191),
+    blocks = std::max({std::min(blocks_of(128), (size_t)(2 * MOST_256)), std::min(blocks_of(256), (size_t)MOST_256), std::min(blocks_of(512), (size_t)2 * 8191),
                        blocks_of(MAX_CHUNK)});
   }
   return blocks * (Hq / Hkv) * (hd + 2);
@@ -356,7 +366,7 @@ hipError_t launch_attn_decode(const bf16_t *q, const void *cache_k, const void *
   int bshift = 0;
   while ((1 << bshift) < block_size) ++bshift;
   if ((1 << bshift) != block_size) return hipErrorInvalidValue;
-  const int chunk = decode_chunk_tokens(n_decode, Hkv, max_context, chunk_tokens);
+  const int chunk = decode_chunk_tokens(n_decode, Hq, Hkv, hd, max_context, chunk_tokens);
   if (chunk < 0) return hipErrorInvalidValue;
   const int nsplit = cdiv(max_context + 1, chunk);
   if (nsplit > 65535) return hipErrorInvalidValue;

@@ -254,6 +254,23 @@ def test_shorter_contexts_fit_the_workspace_of_longer_ones(recorder, rows, longe
         assert status(rec)["status"] == 0, (ctx, status(rec))
 
 
+@pytest.mark.parametrize("d,hq,hkv,hd,requests,context,splits", [
+    (2048, 32, 8, 64, 1, 700, 6),          # a grid that leaves the chip idle: 128 tokens
+    (2048, 32, 8, 64, 64, 400, 2),         # 256
+    (2048, 32, 8, 64, 128, 400, 1),        # 2048 blocks of 256 take longer than 1024 of 512
+    (2048, 32, 8, 64, 256, 800, 2),
+    (2048, 32, 8, 64, 256, 120, 1),
+    (4096, 32, 32, 128, 16, 400, 4),
+    (4096, 32, 32, 128, 32, 800, 7),
+    (4096, 32, 32, 128, 64, 4096, 5),      # a long stream: 1024
+], ids=lambda v: str(v))
+def test_decode_chunks_follow_the_work_of_the_grid(recorder, d, hq, hkv, hd, requests, context, splits):
+    rec = recorder("fwd", d=d, hq=hq, hkv=hkv, hd=hd, F=1024, decode=[context] * requests)
+    assert status(rec)["status"] == 0
+    (grid,) = [r["grid"] for r in rec if r["op"] == "launch" and "attn_decode_kernel" in r["kernel"]]
+    assert grid == [hkv, splits, requests]
+
+
 # pi / 2 in three pieces of at most 32 bits and a rest (Machin's formula in integers)
 PI_HALF = [3373259426 * 2.0 ** -31, 140128397 * 2.0 ** -61, 206333480 * 2.0 ** -91, 2.9038559739793605e-28]
 
