@@ -577,9 +577,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   // code: an access to a row past the last is out of the view's range, which the hardware drops (a load
   // returns zero), a lane whose columns do not exist carries an offset beyond any view, and an output that was
   // not asked for is an empty view.
-  // fp32: the four columns of a lane are one 16-byte access, 64 bytes of 16 rows per instruction.  bf16: the words of two
-  // neighbouring blocks go through v_permlane16_swap, which gives every lane eight neighbouring columns: 16 bytes again.
-  // Column counts that do not divide by that (the NT form only) take narrow accesses at the same places (WIDE = 0).
+  // fp32: lines of 32 columns, eight rows a store (emit).  bf16: the words of two
+  // neighbouring blocks go through v_permlane16_swap, which gives every lane eight neighbouring columns: 16 bytes, 64 of 16 rows a store.
+  // Column counts that do not divide by that (the NT form only) take narrow accesses at the same places (WIDE = 0, emit_narrow).
   // Against 32x32 blocks, whose lanes own columns of single rows: a quarter of the store instructions, no pair swaps.
   // (no lambda below may name p, G or S: captured by reference the kernel arguments are copied to private memory)
   // (the reads of the accumulators are asm, which the compiler's hazard handling does not look into: the wait
@@ -599,10 +599,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   auto view = [](const void *base, long long bytes) W4_INL {
     return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000);
   };
-  // Stores of the forms that move most beside the tile itself - residuals, the four outputs of a fine-tune row's SwiGLU -
-  // carry the non-temporal hint, which keeps them out of the way of the operand panels in L2: two passes over 16384 x 4096 x 4096
-  // with fp32 / bf16 residual 820 / 806 -> 810 / 800 us, SwiGLU of 16384 x 11008 x 4096 4252 -> 4187.  Plain
-  // fp32 and bf16 outputs lose by it (half lines leave L2 before their other half has come): 16384 x 4096 x 1024 137 -> 149 and 119 -> 124 us.
+  // Cache policy of the stores.  Residual forms and the four outputs of a fine-tune row's SwiGLU, which move most beside the tile itself,
+  // carry the non-temporal hint (2), which keeps them out of the way of the operand panels in L2: two passes over 16384 x 4096 x 4096
+  // with fp32 / bf16 residual 820 / 806 -> 810 / 800 us, SwiGLU of 16384 x 11008 x 4096 4252 -> 4187.  So do weight gradients (TN), which nothing reads in this call
+  // and which would push the weights out of the memory cache: 1 pair on the edge layer, 84 rows, 674 -> 636 us a step.  Other fp32 outputs, slices among them, are read by
+  // the next launch and are written through (16): left in L2 they are written back behind the last block, 256 x 16384 x 512 20.5 us, written through 18.1,
+  // non-temporal 18.5 but 5 - 8 us more in the readers of an edge layer of 256 rows.  bf16 outputs lose by the hint: 16384 x 4096 x 1024 119 -> 124 us.
+  constexpr int PLAIN_STORE = LA == 1 ? 2 : 16, RES_STORE = 2;
   auto store32 = [](uint32_t w, __amdgpu_buffer_rsrc_t q, uint32_t voff, uint32_t soff) W4_INL {
     __builtin_amdgcn_raw_buffer_store_b32(w, q, (int)voff, (int)soff, 0);
   };
@@ -860,9 +863,72 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   // fp32 output; RES 0: no residual, 1: + fp32 residual (projections onto an fp32 stream, weight gradients that
   // accumulate), 2: + bf16 residual.  The residuals of 64 rows are requested together before the first is
   // added: with one wave per SIMD nothing else covers the latency of a request.
-  auto emit = [&](auto RES, auto WIDE) W4_INL {
+  // A CU takes a 16-byte access of 64 lanes in 16 cycles where every four neighbouring lanes lie in one piece of 64 bytes, and lane by lane, in 64, where they
+  // do not: the rows of a block, one in each of 16 neighbouring lanes, cost 8 us a tile of 256 KB.  So two neighbouring blocks, 32 columns or a line of 128 bytes, are
+  // turned: the lanes of eight rows exchange their pieces with those of the other eight (a rotation by eight inside sixteen lanes), which
+  // makes two halves of eight whole rows, and a permutation puts the eight pieces of a row into eight neighbouring lanes.  us of 256 x 4096 x 512, 1024 x 4096 x 1024,
+  // 4096 x 4096 x 4096 with 64 bytes of 16 rows a store and so: plain 21.0 / 31.2 / 109 -> 17.7 / 26.4 / 107, fp32 residual 27.3 / 36.1 / 120 -> 20.8 / 30.2 / 114.
+  auto emit = [&](auto RES) W4_INL {
     constexpr int res = decltype(RES)::value, rsz = res == 2 ? 2 : 4;
-    constexpr bool wide = decltype(WIDE)::value != 0;
+    const int prow = lane >> 3, pcol4 = 4 * (lane & 7), from = 4 * (16 * (lane & 3) + 8 * ((lane >> 2) & 1) + prow);
+    uint32_t vc[TN / 2], vr[TN / 2];      // lane offsets by pair of blocks, in C and in the residual
+#pragma unroll
+    for (int jp = 0; jp < TN / 2; ++jp) {
+      const bool ok = col_u + 32 * jp + pcol4 < N;
+      vc[jp] = ok ? (uint32_t)((int)(prow * ldc) + 32 * jp + pcol4) * 4u : OUT;
+      vr[jp] = ok ? (uint32_t)((int)(prow * ldr) + 32 * jp + pcol4) * (uint32_t)rsz : OUT;
+    }
+    const auto qc = view((char *)Cp + ((long long)row_u * ldc + c_col0 + col_u) * 4, rows_v * ldc * 4);
+    const auto qr = view((const char *)Rp + ((long long)row_u * ldr + c_col0 + col_u) * rsz, res ? rows_v * ldr * rsz : 0);
+    const uint32_t c8 = w4_sgpr((uint32_t)(ldc * 32)), r8 = w4_sgpr((uint32_t)(ldr * (8 * rsz)));      // 8 rows
+    uint32_t sc = 0, sr = 0;
+    static_for<0, TM / 4>([&](auto IH) W4_INL {
+      u32x4_t rv[8][TN / 2];      // by eight rows
+      if constexpr (res != 0) {
+        static_for<0, 8>([&](auto R8) W4_INL {
+          static_for<0, TN / 2>([&](auto JP) W4_INL {
+            constexpr int r = decltype(R8)::value, jp = decltype(JP)::value;
+            if constexpr (res == 1) {
+              rv[r][jp] = __builtin_amdgcn_raw_buffer_load_b128(qr, (int)vr[jp], (int)sr, 0);
+            } else {
+              const u32x2_t t = __builtin_amdgcn_raw_buffer_load_b64(qr, (int)vr[jp], (int)sr, 0);
+              rv[r][jp] = u32x4_t{t[0], t[1], 0u, 0u};      // widened when it is added
+            }
+          });
+          sr += r8;
+        });
+        W4_SB;
+      }
+      static_for<0, 4>([&](auto II) W4_INL {
+        constexpr int ii = decltype(II)::value, i = 4 * decltype(IH)::value + ii;
+        static_for<0, TN / 2>([&](auto JP) W4_INL {
+          constexpr int jp = decltype(JP)::value;
+          u32x4_t v[2];      // rows 0 .. 7 and 8 .. 15
+          static_for<0, 4>([&](auto E) W4_INL {
+            constexpr int e = decltype(E)::value;
+            const int x = __float_as_int(w4_acc_rd(acc[i][2 * jp][e])), y = __float_as_int(w4_acc_rd(acc[i][2 * jp + 1][e]));
+            v[0][e] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, __builtin_amdgcn_update_dpp(x, y, 0x128, 0xF, 0xC, false));      // lanes 8 .. 15: y of the lane eight before
+            v[1][e] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, __builtin_amdgcn_update_dpp(y, x, 0x128, 0xF, 0x3, false));      // lanes 0 .. 7: x of the lane eight behind
+          });
+          static_for<0, 2>([&](auto H) W4_INL {
+            constexpr int h = decltype(H)::value;
+            static_for<0, 4>([&](auto E) W4_INL {
+              constexpr int e = decltype(E)::value;
+              const u32x4_t &t = rv[2 * ii + h][jp];
+              if constexpr (res == 1) v[h][e] = __float_as_uint(__uint_as_float(v[h][e]) + __uint_as_float(t[e]));
+              if constexpr (res == 2) v[h][e] = __float_as_uint(__uint_as_float(v[h][e]) + __uint_as_float(e % 2 ? t[e / 2] & 0xffff0000u : t[e / 2] << 16));
+            });
+            __builtin_amdgcn_raw_buffer_store_b128(v[h], qc, (int)vc[jp], (int)(sc + h * c8), res ? RES_STORE : PLAIN_STORE);
+          });
+        });
+        sc += 2 * c8;
+        W4_SB;
+      });
+    });
+  };
+  // The same value by value, for column counts and bf16 residual rows that have no whole pieces (NT form only, but for the latter).
+  auto emit_narrow = [&](auto RES) W4_INL {
+    constexpr int res = decltype(RES)::value, rsz = res == 2 ? 2 : 4;
     uint32_t vc[TN], vr[TN];      // lane offsets by column block, in C and in the residual
     int left[TN];                 // how many columns exist from the lane's first one on
 #pragma unroll
@@ -880,20 +946,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       if constexpr (res != 0) {
         static_for<0, 4>([&](auto II) W4_INL {
           static_for<0, TN>([&](auto J) W4_INL {
-            constexpr int ii = decltype(II)::value, j = decltype(J)::value;
-            if constexpr (wide && res == 1) {
-              rv[ii][j] = __builtin_amdgcn_raw_buffer_load_b128(qr, (int)vr[j], (int)sr, 0);
-            } else if constexpr (wide) {
-              const u32x2_t t = __builtin_amdgcn_raw_buffer_load_b64(qr, (int)vr[j], (int)sr, 0);
-              rv[ii][j] = u32x4_t{t[0], t[1], 0u, 0u};      // widened when it is added
-            } else {
-              static_for<0, 4>([&](auto E) W4_INL {
-                constexpr int e = decltype(E)::value;
-                const int o = left[j] > e ? (int)(vr[j] + e * rsz) : (int)OUT;
-                if constexpr (res == 1) rv[ii][j][e] = __builtin_amdgcn_raw_buffer_load_b32(qr, o, (int)sr, 0);
-                else rv[ii][j][e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(qr, o, (int)sr, 0) << 16;
-              });
-            }
+            static_for<0, 4>([&](auto E) W4_INL {
+              constexpr int ii = decltype(II)::value, j = decltype(J)::value, e = decltype(E)::value;
+              const int o = left[j] > e ? (int)(vr[j] + e * rsz) : (int)OUT;
+              if constexpr (res == 1) rv[ii][j][e] = __builtin_amdgcn_raw_buffer_load_b32(qr, o, (int)sr, 0);
+              else rv[ii][j][e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(qr, o, (int)sr, 0) << 16;
+            });
           });
           sr += r16;
         });
@@ -902,23 +960,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       static_for<0, 4>([&](auto II) W4_INL {
         constexpr int ii = decltype(II)::value, i = 4 * decltype(IH)::value + ii;
         static_for<0, TN>([&](auto J) W4_INL {
-          constexpr int j = decltype(J)::value;
-          u32x4_t v;
           static_for<0, 4>([&](auto E) W4_INL {
-            constexpr int e = decltype(E)::value;
+            constexpr int j = decltype(J)::value, e = decltype(E)::value;
             float f = w4_acc_rd(acc[i][j][e]);
-            if constexpr (res == 2 && wide) f += __uint_as_float(e % 2 ? rv[ii][j][e / 2] & 0xffff0000u : rv[ii][j][e / 2] << 16);
-            else if constexpr (res != 0) f += __uint_as_float(rv[ii][j][e]);
-            v[e] = __float_as_uint(f);
+            if constexpr (res != 0) f += __uint_as_float(rv[ii][j][e]);
+            store32(__float_as_uint(f), qc, left[j] > e ? vc[j] + e * 4u : OUT, sc);
           });
-          if constexpr (wide) {
-            store128(RES, v, qc, vc[j], sc);
-          } else {
-            static_for<0, 4>([&](auto E) W4_INL {
-              constexpr int e = decltype(E)::value;
-              store32(v[e], qc, left[j] > e ? vc[j] + e * 4u : OUT, sc);
-            });
-          }
         });
         sc += c16;
         W4_SB;
@@ -929,16 +976,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   // no more than the 4 bytes every float has)
   const bool wide = LB == 1 || N % 4 == 0, wide_r = wide && rk == 2 && ldr % 2 == 0 && (((uintptr_t)Rp + 2 * c_col0) & 3) == 0;
   if (rk == 0) {
-    if constexpr (LB == 1) emit(W4_IC(0), W4_IC(1));
-    else if (wide) emit(W4_IC(0), W4_IC(1));
-    else emit(W4_IC(0), W4_IC(0));
+    if constexpr (LB == 1) emit(W4_IC(0));
+    else if (wide) emit(W4_IC(0));
+    else emit_narrow(W4_IC(0));
   } else if (rk == 1) {
-    if constexpr (LB == 1) emit(W4_IC(1), W4_IC(1));
-    else if (wide) emit(W4_IC(1), W4_IC(1));
-    else emit(W4_IC(1), W4_IC(0));
+    if constexpr (LB == 1) emit(W4_IC(1));
+    else if (wide) emit(W4_IC(1));
+    else emit_narrow(W4_IC(1));
   } else {
-    if (wide_r) emit(W4_IC(2), W4_IC(1));
-    else emit(W4_IC(2), W4_IC(0));
+    if (wide_r) emit(W4_IC(2));
+    else emit_narrow(W4_IC(2));
   }
 }
 

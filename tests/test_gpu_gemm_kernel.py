@@ -259,3 +259,25 @@ def test_two_terms_over_short_reductions(torch_mod, handle, k_tiles):
     binding.mace_gemm_bf16(handle, 0, 0, M, N, K, a, b, c, a_lo=a_lo, ldc=N + 8, kernel=1)
     torch.cuda.synchronize()
     check_out(c, ref, M, N, 1e-5, f"two terms, {k_tiles} k tiles")
+
+
+@pytest.mark.parametrize("la,lb,N", [(0, 0, 4), (0, 0, 36), (0, 0, 148), (0, 0, 284), (0, 0, 508), (0, 1, 8), (0, 1, 40), (0, 1, 280), (1, 1, 24), (1, 1, 296)])
+@pytest.mark.parametrize("resid", [None, "f32", "bf16"])
+def test_edges_of_the_turned_column_pairs(torch_mod, handle, la, lb, N, resid):
+    """fp32 output leaves in lines of 32 columns, eight rows at a time: columns that end inside a line, in either half of it, and rows that end in either
+    half of a block, with and without a residual; what lies beside them stays untouched."""
+    torch = torch_mod
+    from paper_2510_03283_amd import binding
+    K = 128
+    for M in (8, 16, 24, 136, 152, 264) if la else (1, 7, 8, 9, 15, 16, 23, 129, 140, 265):
+        rng = np.random.default_rng(1000 * N + M)
+        a, b, A, B = operands(torch, rng, la, lb, M, N, K)
+        ref, r = A @ B.T, None
+        if resid:
+            r = torch.from_numpy(rng.uniform(-20, 20, (M, N + 4)).astype(np.float32)).cuda()
+            r = r.to(torch.bfloat16) if resid == "bf16" else r
+            ref = ref + f64(r)[:, :N]
+        c = out_buffer(torch, M + 5, N + 8, torch.float32)
+        binding.mace_gemm_bf16(handle, la, lb, M, N, K, a, b, c, resid=r, ldc=N + 8, ldr=N + 4, kernel=1)
+        torch.cuda.synchronize()
+        check_out(c, ref, M, N, 1e-5, f"{M}x{N}x{K} {resid}")
