@@ -738,6 +738,7 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
     for (int g = 0; g < plain.n_mg; ++g) {
       const int nk = cdiv(plain.K, BK), it = w4_tile_steps(LA, LB, nk, plain.mg[g].npass);
       ks[g] = std::max(1, (c * plain.mg[g].npass + most / 2) / most);
+      if (it < nk * plain.mg[g].npass) ks[g] = cdiv(it, cdiv(it, ks[g]));      // steps of two passes: 88 make no 12 slices, but 11 (a training step of 84 rows, edge layer: 640 us with 8, 635 with 11)
       ok = ok && nk * plain.mg[g].npass / ks[g] >= 4 && cdiv(it, ks[g]) * (ks[g] - 1) < it;
       floats += (double)ks[g] * plain.mg[g].M * plain.ldc;
     }

@@ -147,6 +147,16 @@ def test_slices_of_the_forward_do_not_meet(recorder, lora, single_stream):
     assert n > 0
 
 
+@pytest.mark.parametrize("rows", [80, 200, 400])
+def test_two_pass_products_are_cut_as_fine_as_their_steps_allow(recorder, rows):
+    """Both passes of a k tile are one step, so a reduction over 5632 has 88 of them: slices of eight are eleven, where twelve leave one empty."""
+    rec = recorder("fwd", d=2048, hq=32, hkv=8, hd=64, F=5632, decode=[200] * 4, ft=[rows // 2] * 2)
+    assert status(rec)["status"] == 0
+    assert check_slices(rec)
+    (down,) = [r for r in plan(rec) if r["k"] == 5632]
+    assert down["k_splits"] == 11, down
+
+
 MACE_BAD_SHAPE = -2
 
 
