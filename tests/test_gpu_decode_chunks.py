@@ -1,4 +1,4 @@
-"""Decode attention of small batches: the launcher takes 128 or 256 tokens a block where the grid is small, and the merge of the
+"""Decode attention with short chunks: the launcher takes 128, 256 or 512 tokens a block by the work of the grid, and the merge of the
 partial states walks them in groups.  Contexts on and around the chunk edges and around the groups' turns (4 groups of 4 splits), against the
 oracle, and against the pinned 512-token chunks, whose partial states are merged from fewer splits."""
 import pytest
@@ -21,13 +21,44 @@ def test_short_chunks(torch_mod, hq, hkv, hd, longest):
 
 @pytest.mark.parametrize("hq,hkv,hd", [(32, 8, 64), (16, 16, 128)])
 def test_batches_on_both_sides_of_the_rule(torch_mod, hq, hkv, hd):
-    """Up to 4096 blocks of 128 tokens and 10240 of 256: 11 requests of up to 2000 tokens are 1408 and 2816 blocks of 128, 33 requests 4224 and
-    8448, which makes their chunks 256."""
+    """11 requests of up to 2000 tokens take chunks of 256 (8 kv heads) and 128 (16), 33 requests of 512 and 256."""
     dims = synth.ModelDims(n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, **SMALL)
     for n in (11, 33):
         ctx = [(i * 197) % 2000 for i in range(n - 1)] + [2000]
         wl = custom_workload("rule", dims, prefill=[], decode=ctx, n_pairs=0, prompt=3, resp=(2, 9))
         check_iteration(torch_mod, wl, f"{n} requests Hq{hq} Hkv{hkv} hd{hd}")
+
+
+@pytest.mark.parametrize("hq,hkv,hd,ctx", [
+    (8, 2, 64, EDGES + [500, 2046, 4400]),      # 128 against 512
+    (4, 4, 128, EDGES + [2048, 4400]),
+    (8, 1, 64, [1300] * 100),                   # 256
+    (16, 16, 64, [257] * 320),                  # 10240 blocks of 256: the last batch whose chunk is priced (128), and the first of the others (512)
+    (16, 16, 64, [257] * 321),
+], ids=["edges64", "edges128", "256", "priced", "stream"])
+def test_against_pinned_chunks(torch_mod, hq, hkv, hd, ctx):
+    """Norms of the heads' outputs: a lane adds at most 4400 / 8 products, then the states of lanes, waves and splits are merged in about 20 steps, so either
+    evaluation is within 600 * 2^-24 = 3.5e-5 of the sum.  y: the merged outputs round to bf16 either way, which the oracle's bar for y covers."""
+    import numpy as np
+    from paper_2510_03283_amd import binding
+    from paper_2510_03283_amd.harness import DeviceIteration
+    dims = synth.ModelDims(n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, **SMALL)
+    synth.CONFIGS["pinned"] = synth.ConfigSpec("pinned", 77, dims, [], None, list(ctx), None, 0, 3, None, (2, 9), ref_mode="len", block_size=16)
+    try:
+        wl = synth.make_workload("pinned", with_cache=False)
+    finally:
+        del synth.CONFIGS["pinned"]
+    got = []
+    for options in (None, {binding.MACE_OPT_DECODE_CHUNK: 512}):
+        it = DeviceIteration(wl, device_cache_seed=5, options=options)
+        it.forward()
+        torch_mod.cuda.synchronize()
+        got.append((it.y.cpu().numpy(), it.head_norms.cpu().numpy()))
+        it.close()
+    (y, n), (y512, n512) = got
+    assert np.isfinite(y).all() and n512.min() > 0
+    assert np.abs(n / n512 - 1).max() <= 7e-5
+    assert np.abs(y - y512).max() <= 1e-2 * np.abs(y512).max()
 
 
 @pytest.mark.parametrize("hd", [64, 128])
