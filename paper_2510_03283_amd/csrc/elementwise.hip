@@ -54,8 +54,8 @@ __device__ __forceinline__ void row_ld(const void *p, int bf16, size_t at, int d
 
 // One block per row; NV float4 chunks per thread stay in registers between the reduction and the output.  With few rows
 // the time is the chain of load latencies, so all chunks of an operand are asked for together, and the gain before the row.
-// (Chunk by chunk, each asked for when the one before it had arrived, and the gain behind the reduction: a decode pass of the 7B-class layer,
-// 64 rows of 4096, 626.5 us, now 623.3; of the edge layer, 32 rows of 2048, 113.0 and 111.3; its prefill of 2329 rows 364 and 358.)
+// (Chunk by chunk, each asked for when the one before it had arrived, and the gain behind the reduction: a decode pass of the
+// edge layer, 32 rows of 2048, 113.0 us, now 111.3; its prefill of 2329 rows 364 and 358.)
 template <int NV, bool GBF>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const NormRows g0, const NormRows g1, const void *gain, int d, float eps) {
   __shared__ float red[4];

@@ -520,14 +520,15 @@ hipError_t launch_w4(GemmParams &p, hipStream_t stream) {
 
 bool aligned16(const void *q) { return ((uintptr_t)q & 15) == 0; }
 
-// Tile choice.  256x256 tiles (four waves with 128x128 wave tiles, one block per CU) do 0.5 LDS fragment
-// reads per MFMA and half the L2 traffic of 128x128 tiles (4 waves, two blocks per CU), but quantise worse on
+// Tile choice.  256x256 tiles (four waves with 128x128 wave tiles, one block per CU) do half the LDS
+// reads and half the L2 traffic of 128x128 tiles (4 waves, two blocks per CU), but quantise worse on
 // small problems; 192x256 (8 waves) sits between.  Each candidate is priced as
 //   length of its schedule over the (CU x resident block) slots  x  tile area  /  relative efficiency,
 // a tile of a row group with p passes taking p time units on its slot, and the cheapest is launched.  The
 // efficiencies (0.69 for 192x256, 0.62 for 128x128, relative to the four-wave kernel) are fitted to whole steps
-// of the benchmark configurations: step time is flat for factors between 0.68 and 0.8 of the kernels' long-run
-// ratios (0.92, 0.83) and 1 - 6 % worse on either side.
+// of the benchmark configurations: step time was flat for factors between 0.68 and 0.8 of the kernels' long-run
+// ratios (0.92, 0.83) and 1 - 6 % worse on either side.  (Fitted to the 32x32x16 loop of the four-wave kernel, which took 6 - 8 % longer
+// on long reductions; kept, see product_us.)
 template <int BM, int BN>
 double tile_cost(const GemmParams &p, int slots, double slot_share, double eff) {
   int nt = 0;
@@ -604,8 +605,10 @@ double makespan(int slots, int n_mg, const long long *n, const double *d) {
 
 // Estimated time of a product, microseconds.  A k tile takes a block of the four-wave kernel 1.07 us while most CUs are
 // idle and 1.37 us when all are busy, a block of the 192x256 tile 1.45 us, of the 128x128 tile 0.68 us alone on its CU and
-// 1.15 us beside a second one; starting and storing a tile adds 6 - 8 us (measured over 15 shapes from 128 x 4096 x
-// 4096 to 3108 x 4096 x 11008, 2329 x 2048 x 2048 .. 5632; within 15 %).  tile as in choose_tile.
+// 1.15 us beside a second one; starting and storing a tile adds 6 - 8 us.  Measured over 15 shapes from 128 x 4096 x
+// 4096 to 3108 x 4096 x 11008, 2329 x 2048 x 2048 .. 5632, within 15 %, with the 32x32x16 loop of the four-wave kernel.  The present
+// one takes 1.00 us a k tile at 12 - 64 blocks and 1.32 with all CUs busy, and 9.6 us a launch besides (256 x 3072 .. 16384, K = 512 and 1024).  Prices refitted to it changed 13 of 88
+// choices, by at most 4 us and mostly for the worse, so the constants stay.  tile as in choose_tile.
 double product_us(const GemmParams &p, int tile, const int *ks) {
   const int bm = tile == 1 ? 256 : (tile == 2 ? 192 : 128), bn = tile == 0 ? 128 : 256;
   long long nt = 0, n[3] = {0, 0, 0}, blocks = 0;

@@ -3,8 +3,8 @@
 //
 // One wave per SIMD owns all 512 registers of a lane: 256 accumulator registers (AGPRs) and 256
 // VGPRs, of which 128 are two register sets that stage operand tiles on their way global -> VGPR
-// -> LDS.  Compared with the 8-wave kernel (wave tile 128x64) a k step needs 0.5 instead of 0.75
-// fragment reads per MFMA, the tiles reach LDS through 16-byte ds_writes (a quarter of the LDS time of
+// -> LDS.  Compared with the 8-wave kernel (wave tile 128x64) the fragments of a k tile are 128 KB
+// of LDS reads instead of 192 (a wave reads 32 for its 128 MFMAs), the tiles reach LDS through 16-byte ds_writes (a quarter of the LDS time of
 // a direct global->LDS load) and every global load has two tile times to land.  Nothing covers a
 // stall of the only wave of a SIMD, so the loop is written as an explicit schedule: one fragment
 // read, or one half of a "move" (wait for a staged register and ds_write it; request the same register again for
