@@ -124,6 +124,17 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const bf16_t *__restri
         vr[u][0] = a.x; vr[u][1] = a.y; vr[u][2] = a.z; vr[u][3] = a.w; vr[u][4] = b2.x; vr[u][5] = b2.y; vr[u][6] = b2.z; vr[u][7] = b2.w;
       }
     }
+    // Ignored tokens have loaded the first token of the pool, which may hold anything, and weight 0 does not remove an infinity or a NaN.  Only the
+    // last turn of a wave has any, or one with a bad table entry.
+    bool whole = true;
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) whole = whole && ok[u];
+    if (!__all(whole)) {
+#pragma unroll
+      for (int u = 0; u < UNR; ++u)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) vr[u][w] = ok[u] ? vr[u][w] : 0u;
+    }
     float vf[UNR][8];
 #pragma unroll
     for (int u = 0; u < UNR; ++u)

@@ -80,3 +80,34 @@ def test_an_infinite_value_stays_in_its_head(torch_mod, hd):
     it.close()
     assert np.isfinite(norms[:, 0]).all(), norms
     assert [bool(np.isinf(n)) for n in norms[:, 1]] == [p is not None for _, p in at] and not np.isnan(norms).any(), norms
+
+
+@pytest.mark.parametrize("hq,hkv,hd,bf16,block", [(8, 2, 64, True, 16), (4, 4, 128, True, 16), (4, 4, 128, True, 2), (4, 2, 64, False, 16)])
+def test_unused_blocks_of_the_pool_may_hold_anything(torch_mod, hq, hkv, hd, bf16, block):
+    """A pool is not cleared before its blocks are handed out: with NaN in every block that no request owns, and behind the last token of those that are
+    owned, the pool's first block among the unused ones, y and the head norms are what they are with zeros there."""
+    import numpy as np
+    from paper_2510_03283_amd.harness import DeviceIteration
+    dims = synth.ModelDims(n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, io_bf16=bf16, **SMALL)
+    for seed in range(77, 177):
+        wl = custom_workload("pool", dims, prefill=[], decode=EDGES + [700, 1111], n_pairs=0, prompt=3, resp=(2, 9), block_size=block, seed=seed)
+        b = wl.batch
+        used = np.zeros((b.num_blocks, block), bool)
+        for j, n in enumerate(b.decode_ctx):
+            for t in range(int(n) + 1):
+                used[b.decode_block_tables[j][t // block], t % block] = True
+        if not used[0].any():
+            break
+    assert not used[0].any()
+    free = torch_mod.from_numpy(~used).cuda()
+    got = []
+    for fill in (0.0, float("nan")):
+        it = DeviceIteration(wl)
+        for c in (it.cache_k, it.cache_v):
+            c.masked_fill_(free[:, None, :, None], fill)
+        it.forward()
+        torch_mod.cuda.synchronize()
+        got.append((it.y.cpu().numpy(), it.head_norms.cpu().numpy()))
+        it.close()
+    for a, z in zip(got[1], got[0]):
+        assert np.isfinite(z).all() and np.array_equal(a, z)
