@@ -239,7 +239,7 @@ FwdWs plan_fwd(const Dims &D, size_t Ti, size_t Tf, int n_decode, int max_ctx, i
   F.b_i = w.take<bf16_t>(Tr * D.d);
   F.hm_i = w.take<bf16_t>(Tr * D.F);
   F.dec_partial = w.take<float>(decode_partial_floats(n_decode, D.Hq, D.Hkv, D.hd, max_ctx, decode_chunk));
-  F.ss = w.take<float>(Ti <= SKINNY_MAX_ROWS ? Ti * skinny_parts(D.d) : 0);
+  F.ss = w.take<float>(std::min(Ti, (size_t)SKINNY_MAX_ROWS) * skinny_parts(D.d));
   F.qkv_f = w.take<float>(Tf * D.nqkv);
   F.a_lo = w.take<bf16_t>(Tf * D.d);
   F.q_lo = w.take<bf16_t>(Tf * D.qd);
@@ -752,9 +752,11 @@ size_t mace_workspace_bytes(mace_handle_t h, int32_t n_tokens, int32_t n_ft_toke
   return align_up(m, 256) + 256;
 }
 
+// (More than 96 rows with a long down projection stay on the large kernel: every block of that product reads all of its activations.  128 rows, d_ff 11008: 221 us
+// here, 218 there; d_ff 5632: 97 and 130.)
 static bool skinny_fits(const Dims &D, long long rows) {
   const long long lim = 1ll << 31;
-  return D.bf && rows <= SKINNY_MAX_ROWS && (long long)D.nqkv * D.d < lim && (long long)D.F * D.d < lim && (long long)D.d * D.qd < lim;
+  return D.bf && rows <= (D.F <= 8192 ? SKINNY_MAX_ROWS : 96) && (long long)D.nqkv * D.d < lim && (long long)D.F * D.d < lim && (long long)D.d * D.qd < lim;
 }
 static int run_skinny(mace_ctx *h, const SkinnyParams &p, int asrc, int epi, double flops, hipStream_t st, const char *where) {
   prof_mark(h, st, T_GEMM_NT, flops);

@@ -90,16 +90,17 @@ hipError_t launch_sum_parts(const SumRange *ranges, int n_ranges, bool out_bf16,
 // ---- gemm_skinny.hip --------------------------------------------------------------------------
 // C[m, n] = sum_k A[m, k] W[n, k] for at most SKINNY_MAX_ROWS rows, W bf16 [N, K] read once; see the file for the
 // forms.  K a multiple of 64, N of 16; weights below 4 GB.
-// The forms end at four 16-row tiles; that is the line, not a break-even, for the large kernel with its row steps is still the
-// slower side there.  Forward of a decode batch with short contexts at 48 / 64 rows here and 65 / 128 rows there, us: 2048 wide with d_ff
-// 5632 48 / 54 against 126 / 129, 4096 wide with d_ff 11008 139 / 151 against 226 / 226; logits 28 / 31 against 38 / 39, 50 / 54 against 74 / 77.
+// The forms end at eight 16-row tiles, whose accumulators and activations fill a wave's registers.  Forward of a decode batch with short contexts here and
+// on the large kernel with its row steps, us: 2048 wide with d_ff 5632, 65 / 96 / 128 rows 74 / 81 / 97 against 127 / 127 / 130; 4096 wide with d_ff 11008 163 / 193 / 221
+// against 201 / 209 / 218; logits of 32000 columns, 65 / 128 rows 41 / 52 against 54 / 54, 67 / 85 against 88 / 89.
 // RMSNorm in the prologue of QKV (every block reads and converts the rows itself; a launch less) exists for one row tile.
-constexpr int SKINNY_MAX_ROWS = 64, SKINNY_NORM_ROWS = 16;
+constexpr int SKINNY_MAX_ROWS = 128, SKINNY_NORM_ROWS = 16;
 // A: bf16 in fragment order (frag_index); or RMSNorm of row-major bf16 rows (gain bf16, eps), at most SKINNY_NORM_ROWS
 enum { SK_A_FRAG, SK_A_NORM_BF16 };
 enum { SK_E_F32, SK_E_SWIGLU, SK_E_QKV };
 struct SkinnyParams {
   const void *a;            // activations
+  int stream;               // (filled by launch_skinny) weights are read past the last-level cache
   const bf16_t *gain;
   float eps;
   int M, N, K;
