@@ -752,11 +752,11 @@ size_t mace_workspace_bytes(mace_handle_t h, int32_t n_tokens, int32_t n_ft_toke
   return align_up(m, 256) + 256;
 }
 
-// (More than 96 rows with a long down projection stay on the large kernel: every block of that product reads all of its activations.  128 rows, d_ff 11008: 221 us
-// here, 218 there; d_ff 5632: 97 and 130.)
-static bool skinny_fits(const Dims &D, long long rows) {
+// More than 64 rows: decode batches only (a prefill request of that many rows then gives the same bits alone as beside decode or fine-tune rows), and with a long down
+// projection, every block of which reads all of its activations, up to 96.  128 rows, d_ff 11008: 221 us here, 218 on the large kernel; d_ff 5632: 97 and 130.
+static bool skinny_fits(const Dims &D, long long rows, bool prefill) {
   const long long lim = 1ll << 31;
-  return D.bf && rows <= (D.F <= 8192 ? SKINNY_MAX_ROWS : 96) && (long long)D.nqkv * D.d < lim && (long long)D.F * D.d < lim && (long long)D.d * D.qd < lim;
+  return D.bf && rows <= (prefill ? 64 : (D.F <= 8192 ? SKINNY_MAX_ROWS : 96)) && (long long)D.nqkv * D.d < lim && (long long)D.F * D.d < lim && (long long)D.d * D.qd < lim;
 }
 static int run_skinny(mace_ctx *h, const SkinnyParams &p, int asrc, int epi, double flops, hipStream_t st, const char *where) {
   prof_mark(h, st, T_GEMM_NT, flops);
@@ -1070,7 +1070,7 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     prof_mark(h, st, T_MISC);
     TRY(prepare_lora(D, lora, L, 1.0f, st));
   }
-  if (!lora && I.Tf == 0 && skinny_fits(D, I.Ti)) return layer_fwd_skinny(h, D, I, w, batch, cache, x, y, F, st);
+  if (!lora && I.Tf == 0 && skinny_fits(D, I.Ti, I.Tp > 0)) return layer_fwd_skinny(h, D, I, w, batch, cache, x, y, F, st);
   Saved S = plan_saved(D, I.Tf, svb);
   const int np_ft = D.bf ? 2 : 3;
   const size_t es = D.bf ? 2 : 4;

@@ -18,8 +18,7 @@ SHAPES = {(2752, 10304): (344, 644), (5504, 20800): (688, 1300), (704, 32064): (
 def test_even_blocks(torch_mod, F, V, rows):
     assert SHAPES[F, V] == (F // 8, V // 16)
     dims = synth.ModelDims(1024, 32, 8, 64, F, V, io_bf16=True)
-    n_dec = 5 if rows < 16 else 7
-    wl = custom_workload("even", dims, prefill=() if rows == n_dec else (rows - n_dec,), decode=(0, 15, 300, 16, 33, 128, 1)[:n_dec],
-                         n_pairs=0, prompt=3, resp=(2, 9), seed=700 + rows)
+    ctx = (0, 15, 300, 16, 33, 128, 1)
+    wl = custom_workload("even", dims, prefill=(), decode=[ctx[i % 7] + i // 7 for i in range(rows)], n_pairs=0, prompt=3, resp=(2, 9), seed=700 + rows)
     check_iteration(torch_mod, wl, f"rows {rows} F{F} V{V}")
     _check_logits(torch_mod, wl, f"rows {rows} F{F} V{V}")
