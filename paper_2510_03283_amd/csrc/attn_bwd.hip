@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16_t *__res
   bf16_t *lds = (bf16_t *)smem_raw;         // [2][STAGE]
   // blocks are dealt to the XCDs round-robin: block x takes head (x % Hkv) * group + x / Hkv, so the query heads
   // of one kv head (and all their row tiles) run on one XCD and its K and V stay in that XCD's L2
-  const int kvh = blockIdx.x % Hkv, h = kvh * (Hq / Hkv) + blockIdx.x / Hkv, s = blockIdx.y;
+  const int kvh = blockIdx.x % Hkv, h = kvh * (Hq / Hkv) + blockIdx.x / Hkv, s = turned_sequence();
   const int r0 = seg[s] - row_base, L = seg[s + 1] - seg[s];
   const int q0 = (gridDim.z - 1 - blockIdx.z) * 128;
   if (q0 >= L) return;
@@ -183,8 +183,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const bf16_t *__res
 }
 
 // ------------------------------------------------------------------ dK, dV
-template <int HD>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
+// QS teams of four waves share a block's 128 keys and take every QS-th query tile each; their sums are added in LDS at the end.
+template <int HD, int QS>
+__global__ __launch_bounds__(256 * QS, QS == 1 ? 2 : 1) void attn_bwd_dkdv_kernel(const bf16_t *__restrict__ q, const bf16_t *__restrict__ k,
                                                             const bf16_t *__restrict__ v, const bf16_t *__restrict__ d_o,
                                                             const float *__restrict__ lse, const float *__restrict__ dvec,
                                                             const int32_t *__restrict__ seg, int row_base, int Hq,
@@ -194,24 +195,25 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const bf16_t *__r
   using T = Tile<TB, HD, 256>;
   constexpr int STAGE = 2 * T::ELEMS + 4 * TB;    // Q tile, dO tile, lse[TB] and D[TB] as fp32 (2 bf16 slots each)
   extern __shared__ __align__(1024) unsigned char smem_raw[];
-  bf16_t *lds = (bf16_t *)smem_raw;               // [2][STAGE]
-  const int kvh = blockIdx.x, s = blockIdx.y, grp = Hq / Hkv;
+  const int team = QS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  bf16_t *lds = (bf16_t *)smem_raw + team * 2 * STAGE;      // [QS][2][STAGE]
+  const int kvh = blockIdx.x, s = turned_sequence(), grp = Hq / Hkv;
   const int r0 = seg[s] - row_base, L = seg[s + 1] - seg[s];
   const int k0 = blockIdx.z * 128;
   if (k0 >= L) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, j = lane & 31;
+  const int tid = QS == 1 ? threadIdx.x : threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, j = lane & 31;
   const int kw0 = k0 + wave * 32, ki = kw0 + j;      // this lane's key
   const size_t qld = (size_t)Hq * HD, kld = (size_t)Hkv * HD;
   const int xlo = excl_lo ? excl_lo[s] : L, xhi = excl_lo ? excl_hi[s] : L;   // queries >= xhi skip keys xlo .. xhi-1
   const int nqt = (L - k0 + TB - 1) / TB;            // query tiles per head (k0 is a multiple of TB)
   const int niter = grp * nqt;
-  const uint32_t lane_off = T::lane_offset(qld);
+  const uint32_t lane_off = T::lane_offset(qld, tid);
   auto issue_tile = [&](int it) {
     const int gi = it / nqt, qb = k0 + (it % nqt) * TB;
     const int h = kvh * grp + gi;
-    bf16_t *S = lds + (it & 1) * STAGE;
-    T::issue(q + (size_t)r0 * qld + (size_t)h * HD, qld, qb, L, lane_off, S);
-    T::issue(d_o + (size_t)r0 * qld + (size_t)h * HD, qld, qb, L, lane_off, S + T::ELEMS);
+    bf16_t *S = lds + (it / QS & 1) * STAGE;
+    T::issue(q + (size_t)r0 * qld + (size_t)h * HD, qld, qb, L, lane_off, S, tid);
+    T::issue(d_o + (size_t)r0 * qld + (size_t)h * HD, qld, qb, L, lane_off, S + T::ELEMS, tid);
     if (wave < 2) {                                  // one 4-byte element per lane: lane's value lands at base + 4*lane
       const int qq = qb + lane;
       const float *src = wave ? dvec : lse;
@@ -219,7 +221,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const bf16_t *__r
       __builtin_amdgcn_global_load_lds((gbl_void_t *)p, (lds_void_t *)(S + 2 * T::ELEMS + wave * 2 * TB), 4, 0, 0);
     }
   };
-  issue_tile(0);
+  if (team < niter) issue_tile(team);
 
   bf16x8_t kf[NKK], vf[NKK];
 #pragma unroll
@@ -243,14 +245,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const bf16_t *__r
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dka[t][r] = 0.f; dva[t][r] = 0.f; }
 
-  for (int it = 0; it < niter; ++it) {
+  for (int it = team; it - team < niter; it += QS) {      // (every team takes as many turns)
     wait_vmcnt<0>();
     __syncthreads();                                 // tile it has landed; the other stage is free
-    if (it + 1 < niter) issue_tile(it + 1);
+    if (QS > 1 && it >= niter) continue;
+    if (it + QS < niter) issue_tile(it + QS);
     const int qb = k0 + (it % nqt) * TB;
     if (qb + TB - 1 < kw0) continue;                 // every query of the tile precedes this wave's keys
     if (kw0 >= xlo && kw0 + 32 <= xhi && qb >= xhi) continue;   // ... or none of them may see these keys
-    const bf16_t *const stage = lds + (it & 1) * STAGE;
+    const bf16_t *const stage = lds + (it / QS & 1) * STAGE;
     const uint32_t Qs = T::lds_addr(stage), Os = Qs + T::ELEMS * 2;
     const float *lse_s = (const float *)(stage + 2 * T::ELEMS), *d_s = lse_s + TB;
     static_for<0, 2>([&](auto ST) __attribute__((always_inline)) {
@@ -328,6 +331,30 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const bf16_t *__r
       }
     });
   }
+  if constexpr (QS > 1) {
+    static_assert(QS == 2, "one or two teams");
+    float *const sum = (float *)smem_raw;            // [2 NOT * 16][256], in the place of the stages
+    static_assert(2 * NOT * 16 * 256 * 4 <= QS * 2 * STAGE * 2, "the sums of a team fit the stages");
+    __syncthreads();
+    if (team == 1) {
+#pragma unroll
+      for (int t = 0; t < NOT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sum[((2 * t) * 16 + r) * 256 + tid] = dka[t][r];
+          sum[((2 * t + 1) * 16 + r) * 256 + tid] = dva[t][r];
+        }
+    }
+    __syncthreads();
+    if (team == 1) return;
+#pragma unroll
+    for (int t = 0; t < NOT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        dka[t][r] += sum[((2 * t) * 16 + r) * 256 + tid];
+        dva[t][r] += sum[((2 * t + 1) * 16 + r) * 256 + tid];
+      }
+  }
   if (ki < L) {
     bf16_t *row = dqkv + (size_t)(r0 + ki) * (qld + 2 * kld) + qld + (size_t)kvh * HD;     // dk of this kv head; dv sits kld further
     store_grad_row<HD>(dka, cs + (size_t)(r0 + ki) * (HD / 2), g, row);
@@ -346,7 +373,9 @@ hipError_t launch_t(const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf1
   if (!attr_done.test()) {
     hipError_t e = hipFuncSetAttribute((const void *)attn_bwd_dq_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_q);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)attn_bwd_dkdv_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_k);
+    e = hipFuncSetAttribute((const void *)attn_bwd_dkdv_kernel<HD, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_k);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute((const void *)attn_bwd_dkdv_kernel<HD, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * lds_k));
     if (e != hipSuccess) return e;
     attr_done.set();
   }
@@ -354,7 +383,13 @@ hipError_t launch_t(const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf1
   hipLaunchKernelGGL((attn_bwd_dq_kernel<HD>), grid_q, dim3(256), lds_q, st, q, k, v, o, d_o, lse, dvec, seg, row_base, Hq, Hkv, cs, dqkv, excl_lo, excl_hi);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<HD>), grid_k, dim3(256), lds_k, st, q, k, v, d_o, lse, dvec, seg, row_base, Hq, Hkv, cs, dqkv, excl_lo, excl_hi);
+  // Two teams where one wave a SIMD would be left (a block's turns are a chain: load, products, soft-max, products), i.e. up to about one block a CU.
+  // 8 sequences of 327 - 505 rows, 32 query and 8 kv heads of 64 (204 blocks with rows): 90 -> 58 us; a step of one pair of that layer 936 -> 918.  At 384 blocks of 128-wide
+  // heads every SIMD has its second wave already.
+  if ((long long)Hkv * (rows / 128 + n_seq / 2) <= 320)
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<HD, 2>), grid_k, dim3(512), 2 * lds_k, st, q, k, v, d_o, lse, dvec, seg, row_base, Hq, Hkv, cs, dqkv, excl_lo, excl_hi);
+  else
+    hipLaunchKernelGGL((attn_bwd_dkdv_kernel<HD, 1>), grid_k, dim3(256), lds_k, st, q, k, v, d_o, lse, dvec, seg, row_base, Hq, Hkv, cs, dqkv, excl_lo, excl_hi);
   return hipGetLastError();
 }
 

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_fwd_kernel(cons
 
   // blocks are dealt to the XCDs round-robin: block x takes head (x % Hkv) * group + x / Hkv, so the query heads
   // of one kv head (and all their row tiles) run on one XCD and its K and V stay in that XCD's L2
-  const int kvh = blockIdx.x % Hkv, h = kvh * (Hq / Hkv) + blockIdx.x / Hkv, s = blockIdx.y;
+  const int kvh = blockIdx.x % Hkv, h = kvh * (Hq / Hkv) + blockIdx.x / Hkv, s = turned_sequence();
   const int r0 = seg[s] - row_base, L = seg[s + 1] - seg[s];
   const int q0 = (gridDim.z - 1 - blockIdx.z) * QB;      // long tiles first
   if (q0 >= L) return;

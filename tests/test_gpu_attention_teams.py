@@ -1,0 +1,24 @@
+"""GPU parity of the attention kernels where a grid is small: the dK/dV kernel with two teams of waves a block (the number of query
+tiles odd and even, one tile, keys that a team's tiles all precede) on both sides of its rule, and sequences turned by the row tile
+(more and fewer sequences than row tiles, ragged)."""
+import pytest
+
+from paper_2510_03283_amd import synth
+from test_gpu_parity import SMALL, check_iteration, custom_workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hq,hkv,hd", [(8, 2, 64), (4, 4, 128), (8, 1, 128)])
+@pytest.mark.parametrize("pairs,prompt,resp", [(1, 3, (2, 60)), (1, 60, (5, 70)), (2, 130, (1, 330)), (5, 200, (1, 90))])
+def test_two_teams(torch_mod, hq, hkv, hd, pairs, prompt, resp):
+    dims = synth.ModelDims(n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, **SMALL)
+    wl = custom_workload("teams", dims, prefill=[5, 300, 129], decode=[7], n_pairs=pairs, prompt=prompt, resp=resp)
+    check_iteration(torch_mod, wl, f"Hq{hq} Hkv{hkv} hd{hd} pairs {pairs} prompt {prompt} resp {resp}")
+
+
+def test_one_team(torch_mod):
+    """32 kv heads and 20 sequences: past the rule."""
+    dims = synth.ModelDims(n_q_heads=32, n_kv_heads=32, head_dim=64, **SMALL)
+    wl = custom_workload("one_team", dims, prefill=[40], decode=[7], n_pairs=10, prompt=20, resp=(5, 120))
+    check_iteration(torch_mod, wl, "one team")
