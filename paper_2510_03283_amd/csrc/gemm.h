@@ -84,5 +84,8 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
 // force_w4 is set, and the problem fits the kernel).  Forms that only that kernel has are launched after asking.
 bool gemm_uses_four_wave(int LA, int LB, const GemmParams &p);
 
+// About how long the product takes on an otherwise idle GPU, microseconds.
+double gemm_estimate_us(const GemmParams &p);
+
 // Returns hipSuccess or the launch error; a non-null *why is set on a rejected shape.
 hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const char **why);

@@ -53,9 +53,12 @@ struct DirectStage {
 
   // LAYOUT 0: LDS [row][BKT], chunk position pos holds logical k-chunk pos ^ ((row / RPB) % CPR)
   // LAYOUT 1: LDS [k][ROWS],  logical row-chunk c sits at position c ^ ((k & 3) << 2) when CPR is a
-  //           power of two, else at (c + 4 * (k & 3)) % CPR (same bank spread, any CPR % 4 == 0)
+  //           power of two, else at (c + 4 * (k & 3)) % CPR (same bank spread, any CPR % 4 == 0).  Of eight chunks, rows of 128
+  //           bytes, every other row is half the banks further on by itself, and c ^ ((k & 2) << 1) spreads four of them.
   static constexpr bool POW2 = (CPR & (CPR - 1)) == 0;
+  static __device__ __forceinline__ int swz(int k) { return CPR == 8 ? (k & 2) << 1 : (k & 3) << 2; }
   static_assert(LAYOUT == 0 || CPR % 4 == 0, "row-contiguous tiles need a multiple of 32 rows");
+  static_assert(LAYOUT == 0 || !POW2 || CPR >= 8, "the swizzle stays inside a row");
   static __device__ __forceinline__ void issue(const bf16_t *base, long long ld, int row0, int rows, int k0, int K, bf16_t *S) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
@@ -71,7 +74,7 @@ struct DirectStage {
         ok = gr < rows;
         src = base + (long long)gr * ld + k0 + kc * 8;
       } else {
-        const int c = POW2 ? pos ^ ((lr & 3) << 2) : (pos + CPR - 4 * (lr & 3)) % CPR;
+        const int c = POW2 ? pos ^ swz(lr) : (pos + CPR - 4 * (lr & 3)) % CPR;
         const int k = k0 + lr, gr = row0 + 8 * c;
         ok = k < K && gr < rows;
         src = base + (long long)k * ld + gr;
@@ -114,7 +117,7 @@ struct DirectStage {
         const int kc = pos ^ ((lr / RPB) % CPR);
         off[i] = (uint32_t)(((long long)min(lr, rows - 1 - row0) * ld + kc * 8) * 2);
       } else {
-        const int c = POW2 ? pos ^ ((lr & 3) << 2) : (pos + CPR - 4 * (lr & 3)) % CPR;
+        const int c = POW2 ? pos ^ swz(lr) : (pos + CPR - 4 * (lr & 3)) % CPR;
         off[i] = (uint32_t)(((long long)lr * ld + min(8 * c, rows - 8 - row0)) * 2);
       }
     }
@@ -174,7 +177,7 @@ struct DirectStage {
       } else {
         const int grp = lane >> 4, j = lane & 15;
         const int cl = ((r0 + 32 * x) >> 3) + 2 * (grp & 1) + ((j & 3) >> 1);
-        const int chunk = POW2 ? cl ^ ((j >> 2) << 2) : (cl + 4 * (j >> 2)) % CPR;
+        const int chunk = POW2 ? cl ^ swz(j >> 2) : (cl + 4 * (j >> 2)) % CPR;
         f.v[x] = x < NF ? (uint32_t)(((8 * (grp >> 1) + (j >> 2)) * ROWS + chunk * 8 + 4 * (j & 1)) * 2) : 0u;
       }
     }
@@ -555,13 +558,7 @@ double tile_cost(const GemmParams &p, int slots, double slot_share, double eff) 
   return (double)end * BM * BN * slot_share / eff;
 }
 
-// 1: 256x256, 2: 192x256, 0: 128x128
-int choose_tile(const GemmParams &p) {
-  const double c256 = tile_cost<256, 256>(p, 256, 1.0, 1.0);
-  const double c192 = tile_cost<192, 256>(p, 256, 1.0, 0.69);
-  const double c128 = tile_cost<128, 128>(p, 512, 2.0, 0.62);
-  return c256 <= c192 && c256 <= c128 ? 1 : (c192 <= c128 ? 2 : 0);
-}
+int choose_tile(const GemmParams &p);
 
 bool has_rope(const GemmParams &p) {
   for (int g = 0; g < p.n_mg; ++g)
@@ -609,17 +606,37 @@ double makespan(int slots, int n_mg, const long long *n, const double *d) {
 // 4096 to 3108 x 4096 x 11008, 2329 x 2048 x 2048 .. 5632, within 15 %, with the 32x32x16 loop of the four-wave kernel.  The present
 // one takes 1.00 us a k tile at 12 - 64 blocks and 1.32 with all CUs busy, and 9.6 us a launch besides (256 x 3072 .. 16384, K = 512 and 1024).  Prices refitted to it changed 13 of 88
 // choices, by at most 4 us and mostly for the worse, so the constants stay.  tile as in choose_tile.
+// The 64x64 (64x128) tile, four (three) blocks of which share a CU: a k tile takes 0.29 (0.45) us with one block on a CU and 0.15 (0.3) more for each further one, 0.5 where the weights
+// come from beyond L2; a tile 4.5 us besides.  us, NT, K = 2048, 136 / 400 / 704 / 1024 rows x 2048: 128x128 27.4 / 27.6 / 28.1 / 31.0, 64x64 14.5 / 15.4 / 20.7 / 20.2; x 3072: 27.6 / 28.2 / 30.6 / 31.8 and 14.9 /
+// 18.8 / 24.9 / 25.6; 1536 x 3072 40.8, 42.6, 64x128 35.8; K = 4096, x 4096: 47.3 / 48.1 / 49.7 / 52.1 and 34.6 / 36.0 / 43.3 / 51.6.
 double product_us(const GemmParams &p, int tile, const int *ks) {
-  const int bm = tile == 1 ? 256 : (tile == 2 ? 192 : 128), bn = tile == 0 ? 128 : 256;
-  long long nt = 0, n[3] = {0, 0, 0}, blocks = 0;
-  for (int s = 0; s < p.n_ns; ++s) nt += cdiv(p.ns[s].N, bn);
+  const int bm = tile == 1 ? 256 : (tile == 2 ? 192 : (tile == 0 ? 128 : 64)), bn = tile == 0 || tile == 4 ? 128 : (tile == 3 ? 64 : 256);
+  long long nt = 0, n[3] = {0, 0, 0}, blocks = 0, cols = 0;
+  for (int s = 0; s < p.n_ns; ++s) { nt += cdiv(p.ns[s].N, bn); cols += p.ns[s].N; }
   for (int g = 0; g < p.n_mg; ++g) blocks += n[g] = (long long)cdiv(p.mg[g].M, bm) * nt * (ks ? ks[g] : 1);
+  const int most = tile == 3 ? 4 : 3, per_cu = (int)std::min<long long>(most, std::max<long long>(1, (blocks + 255) / 256));      // resident blocks of the small tiles
   double d[3] = {0, 0, 0};
   for (int g = 0; g < p.n_mg; ++g) {
     const double it = std::ceil((double)cdiv(p.K, BK) * p.mg[g].npass / (ks ? ks[g] : 1));
-    d[g] = tile == 1 ? it * (1.07 + 0.3 * std::min(1.0, blocks / 256.0)) + 8 : (tile == 2 ? it * 1.45 + 8 : it * (blocks <= 256 ? 0.68 : 1.15) + 6);
+    if (tile >= 3) d[g] = it * std::max(tile == 3 ? 0.14 + 0.15 * per_cu : 0.15 + 0.3 * per_cu, cols * p.K > (8 << 20) ? 0.5 : 0.0) + 4.5;
+    else d[g] = tile == 1 ? it * (1.07 + 0.3 * std::min(1.0, blocks / 256.0)) + 8 : (tile == 2 ? it * 1.45 + 8 : it * (blocks <= 256 ? 0.68 : 1.15) + 6);
   }
-  return makespan(tile == 0 ? 512 : 256, p.n_mg, n, d);
+  return makespan(tile == 0 ? 512 : (tile >= 3 ? 256 * per_cu : 256), p.n_mg, n, d);
+}
+
+// 1: 256x256, 2: 192x256, 0: 128x128, 3: 64x64, 4: 64x128.  The small tiles, which read twice to four times as much per product, for reductions too short to be cut into slices of
+// four k tiles several times over (longer ones of few rows are: 136 x 4096 x 11008 84 us on 64x64 tiles, 33 in 16 slices), where they are at least a tenth faster by product_us: few rows.  (SwiGLU
+// mode needs the gate and the up columns of a wave in one tile: 64x128.)
+int choose_tile(const GemmParams &p) {
+  const double c256 = tile_cost<256, 256>(p, 256, 1.0, 1.0);
+  const double c192 = tile_cost<192, 256>(p, 256, 1.0, 0.69);
+  const double c128 = tile_cost<128, 128>(p, 512, 2.0, 0.62);
+  const int tile = c256 <= c192 && c256 <= c128 ? 1 : (c192 <= c128 ? 2 : 0);
+  int steps = 0;
+  for (int g = 0; g < p.n_mg; ++g) steps = std::max(steps, cdiv(p.K, BK) * p.mg[g].npass);
+  if (steps > 12) return tile;
+  const double us = 0.9 * product_us(p, tile, nullptr), u64 = p.swiglu ? us : product_us(p, 3, nullptr), u128 = product_us(p, 4, nullptr);
+  return u64 < us || u128 < us ? (u64 <= u128 ? 3 : 4) : tile;
 }
 
 template <int LA, int LB>
@@ -636,6 +653,8 @@ hipError_t launch_layout(GemmParams &p, hipStream_t stream, const char **why) {
     return launch_dl<256, 256, 2, 4, LA, LB, BK, NSTAGES>(p, stream);
   }
   if (tile == 2) return launch_dl<192, 256, 2, 4, LA, LB, BK, NSTAGES>(p, stream);
+  if (tile == 3) return launch_dl<64, 64, 2, 2, LA, LB, BK, NSTAGES>(p, stream);
+  if (tile == 4) return launch_dl<64, 128, 2, 2, LA, LB, BK, NSTAGES>(p, stream);
   return launch_dl<128, 128, 2, 2, LA, LB, BK, NSTAGES>(p, stream);
 }
 
@@ -712,6 +731,8 @@ hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const 
   *why = "gemm: unsupported layout";
   return hipErrorInvalidValue;
 }
+
+double gemm_estimate_us(const GemmParams &p) { return product_us(p, choose_tile(p), nullptr); }
 
 bool gemm_uses_four_wave(int LA, int LB, const GemmParams &p) {
   if (LA == 0 && LB == 0) return uses_w4<0, 0>(p);
