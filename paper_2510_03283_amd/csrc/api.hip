@@ -595,8 +595,8 @@ int mace_create(mace_handle_t *out, const mace_model_t *model) {
     return e != hipSuccess ? hip_fail(e, "mace_create: static scratch address") : fail(MACE_HIP_ERROR, "mace_create: static scratch address is null");
   }
   e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
-  for (int i = 0; i < N_FORK_EVENTS && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&c->ev_fork[i], hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
+  for (int i = 0; i < N_FORK_EVENTS && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&c->ev_fork[i], hipEventDisableTiming | hipEventDisableSystemFence);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming | hipEventDisableSystemFence);
   if (e != hipSuccess) {
     mace_destroy(c);
     return hip_fail(e, "mace_create: side stream");
