@@ -499,26 +499,35 @@ hipError_t launch_dl(GemmParams &p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int LA, int LB>
-hipError_t launch_w4(GemmParams &p, hipStream_t stream) {
-  const int tiles = count_tiles<256, 256>(p);
+template <int LA, int LB, int TM>
+hipError_t launch_w4_rows(GemmParams &p, hipStream_t stream) {
+  const int tiles = count_tiles<32 * TM, 256>(p);
   if (tiles == 0) return hipSuccess;
   constexpr size_t lds = w4_lds_bytes<LA, LB>();
   static_assert(lds <= 160 * 1024, "LDS budget of a gfx950 CU");
   static DeviceOnce attr_done;
   if (!attr_done.test()) {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_w4_kernel<LA, LB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_bf16_w4_kernel<LA, LB, TM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_done.set();
   }
-  p.tile_m = 256; p.tile_n = 256;
+  p.tile_m = 32 * TM; p.tile_n = 256;
   int blocks = 0;
   for (int g = 0; g < p.n_mg; ++g) {
     p.k_splits[g] = std::max(1, p.k_splits[g]);
     blocks += (p.mt_start[g + 1] - p.mt_start[g]) * (tiles / p.mt_start[p.n_mg]) * p.k_splits[g];
   }
-  hipLaunchKernelGGL((gemm_bf16_w4_kernel<LA, LB>), dim3((unsigned)blocks), dim3(256), lds, stream, p);
+  hipLaunchKernelGGL((gemm_bf16_w4_kernel<LA, LB, TM>), dim3((unsigned)blocks), dim3(256), lds, stream, p);
   return hipGetLastError();
+}
+// tile: as in choose_tile
+template <int LA, int LB>
+hipError_t launch_w4(GemmParams &p, int tile, hipStream_t stream) {
+  if constexpr (LA == 0) {
+    if (tile == 5) return launch_w4_rows<LA, LB, 7>(p, stream);
+    if (tile == 2) return launch_w4_rows<LA, LB, 6>(p, stream);
+  }
+  return launch_w4_rows<LA, LB, 8>(p, stream);
 }
 
 bool aligned16(const void *q) { return ((uintptr_t)q & 15) == 0; }
@@ -532,8 +541,15 @@ bool aligned16(const void *q) { return ((uintptr_t)q & 15) == 0; }
 // of the benchmark configurations: step time was flat for factors between 0.68 and 0.8 of the kernels' long-run
 // ratios (0.92, 0.83) and 1 - 6 % worse on either side.  (Fitted to the 32x32x16 loop of the four-wave kernel, which took 6 - 8 % longer
 // on long reductions; kept, see product_us.)
+//
+// Tiles of 224 and 192 rows of the same kernel (k-contiguous A) take 0.90 and 0.80 of the time of one of 256 (0.875 and 0.75 of its products; its B tile in full).  us at 160, 256 and 512
+// tiles, N = 4096, K = 4096, 256 / 224 / 192 rows: 83.7 / 74.9 / 65.4, 96.3 / 88.7 / 79.2, 192 / 171 / 155; two passes, 256 tiles: 169 / 156 / 138.  They pay where they leave less of the last m tile
+// or of the last round empty.  CUs that stand idle leave the others their power: with few tiles a tile takes 0.77 of its time in a full round, so a round that is not full is priced by how full it is
+// (among these three).  With the choice, us a pass: 3108 rows of a 7B layer (13 m tiles of 256,
+// 14 of 224) 1659 -> 1592, a training step of an edge layer 2319 -> 2236, of a 7B layer beside 256 decode rows 6418 -> 6281.
+constexpr double W4_224_TIME = 0.90, W4_192_TIME = 0.80, W4_IDLE_GAIN = 0.23;
 template <int BM, int BN>
-double tile_cost(const GemmParams &p, int slots, double slot_share, double eff) {
+double tile_cost(const GemmParams &p, int slots, double slot_share, double eff, double idle_gain = 0.0) {
   int nt = 0;
   for (int s = 0; s < p.n_ns; ++s) nt += cdiv(p.ns[s].N, BN);
   // The dispatcher hands the next block to whichever slot is free, in block-id order (row groups one
@@ -543,6 +559,7 @@ double tile_cost(const GemmParams &p, int slots, double slot_share, double eff) 
   std::vector<int> free_at((size_t)(w / slots) + 8, 0);
   free_at[0] = slots;
   size_t t = 0, end = 0;
+  long long last = 0;      // tiles that end last
   for (int g = 0; g < p.n_mg; ++g) {
     long long n = (long long)cdiv(p.mg[g].M, BM) * nt;
     const size_t c = (size_t)p.mg[g].npass;
@@ -552,13 +569,15 @@ double tile_cost(const GemmParams &p, int slots, double slot_share, double eff) 
       free_at[t] -= k;
       free_at[t + c] += k;
       n -= k;
+      last = t + c > end ? k : (t + c == end ? last + k : last);
       end = std::max(end, t + c);
     }
   }
-  return (double)end * BM * BN * slot_share / eff;
+  return ((double)end - idle_gain * (1.0 - (double)last / slots)) * BM * BN * slot_share / eff;
 }
 
-int choose_tile(const GemmParams &p);
+int choose_tile(int LA, const GemmParams &p);
+bool is_w4_tile(int LA, int tile);
 
 bool has_rope(const GemmParams &p) {
   for (int g = 0; g < p.n_mg; ++g)
@@ -574,7 +593,7 @@ bool is_split(const GemmParams &p) {
 
 template <int LA, int LB>
 bool uses_w4(const GemmParams &p) {
-  return (p.force_w4 || choose_tile(p) == 1) && w4_fits<LA, LB>(p);
+  return (p.force_w4 || is_w4_tile(LA, choose_tile(LA, p))) && w4_fits<LA, LB>(p);
 }
 
 // Length in microseconds of a schedule of equal blocks per row group on `slots` slots, in block-id order.
@@ -609,8 +628,8 @@ double makespan(int slots, int n_mg, const long long *n, const double *d) {
 // The 64x64 (64x128) tile, four (three) blocks of which share a CU: a k tile takes 0.29 (0.45) us with one block on a CU and 0.15 (0.3) more for each further one, 0.5 where the weights
 // come from beyond L2; a tile 4.5 us besides.  us, NT, K = 2048, 136 / 400 / 704 / 1024 rows x 2048: 128x128 27.4 / 27.6 / 28.1 / 31.0, 64x64 14.5 / 15.4 / 20.7 / 20.2; x 3072: 27.6 / 28.2 / 30.6 / 31.8 and 14.9 /
 // 18.8 / 24.9 / 25.6; 1536 x 3072 40.8, 42.6, 64x128 35.8; K = 4096, x 4096: 47.3 / 48.1 / 49.7 / 52.1 and 34.6 / 36.0 / 43.3 / 51.6.
-double product_us(const GemmParams &p, int tile, const int *ks) {
-  const int bm = tile == 1 ? 256 : (tile == 2 ? 192 : (tile == 0 ? 128 : 64)), bn = tile == 0 || tile == 4 ? 128 : (tile == 3 ? 64 : 256);
+double product_us(int LA, const GemmParams &p, int tile, const int *ks) {
+  const int bm = tile == 1 ? 256 : (tile == 5 ? 224 : (tile == 2 ? 192 : (tile == 0 ? 128 : 64))), bn = tile == 0 || tile == 4 ? 128 : (tile == 3 ? 64 : 256);
   long long nt = 0, n[3] = {0, 0, 0}, blocks = 0, cols = 0;
   for (int s = 0; s < p.n_ns; ++s) { nt += cdiv(p.ns[s].N, bn); cols += p.ns[s].N; }
   for (int g = 0; g < p.n_mg; ++g) blocks += n[g] = (long long)cdiv(p.mg[g].M, bm) * nt * (ks ? ks[g] : 1);
@@ -619,23 +638,38 @@ double product_us(const GemmParams &p, int tile, const int *ks) {
   for (int g = 0; g < p.n_mg; ++g) {
     const double it = std::ceil((double)cdiv(p.K, BK) * p.mg[g].npass / (ks ? ks[g] : 1));
     if (tile >= 3) d[g] = it * std::max(tile == 3 ? 0.14 + 0.15 * per_cu : 0.15 + 0.3 * per_cu, cols * p.K > (8 << 20) ? 0.5 : 0.0) + 4.5;
-    else d[g] = tile == 1 ? it * (1.07 + 0.3 * std::min(1.0, blocks / 256.0)) + 8 : (tile == 2 ? it * 1.45 + 8 : it * (blocks <= 256 ? 0.68 : 1.15) + 6);
+    else if (is_w4_tile(LA, tile)) d[g] = (it * (1.07 + 0.3 * std::min(1.0, blocks / 256.0)) + 8) * (tile == 1 ? 1.0 : (tile == 5 ? W4_224_TIME : W4_192_TIME));
+    else d[g] = (tile == 2 ? it * 1.45 + 8 : it * (blocks <= 256 ? 0.68 : 1.15) + 6);
   }
   return makespan(tile == 0 ? 512 : (tile >= 3 ? 256 * per_cu : 256), p.n_mg, n, d);
 }
 
-// 1: 256x256, 2: 192x256, 0: 128x128, 3: 64x64, 4: 64x128.  The small tiles, which read twice to four times as much per product, for reductions too short to be cut into slices of
+// 1: 256x256, 5: 224x256, 2: 192x256, 0: 128x128, 3: 64x64, 4: 64x128.  The small tiles, which read twice to four times as much per product, for reductions too short to be cut into slices of
 // four k tiles several times over (longer ones of few rows are: 136 x 4096 x 11008 84 us on 64x64 tiles, 33 in 16 slices), where they are at least a tenth faster by product_us: few rows.  (SwiGLU
 // mode needs the gate and the up columns of a wave in one tile: 64x128.)
-int choose_tile(const GemmParams &p) {
-  const double c256 = tile_cost<256, 256>(p, 256, 1.0, 1.0);
-  const double c192 = tile_cost<192, 256>(p, 256, 1.0, 0.69);
-  const double c128 = tile_cost<128, 128>(p, 512, 2.0, 0.62);
-  const int tile = c256 <= c192 && c256 <= c128 ? 1 : (c192 <= c128 ? 2 : 0);
+bool is_w4_tile(int LA, int tile) { return tile == 1 || (LA == 0 && (tile == 2 || tile == 5)); }
+int choose_tile(int LA, const GemmParams &p) {
+  const double c256 = tile_cost<256, 256>(p, 256, 1.0, 1.0), c128 = tile_cost<128, 128>(p, 512, 2.0, 0.62);
+  int tile;
+  if (LA == 1) {
+    const double c192 = tile_cost<192, 256>(p, 256, 1.0, 0.69);
+    tile = c256 <= c192 && c256 <= c128 ? 1 : (c192 <= c128 ? 2 : 0);
+  } else {
+    // 256, 224 or 192 rows, then that against 128x128
+    const double w256 = tile_cost<256, 256>(p, 256, 1.0, 1.0, W4_IDLE_GAIN), w224 = tile_cost<224, 256>(p, 256, 1.0, 0.875 / W4_224_TIME, W4_IDLE_GAIN),
+                 w192 = tile_cost<192, 256>(p, 256, 1.0, 0.75 / W4_192_TIME, W4_IDLE_GAIN);
+    tile = 0.98 * w256 <= std::min(w224, w192) ? 1 : (w224 <= w192 ? 5 : 2);
+    const double c = tile == 1 ? c256 : (tile == 5 ? tile_cost<224, 256>(p, 256, 1.0, 0.875 / W4_224_TIME) : tile_cost<192, 256>(p, 256, 1.0, 0.75 / W4_192_TIME));
+    // (one 128x128 block alone on its CU takes 0.6 of what two there take: 136 - 1024 rows x 2048, K = 2048, 27 - 31 us, on 192 rows 33 - 35; 1536 x 3072, 288 blocks, 41 and 33)
+    int blocks128 = 0;
+    for (int g = 0; g < p.n_mg; ++g)
+      for (int s = 0; s < p.n_ns; ++s) blocks128 += cdiv(p.mg[g].M, 128) * cdiv(p.ns[s].N, 128);
+    if ((blocks128 <= 256 ? 0.8 : 1.0) * c128 < c) tile = 0;
+  }
   int steps = 0;
   for (int g = 0; g < p.n_mg; ++g) steps = std::max(steps, cdiv(p.K, BK) * p.mg[g].npass);
   if (steps > 12) return tile;
-  const double us = 0.9 * product_us(p, tile, nullptr), u64 = p.swiglu ? us : product_us(p, 3, nullptr), u128 = product_us(p, 4, nullptr);
+  const double us = 0.9 * product_us(LA, p, tile, nullptr), u64 = p.swiglu ? us : product_us(LA, p, 3, nullptr), u128 = product_us(LA, p, 4, nullptr);
   return u64 < us || u128 < us ? (u64 <= u128 ? 3 : 4) : tile;
 }
 
@@ -643,14 +677,14 @@ template <int LA, int LB>
 hipError_t launch_layout(GemmParams &p, hipStream_t stream, const char **why) {
   if (p.force_w4 || p.swiglu_bwd || has_rope(p) || is_split(p)) {      // forms that only the four-wave kernel has
     if (is_split(p) ? !w4_fits<LA, LB>(p) : !uses_w4<LA, LB>(p)) { *why = "gemm: the problem does not run on the four-wave kernel"; return hipErrorInvalidValue; }
-    return launch_w4<LA, LB>(p, stream);
+    return launch_w4<LA, LB>(p, p.force_w4 || is_split(p) ? 1 : choose_tile(LA, p), stream);
   }
-  const int tile = choose_tile(p);
-  if (tile == 1) {
+  const int tile = choose_tile(LA, p);
+  if (is_w4_tile(LA, tile)) {
     // the four-wave kernel, at every reduction length (measured against the eight-wave kernel of the same tile:
     // 5 % faster at K = 1024 .. 2048, 7 - 12 % at K >= 4096); the eight-wave kernel takes what does not fit it
-    if (w4_fits<LA, LB>(p)) return launch_w4<LA, LB>(p, stream);
-    return launch_dl<256, 256, 2, 4, LA, LB, BK, NSTAGES>(p, stream);
+    if (w4_fits<LA, LB>(p)) return launch_w4<LA, LB>(p, tile, stream);
+    if (tile != 2) return launch_dl<256, 256, 2, 4, LA, LB, BK, NSTAGES>(p, stream);
   }
   if (tile == 2) return launch_dl<192, 256, 2, 4, LA, LB, BK, NSTAGES>(p, stream);
   if (tile == 3) return launch_dl<64, 64, 2, 2, LA, LB, BK, NSTAGES>(p, stream);
@@ -732,7 +766,7 @@ hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const 
   return hipErrorInvalidValue;
 }
 
-double gemm_estimate_us(const GemmParams &p) { return product_us(p, choose_tile(p), nullptr); }
+double gemm_estimate_us(int LA, const GemmParams &p) { return product_us(LA, p, choose_tile(LA, p), nullptr); }
 
 bool gemm_uses_four_wave(int LA, int LB, const GemmParams &p) {
   if (LA == 0 && LB == 0) return uses_w4<0, 0>(p);
@@ -749,7 +783,7 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
   for (int g = 0; g < plain.n_mg; ++g) { units += cdiv(plain.mg[g].M, 256) * nt * plain.mg[g].npass; rows += plain.mg[g].M; }
   if (!fits || units >= 5 * 256) return false;           // five rounds and more: the last one is short beside the rest
   const bool round_trip = !(base.out_bf16 || base.swiglu || base.swiglu_bwd || has_rope(base));   // fp32 result written and read back anyway
-  const double t0 = product_us(base, choose_tile(base), nullptr);
+  const double t0 = product_us(LA, base, choose_tile(LA, base), nullptr);
   double best = 0.93 * t0;
   bool found = false;
   static const int cand[] = {2, 3, 4, 5, 6, 8, 12, 16};
@@ -768,7 +802,7 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
     }
     if (!ok || floats > (double)part_floats) continue;
     // every partial result is written and read once: 5 TB/s
-    const double t = product_us(plain, 1, ks) + extra_us + (floats - (round_trip ? 1.0 : 0.0) * rows * plain.ldc) * 8.0 / 5e6;
+    const double t = product_us(LA, plain, 1, ks) + extra_us + (floats - (round_trip ? 1.0 : 0.0) * rows * plain.ldc) * 8.0 / 5e6;
     if (t < best) {
       best = t;
       found = true;

@@ -152,12 +152,26 @@ __device__ __forceinline__ void w4_clear(f32x4_t &c) {
 // every k tile together - k tiles.
 __host__ __device__ constexpr int w4_tile_steps(int LA, int LB, int nk, int npass) { return LA == 0 && LB == 0 && npass == 2 ? nk : nk * npass; }
 
-template <int LA, int LB>
+// Moves of the quarters of a tile time, by how many there are in all, and how many are done before a quarter.
+constexpr int w4_quarter_moves(int all, int quarter) {
+  constexpr int PER_Q[7][8] = {{2, 2, 1, 1, 2, 2, 0, 0}, {2, 2, 1, 2, 2, 2, 0, 0}, {2, 2, 2, 2, 2, 2, 0, 0}, {}, {3, 3, 2, 2, 2, 2, 0, 0}, {3, 3, 2, 2, 3, 2, 0, 0}, {3, 3, 3, 3, 2, 2, 0, 0}};
+  return PER_Q[all - 10][quarter];
+}
+constexpr int w4_moves_before(int all, int quarter) {
+  int n = 0;
+  for (int x = 0; x < quarter; ++x) n += w4_quarter_moves(all, x);
+  return n;
+}
+
+// TM: blocks of 16 rows of a wave, 8 (256-row tiles), 7 or 6 (224 and 192 rows, k-contiguous A): row counts and rounds of tiles that 256 does not divide.
+template <int LA, int LB, int TM>
 __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
-  constexpr int BM = 256, BN = 256, BKT = 64, NTHR = 256, WGN = 2, WTM = 128, WTN = 128, TM = 8, TN = 8;      // TM x TN blocks of 16x16
+  constexpr int BM = 32 * TM, BN = 256, BKT = 64, NTHR = 256, WGN = 2, WTM = 16 * TM, WTN = 128, TN = 8;      // TM x TN blocks of 16x16
+  static_assert(TM == 8 || (LA == 0 && (TM == 6 || TM == 7)), "six to eight blocks of rows; fewer than eight only of a k-contiguous A");
   using SA = W4Tile<LA>;
   using SB = W4Tile<LB>;
-  constexpr int NL = BM * BKT / 8 / NTHR;      // 16-byte loads per lane and operand tile (8)
+  constexpr int NL = BN * BKT / 8 / NTHR, NLA = BM * BKT / 8 / NTHR, NM = NLA + NL;      // 16-byte loads per lane of a B tile (8), of an A tile (TM), and both
+  constexpr int AC0 = (TM + 1) / 2;            // A fragments of a wave's first half
   // LDS: A stage 0 | A stage 1 | B stage 0 | B stage 1
   extern __shared__ __align__(16) unsigned char smem_raw[];
   lds_char_t *const lbase = (lds_char_t *)(lds_void_t *)smem_raw;
@@ -256,27 +270,27 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
   asm volatile("" : "+v"(wofs));
   asm volatile("" : "+v"(wofs_b));
 
-  u32x4_t ra[2][NL], rb[2][NL];        // register sets: tile t waits in set (t + 1) & 1
+  u32x4_t ra[2][NLA], rb[2][NL];        // register sets: tile t waits in set (t + 1) & 1
   u32x4_t fra[TM], frb[TN];            // fragments of the current k step; a half of them is replaced as soon as it has been used
 
   auto bload = [&](u32x4_t &dst, const u32x4_t &rs, uint32_t voff, uint32_t soff) W4_INL {
     asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(dst) : "v"(voff), "s"(rs), "s"(soff));
   };
-  // load x (0..7: A, 8..15: B) of the tile described by `src`
+  // load x (below NLA: A, then B) of the tile described by `src`
   auto request = [&](auto SET, auto X, const Src &src) W4_INL {
     constexpr int set = decltype(SET)::value, x = decltype(X)::value;
-    if constexpr (x < NL) {
+    if constexpr (x < NLA) {
       bload(ra[set][x], src.qa, offA, src.oa + x * strA);
     } else {
-      constexpr int y = x - NL;
+      constexpr int y = x - NLA;
       if constexpr (LB == 0) bload(rb[set][y], (y & 2) ? src.qu : src.qb, offB, src.ob + (y >> 2) * strB_w + ((y >> 1) & 1) * strB_u + (y & 1) * strB);
       else bload(rb[set][y], src.qb, offB, src.ob + y * strB);
     }
   };
   auto stage_write = [&](auto SET, auto X, auto ST) W4_INL {
     constexpr int set = decltype(SET)::value, x = decltype(X)::value, st = decltype(ST)::value;
-    if constexpr (x < NL) *(lds_u32x4_t *)(lbase + wofs + st * SA::BYTES + x * SA::LOAD_STEP) = ra[set][x];
-    else *(lds_u32x4_t *)(lbase + wofs_b + st * SB::BYTES + (x - NL) * SB::LOAD_STEP) = rb[set][x - NL];
+    if constexpr (x < NLA) *(lds_u32x4_t *)(lbase + wofs + st * SA::BYTES + x * SA::LOAD_STEP) = ra[set][x];
+    else *(lds_u32x4_t *)(lbase + wofs_b + st * SB::BYTES + (x - NLA) * SB::LOAD_STEP) = rb[set][x - NLA];
   };
   // fragment f of half HF of an operand (OP 0: A, 1: B) for k step kk out of stage st
   auto frag = [&](auto TL, uint32_t base, auto O) W4_INL -> u32x4_t {
@@ -292,7 +306,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     }
   };
   auto read1 = [&](auto OP, auto ST, auto KK, auto HF, auto FF) W4_INL {
-    constexpr int op = decltype(OP)::value, st = decltype(ST)::value, kk = decltype(KK)::value, f = 4 * decltype(HF)::value + decltype(FF)::value;
+    constexpr int op = decltype(OP)::value, st = decltype(ST)::value, kk = decltype(KK)::value, f = (op == 0 ? AC0 : 4) * decltype(HF)::value + decltype(FF)::value;
     if constexpr (op == 0) fra[f] = frag(SA{}, fa[SA::NFA == 2 ? kk : 0], W4_IC(st * SA::BYTES + SA::frag_const(kk, f)));
     else frb[f] = frag(SB{}, fb[SB::NFA == 2 ? kk : 0], W4_IC(st * SB::BYTES + SB::frag_const(kk, f)));
   };
@@ -321,24 +335,26 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       constexpr int AH[8] = {0, 0, 1, 1, 0, 0, 1, 1}, BH[8] = {0, 1, 1, 0, 1, 0, 0, 1};
       constexpr int RO[8] = {1, 0, 0, 1, 1, 0, 0, 1}, RH[8] = {1, 1, 0, 1, 0, 1, 0, 0}, RK[8] = {0, 0, 1, 1, 1, 1, 0, 0};
       constexpr bool OUTER_B[8] = {true, true, false, false, true, true, false, false};
-      constexpr int PER_Q16[8] = {3, 3, 3, 3, 2, 2, 0, 0}, M0_16[8] = {0, 3, 6, 9, 12, 14, 16, 16};      // moves of a quarter, and its first
-      constexpr bool m16 = decltype(MOVES)::value == 16;
-      static_assert(m16 || decltype(MOVES)::value == 12, "16 or 12 moves");
-      constexpr int per_q = m16 ? PER_Q16[pp] : (pp < 6 ? 2 : 0), m0_q = m16 ? M0_16[pp] : 2 * pp;
-      static_for<0, 16>([&](auto Q) W4_INL {
-        constexpr int q = decltype(Q)::value, o = q >> 2, n = o & 1 ? 3 - (q & 3) : q & 3;
-        mfma1(W4_IC(4 * AH[pp] + (OUTER_B[pp] ? n : o)), W4_IC(4 * BH[pp] + (OUTER_B[pp] ? o : n)));
+      // (a quarter of three A fragments has twelve MFMAs)
+      constexpr int NMV = decltype(MOVES)::value;
+      static_assert(NMV == 16 || NMV == 15 || NMV == 14 || NMV == 12 || NMV == 11 || NMV == 10, "moves of a tile time");
+      constexpr int per_q = w4_quarter_moves(NMV, pp), m0_q = w4_moves_before(NMV, pp);
+      constexpr int ac = AH[pp] ? TM - AC0 : AC0, nq = 4 * ac;
+      static_assert(nq == 16 || nq == 12, "three or four A fragments a half");
+      static_for<0, nq>([&](auto Q) W4_INL {
+        constexpr int q = decltype(Q)::value, in = OUTER_B[pp] ? ac : 4, o = q / in, n = o & 1 ? in - 1 - q % in : q % in;
+        mfma1(W4_IC(AC0 * AH[pp] + (OUTER_B[pp] ? n : o)), W4_IC(4 * BH[pp] + (OUTER_B[pp] ? o : n)));
         W4_SB;
-        constexpr int RD[16] = {0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, 3, -1, -1, -1};
-        constexpr int RD6[16] = {-1, -1, -1, -1, -1, -1, -1, -1, 0, -1, 1, -1, 2, -1, 3, -1};      // behind the barrier
-        constexpr int MW[16] = {-1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1, -1};
-        constexpr int MR[16] = {-1, -1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1};
-        constexpr int rd = pp == 6 ? RD6[q] : RD[q];
+        constexpr int RD[2][16] = {{0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, 3, -1, -1, -1}, {0, -1, -1, 1, -1, -1, 2, -1, -1, 3, -1, -1, -1, -1, -1, -1}};
+        constexpr int RD6[2][16] = {{-1, -1, -1, -1, -1, -1, -1, -1, 0, -1, 1, -1, 2, -1, 3, -1}, {-1, -1, -1, -1, -1, 0, -1, 1, -1, 2, -1, 3, -1, -1, -1, -1}};      // behind the barrier
+        constexpr int MW[2][16] = {{-1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1, -1}, {-1, 0, -1, -1, 1, -1, -1, 2, -1, -1, -1, -1, -1, -1, -1, -1}};
+        constexpr int MR[2][16] = {{-1, -1, 0, -1, -1, -1, 1, -1, -1, -1, 2, -1, -1, -1, -1, -1}, {-1, -1, 0, -1, -1, 1, -1, -1, 2, -1, -1, -1, -1, -1, -1, -1}};
+        constexpr int tw = nq == 12, rd = pp == 6 ? RD6[tw][q] : RD[tw][q];
         if constexpr (pp == 6 && q == 2) { mid(); W4_SB; }
-        if constexpr (pp == 6 && q == 6) { __syncthreads(); W4_SB; turn(); W4_SB; }
-        if constexpr (rd >= 0) { read(W4_IC(RO[pp]), W4_IC(pp >= 6), W4_IC(RK[pp]), W4_IC(RH[pp]), W4_IC(rd)); W4_SB; }
-        if constexpr (MW[q] >= 0 && MW[q] < per_q) { write(W4_IC(m0_q + MW[q])); W4_SB; }
-        if constexpr (MR[q] >= 0 && MR[q] < per_q) { request_(W4_IC(m0_q + MR[q])); W4_SB; }
+        if constexpr (pp == 6 && q == (tw ? 4 : 6)) { __syncthreads(); W4_SB; turn(); W4_SB; }
+        if constexpr (rd >= 0 && rd < (RO[pp] == 1 ? 4 : (RH[pp] ? TM - AC0 : AC0))) { read(W4_IC(RO[pp]), W4_IC(pp >= 6), W4_IC(RK[pp]), W4_IC(RH[pp]), W4_IC(rd)); W4_SB; }
+        if constexpr (MW[tw][q] >= 0 && MW[tw][q] < per_q) { write(W4_IC(m0_q + MW[tw][q])); W4_SB; }
+        if constexpr (MR[tw][q] >= 0 && MR[tw][q] < per_q) { request_(W4_IC(m0_q + MR[tw][q])); W4_SB; }
       });
     });
   };
@@ -370,7 +386,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       };
       auto wr_h = [&](auto X) W4_INL { stage_write(W4_IC(0), X, W4_IC(0)); };
       auto wr_l = [&](auto X) W4_INL { stage_write(W4_IC(1), X, W4_IC(1)); };
-      auto wr_b = [&](auto X) W4_INL { stage_write(W4_IC(0), W4_IC(NL + decltype(X)::value), W4_IC(0)); };      // (wofs_b turns with the B stages)
+      auto wr_b = [&](auto X) W4_INL { stage_write(W4_IC(0), W4_IC(NLA + decltype(X)::value), W4_IC(0)); };      // (wofs_b turns with the B stages)
       auto step_hb = [&](int tile) W4_INL {      // to this tile of the slice
         oa += stepA;
         ob += stepB;
@@ -380,9 +396,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
         s0.qu[2] = live ? b_bytes : 0u;
       };
       // prologue: tile 0 of the first term and of B into LDS; the rest in the order in which the loop moves it
-      static_for<0, NL>(rq_h);
+      static_for<0, NLA>(rq_h);
       static_for<0, NL>(rq_b);
-      static_for<0, NL>(rq_l);
+      static_for<0, NLA>(rq_l);
       W4_SB;
       step_hb(1);
       ol += stepA;
@@ -390,19 +406,19 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       W4_SB;
       clear();
       W4_SB;
-      wait_vmcnt<NL>();
+      wait_vmcnt<NLA>();
       W4_SB;
-      static_for<0, NL>(wr_h);
+      static_for<0, NLA>(wr_h);
       static_for<0, NL>(wr_b);
       W4_SB;
       static_for<0, NL / 2>(rq_b);
-      static_for<0, NL>(rq_h);
+      static_for<0, NLA>(rq_h);
       static_for<NL / 2, NL>(rq_b);
       W4_SB;
       step_hb(2);
       wofs_b ^= (uint32_t)SB::BYTES;      // (the B stages lie 64 and 96 KB into LDS)
       __syncthreads();
-      static_for<0, 4>([&](auto F) W4_INL { read1(W4_IC(0), W4_IC(0), W4_IC(0), W4_IC(0), F); });
+      static_for<0, AC0>([&](auto F) W4_INL { read1(W4_IC(0), W4_IC(0), W4_IC(0), W4_IC(0), F); });
       static_for<0, 4>([&](auto F) W4_INL { read1(W4_IC(1), W4_IC(0), W4_IC(0), W4_IC(0), F); });
       W4_SB;
       // Pass ph over k tile u: the other term's tile (ph 0: second term of u; 1: first term of u + 1) into the other A stage and half of B
@@ -413,22 +429,22 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
         auto write = [&](auto M) W4_INL {
           constexpr int m = decltype(M)::value;
           if constexpr (!tail) {
-            wait_vmcnt<3 * NL - 1>();
+            wait_vmcnt<2 * NLA + NL - 1>();
             W4_SB;
           }
-          if constexpr (tail && (ph == 1 || m >= NL)) return;
-          else if constexpr (m >= NL) wr_b(W4_IC(m - NL + ph * (NL / 2)));
+          if constexpr (tail && (ph == 1 || m >= NLA)) return;
+          else if constexpr (m >= NLA) wr_b(W4_IC(m - NLA + ph * (NL / 2)));
           else if constexpr (ph == 0) wr_l(M);
           else wr_h(M);
         };
         auto request2 = [&](auto M) W4_INL {
           constexpr int m = decltype(M)::value;
           if constexpr (tail) return;
-          else if constexpr (m >= NL) rq_b(W4_IC(m - NL + ph * (NL / 2)));
+          else if constexpr (m >= NLA) rq_b(W4_IC(m - NLA + ph * (NL / 2)));
           else if constexpr (ph == 0) rq_l(M);
           else rq_h(M);
         };
-        tile_time(W4_IC(12),
+        tile_time(W4_IC(NLA + NL / 2),
                   [&](auto OP, auto NEXT, auto KK, auto HF, auto FF) W4_INL {
                     read1(OP, W4_IC(decltype(OP)::value == 0 ? (decltype(NEXT)::value ? ph ^ 1 : ph) : 0), KK, HF, FF);
                   },
@@ -497,27 +513,27 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     // the last one (their data is never multiplied): the loop's wait counts assume every request is issued.
     {
       const Src s0 = tile_src(tt0);
-      static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(1), X, s0); });
+      static_for<0, NM>([&](auto X) W4_INL { request(W4_IC(1), X, s0); });
       W4_SB;
       const Src s1 = w4_resources(tile_cur(tt0 + min(1, n_it - 1)), a_bytes, n_it < 2);
-      static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(0), X, s1); });
+      static_for<0, NM>([&](auto X) W4_INL { request(W4_IC(0), X, s1); });
       W4_SB;
       clear();
       W4_SB;
-      wait_vmcnt<2 * NL>();      // tile 0 is in
+      wait_vmcnt<NM>();      // tile 0 is in
       W4_SB;
-      static_for<0, 2 * NL>([&](auto X) W4_INL { stage_write(W4_IC(1), X, W4_IC(0)); });
+      static_for<0, NM>([&](auto X) W4_INL { stage_write(W4_IC(1), X, W4_IC(0)); });
       W4_SB;
       rq_tt = tt0 + min(2, n_it - 1);
       rq = w4_resources(tile_cur(rq_tt), a_bytes, n_it < 3);
       rq_left = n_it < 3 ? 0x7fffffff : run_length(rq_tt);
       rq_tt += n_it < 3 ? 0 : rq_left;
-      static_for<0, 2 * NL>([&](auto X) W4_INL { request(W4_IC(1), X, rq); });
+      static_for<0, NM>([&](auto X) W4_INL { request(W4_IC(1), X, rq); });
       W4_SB;
       advance();
       W4_SB;
       __syncthreads();
-      static_for<0, 4>([&](auto F) W4_INL { read1(W4_IC(0), W4_IC(0), W4_IC(0), W4_IC(0), F); });
+      static_for<0, AC0>([&](auto F) W4_INL { read1(W4_IC(0), W4_IC(0), W4_IC(0), W4_IC(0), F); });
       static_for<0, 4>([&](auto F) W4_INL { read1(W4_IC(1), W4_IC(0), W4_IC(0), W4_IC(0), F); });
       W4_SB;
     }
@@ -533,7 +549,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       // by then; the last of them moves nothing either)
       auto move_write = [&](auto X) W4_INL {
         if constexpr (!tail) {
-          wait_vmcnt<4 * NL - 1>();      // the load that filled this register is followed by 31 younger ones
+          wait_vmcnt<2 * NM - 1>();      // the load that filled this register is followed by 31 younger ones (fewer with a smaller A tile)
           W4_SB;
         }
         if constexpr (!(tail && ph == 1)) stage_write(W4_IC(ph), X, W4_IC(ph ^ 1));
@@ -541,7 +557,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       auto move_request = [&](auto X) W4_INL {
         if constexpr (!tail) request(W4_IC(ph), X, rq);
       };
-      tile_time(W4_IC(16),
+      tile_time(W4_IC(NM),
                 [&](auto OP, auto NEXT, auto KK, auto HF, auto FF) W4_INL { read1(OP, W4_IC(decltype(NEXT)::value ? ph ^ 1 : ph), KK, HF, FF); },
                 move_write, move_request, [&]() W4_INL { if constexpr (!tail) advance(); }, []() W4_INL {});
       // The compiler does not know which registers have a load in flight, and where control leaves the loop it
@@ -708,13 +724,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       const auto qt = view(p.rope_cs + (long long)row_u * 128, (long long)rows_v * 512);
       const uint32_t o16 = w4_sgpr((uint32_t)N * 32u);      // 16 output rows
       uint32_t so = 0, st = 0;      // row offsets of the outputs and of the table
-      static_for<0, TM / 2>([&](auto IH) W4_INL {
+      static_for<0, (TM + 1) / 2>([&](auto IH) W4_INL {
         u32x4_t cs[2][4][2];      // the table entries of 32 rows, requested together: (cos, sin) of columns +0, +1 and +2, +3
         static_for<0, 2>([&](auto II) W4_INL {
           static_for<0, 4>([&](auto J) W4_INL {
             static_for<0, 2>([&](auto E) W4_INL {
               constexpr int ii = decltype(II)::value, j = decltype(J)::value, e = decltype(E)::value;
-              cs[ii][j][e] = __builtin_amdgcn_raw_buffer_load_b128(qt, (int)(vt + j * 128u + e * 16u), (int)(st + ii * 8192u), 0);
+              if constexpr (2 * decltype(IH)::value + ii < TM) cs[ii][j][e] = __builtin_amdgcn_raw_buffer_load_b128(qt, (int)(vt + j * 128u + e * 16u), (int)(st + ii * 8192u), 0);
             });
           });
         });
@@ -722,7 +738,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
         W4_SB;
         static_for<0, 2>([&](auto II) W4_INL {
           constexpr int ii = decltype(II)::value, i = 2 * decltype(IH)::value + ii;
-          static_for<0, 2>([&](auto JP) W4_INL {
+          if constexpr (i < TM) static_for<0, 2>([&](auto JP) W4_INL {
             constexpr int jp = decltype(JP)::value;
             uint32_t wh[2][4], wl[2][4];      // first half of the head, second half
             static_for<0, 4>([&](auto W) W4_INL {
@@ -775,7 +791,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       const auto qi = view((const bf16_t *)G.c_gu + (long long)row_u * 2 * F + col_u, (long long)rows_v * F * 4);
       const uint32_t s16 = w4_sgpr((uint32_t)F * 64u);      // 16 rows
       uint32_t sc = 0;
-      static_for<0, TM / 4>([&](auto IH) W4_INL {
+      static_for<0, (TM + 3) / 4>([&](auto IH) W4_INL {
         // G and U of 64 rows are requested together (nothing else covers the latency)
         u32x4_t gw[4][4], uw[4][4];
         {
@@ -783,8 +799,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
           static_for<0, 4>([&](auto II) W4_INL {
             static_for<0, 4>([&](auto JP) W4_INL {
               constexpr int ii = decltype(II)::value, jp = decltype(JP)::value;
-              gw[ii][jp] = __builtin_amdgcn_raw_buffer_load_b128(qi, (int)vg[jp], (int)q, 0);
-              uw[ii][jp] = __builtin_amdgcn_raw_buffer_load_b128(qi, (int)vu[jp], (int)q, 0);
+              if constexpr (4 * decltype(IH)::value + ii < TM) {
+                gw[ii][jp] = __builtin_amdgcn_raw_buffer_load_b128(qi, (int)vg[jp], (int)q, 0);
+                uw[ii][jp] = __builtin_amdgcn_raw_buffer_load_b128(qi, (int)vu[jp], (int)q, 0);
+              }
             });
             q += s16;
           });
@@ -792,7 +810,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
         W4_SB;
         static_for<0, 4>([&](auto II) W4_INL {
           constexpr int ii = decltype(II)::value, i = 4 * decltype(IH)::value + ii;
-          static_for<0, 4>([&](auto JP) W4_INL {
+          if constexpr (i < TM) static_for<0, 4>([&](auto JP) W4_INL {
             constexpr int jp = decltype(JP)::value;
             float dh[8];
             static_for<0, 4>([&](auto R) W4_INL {
@@ -882,13 +900,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     const auto qr = view((const char *)Rp + ((long long)row_u * ldr + c_col0 + col_u) * rsz, res ? rows_v * ldr * rsz : 0);
     const uint32_t c8 = w4_sgpr((uint32_t)(ldc * 32)), r8 = w4_sgpr((uint32_t)(ldr * (8 * rsz)));      // 8 rows
     uint32_t sc = 0, sr = 0;
-    static_for<0, TM / 4>([&](auto IH) W4_INL {
+    static_for<0, (TM + 3) / 4>([&](auto IH) W4_INL {
       u32x4_t rv[8][TN / 2];      // by eight rows
       if constexpr (res != 0) {
         static_for<0, 8>([&](auto R8) W4_INL {
           static_for<0, TN / 2>([&](auto JP) W4_INL {
             constexpr int r = decltype(R8)::value, jp = decltype(JP)::value;
-            if constexpr (res == 1) {
+            if constexpr (4 * decltype(IH)::value + r / 2 >= TM) {
+              rv[r][jp] = u32x4_t{0u, 0u, 0u, 0u};
+            } else if constexpr (res == 1) {
               rv[r][jp] = __builtin_amdgcn_raw_buffer_load_b128(qr, (int)vr[jp], (int)sr, 0);
             } else {
               const u32x2_t t = __builtin_amdgcn_raw_buffer_load_b64(qr, (int)vr[jp], (int)sr, 0);
@@ -901,7 +921,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       }
       static_for<0, 4>([&](auto II) W4_INL {
         constexpr int ii = decltype(II)::value, i = 4 * decltype(IH)::value + ii;
-        static_for<0, TN / 2>([&](auto JP) W4_INL {
+        if constexpr (i < TM) static_for<0, TN / 2>([&](auto JP) W4_INL {
           constexpr int jp = decltype(JP)::value;
           u32x4_t v[2];      // rows 0 .. 7 and 8 .. 15
           static_for<0, 4>([&](auto E) W4_INL {
@@ -941,7 +961,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
     const auto qr = view((const char *)Rp + ((long long)row_u * ldr + c_col0 + col_u) * rsz, res ? rows_v * ldr * rsz : 0);
     const uint32_t c16 = w4_sgpr((uint32_t)(ldc * 64)), r16 = w4_sgpr((uint32_t)(ldr * (16 * rsz)));      // 16 rows
     uint32_t sc = 0, sr = 0;
-    static_for<0, TM / 4>([&](auto IH) W4_INL {
+    static_for<0, (TM + 3) / 4>([&](auto IH) W4_INL {
       u32x4_t rv[4][TN];
       if constexpr (res != 0) {
         static_for<0, 4>([&](auto II) W4_INL {
@@ -949,7 +969,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
             static_for<0, 4>([&](auto E) W4_INL {
               constexpr int ii = decltype(II)::value, j = decltype(J)::value, e = decltype(E)::value;
               const int o = left[j] > e ? (int)(vr[j] + e * rsz) : (int)OUT;
-              if constexpr (res == 1) rv[ii][j][e] = __builtin_amdgcn_raw_buffer_load_b32(qr, o, (int)sr, 0);
+              if constexpr (4 * decltype(IH)::value + ii >= TM) rv[ii][j][e] = 0u;
+              else if constexpr (res == 1) rv[ii][j][e] = __builtin_amdgcn_raw_buffer_load_b32(qr, o, (int)sr, 0);
               else rv[ii][j][e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(qr, o, (int)sr, 0) << 16;
             });
           });
@@ -959,7 +980,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_w4_kernel(const GemmParams p) {
       }
       static_for<0, 4>([&](auto II) W4_INL {
         constexpr int ii = decltype(II)::value, i = 4 * decltype(IH)::value + ii;
-        static_for<0, TN>([&](auto J) W4_INL {
+        if constexpr (i < TM) static_for<0, TN>([&](auto J) W4_INL {
           static_for<0, 4>([&](auto E) W4_INL {
             constexpr int j = decltype(J)::value, e = decltype(E)::value;
             float f = w4_acc_rd(acc[i][j][e]);
