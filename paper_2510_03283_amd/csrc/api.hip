@@ -657,6 +657,7 @@ int mace_gemm_bf16(mace_handle_t h, const mace_gemm_desc_t *d, void *stream) {
     p.out_bf16 = 0;
     p.mg[0].rope = 1;
     p.rope_cs = d->rope_cs;
+    p.rope_hd = 128;
     p.ns[0].rope_hi = d->c; p.ns[0].rope_lo = d->c_lo; p.ns[0].rope_rot = d->rope_rotate ? 1 : 0;
   }
   h->plan.clear();
@@ -1101,9 +1102,9 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     if (s2 != st) prof_mark(h, s2, -1);
   }
   // Where the product runs on the four-wave kernel (and no adapter correction has to be added to it first), the
-  // rotary embedding and the operand split of the fine-tune rows happen in its epilogue: those rows of qkv never
-  // exist in fp32, and their angle table takes the place of the fp32 buffer.
-  bool rope_fused = false;
+  // rotary embedding, the operand split and the append to a bf16 cache happen in its epilogue: qkv never exists in
+  // fp32, and the rows' angle table takes the place of one of the fp32 buffers.
+  bool rope_fused = false, inf_fused = false;
   Parts qkv_i = {F.qkv_i, 1, 0}, qkv_f = {F.qkv_f, 1, 0};
   {
     GemmParams p = gp_init(D.d, D.d, D.d, D.nqkv);
@@ -1113,25 +1114,42 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     gp_seg(p, W.hi[W_K], W.lo[W_K], D.kd, D.qd);
     gp_seg(p, W.hi[W_V], W.lo[W_V], D.kd, D.qd + D.kd);
     GemmParams pr = p;
-    if (!lora && D.hd == 128 && I.Tf > 0) {
-      pr.mg[0].rope = 1;
-      pr.rope_cs = F.qkv_f;
-      pr.ns[0].rope_hi = S.q; pr.ns[0].rope_lo = F.q_lo; pr.ns[0].rope_rot = 1;
-      pr.ns[1].rope_hi = S.k; pr.ns[1].rope_lo = F.k_lo; pr.ns[1].rope_rot = 1;
-      pr.ns[2].rope_hi = S.v; pr.ns[2].rope_lo = F.v_lo; pr.ns[2].rope_rot = 0;
+    // (an fp32 cache, or one that is not aligned to the epilogue's 16-byte stores, is filled by the kernel of its own)
+    const bool with_inf = I.Ti > 0 && D.bf && !(((uintptr_t)cache->k | (uintptr_t)cache->v) & 15);
+    // The angle table of the fused rows, in the larger of the buffers that are free then: a row of it takes at most a
+    // third of one of theirs, so either holds that of both groups.
+    float *const table = with_inf && I.Ti > I.Tf ? F.qkv_i : F.qkv_f;
+    const int table_row0 = with_inf ? 0 : I.Ti;
+    if (!lora && (I.Tf > 0 || with_inf) && D.qd % 128 == 0 && D.kd % 128 == 0) {
+      pr.rope_hd = D.hd;
+      if (I.Tf > 0) pr.mg[0].rope = 1;
+      if (with_inf) pr.mg[I.Tf > 0 ? 1 : 0].rope = 2;
+      pr.rope_cs = table + (size_t)(I.Ti - table_row0) * D.hd;
+      pr.rope_cs_inf = table;
+      pr.ns[0].rope_hi = S.q; pr.ns[0].rope_lo = F.q_lo; pr.ns[0].rope_inf = F.q_i; pr.ns[0].rope_rot = 1;
+      pr.ns[1].rope_hi = S.k; pr.ns[1].rope_lo = F.k_lo; pr.ns[1].rope_inf = F.k_i; pr.ns[1].rope_rot = 1;
+      pr.ns[2].rope_hi = S.v; pr.ns[2].rope_lo = F.v_lo; pr.ns[2].rope_inf = F.v_i; pr.ns[2].rope_rot = 0;
+      if (with_inf) {
+        pr.ns[1].rope_cache = cache->k; pr.ns[2].rope_cache = cache->v;
+        pr.rope_slots = batch->slot_mapping;
+        pr.rope_num_slots = cache->num_blocks * cache->block_size;
+        pr.rope_hkv = D.Hkv;
+        while ((1 << pr.rope_bshift) < cache->block_size) ++pr.rope_bshift;
+      }
       rope_fused = gemm_uses_four_wave(0, 0, pr);
+      inf_fused = rope_fused && with_inf;
     }
     Parts part[3];
     bool done = false;
     if (!lora) TRY(run_gemm_parts(h, 0, 0, rope_fused ? pr : p, p, F.pool, 0.0, st, "qkv gemm", part, done));
     if (done) {
-      rope_fused = false;
+      rope_fused = inf_fused = false;
       int g = 0;
       if (I.Tf > 0) qkv_f = part[g++];
       if (I.Ti > 0) qkv_i = part[g];
     } else if (rope_fused) {
       prof_mark(h, st, T_ROPE);
-      HIP_TRY(launch_rope_table(batch->positions + I.Ti, h->inv_freq, I.Tf, D.hd, (float2 *)F.qkv_f, st), "rope table");
+      HIP_TRY(launch_rope_table(batch->positions + table_row0, h->inv_freq, I.T - table_row0, D.hd, (float2 *)table, st), "rope table");
       TRY(run_gemm(h, 0, 0, pr, st, "qkv gemm + rope"));
     } else {
       TRY(run_gemm(h, 0, 0, p, st, "qkv gemm"));
@@ -1147,8 +1165,8 @@ static int layer_fwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
     TRY(run_gemm(h, 0, 0, p2, st, "lora qkv gemm"));
   }
   // 3. RoPE, operand split, KV append of the inference rows
-  if (I.Ti > 0 || !rope_fused) {
-    const RopeRows rr[2] = {{qkv_i, batch->positions, batch->slot_mapping, F.q_i, F.k_i, F.v_i, nullptr, nullptr, nullptr, I.Ti},
+  if ((I.Ti > 0 && !inf_fused) || !rope_fused) {
+    const RopeRows rr[2] = {{qkv_i, batch->positions, batch->slot_mapping, F.q_i, F.k_i, F.v_i, nullptr, nullptr, nullptr, inf_fused ? 0 : I.Ti},
                             {qkv_f, batch->positions + I.Ti, nullptr, S.q, S.k, S.v, F.q_lo, F.k_lo, F.v_lo, rope_fused ? 0 : I.Tf}};
     prof_mark(h, st, T_ROPE);
     HIP_TRY(launch_rope_split(rr, 2, h->inv_freq, D.Hq, D.Hkv, D.hd, I.Ti ? cache->k : nullptr, I.Ti ? cache->v : nullptr, D.bf,

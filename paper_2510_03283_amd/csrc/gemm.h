@@ -24,18 +24,19 @@ struct GemmMGroup {
   // term; c_gu (nullable) G and U as bf16 [M, 2F] (G in columns [0,F), U in [F,2F)).
   void *c_lo;
   void *c_gu;
-  // Rotary mode (NT form, four-wave kernel only - ask gemm_uses_four_wave first; head dimension 128): 1 = the rows
-  // of this group are not written to c; every column segment writes its part as two bf16 terms [M, N] (row stride
-  // N) into its rope_hi / rope_lo, rotated by the group's angle table where the segment says so.
+  // Rotary mode (NT form, four-wave kernel only - ask gemm_uses_four_wave first; head dimension 64 or 128): the rows
+  // of this group are not written to c; every column segment writes its part as bf16 [M, N] (row stride N), rotated by the group's
+  // angle table where the segment says so.  1 (fine-tune rows): two terms into its rope_hi / rope_lo.  2 (inference rows): one term into
+  // its rope_inf, and into its rope_cache (nullable) at the rows' slots.
   int rope;
 };
 struct GemmNSeg {
   const bf16_t *b[2];   // [0] = hi (or only) operand, [1] = lo term (pass 3)
   int N;                // columns in the segment
   int c_col;            // first output column of the segment
-  // rotary mode (row groups with rope = 1): outputs of this segment and whether its heads are rotated (Q, K) or
+  // rotary mode (row groups with rope != 0): outputs of this segment and whether its heads are rotated (Q, K) or
   // only split into two terms (V)
-  void *rope_hi, *rope_lo;
+  void *rope_hi, *rope_lo, *rope_inf, *rope_cache;
   int rope_rot;
 };
 struct GemmParams {
@@ -68,7 +69,12 @@ struct GemmParams {
   // instead of it the epilogue writes dG | dU as bf16 [M, 2F] into c (ldc = 2F) from G | U of the forward, bf16 [M, 2F]
   // in c_gu (read only): dG = dHm U s (1 + G (1 - s)), dU = dHm G s, s = sigmoid(G).
   int swiglu_bwd;
-  const float *rope_cs;   // rotary mode: (cos, sin) of row r of the rope group and pair index i at rope_cs[2 (64 r + i)]
+  // rotary mode: (cos, sin) of row r of a rope group and pair index i at [2 (rope_hd / 2 * r + i)], by kind of group; the paged cache
+  // [blocks, rope_hkv, 1 << rope_bshift, rope_hd] and the rows' slots in it (one outside 0 .. rope_num_slots - 1 is skipped)
+  const float *rope_cs, *rope_cs_inf;
+  const int32_t *rope_slots;
+  long long rope_num_slots;
+  int rope_hd, rope_hkv, rope_bshift;
   int force_w4;     // 1: the 256x256 four-wave kernel whatever the cost model says (rejected if the problem does not fit it)
 };
 

@@ -733,9 +733,14 @@ hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const 
     }
   }
   if (has_rope(p)) {
-    bool ok = LA == 0 && LB == 0 && !p.swiglu && !p.swiglu_bwd && !p.out_bf16 && !p.resid_kind && p.n_kseg <= 1 && p.rope_cs;
-    for (int s = 0; s < p.n_ns; ++s) ok = ok && p.ns[s].N % 128 == 0 && p.ns[s].rope_hi;
-    if (!ok) { *why = "gemm: rotary mode needs the NT form, plain fp32 output for the other rows, segments of whole 128-wide heads and an angle table"; return hipErrorInvalidValue; }
+    bool ok = LA == 0 && LB == 0 && !p.swiglu && !p.swiglu_bwd && !p.out_bf16 && !p.resid_kind && p.n_kseg <= 1 && (p.rope_hd == 64 || p.rope_hd == 128);
+    for (int s = 0; s < p.n_ns; ++s) ok = ok && p.ns[s].N % 128 == 0;
+    for (int g = 0; g < p.n_mg; ++g)
+      for (int s = 0; s < p.n_ns; ++s) {
+        if (p.mg[g].rope == 1) ok = ok && p.rope_cs && p.ns[s].rope_hi;
+        if (p.mg[g].rope == 2) ok = ok && p.rope_cs_inf && p.ns[s].rope_inf && (!p.ns[s].rope_cache || (p.rope_slots && p.rope_hkv > 0 && p.rope_bshift >= 0));
+      }
+    if (!ok) { *why = "gemm: rotary mode needs the NT form, plain fp32 output for the other rows, segments of a multiple of 128 columns, 64- or 128-wide heads and angle tables"; return hipErrorInvalidValue; }
   }
   if (p.swiglu_bwd) {
     if (LA != 0 || LB != 1 || p.n_ns != 1 || p.ns[0].c_col != 0 || p.ns[0].N % 2 || !p.out_bf16 || p.resid_kind || p.swiglu ||
