@@ -788,8 +788,10 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
   for (int g = 0; g < plain.n_mg; ++g) { units += cdiv(plain.mg[g].M, 256) * nt * plain.mg[g].npass; rows += plain.mg[g].M; }
   if (!fits || units >= 5 * 256) return false;           // five rounds and more: the last one is short beside the rest
   const bool round_trip = !(base.out_bf16 || base.swiglu || base.swiglu_bwd || has_rope(base));   // fp32 result written and read back anyway
-  // (a residual costs an epilogue 3 - 7 us, and a consumer that adds slices next to nothing: 2329 x 2048 x 2048 with a bf16 residual 43 us on 192 rows, 33 in two slices and 6 more in the consumer)
-  const double t0 = product_us(LA, base, choose_tile(LA, base), nullptr) + (base.resid_kind ? 4.0 : 0.0);
+  // (a residual costs an epilogue 3 - 7 us, and a consumer that adds slices next to nothing: 2329 x 2048 x 2048 with a bf16 residual 43 us on 192 rows, 33 in two slices and 6 more in the consumer.
+  // Rotary mode costs the launch of its table, 5 us, and about 7 in the epilogue, which counts where the product is short: inference rows alone, in one pass.  Product, rotation and table or slices in us, in rotary mode / sliced: 1600, 2100 x 3072, K = 2048: 45.6, 47.4 / 40.2,
+  // 47.4; 453 x 12288, K = 4096: 82 / 68; past these the former wins, 2800 x 3072 50 / 57 and 520 .. 2800 x 12288 by a tenth and more)
+  const double t0 = product_us(LA, base, choose_tile(LA, base), nullptr) + (base.resid_kind ? 4.0 : (has_rope(base) && plain.mg[0].npass == 1 ? 12.0 : 0.0));
   double best = 0.93 * t0;
   bool found = false;
   static const int cand[] = {2, 3, 4, 5, 6, 8, 12, 16};
