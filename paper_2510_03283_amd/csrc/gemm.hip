@@ -534,10 +534,10 @@ bool aligned16(const void *q) { return ((uintptr_t)q & 15) == 0; }
 
 // Tile choice.  256x256 tiles (four waves with 128x128 wave tiles, one block per CU) do half the LDS
 // reads and half the L2 traffic of 128x128 tiles (4 waves, two blocks per CU), but quantise worse on
-// small problems; 192x256 (8 waves) sits between.  Each candidate is priced as
+// small problems; tiles of 224 and 192 rows (four waves; TN: 192x256 with 8 waves) sit between.  Each candidate is priced as
 //   length of its schedule over the (CU x resident block) slots  x  tile area  /  relative efficiency,
 // a tile of a row group with p passes taking p time units on its slot, and the cheapest is launched.  The
-// efficiencies (0.69 for 192x256, 0.62 for 128x128, relative to the four-wave kernel) are fitted to whole steps
+// efficiencies (0.69 for the TN form's 192x256, 0.62 for 128x128, relative to the four-wave kernel) are fitted to whole steps
 // of the benchmark configurations: step time was flat for factors between 0.68 and 0.8 of the kernels' long-run
 // ratios (0.92, 0.83) and 1 - 6 % worse on either side.  (Fitted to the 32x32x16 loop of the four-wave kernel, which took 6 - 8 % longer
 // on long reductions; kept, see product_us.)

@@ -1,5 +1,5 @@
-// 256x256x64 block tile on FOUR waves (2 x 2, wave tile 128x128), included by gemm.hip inside its
-// anonymous namespace.
+// 256x256x64 block tile on FOUR waves (2 x 2, wave tile 128x128; with TM = 7 and 6 224 and 192 rows, waves of
+// 112 and 96), included by gemm.hip inside its anonymous namespace.
 //
 // One wave per SIMD owns all 512 registers of a lane: 256 accumulator registers (AGPRs) and 256
 // VGPRs, of which 128 are two register sets that stage operand tiles on their way global -> VGPR
