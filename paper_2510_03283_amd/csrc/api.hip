@@ -461,7 +461,7 @@ int run_gemm_side(mace_ctx *h, int LA, int LB, GemmParams &p, const PartPool &ma
   for (int s = 0; s < p.n_ns; ++s) N += p.ns[s].N;
   const bool main_chain_small = (double)p.K * (double)std::min(M, N) < 2.0 * 256 * 65536.0;
   // A fork costs the caller's stream 6 - 11 us, and the host as much; a shorter product stays (a step of the fp32 configuration on two streams 355 us, on one 328).
-  hipStream_t s2 = main_chain_small && gemm_estimate_us(LA, p) >= 6.0 ? side_fork(h, st) : st;
+  hipStream_t s2 = main_chain_small && gemm_estimate_us(LA, LB, p) >= 6.0 ? side_fork(h, st) : st;
   Parts part[3];
   bool done = false;
   GemmParams plain = p;

@@ -91,7 +91,7 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
 bool gemm_uses_four_wave(int LA, int LB, const GemmParams &p);
 
 // About how long the product takes on an otherwise idle GPU, microseconds.
-double gemm_estimate_us(int LA, const GemmParams &p);
+double gemm_estimate_us(int LA, int LB, const GemmParams &p);
 
 // Returns hipSuccess or the launch error; a non-null *why is set on a rejected shape.
 hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const char **why);

@@ -534,10 +534,11 @@ bool aligned16(const void *q) { return ((uintptr_t)q & 15) == 0; }
 
 // Tile choice.  256x256 tiles (four waves with 128x128 wave tiles, one block per CU) do half the LDS
 // reads and half the L2 traffic of 128x128 tiles (4 waves, two blocks per CU), but quantise worse on
-// small problems; tiles of 224 and 192 rows (four waves; TN: 192x256 with 8 waves) sit between.  Each candidate is priced as
+// small problems; tiles of 224 and 192 rows (four waves; 192x256 with 8 waves for the TN form and for what does not fit
+// the four-wave kernel, bf16 output with a residual above all) sit between.  Each candidate is priced as
 //   length of its schedule over the (CU x resident block) slots  x  tile area  /  relative efficiency,
 // a tile of a row group with p passes taking p time units on its slot, and the cheapest is launched.  The
-// efficiencies (0.69 for the TN form's 192x256, 0.62 for 128x128, relative to the four-wave kernel) are fitted to whole steps
+// efficiencies (0.69 for the eight-wave 192x256, 0.62 for 128x128, relative to the four-wave kernel) are fitted to whole steps
 // of the benchmark configurations: step time was flat for factors between 0.68 and 0.8 of the kernels' long-run
 // ratios (0.92, 0.83) and 1 - 6 % worse on either side.  (Fitted to the 32x32x16 loop of the four-wave kernel, which took 6 - 8 % longer
 // on long reductions; kept, see product_us.)
@@ -576,8 +577,11 @@ double tile_cost(const GemmParams &p, int slots, double slot_share, double eff, 
   return ((double)end - idle_gain * (1.0 - (double)last / slots)) * BM * BN * slot_share / eff;
 }
 
-int choose_tile(int LA, const GemmParams &p);
-bool is_w4_tile(int LA, int tile);
+// The four-wave kernel has tiles of 224 and 192 rows for the product: k-contiguous A, and the product fits that kernel.
+template <int LA, int LB>
+bool w4_low(const GemmParams &p) { return LA == 0 && w4_fits<LA, LB>(p); }
+int choose_tile(bool low, const GemmParams &p);
+bool is_w4_tile(bool low, int tile);
 
 bool has_rope(const GemmParams &p) {
   for (int g = 0; g < p.n_mg; ++g)
@@ -593,7 +597,8 @@ bool is_split(const GemmParams &p) {
 
 template <int LA, int LB>
 bool uses_w4(const GemmParams &p) {
-  return (p.force_w4 || is_w4_tile(LA, choose_tile(LA, p))) && w4_fits<LA, LB>(p);
+  const bool low = w4_low<LA, LB>(p);
+  return (p.force_w4 || is_w4_tile(low, choose_tile(low, p))) && w4_fits<LA, LB>(p);
 }
 
 // Length in microseconds of a schedule of equal blocks per row group on `slots` slots, in block-id order.
@@ -628,7 +633,9 @@ double makespan(int slots, int n_mg, const long long *n, const double *d) {
 // The 64x64 (64x128) tile, four (three) blocks of which share a CU: a k tile takes 0.29 (0.45) us with one block on a CU and 0.15 (0.3) more for each further one, 0.5 where the weights
 // come from beyond L2; a tile 4.5 us besides.  us, NT, K = 2048, 136 / 400 / 704 / 1024 rows x 2048: 128x128 27.4 / 27.6 / 28.1 / 31.0, 64x64 14.5 / 15.4 / 20.7 / 20.2; x 3072: 27.6 / 28.2 / 30.6 / 31.8 and 14.9 /
 // 18.8 / 24.9 / 25.6; 1536 x 3072 40.8, 42.6, 64x128 35.8; K = 4096, x 4096: 47.3 / 48.1 / 49.7 / 52.1 and 34.6 / 36.0 / 43.3 / 51.6.
-double product_us(int LA, const GemmParams &p, int tile, const int *ks) {
+// A bf16 output with a residual, which the four-wave kernel does not take, costs 0.3 us for each element a thread stores (each is loaded, added and stored before the next).  us, NN, K = 64, 64x64 / 64x128 / 128x128 /
+// 192x256 / 256x256, x 4096: 900 rows 12.5 / 15.3 / 23.6 / 35.8 / 45.7, 2255 37.2 / 36.0 / 59.6 / 46.6 / 62.7, 5000 65.7 / 69.8 / 93.7 / 89.1 / 117, 16000 194 / 198 / 268 / 257 / 255.
+double product_us(bool low, const GemmParams &p, int tile, const int *ks) {
   const int bm = tile == 1 ? 256 : (tile == 5 ? 224 : (tile == 2 ? 192 : (tile == 0 ? 128 : 64))), bn = tile == 0 || tile == 4 ? 128 : (tile == 3 ? 64 : 256);
   long long nt = 0, n[3] = {0, 0, 0}, blocks = 0, cols = 0;
   for (int s = 0; s < p.n_ns; ++s) { nt += cdiv(p.ns[s].N, bn); cols += p.ns[s].N; }
@@ -638,8 +645,9 @@ double product_us(int LA, const GemmParams &p, int tile, const int *ks) {
   for (int g = 0; g < p.n_mg; ++g) {
     const double it = std::ceil((double)cdiv(p.K, BK) * p.mg[g].npass / (ks ? ks[g] : 1));
     if (tile >= 3) d[g] = it * std::max(tile == 3 ? 0.14 + 0.15 * per_cu : 0.15 + 0.3 * per_cu, cols * p.K > (8 << 20) ? 0.5 : 0.0) + 4.5;
-    else if (is_w4_tile(LA, tile)) d[g] = (it * (1.07 + 0.3 * std::min(1.0, blocks / 256.0)) + 8) * (tile == 1 ? 1.0 : (tile == 5 ? W4_224_TIME : W4_192_TIME));
+    else if (is_w4_tile(low, tile)) d[g] = (it * (1.07 + 0.3 * std::min(1.0, blocks / 256.0)) + 8) * (tile == 1 ? 1.0 : (tile == 5 ? W4_224_TIME : W4_192_TIME));
     else d[g] = (tile == 2 ? it * 1.45 + 8 : it * (blocks <= 256 ? 0.68 : 1.15) + 6);
+    if (p.out_bf16 && !p.swiglu && p.resid_kind) d[g] += 0.3 * bm * bn / (bm > 128 ? 512 : 256);
   }
   return makespan(tile == 0 ? 512 : (tile >= 3 ? 256 * per_cu : 256), p.n_mg, n, d);
 }
@@ -647,11 +655,11 @@ double product_us(int LA, const GemmParams &p, int tile, const int *ks) {
 // 1: 256x256, 5: 224x256, 2: 192x256, 0: 128x128, 3: 64x64, 4: 64x128.  The small tiles, which read twice to four times as much per product, for reductions too short to be cut into slices of
 // four k tiles several times over (longer ones of few rows are: 136 x 4096 x 11008 84 us on 64x64 tiles, 33 in 16 slices), where they are at least a tenth faster by product_us: few rows.  (SwiGLU
 // mode needs the gate and the up columns of a wave in one tile: 64x128.)
-bool is_w4_tile(int LA, int tile) { return tile == 1 || (LA == 0 && (tile == 2 || tile == 5)); }
-int choose_tile(int LA, const GemmParams &p) {
+bool is_w4_tile(bool low, int tile) { return tile == 1 || (low && (tile == 2 || tile == 5)); }
+int choose_tile(bool low, const GemmParams &p) {
   const double c256 = tile_cost<256, 256>(p, 256, 1.0, 1.0), c128 = tile_cost<128, 128>(p, 512, 2.0, 0.62);
   int tile;
-  if (LA == 1) {
+  if (!low) {
     const double c192 = tile_cost<192, 256>(p, 256, 1.0, 0.69);
     tile = c256 <= c192 && c256 <= c128 ? 1 : (c192 <= c128 ? 2 : 0);
   } else {
@@ -669,22 +677,23 @@ int choose_tile(int LA, const GemmParams &p) {
   int steps = 0;
   for (int g = 0; g < p.n_mg; ++g) steps = std::max(steps, cdiv(p.K, BK) * p.mg[g].npass);
   if (steps > 12) return tile;
-  const double us = 0.9 * product_us(LA, p, tile, nullptr), u64 = p.swiglu ? us : product_us(LA, p, 3, nullptr), u128 = product_us(LA, p, 4, nullptr);
+  const double us = 0.9 * product_us(low, p, tile, nullptr), u64 = p.swiglu ? us : product_us(low, p, 3, nullptr), u128 = product_us(low, p, 4, nullptr);
   return u64 < us || u128 < us ? (u64 <= u128 ? 3 : 4) : tile;
 }
 
 template <int LA, int LB>
 hipError_t launch_layout(GemmParams &p, hipStream_t stream, const char **why) {
+  const bool low = w4_low<LA, LB>(p);
   if (p.force_w4 || p.swiglu_bwd || has_rope(p) || is_split(p)) {      // forms that only the four-wave kernel has
     if (is_split(p) ? !w4_fits<LA, LB>(p) : !uses_w4<LA, LB>(p)) { *why = "gemm: the problem does not run on the four-wave kernel"; return hipErrorInvalidValue; }
-    return launch_w4<LA, LB>(p, p.force_w4 || is_split(p) ? 1 : choose_tile(LA, p), stream);
+    return launch_w4<LA, LB>(p, p.force_w4 || is_split(p) ? 1 : choose_tile(low, p), stream);
   }
-  const int tile = choose_tile(LA, p);
-  if (is_w4_tile(LA, tile)) {
+  const int tile = choose_tile(low, p);
+  if (is_w4_tile(low, tile)) {
     // the four-wave kernel, at every reduction length (measured against the eight-wave kernel of the same tile:
     // 5 % faster at K = 1024 .. 2048, 7 - 12 % at K >= 4096); the eight-wave kernel takes what does not fit it
     if (w4_fits<LA, LB>(p)) return launch_w4<LA, LB>(p, tile, stream);
-    if (tile != 2) return launch_dl<256, 256, 2, 4, LA, LB, BK, NSTAGES>(p, stream);
+    return launch_dl<256, 256, 2, 4, LA, LB, BK, NSTAGES>(p, stream);
   }
   if (tile == 2) return launch_dl<192, 256, 2, 4, LA, LB, BK, NSTAGES>(p, stream);
   if (tile == 3) return launch_dl<64, 64, 2, 2, LA, LB, BK, NSTAGES>(p, stream);
@@ -771,7 +780,12 @@ hipError_t gemm_launch(int LA, int LB, GemmParams &p, hipStream_t stream, const 
   return hipErrorInvalidValue;
 }
 
-double gemm_estimate_us(int LA, const GemmParams &p) { return product_us(LA, p, choose_tile(LA, p), nullptr); }
+static bool low_tiles(int LA, int LB, const GemmParams &p) { return LA == 0 && (LB == 0 ? w4_low<0, 0>(p) : w4_low<0, 1>(p)); }
+
+double gemm_estimate_us(int LA, int LB, const GemmParams &p) {
+  const bool low = low_tiles(LA, LB, p);
+  return product_us(low, p, choose_tile(low, p), nullptr);
+}
 
 bool gemm_uses_four_wave(int LA, int LB, const GemmParams &p) {
   if (LA == 0 && LB == 0) return uses_w4<0, 0>(p);
@@ -791,7 +805,8 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
   // (a residual costs an epilogue 3 - 7 us, and a consumer that adds slices next to nothing: 2329 x 2048 x 2048 with a bf16 residual 43 us on 192 rows, 33 in two slices and 6 more in the consumer.
   // Rotary mode costs the launch of its table, 5 us, and about 7 in the epilogue, which counts where the product is short: inference rows alone, in one pass.  Product, rotation and table or slices in us, in rotary mode / sliced: 1600, 2100 x 3072, K = 2048: 45.6, 47.4 / 40.2,
   // 47.4; 453 x 12288, K = 4096: 82 / 68; past these the former wins, 2800 x 3072 50 / 57 and 520 .. 2800 x 12288 by a tenth and more)
-  const double t0 = product_us(LA, base, choose_tile(LA, base), nullptr) + (base.resid_kind ? 4.0 : (has_rope(base) && plain.mg[0].npass == 1 ? 12.0 : 0.0));
+  const bool low = low_tiles(LA, LB, base);
+  const double t0 = product_us(low, base, choose_tile(low, base), nullptr) + (base.resid_kind ? 4.0 : (has_rope(base) && plain.mg[0].npass == 1 ? 12.0 : 0.0));
   double best = 0.93 * t0;
   bool found = false;
   static const int cand[] = {2, 3, 4, 5, 6, 8, 12, 16};
@@ -810,7 +825,7 @@ bool gemm_pick_splits(int LA, int LB, const GemmParams &base, const GemmParams &
     }
     if (!ok || floats > (double)part_floats) continue;
     // every partial result is written and read once: 5 TB/s
-    const double t = product_us(LA, plain, 1, ks) + extra_us + (floats - (round_trip ? 1.0 : 0.0) * rows * plain.ldc) * 8.0 / 5e6;
+    const double t = product_us(false, plain, 1, ks) + extra_us + (floats - (round_trip ? 1.0 : 0.0) * rows * plain.ldc) * 8.0 / 5e6;
     if (t < best) {
       best = t;
       found = true;

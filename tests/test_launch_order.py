@@ -157,6 +157,17 @@ def test_two_pass_products_are_cut_as_fine_as_their_steps_allow(recorder, rows):
     assert down["k_splits"] == 11, down
 
 
+@pytest.mark.parametrize("d,hq,hkv,hd,F", [(4096, 32, 32, 128, 11008), (2048, 32, 8, 64, 5632)])
+def test_products_outside_the_four_wave_kernel_are_not_priced_as_its_tiles(recorder, d, hq, hkv, hd, F):
+    """The adapter correction of dattn (bf16 output with a bf16 residual, K = 64) runs on the other kernel, whose tiles of 192 and 256 rows take
+    two to three times as long there as four small ones: 36 - 59 us at 2255 x 4096, and the small ones are ahead at every number of rows."""
+    for rows in (64, 700, 1622, 1833, 2044, 3521, 4154, 6053, 8800):
+        rec = recorder("bwd", d=d, hq=hq, hkv=hkv, hd=hd, F=F, ft=[rows // 2, rows - rows // 2], lora=16)
+        assert status(rec)["status"] == 0
+        (r,) = [r for r in plan(rec) if r["name"] == "lora dattn gemm"]
+        assert r["tile"] in ([64, 64], [64, 128]), (rows, r)
+
+
 MACE_BAD_SHAPE = -2
 
 
