@@ -168,6 +168,32 @@ def test_products_outside_the_four_wave_kernel_are_not_priced_as_its_tiles(recor
         assert r["tile"] in ([64, 64], [64, 128]), (rows, r)
 
 
+@pytest.mark.parametrize("hq,hkv,hd,ft,teams", [
+    (32, 8, 64, [505, 470, 327, 400] * 2, 2), (32, 8, 64, [950, 941], 2), (32, 8, 64, [64] * 32, 2), (32, 8, 64, [134] * 24, 2),
+    (32, 8, 64, [10] * 60, 1), (32, 8, 64, [30] * 40, 1), (32, 8, 64, [64] * 36, 1),          # many short sequences: more blocks than CUs
+    (32, 8, 128, [396] * 8, 2), (32, 8, 128, [134] * 20, 2), (16, 8, 128, [134] * 20, 2),
+    (32, 8, 128, [10] * 60, 1), (32, 8, 128, [60] * 28, 1), (32, 8, 128, [134] * 24, 1), (16, 8, 128, [134] * 22, 1),
+    (8, 8, 64, [60] * 16, 1), (8, 8, 64, [64] * 36, 1),                                        # one query tile: nothing for a second team
+    (8, 8, 64, [134] * 20, 2), (8, 8, 64, [134] * 22, 1), (8, 8, 64, [396] * 8, 2),
+    (32, 32, 64, [456] * 8, 1), (32, 32, 128, [1024] * 4, 1),
+], ids=lambda v: f"{len(v)}x{v[0]}" if isinstance(v, list) else str(v))
+def test_teams_of_the_attention_backward(recorder, hq, hkv, hd, ft, teams):
+    """A block's second team of waves takes half of its turns where the long blocks fit one a CU; past that, or without turns to share, it costs."""
+    rec = recorder("bwd", d=512, hq=hq, hkv=hkv, hd=hd, F=512, ft=ft)
+    assert status(rec)["status"] == 0
+    (r,) = [r for r in rec if r["op"] == "launch" and "attn_bwd_dkdv_kernel" in r["kernel"]]
+    assert f"ILi{hd}ELi{teams}E" in r["kernel"] and r["block"] == 256 * teams, r
+
+
+def test_teams_of_the_checked_forms(recorder):
+    """The GPU tests of the two forms run the form they name."""
+    from test_gpu_attention_teams import FORMS, form_workload
+    for form, teams in FORMS.items():
+        rec = recorder("bwd", d=256, hq=form[0], hkv=form[1], hd=form[2], F=448, ft=[int(n) for n in form_workload(*form).batch.ft_lens])
+        (r,) = [r for r in rec if r["op"] == "launch" and "attn_bwd_dkdv_kernel" in r["kernel"]]
+        assert f"ELi{teams}E" in r["kernel"], (form, r)
+
+
 MACE_BAD_SHAPE = -2
 
 
