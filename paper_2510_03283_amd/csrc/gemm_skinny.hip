@@ -115,9 +115,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const SkinnyParams p) {
   constexpr int NJ = WR / 8;                         // direct loads per group and chunk (8 rows x 128 bytes each)
   constexpr int SLOT = NC * WR * SK_KC * 2;          // bytes of a ring slot
   constexpr int RING = SK_WAVES * D * SLOT;
-  // the partial tiles of the waves are added in the ring's place, the row tiles in as many turns as that takes
-  constexpr int TURNS = SK_WAVES * MT * NC * 1024 <= 128 * 1024 || MT % 2 ? 1 : 2;
-  constexpr int RED = SK_WAVES * (MT / TURNS) * NC * 1024;
+  constexpr int RED = SK_WAVES * MT * NC * 1024;      // the partial tiles of the waves, in the ring's place
   static_assert(RING <= 144 * 1024 && RED <= 144 * 1024, "LDS budget of a gfx950 CU");
   __shared__ __align__(16) unsigned char smem[RING > RED ? RING : RED];
   __shared__ float ssq[NORM ? SK_WAVES : 1][MT * 16];      // sums of squares by wave (SCALE: complete)
@@ -279,108 +277,101 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const SkinnyParams p) {
       if (lane < 16) ssq[wave][t * 16 + lane] = v;
     }
   }
-  typedef float4 (*red_t)[MT / TURNS * NC][64];
+  typedef float4 (*red_t)[MT * NC][64];
   const red_t red = (red_t)smem;
+  __syncthreads();      // the ring becomes the place of the partial tiles
+  // sum over the waves: unit (tile, lane) of four outputs per thread
 #pragma unroll
-  for (int turn = 0; turn < TURNS; ++turn) {
-    constexpr int TT = MT / TURNS;
-    __syncthreads();      // the ring (the tiles of the turn before) becomes the place of the partial tiles
-    // sum over the waves: unit (tile, lane) of four outputs per thread
+  for (int t = 0; t < MT; ++t)
 #pragma unroll
-    for (int t = 0; t < TT; ++t)
+    for (int c = 0; c < NC; ++c) red[wave][t * NC + c][lane] = make_float4(acc[t][c][0], acc[t][c][1], acc[t][c][2], acc[t][c][3]);
+  __syncthreads();
+  for (int unit = wave; unit < MT * NC; unit += SK_WAVES) {
+    const int t = unit / NC, c = unit % NC, G = G0 + c;
+    if (c >= own) continue;
+    float4 v = red[0][unit][lane];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const f32x4_t &q = acc[turn * TT + t][c];
-        red[wave][t * NC + c][lane] = make_float4(q[0], q[1], q[2], q[3]);
-      }
-    __syncthreads();
-    for (int unit = wave; unit < TT * NC; unit += SK_WAVES) {
-      const int t = turn * TT + unit / NC, c = unit % NC, G = G0 + c;
-      if (c >= own) continue;
-      float4 v = red[0][unit][lane];
+    for (int w = 1; w < SK_WAVES; ++w) {
+      const float4 o = red[w][unit][lane];
+      v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+    }
+    const int m = t * 16 + n;      // this lane: output row m, weight rows 4 g .. 4 g + 3 of the group
+    if constexpr (NORM) {
+      float s = 0.f;
 #pragma unroll
-      for (int w = 1; w < SK_WAVES; ++w) {
-        const float4 o = red[w][unit][lane];
-        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-      }
-      const int m = t * 16 + n;      // this lane: output row m, weight rows 4 g .. 4 g + 3 of the group
-      if constexpr (NORM) {
-        float s = 0.f;
-#pragma unroll
-        for (int w = 0; w < SK_WAVES; ++w) s += ssq[w][m];
-        const float rs = 1.0f / sqrtf(s / (float)p.K + p.eps);
+      for (int w = 0; w < SK_WAVES; ++w) s += ssq[w][m];
+      const float rs = 1.0f / sqrtf(s / (float)p.K + p.eps);
+      v.x *= rs; v.y *= rs; v.z *= rs; v.w *= rs;
+    }
+    if constexpr (SCALE) {
+      if (p.ss_in) {
+        const float rs = 1.0f / sqrtf(ssq[0][m] / (float)p.K + p.eps);
         v.x *= rs; v.y *= rs; v.z *= rs; v.w *= rs;
       }
-      if constexpr (SCALE) {
-        if (p.ss_in) {
-          const float rs = 1.0f / sqrtf(ssq[0][m] / (float)p.K + p.eps);
-          v.x *= rs; v.y *= rs; v.z *= rs; v.w *= rs;
+    }
+    if constexpr (EPI == SK_E_F32) {
+      const int col = HALF ? G * 8 + 4 * g : G * 16 + 4 * g;
+      if (m < p.M && (!HALF || g < 2)) {
+        const size_t o = (size_t)m * p.N + col;
+        if (p.resid_kind == 1) {
+          const float4 r = *(const float4 *)((const float *)p.resid + o);
+          v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
+        } else if (p.resid_kind == 2) {
+          const uint2 r = *(const uint2 *)((const bf16_t *)p.resid + o);
+          v.x += sk_lo(r.x); v.y += sk_hi(r.x); v.z += sk_lo(r.y); v.w += sk_hi(r.y);
+        }
+        *(float4 *)((float *)p.c + o) = v;
+        if (p.next_a) {
+          // what the product behind the next RMSNorm needs of this row: bf16(v gain) in fragment order, and the
+          // block's share of the sum of squares (columns of one row sit in lanes n, n + 16, ...)
+          const uint2 gn = *(const uint2 *)(p.next_gain + col);
+          *(uint2 *)((bf16_t *)p.next_a + frag_index(m, col, p.N)) =
+              make_uint2(cvt_pk_bf16(v.x * sk_lo(gn.x), v.y * sk_hi(gn.x)), cvt_pk_bf16(v.z * sk_lo(gn.y), v.w * sk_hi(gn.y)));
         }
       }
-      if constexpr (EPI == SK_E_F32) {
-        const int col = HALF ? G * 8 + 4 * g : G * 16 + 4 * g;
-        if (m < p.M && (!HALF || g < 2)) {
-          const size_t o = (size_t)m * p.N + col;
-          if (p.resid_kind == 1) {
-            const float4 r = *(const float4 *)((const float *)p.resid + o);
-            v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
-          } else if (p.resid_kind == 2) {
-            const uint2 r = *(const uint2 *)((const bf16_t *)p.resid + o);
-            v.x += sk_lo(r.x); v.y += sk_hi(r.x); v.z += sk_lo(r.y); v.w += sk_hi(r.y);
-          }
-          *(float4 *)((float *)p.c + o) = v;
-          if (p.next_a) {
-            // what the product behind the next RMSNorm needs of this row: bf16(v gain) in fragment order, and the
-            // block's share of the sum of squares (columns of one row sit in lanes n, n + 16, ...)
-            const uint2 gn = *(const uint2 *)(p.next_gain + col);
-            *(uint2 *)((bf16_t *)p.next_a + frag_index(m, col, p.N)) =
-                make_uint2(cvt_pk_bf16(v.x * sk_lo(gn.x), v.y * sk_hi(gn.x)), cvt_pk_bf16(v.z * sk_lo(gn.y), v.w * sk_hi(gn.y)));
-          }
-        }
-        if (p.next_a) {
-          float q = m < p.M && (!HALF || g < 2) ? v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w : 0.f;
-          q += __shfl_xor(q, 16, 64);
-          q += __shfl_xor(q, 32, 64);
-          if (lane < 16 && m < p.M) p.ss_out[(size_t)m * groups + G] = q;
+      if (p.next_a) {
+        float q = m < p.M && (!HALF || g < 2) ? v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w : 0.f;
+        q += __shfl_xor(q, 16, 64);
+        q += __shfl_xor(q, 32, 64);
+        if (lane < 16 && m < p.M) p.ss_out[(size_t)m * groups + G] = q;
+      }
+    } else {
+      // lanes of g = 0, 1 hold the first partner of rows 4 g .. 4 g + 3, lanes of g = 2, 3 the second
+      const float4 q = make_float4(__shfl_xor(v.x, 32, 64), __shfl_xor(v.y, 32, 64), __shfl_xor(v.z, 32, 64), __shfl_xor(v.w, 32, 64));
+      if constexpr (EPI == SK_E_SWIGLU) {
+        if (g < 2 && m < p.M) {
+          const float gg[4] = {v.x, v.y, v.z, v.w}, uu[4] = {q.x, q.y, q.z, q.w};
+          float h[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) h[e] = gg[e] / (1.0f + expf(-gg[e])) * uu[e];
+          *(uint2 *)((bf16_t *)p.c + frag_index(m, G * 8 + 4 * g, p.N)) = make_uint2(cvt_pk_bf16(h[0], h[1]), cvt_pk_bf16(h[2], h[3]));
         }
       } else {
-        // lanes of g = 0, 1 hold the first partner of rows 4 g .. 4 g + 3, lanes of g = 2, 3 the second
-        const float4 q = make_float4(__shfl_xor(v.x, 32, 64), __shfl_xor(v.y, 32, 64), __shfl_xor(v.z, 32, 64), __shfl_xor(v.w, 32, 64));
-        if constexpr (EPI == SK_E_SWIGLU) {
-          if (g < 2 && m < p.M) {
-            const float gg[4] = {v.x, v.y, v.z, v.w}, uu[4] = {q.x, q.y, q.z, q.w};
-            float h[4];
+        if (m >= p.M) continue;
+        const int hd = p.hd, half = hd >> 1, gph = hd >> 4, head = G / gph, i = (G % gph) * 8 + 4 * (g & 1);
+        float o[4] = {v.x, v.y, v.z, v.w};
+        if (head < p.Hq + p.Hkv) {
+          const float x[4] = {v.x, v.y, v.z, v.w}, y[4] = {q.x, q.y, q.z, q.w};
+          const int pos = p.positions[m];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) h[e] = gg[e] / (1.0f + expf(-gg[e])) * uu[e];
-            *(uint2 *)((bf16_t *)p.c + frag_index(m, G * 8 + 4 * g, p.N)) = make_uint2(cvt_pk_bf16(h[0], h[1]), cvt_pk_bf16(h[2], h[3]));
+          for (int e = 0; e < 4; ++e) {
+            const float2 cs = rope_angle((double)pos * p.inv_freq[i + e]);
+            o[e] = g < 2 ? x[e] * cs.x - y[e] * cs.y : x[e] * cs.x + y[e] * cs.y;
           }
+        }
+        const uint2 w = make_uint2(cvt_pk_bf16(o[0], o[1]), cvt_pk_bf16(o[2], o[3]));
+        const int e0 = i + (g < 2 ? 0 : half);
+        if (head < p.Hq) {
+          *(uint2 *)((bf16_t *)p.q + (size_t)m * p.Hq * hd + head * hd + e0) = w;
         } else {
-          if (m >= p.M) continue;
-          const int hd = p.hd, half = hd >> 1, gph = hd >> 4, head = G / gph, i = (G % gph) * 8 + 4 * (g & 1);
-          float o[4] = {v.x, v.y, v.z, v.w};
-          if (head < p.Hq + p.Hkv) {
-            const float x[4] = {v.x, v.y, v.z, v.w}, y[4] = {q.x, q.y, q.z, q.w};
-            const int pos = p.positions[m];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float2 cs = rope_angle((double)pos * p.inv_freq[i + e]);
-              o[e] = g < 2 ? x[e] * cs.x - y[e] * cs.y : x[e] * cs.x + y[e] * cs.y;
-            }
-          }
-          const uint2 w = make_uint2(cvt_pk_bf16(o[0], o[1]), cvt_pk_bf16(o[2], o[3]));
-          const int e0 = i + (g < 2 ? 0 : half);
-          if (head < p.Hq) {
-            *(uint2 *)((bf16_t *)p.q + (size_t)m * p.Hq * hd + head * hd + e0) = w;
-          } else {
-            const bool isk = head < p.Hq + p.Hkv;
-            const int kh = head - p.Hq - (isk ? 0 : p.Hkv);
-            *(uint2 *)((bf16_t *)(isk ? p.k : p.v) + (size_t)m * p.Hkv * hd + kh * hd + e0) = w;
-            const long long slot = p.slots[m];
-            if (slot >= 0 && slot < p.num_slots) {
-              const long long B = p.block_size;
-              bf16_t *cache = (bf16_t *)(isk ? p.cache_k : p.cache_v);
-              *(uint2 *)(cache + ((slot / B) * p.Hkv + kh) * B * hd + (slot % B) * hd + e0) = w;
-            }
+          const bool isk = head < p.Hq + p.Hkv;
+          const int kh = head - p.Hq - (isk ? 0 : p.Hkv);
+          *(uint2 *)((bf16_t *)(isk ? p.k : p.v) + (size_t)m * p.Hkv * hd + kh * hd + e0) = w;
+          const long long slot = p.slots[m];
+          if (slot >= 0 && slot < p.num_slots) {
+            const long long B = p.block_size;
+            bf16_t *cache = (bf16_t *)(isk ? p.cache_k : p.cache_v);
+            *(uint2 *)(cache + ((slot / B) * p.Hkv + kh) * B * hd + (slot % B) * hd + e0) = w;
           }
         }
       }
@@ -426,6 +417,20 @@ hipError_t sk_even(const SkinnyParams &p, int groups, hipStream_t st, int tile[2
   return sk_launch<MT, NC, D, false, ASRC, EPI, NW>(p, cdiv(groups, even) == NC ? std::min(groups, even) : blocks, st, tile);
 }
 template <int ASRC, int EPI, int MT>
+hipError_t sk_cheapest(const SkinnyParams &p, int groups, hipStream_t st, int tile[2]) {
+  const double c1 = sk_cost<1, MT>(groups, p.K), c2 = sk_cost<2, MT>(groups, p.K), c3 = sk_cost<3, MT>(groups, p.K), c4 = sk_cost<4, MT>(groups, p.K);
+  const double c = std::min(std::min(c1, c2), std::min(c3, c4));
+  if constexpr (MT <= 4) {
+    const double c6 = sk_cost<6, MT>(groups, p.K), c8 = sk_cost<8, MT>(groups, p.K);
+    if (c8 < c && c8 < c6) return sk_even<ASRC, EPI, MT, 8>(p, groups, st, tile);
+    if (c6 < c) return sk_even<ASRC, EPI, MT, 6>(p, groups, st, tile);
+  }
+  if (c == c1) return sk_even<ASRC, EPI, MT, 1>(p, groups, st, tile);
+  if (c == c2) return sk_even<ASRC, EPI, MT, 2>(p, groups, st, tile);
+  if (c == c3) return sk_even<ASRC, EPI, MT, 3>(p, groups, st, tile);
+  return sk_even<ASRC, EPI, MT, 4>(p, groups, st, tile);
+}
+template <int ASRC, int EPI, int MT>
 hipError_t sk_pick(const SkinnyParams &p, hipStream_t st, int tile[2]) {
   const int groups = sk_groups<false, EPI>(p.N);
   if constexpr (EPI == SK_E_F32) {
@@ -434,36 +439,26 @@ hipError_t sk_pick(const SkinnyParams &p, hipStream_t st, int tile[2]) {
       else return sk_launch<MT, 1, 3, true, ASRC, EPI>(p, 2 * groups, st, tile);
     }
   }
-  if constexpr (MT > 1) {
-    if (MT > 4 || (p.K >= 1024 && groups >= SK_HALF_BELOW)) {
-      const double c1 = sk_cost<1, MT>(groups, p.K), c2 = sk_cost<2, MT>(groups, p.K), c3 = sk_cost<3, MT>(groups, p.K), c4 = sk_cost<4, MT>(groups, p.K);
-      const double c = std::min(std::min(c1, c2), std::min(c3, c4));
-      if constexpr (MT <= 4) {
-        const double c6 = sk_cost<6, MT>(groups, p.K), c8 = sk_cost<8, MT>(groups, p.K);
-        if (c8 < c && c8 < c6) return sk_even<ASRC, EPI, MT, 8>(p, groups, st, tile);
-        if (c6 < c) return sk_even<ASRC, EPI, MT, 6>(p, groups, st, tile);
-      }
-      if (c == c1) return sk_even<ASRC, EPI, MT, 1>(p, groups, st, tile);
-      if (c == c2) return sk_even<ASRC, EPI, MT, 2>(p, groups, st, tile);
-      if (c == c3) return sk_even<ASRC, EPI, MT, 3>(p, groups, st, tile);
-      return sk_even<ASRC, EPI, MT, 4>(p, groups, st, tile);
-    }
-  }
-  if constexpr (MT <= 4) {
-    if constexpr (MT == 1) {
+  if constexpr (MT > 4) {
+    return sk_cheapest<ASRC, EPI, MT>(p, groups, st, tile);
+  } else {
+    if constexpr (MT > 1) {
+      if (p.K >= 1024 && groups >= SK_HALF_BELOW) return sk_cheapest<ASRC, EPI, MT>(p, groups, st, tile);
+    } else {
       if (p.K >= 1024 && groups > 2 * SK_CUS && groups <= 4 * SK_CUS - 1)
         return groups <= 3 * SK_CUS ? sk_launch<MT, 3, 2, false, ASRC, EPI>(p, SK_CUS, st, tile) : sk_launch<MT, 4, 2, false, ASRC, EPI>(p, SK_CUS, st, tile);
       const bool short_round = p.K >= 1024 && cdiv(groups, 4 * SK_CUS) * 4 * SK_CUS * 7 > 8 * groups;
       if ((p.K <= 2048 || short_round) && groups >= 1024 && groups % 2 == 0) return sk_launch<MT, 2, 2, false, ASRC, EPI>(p, groups / 2, st, tile);
     }
     if (groups >= 640 && groups % 4 == 0) return sk_launch<MT, 4, 2, false, ASRC, EPI>(p, groups / 4, st, tile);
+    return sk_launch<MT, 1, 3, false, ASRC, EPI>(p, groups, st, tile);
   }
-  return sk_launch<MT, 1, (MT > 4 ? 4 : 3), false, ASRC, EPI, (MT > 4 ? 4 : 8)>(p, groups, st, tile);
 }
 
 template <int ASRC, int EPI>
 hipError_t sk_rows(const SkinnyParams &p, hipStream_t st, int tile[2]) {
-  if (p.M <= 16) return sk_pick<ASRC, EPI, 1>(p, st, tile);
+  if constexpr (ASRC != SK_A_FRAG || EPI != SK_E_QKV)      // (so few rows of QKV come with their RMSNorm)
+    if (p.M <= 16) return sk_pick<ASRC, EPI, 1>(p, st, tile);
   if constexpr (ASRC == SK_A_FRAG) {
     if (p.M <= 32) return sk_pick<ASRC, EPI, 2>(p, st, tile);
     if (p.M <= 48) return sk_pick<ASRC, EPI, 3>(p, st, tile);      // never many more tiles than the rows fill: they cost as if they were full

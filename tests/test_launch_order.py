@@ -265,6 +265,26 @@ def test_plan_records_the_tiles_of_few_row_products(recorder, rows, d, hq, hkv, 
             assert r["tile"] == [-(-rows // 16) * 16, r["n"] // g], (r, g)
 
 
+def skinny_forms(rec):
+    """Template arguments of the weight-streaming launches: row tiles, groups a block, ring slots, 8-row groups, source of the activations, epilogue, waves."""
+    return [tuple(map(int, re.findall(r"L[ib](\d+)E", r["kernel"].split("skinny_kernelI")[1]))) for r in rec if r["op"] == "launch" and "skinny_kernelI" in r["kernel"]]
+
+
+def test_every_few_row_form_is_launched_by_some_batch(recorder):
+    """A form of the kernel that nothing launches is not compiled."""
+    from paper_2510_03283_amd import build
+    names = subprocess.run(["nm", os.path.join(build.BUILD_DIR, "gemm_skinny.o")], capture_output=True, text=True, check=True).stdout
+    compiled = {tuple(map(int, re.findall(r"L[ib](\d+)E", n))) for n in re.findall(r"skinny_kernelI(\S+)", names)}
+    launched = set()
+    for rows in (5, 17, 33, 49, 65, 81, 97):
+        for d, hq, hkv, hd, F, V in ((320, 4, 4, 64, 704, 1024), (320, 64, 8, 128, 5120, 10240), (320, 64, 32, 128, 8192, 16384), (3072, 4, 4, 64, 14336, 4096), (1024, 32, 8, 64, 2752, 10304),
+                                     (1024, 72, 36, 64, 4096, 12800), (1024, 50, 50, 128, 5504, 20800), (1024, 100, 50, 64, 7040, 32064), (1024, 256, 128, 64, 11008, 8192),
+                                     (1024, 64, 32, 64, 5504, 8192), (4096, 64, 64, 64, 22016, 8192), (8192, 64, 32, 128, 5632, 32000)):
+            opts = dict(d=d, hq=hq, hkv=hkv, hd=hd, F=F, V=V, n=rows, decode=[5] * rows)
+            launched.update(skinny_forms(recorder("fwd", **opts)), skinny_forms(recorder("logits", **opts)))
+    assert compiled - launched == set()
+
+
 @pytest.mark.parametrize("groups", [[(300, 1, 2), (500, 2, 4)], [(256, 1, 1), (300, 2, 3), (700, 3, 5)], [(500, 2, 4), (300, 1, 2)]])
 def test_slices_follow_their_row_group(recorder, groups):
     """The launcher starts row groups of more passes first; the slices of a group have to move with it."""
