@@ -270,6 +270,21 @@ def skinny_forms(rec):
     return [tuple(map(int, re.findall(r"L[ib](\d+)E", r["kernel"].split("skinny_kernelI")[1]))) for r in rec if r["op"] == "launch" and "skinny_kernelI" in r["kernel"]]
 
 
+def test_groups_of_the_checked_few_row_products(recorder):
+    """The GPU tests of the evenly shared groups run the forms that they name."""
+    from test_gpu_skinny_even import FORMS
+    F32, SWIGLU, QKV = 0, 1, 2
+    for dims, by_rows in FORMS.items():
+        opts = dict(zip(("d", "hq", "hkv", "hd", "F", "V"), dims))
+        for rows, (qkv, gate_up, head) in by_rows.items():
+            fwd, (last,) = (skinny_forms(recorder(call, n=rows, decode=[5] * rows, **opts)) for call in ("fwd", "logits"))
+            tiles = -(-rows // 16) if rows <= 96 else 8
+            got = {f[5]: f[:2] for f in fwd if f[5] != F32}
+            if dims[4] <= 8192 or rows <= 96:
+                assert got == {QKV: (tiles, qkv), SWIGLU: (tiles, gate_up)}, (dims, rows, fwd)
+            assert last[:2] == (tiles, head) and last[5] == F32, (dims, rows, last)
+
+
 def test_every_few_row_form_is_launched_by_some_batch(recorder):
     """A form of the kernel that nothing launches is not compiled."""
     from paper_2510_03283_amd import build
