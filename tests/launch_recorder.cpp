@@ -193,6 +193,23 @@ int main(int argc, char **argv) {
   if (g_uploads) return 0;
   if (num("single_stream", 0)) mace_set_option(h, MACE_OPT_SINGLE_STREAM, 1);
 
+  if (call == "product") {      // mace_gemm_bf16: la= lb= M= N= K=, ldc= ldr= beside N, out_bf16= resid= swiglu= kernel=, two= a second term of A, keep= what the forward keeps
+    mace_gemm_desc_t p;
+    memset(&p, 0, sizeof(p));
+    p.layout_a = (int32_t)num("la", 0); p.layout_b = (int32_t)num("lb", 0);
+    p.M = (int32_t)num("M", 64); p.N = (int32_t)num("N", 64); p.K = (int32_t)num("K", 64);
+    p.lda = p.layout_a ? p.M : p.K; p.ldb = p.layout_b ? p.N : p.K;
+    p.ldc = num("ldc", p.N); p.ldr = num("ldr", p.ldc);
+    p.a = fake(256); p.b = fake(256); p.c = fake(256);
+    if (num("two", 0)) p.a_lo = fake(256);
+    if (num("swiglu", 0) == 1) p.b_up = fake(256);
+    if (num("keep", 0)) { p.c_lo = fake(256); p.c_gu = fake(256); }
+    if (num("swiglu", 0) == 2) p.c_gu = fake(256);
+    p.out_bf16 = (int32_t)num("out_bf16", 0); p.swiglu = (int32_t)num("swiglu", 0); p.kernel = (int32_t)num("kernel", 0);
+    p.resid_kind = (int32_t)num("resid", 0);
+    if (p.resid_kind) p.resid = fake(256);
+    return result(h, mace_gemm_bf16(h, &p, nullptr));
+  }
   if (call == "workspace") {      // decode=counts contexts=lengths: the bytes of every pair, tokens=, ft_tokens= other rows
     for (int n : list("decode"))
       for (int c : list("contexts")) {

@@ -300,6 +300,16 @@ def test_every_few_row_form_is_launched_by_some_batch(recorder):
     assert compiled - launched == set()
 
 
+def test_tiles_of_the_checked_small_products(recorder):
+    """The GPU tests of the small tiles run the tile that they name, with either output and any residual."""
+    from test_gpu_small_tiles import SHAPES
+    for (la, lb, M, N, K), tile in SHAPES.items():
+        for out_bf16 in (0, 1):
+            for resid in (0, 1, 2):
+                (r,) = plan(recorder("product", la=la, lb=lb, M=M, N=N, K=K, ldc=N + 24, ldr=N + 2, out_bf16=out_bf16, resid=resid))
+                assert tuple(r["tile"]) == tile, (la, lb, M, N, K, out_bf16, resid, r)
+
+
 @pytest.mark.parametrize("groups", [[(300, 1, 2), (500, 2, 4)], [(256, 1, 1), (300, 2, 3), (700, 3, 5)], [(500, 2, 4), (300, 1, 2)]])
 def test_slices_follow_their_row_group(recorder, groups):
     """The launcher starts row groups of more passes first; the slices of a group have to move with it."""
