@@ -70,3 +70,37 @@ def test_two_terms_and_swiglu(torch_mod, handle, M, K):
     assert np.abs(two - h).max() / np.abs(h).max() <= 5e-5
     check_out(gu, np.concatenate([g, u], axis=1), M, 2 * F, 4e-3, "G | U")
     assert np.all(f64(h_lo)[M:] == SENT)
+
+
+@pytest.mark.parametrize("rows,height", [(298, 192), (576, 192), (578, 192), (1010, 224), (1120, 224)])
+def test_swiglu_backward(torch_mod, rows, height):
+    """dG | dU in the epilogue of dHm, seen through dWg and dWu of a layer whose upstream gradient is zero but in one row of every sixteen, and then but in the
+    last: a block of rows that goes wrong is a sixth of the result and more.  Bar: dy, dG and b are rounded to bf16 once, G and U (two factors of dG) as the
+    forward keeps them, and its operands once more, 2^-9 each: 1.2e-2."""
+    torch = torch_mod
+    from helpers import max_abs_norm_err, run_oracle
+    from oracle import mace_oracle as O
+    from paper_2510_03283_amd import binding, synth
+    from paper_2510_03283_amd.harness import DeviceIteration
+    from test_gpu_parity import custom_workload
+    n = rows // 2 - 40
+    wl = custom_workload("swiglu_rows", synth.ModelDims(832, 4, 4, 64, 11008, 1024, io_bf16=True), prefill=(), decode=(), n_pairs=1, prompt=40, resp=(n, n))
+    ref = run_oracle(wl, backward=False)
+    it = DeviceIteration(wl)
+    try:
+        assert it.Tf == rows
+        it.forward()
+        for picked in ([16 * i + 5 * i % 16 for i in range(rows // 16)], [rows - 1]):
+            dy = np.zeros((rows, 832), np.float32)
+            dy[picked] = np.random.default_rng(rows).uniform(-1, 1, (len(picked), 832))
+            it.backward(torch.from_numpy(dy).cuda())
+            (r,) = [r for r in binding.mace_launch_plan(it.h) if r["name"] == "dhm gemm + swiglu bwd"]
+            assert tuple(r["tile"]) == (height, 256)
+            torch.cuda.synchronize()
+            _, want = O.layer_backward(wl.dims, wl.weights, ref["saved"], [dy[:rows // 2], dy[rows // 2:]])
+            for k in ("wg", "wu"):
+                e = max_abs_norm_err(it.grads[k].cpu().numpy(), want[k])
+                print(f"{rows} rows, {len(picked)} of them picked, d{k}: {e:.2e}", flush=True)
+                assert e <= 1.2e-2, (rows, len(picked), k, e)
+    finally:
+        it.close()
