@@ -754,8 +754,12 @@ size_t mace_workspace_bytes(mace_handle_t h, int32_t n_tokens, int32_t n_ft_toke
   return align_up(m, 256) + 256;
 }
 
-// More than 64 rows: decode batches only (a prefill request of that many rows then gives the same bits alone as beside decode or fine-tune rows), and with a long down
-// projection, every block of which reads all of its activations, up to 96.  128 rows, d_ff 11008: 221 us here, 218 on the large kernel; d_ff 5632: 97 and 130.
+// More than 64 rows: decode batches only, and with a long down projection, every block of which reads all of its activations, up to 96.  Forward in us here / on the large kernel with its row steps, contexts of
+// 64, 2048 wide with heads of 64 and 4096 wide with heads of 128: d_ff 5632, 96 rows 82 / 116 and 143 / 164, 128 rows 96 / 118 and 167 / 175; 8192, 96 rows 91 / 119 and 164 / 175, 97 rows 106 / 120 and 181 / 179, 128 rows 108 / 121 and 192 / 208;
+// 9216, 96 rows 108 / 119 and 183 / 202, 97 rows 125 / 122 and 201 / 205, 128 rows 128 / 123 and 213 / 212; 11008, 96 rows 113 / 123 and 192 / 205, 128 rows 135 / 126 and 221 / 214.
+// Batches with prefill rows stay at 64 for the sake of equal bits, not of time (40 prompt tokens beside 40 decode rows, d_ff 5632: 79 / 119 and 126 / 158): a prefill request past 64 rows gives the same ones alone
+// as beside decode and fine-tune rows, where both batches take the same kernels and cut no reduction.  That holds for short reductions only (width 256); at 2048, 100 rows alone are cut into 8 slices in QKV and beside 300 fine-tune
+// rows into 6, and below 65 rows, as for decode rows, the few-row products differ from the large kernel as well.  What differs is the order of fp32 sums.
 static bool skinny_fits(const Dims &D, long long rows, bool prefill) {
   const long long lim = 1ll << 31;
   return D.bf && rows <= (prefill ? 64 : (D.F <= 8192 ? SKINNY_MAX_ROWS : 96)) && (long long)D.nqkv * D.d < lim && (long long)D.F * D.d < lim && (long long)D.d * D.qd < lim;

@@ -400,6 +400,7 @@ hipError_t sk_launch(const SkinnyParams &p, int blocks, hipStream_t st, int tile
 // (L2, about 110) add up, per block  weights + activations  with one block a CU at a time.  Neither a deeper ring nor more blocks in flight changes that, only
 // fewer activation reads and no partly filled round do: so all blocks run in whole rounds of one a CU, share the groups evenly, and own up to
 // eight (four from 65 rows on, whose accumulators fill the registers); sk_cost prices the candidates.  Four waves leave a block of many groups its registers.
+// (The waves that share K follow from rows and groups, and with them the order in which the products of a row are added: its last bits depend on the size of the batch.)
 // us at 32 / 64 / 128 rows, blocks of four groups (before) and so: 12288 x 4096 21.0 / 26.9 / 39.6 -> 18.4 / 23.2 / 32.2, 2 x 11008 x 4096 43.4 / 50.6 / 77 -> 32.0 / 36.3 /
 // 58.9, 32000 x 4096 47.6 / 54.9 / 78 -> 42.9 / 45.9 / 78, 2 x 5632 x 2048 12.6 / 15.6 / 23.3 -> 11.3 / 14.2 / 19.1, 32000 x 2048 28.2 / 32.9 / 47 -> 25.4 / 28.8 / 47.
 constexpr int SK_CUS = 256;

@@ -167,8 +167,9 @@ def test_empty_classes(torch_mod, prefill, decode, pairs):
 
 
 def test_batch_composition_invariance(torch_mod):
-    """Colocation must not change results (Fig. 1): a decode request alone gives the same bits as
-    inside the mixed batch, and so does a prefill request."""
+    """Colocation must not change results (Fig. 1).  A prefill request gives the same bits alone as inside the mixed batch where both
+    take the same kernels and cut no reduction, as here: 70 rows are past the few-row products, and the layer's reductions are too short
+    to be cut.  Elsewhere the kernel and the slices follow the whole batch, and the fp32 sums of a row have another order."""
     torch = torch_mod
     from paper_2510_03283_amd.harness import DeviceIteration
     dims = synth.ModelDims(n_q_heads=4, n_kv_heads=2, head_dim=64, **SMALL)
