@@ -330,7 +330,8 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const SkinnyParams p) {
         }
       }
       if (p.next_a) {
-        float q = m < p.M && (!HALF || g < 2) ? v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w : 0.f;
+        // (written out: which square is rounded on its own is otherwise up to the code around it)
+        float q = m < p.M && (!HALF || g < 2) ? fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.y, v.y, v.x * v.x))) : 0.f;
         q += __shfl_xor(q, 16, 64);
         q += __shfl_xor(q, 32, 64);
         if (lane < 16 && m < p.M) p.ss_out[(size_t)m * groups + G] = q;
