@@ -364,17 +364,20 @@ __global__ __launch_bounds__(256 * QS, QS == 1 ? 2 : 1) void attn_bwd_dkdv_kerne
 
 // Two teams where one wave a SIMD would be left (a block's turns are a chain: load, products, soft-max, products), i.e. up to about one block a CU: a block of two teams has a CU's
 // waves to itself, so one past that waits for a whole other one.  Counted are blocks of the longest one's turns (query tiles times heads of the group), for the light ones at the end of a sequence
-// fill in; in all there are at most about 320.  The second team's start and the sum cost two to six turns' time, more at 128-wide heads.  us with one / two teams, 8 kv heads, 32 query heads of 64 unless it says otherwise:
-// 8 sequences of 327 - 505 rows 90 / 58 (a step of one pair of that layer 936 -> 918); 32 of 64 rows (256 blocks of 4 turns) 14.8 / 12.6, 36 (288) 16.5 / 21.5, 60 of 10 (480) 14.4 / 17.5; 24 of 134 (12 turns)
-// 35.6 / 27.8, of 128-wide heads, 20 and 24: 56.2 / 47.0 and 57.6 / 61.0, 16 of 60 (4 turns) 22.5 / 22.8, 28 24.1 / 25.3, 16 query heads 20 of 134 (6 turns) 34.4 / 33.3; 8 query heads of 64: 16 of 60 (one turn) 6.7 / 7.0,
-// 20 and 22 of 134 (3 turns) 12.1 / 11.8 and 12.4 / 14.4, 8 of 396 (7 turns) 19.5 / 17.2.  At 384 blocks of 128-wide heads every SIMD has its second wave already.
+// fill in; in all there are at most about 320.  The second team's start and the sum cost two to six turns' time, more at 128-wide heads, where a second round of light blocks counts as well until there are a dozen turns.
+// us with one / two teams, 8 kv heads, 32 query heads of 64 unless it says otherwise: 8 sequences of 327 - 505 rows 90 / 58 (a step of one pair of that layer 936 -> 918); 32 of 64 rows (256 blocks of 4 turns) 14.8 / 12.6,
+// 36 (288) 16.5 / 21.5, 60 of 10 (480) 14.4 / 17.5; 24 of 134 (12 turns) 35.6 / 27.8; 8 query heads of 64: 16 of 60 (one turn) 6.7 / 7.0, 20 and 22 of 134 (3 turns) 12.1 / 11.8 and 12.4 / 14.4, 8 of 396 (7 turns) 19.5 / 17.2.
+// Of 128-wide heads, the dQ kernel included: 10 sequences of 100 (8 turns) 61.7 / 57.9, of 134 (12) 91.8 / 82.2; 16 query heads, 16 of 134 (6) 56.0 / 55.6, 10 of 226 (8) 66.0 / 63.0, 20 (320 blocks) 93.8 / 105.6; 8 query heads, 8 of 226 (4) 47.6 / 50.0,
+// 8 and 10 of 400 (7; 256 and 320 blocks) 64.6 / 64.9 and 68.6 / 78.0, 4 and 8 of 520 (9; 160 and 320) 72.0 / 69.3 and 78.3 / 83.2.  A step of a 7B layer with 2 sequences of 396 (32 kv heads, 7 turns, 256 blocks) 2088 / 2098, of 520 (9, 320) 2558 / 2564,
+// where the products of the side stream share the chip.  At 384 blocks of 128-wide heads every SIMD has its second wave already.
 bool two_teams(const int32_t *seg_host, int n_seq, int max_len, int rows, int group, int Hkv, int hd) {
   if ((long long)Hkv * (rows / 128 + n_seq / 2) > 320) return false;
   const int longest = cdiv(max_len, TB), turns = group * longest;
-  if (turns < (hd == 64 ? 2 : 6)) return false;
-  long long tiles = 0;      // query tiles of all blocks of a kv head, for one query head
+  if (turns < (hd == 64 ? 2 : 8)) return false;
+  long long tiles = 0, blocks = 0;      // query tiles of all blocks of a kv head, for one query head; its blocks
   for (int s = 0; s < n_seq; ++s)
-    for (int L = seg_host[s + 1] - seg_host[s]; L > 0; L -= 128) tiles += cdiv(L, TB);
+    for (int L = seg_host[s + 1] - seg_host[s]; L > 0; L -= 128, ++blocks) tiles += cdiv(L, TB);
+  if (hd != 64 && turns < 12 && Hkv * blocks > 256) return false;
   return Hkv * tiles <= (long long)longest * (hd == 64 && turns >= 4 ? 256 : 224);
 }
 

@@ -171,7 +171,9 @@ def test_products_outside_the_four_wave_kernel_are_not_priced_as_its_tiles(recor
 @pytest.mark.parametrize("hq,hkv,hd,ft,teams", [
     (32, 8, 64, [505, 470, 327, 400] * 2, 2), (32, 8, 64, [950, 941], 2), (32, 8, 64, [64] * 32, 2), (32, 8, 64, [134] * 24, 2),
     (32, 8, 64, [10] * 60, 1), (32, 8, 64, [30] * 40, 1), (32, 8, 64, [64] * 36, 1),          # many short sequences: more blocks than CUs
-    (32, 8, 128, [396] * 8, 2), (32, 8, 128, [134] * 20, 2), (16, 8, 128, [134] * 20, 2),
+    (32, 8, 128, [396] * 8, 2), (32, 8, 128, [134] * 20, 2), (16, 8, 128, [226] * 10, 2), (8, 8, 128, [520] * 4, 2), (16, 8, 128, [400] * 10, 2),
+    (16, 8, 128, [134] * 16, 1), (32, 32, 128, [396] * 2, 1), (8, 8, 128, [330] * 6, 1),       # 128-wide heads: too few turns
+    (16, 8, 128, [226] * 20, 1), (32, 32, 128, [520] * 2, 1), (8, 8, 128, [400] * 10, 1), (8, 8, 128, [520] * 8, 1),      # a second round of light blocks
     (32, 8, 128, [10] * 60, 1), (32, 8, 128, [60] * 28, 1), (32, 8, 128, [134] * 24, 1), (16, 8, 128, [134] * 22, 1),
     (8, 8, 64, [60] * 16, 1), (8, 8, 64, [64] * 36, 1),                                        # one query tile: nothing for a second team
     (8, 8, 64, [134] * 20, 2), (8, 8, 64, [134] * 22, 1), (8, 8, 64, [396] * 8, 2),
