@@ -121,9 +121,15 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const SkinnyParams p) {
   __shared__ float ssq[NORM ? SK_WAVES : 1][MT * 16];      // sums of squares by wave (SCALE: complete)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: matrix instructions ignore the lane mask)
   const int n = lane & 15, g = lane >> 4;
-  // a block's groups: the blocks share all of them evenly, NC is the most one of them owns
+  // A block's groups: the blocks share all of them evenly (block b starts at group b groups / blocks), NC is the most one of them owns.  Whole shares and the rest come from the host: the two 64-bit
+  // divisions were 300 of 400 instructions in front of the first request, 0.2 - 0.4 us of every launch (forward of one row through a layer of four products, 1536 wide, d_ff 3072, weights from HBM: 35.4 -> 33.8 us).
   const int groups = sk_groups<HALF, EPI>(p.N);
-  const int G0 = (int)((long long)blockIdx.x * groups / gridDim.x), own = (int)((long long)(blockIdx.x + 1) * groups / gridDim.x) - G0;
+  int G0 = (int)blockIdx.x * p.share, own = p.share;
+  if (p.rest) {      // (b rest < 2^32: sk_launch)
+    const uint32_t z = blockIdx.x * (uint32_t)p.rest, q = z / gridDim.x;
+    G0 += (int)q;
+    own += z - q * gridDim.x + p.rest >= gridDim.x ? 1 : 0;
+  }
 
   // weight rows: direct load j of group c takes rows 8 j + lane / 8 of the group, 16-byte piece lane % 8 of the chunk,
   // swizzled so that the fragment reads below meet no bank conflicts
@@ -381,9 +387,14 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const SkinnyParams p) {
 }
 
 template <int MT, int NC, int D, bool HALF, int ASRC, int EPI, int NW = 8>
-hipError_t sk_launch(const SkinnyParams &p, int blocks, hipStream_t st, int tile[2]) {
+hipError_t sk_launch(const SkinnyParams &params, int blocks, hipStream_t st, int tile[2]) {
+  const int groups = sk_groups<HALF, EPI>(params.N);
+  if (blocks > 65535) blocks = groups;      // no rest then
+  SkinnyParams p = params;
+  p.share = groups / blocks;
+  p.rest = groups % blocks;
   tile[0] = MT * 16;
-  tile[1] = sk_groups<HALF, EPI>(p.N) * (HALF ? 8 : 16) / blocks;      // on average
+  tile[1] = groups * (HALF ? 8 : 16) / blocks;      // on average
   hipLaunchKernelGGL((skinny_kernel<MT, NC, D, HALF, ASRC, EPI, NW>), dim3(blocks), dim3(64 * NW), 0, st, p);
   return hipGetLastError();
 }
@@ -477,10 +488,11 @@ hipError_t sk_rows(const SkinnyParams &p, hipStream_t st, int tile[2]) {
 // groups of columns a fp32-output product of N columns is cut into
 int skinny_parts(int N) { return N / 16 < SK_HALF_BELOW ? N / 8 : N / 16; }
 
-// Weights of this many bytes are read with the non-temporal hint.  A layer with such products has weights of 60 MB and more, so those of a model of four layers pass
-// through the 256 MB of the last-level cache without ever being found in it again, and the hint spares their way into it.  us without / with it, weights from HBM, 16 rows: 3072 x 2048
+// Weights of this many bytes are read with the non-temporal hint.  A layer with such products has weights of 30 MB and more, so those of a model of nine layers
+// and more (three, from 90 MB a layer on) pass through the 256 MB of the last-level cache without ever being found in it again, and the hint spares their way into it.  us without / with it, weights from HBM, 16 rows: 3072 x 2048
 // (12 MB) 5.6 / 4.6, 2048 x 5632 8.4 / 7.3, 2 x 5632 x 2048 10.9 / 10.0, 12288 x 4096 19.0 / 17.4, 32000 x 2048 24.7 / 21.6, 32000 x 4096 46.2 / 40.5; 2048 x 2048 (8 MB) 4.0
-// / 4.0, and 3.8 / 4.7 where 24 copies in turn stay in the cache.
+// / 4.0, and 3.8 / 4.7 where 24 copies in turn stay in the cache.  Forward of a layer of 30, 47 and 90 MB, 16 rows, layers in turn that do not fit the cache: 34.9 / 32.5, 42.1 / 37.6, 49.6 / 45.6, 64 rows 50.6 / 48.6, 60.1 / 56.4, 73.3 / 68.8.
+// Two layers in turn, which stay in it, pay for the hint: 33.7 / 33.9, 39.6 / 41.3, 44.7 / 47.7, and at 64 rows 46.4 / 47.5, 54.7 / 58.0, 63.2 / 71.3.
 constexpr long long SK_STREAM_BYTES = 12ll << 20;
 
 hipError_t launch_skinny(const SkinnyParams &params, int asrc, int epi, hipStream_t st, const char **why, int tile[2]) {

@@ -101,6 +101,7 @@ enum { SK_E_F32, SK_E_SWIGLU, SK_E_QKV };
 struct SkinnyParams {
   const void *a;            // activations
   int stream;               // (filled by launch_skinny) weights are read past the last-level cache
+  int share, rest;          // (filled by launch_skinny) row groups / blocks and its remainder
   const bf16_t *gain;
   float eps;
   int M, N, K;

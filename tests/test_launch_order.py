@@ -222,7 +222,7 @@ def skinny_reads(rec):
         if r["op"] == "launch" and "skinny_kernelI" in r["kernel"]:
             mt, _, _, _, asrc, _ = re.search(r"skinny_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)ELi(\d+)ELi(\d+)E", r["kernel"]).groups()
             if int(asrc) == 0:
-                _, a, m, _, k = r["ranges"][0]
+                _, a, m, _, k, _, _ = r["ranges"][0]
                 out.append((a, int(mt) * 16 * k * 2, m))
     return out
 
@@ -300,6 +300,27 @@ def test_every_few_row_form_is_launched_by_some_batch(recorder):
             opts = dict(d=d, hq=hq, hkv=hkv, hd=hd, F=F, V=V, n=rows, decode=[5] * rows)
             launched.update(skinny_forms(recorder("fwd", **opts)), skinny_forms(recorder("logits", **opts)))
     assert compiled - launched == set()
+
+
+def test_blocks_of_few_row_products_share_their_groups_evenly(recorder):
+    """A block takes its first group and its number of groups from the whole shares and the rest it is given, in 32 bits: together they are all groups once, and no block has more than its form holds."""
+    n = 0
+    for d, hq, hkv, hd, F, V in ((1024, 72, 36, 64, 11008, 10304), (2048, 32, 8, 64, 5632, 32000), (1024, 50, 50, 128, 7040, 12800), (4096, 32, 32, 128, 11008, 128256)):
+        for rows in (1, 20, 40, 64, 80, 128):
+            for call in ("fwd", "logits"):
+                for r in recorder(call, d=d, hq=hq, hkv=hkv, hd=hd, F=F, V=V, n=rows, decode=[5] * rows):
+                    if r["op"] != "launch" or "skinny_kernelI" not in r["kernel"]:
+                        continue
+                    _, nc, _, half, _, epi, _ = map(int, re.findall(r"L[ib](\d+)E", r["kernel"].split("skinny_kernelI")[1]))
+                    _, _, _, N, _, share, rest = r["ranges"][0]
+                    groups, blocks = N // (8 if epi == 1 or half else 16), r["grid"][0]
+                    b = np.arange(blocks, dtype=np.int64)
+                    assert 0 <= rest < blocks and (b * rest < 2 ** 32).all()
+                    first = b * share + b * rest // blocks
+                    own = share + (b * rest % blocks + rest >= blocks)
+                    assert first[0] == 0 and (first + own == np.append(first[1:], groups)).all() and 1 <= own.min() and own.max() <= nc, (groups, blocks, r["kernel"])
+                    n += rest > 0
+    assert n > 20
 
 
 def test_tiles_of_the_checked_small_products(recorder):
