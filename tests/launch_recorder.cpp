@@ -53,7 +53,7 @@ static void describe(const std::string &k, void **a) {
         range("parts_out", p.mg[g].c, (size_t)(p.k_splits[g] > 1 ? p.k_splits[g] : 1) * p.mg[g].c_split_stride * 4);
   } else if (is("skinny_kernel")) {
     const SkinnyParams &p = arg<SkinnyParams>(a, 0);
-    printf("%s[\"skinny\", %llu, %d, %d, %d, %d, %d]", g_sep, (unsigned long long)(uintptr_t)p.a, p.M, p.N, p.K, p.share, p.rest);
+    printf("%s[\"skinny\", %llu, %d, %d, %d], [\"shares\", %d, %d]", g_sep, (unsigned long long)(uintptr_t)p.a, p.M, p.N, p.K, p.share, p.rest);
     g_sep = ", ";
   } else if (is("sum_parts_kernel")) {
     for (int i = 0; i < 3; ++i) read_parts(arg<SumRange>(a, i).parts);

@@ -222,7 +222,7 @@ def skinny_reads(rec):
         if r["op"] == "launch" and "skinny_kernelI" in r["kernel"]:
             mt, _, _, _, asrc, _ = re.search(r"skinny_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)ELi(\d+)ELi(\d+)E", r["kernel"]).groups()
             if int(asrc) == 0:
-                _, a, m, _, k, _, _ = r["ranges"][0]
+                _, a, m, _, k = r["ranges"][0]
                 out.append((a, int(mt) * 16 * k * 2, m))
     return out
 
@@ -312,7 +312,7 @@ def test_blocks_of_few_row_products_share_their_groups_evenly(recorder):
                     if r["op"] != "launch" or "skinny_kernelI" not in r["kernel"]:
                         continue
                     _, nc, _, half, _, epi, _ = map(int, re.findall(r"L[ib](\d+)E", r["kernel"].split("skinny_kernelI")[1]))
-                    _, _, _, N, _, share, rest = r["ranges"][0]
+                    (_, _, _, N, _), (_, share, rest) = r["ranges"]
                     groups, blocks = N // (8 if epi == 1 or half else 16), r["grid"][0]
                     b = np.arange(blocks, dtype=np.int64)
                     assert 0 <= rest < blocks and (b * rest < 2 ** 32).all()
