@@ -1491,8 +1491,8 @@ static int layer_bwd_impl(mace_handle_t h, const mace_layer_w_t *w, const mace_l
   prof_mark(h, st, T_ROPE);
   HIP_TRY(launch_rope_table(batch->positions + I.Ti, h->inv_freq, Tf, D.hd, B.cs, st), "rope table");
   prof_mark(h, st, T_ATTN_BWD, 10.0 * D.hd * D.Hq * I.pairs_ft);
-  HIP_TRY(launch_attn_bwd(S.q, S.k, S.v, S.o, B.dattn, S.lse, batch->seg_offsets + batch->n_prefill + batch->n_decode,
-                          batch->seg_offsets_host + batch->n_prefill + batch->n_decode, I.Ti, batch->n_ft_seq, I.max_ft, Tf, D.Hq, D.Hkv, D.hd, B.dvec, B.cs, B.dqkv, st, batch->ft_excl_lo, batch->ft_excl_hi), "attention bwd");
+  HIP_TRY(launch_attn_bwd(S.q, S.k, S.v, S.o, B.dattn, S.lse, batch->seg_offsets + batch->n_prefill + batch->n_decode, I.Ti, batch->n_ft_seq, I.max_ft, Tf,
+                          D.Hq, D.Hkv, D.hd, B.dvec, B.cs, B.dqkv, st, batch->ft_excl_lo, batch->ft_excl_hi), "attention bwd");
   // da = dq Wq + dk Wk + dv Wv ; dWq, dWk, dWv
   Parts da = {B.da, 1, 0};
   {

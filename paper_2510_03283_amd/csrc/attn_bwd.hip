@@ -363,27 +363,19 @@ __global__ __launch_bounds__(256 * QS, QS == 1 ? 2 : 1) void attn_bwd_dkdv_kerne
 }
 
 // Two teams where one wave a SIMD would be left (a block's turns are a chain: load, products, soft-max, products), i.e. up to about one block a CU: a block of two teams has a CU's
-// waves to itself, so one past that waits for a whole other one.  Counted are blocks of the longest one's turns (query tiles times heads of the group), for the light ones at the end of a sequence
-// fill in; in all there are at most about 320.  The second team's start and the sum cost two to six turns' time, more at 128-wide heads, where a second round of light blocks counts as well until there are a dozen turns.
-// us with one / two teams, 8 kv heads, 32 query heads of 64 unless it says otherwise: 8 sequences of 327 - 505 rows 90 / 58 (a step of one pair of that layer 936 -> 918); 32 of 64 rows (256 blocks of 4 turns) 14.8 / 12.6,
-// 36 (288) 16.5 / 21.5, 60 of 10 (480) 14.4 / 17.5; 24 of 134 (12 turns) 35.6 / 27.8; 8 query heads of 64: 16 of 60 (one turn) 6.7 / 7.0, 20 and 22 of 134 (3 turns) 12.1 / 11.8 and 12.4 / 14.4, 8 of 396 (7 turns) 19.5 / 17.2.
-// Of 128-wide heads, the dQ kernel included: 10 sequences of 100 (8 turns) 61.7 / 57.9, of 134 (12) 91.8 / 82.2; 16 query heads, 16 of 134 (6) 56.0 / 55.6, 10 of 226 (8) 66.0 / 63.0, 20 (320 blocks) 93.8 / 105.6; 8 query heads, 8 of 226 (4) 47.6 / 50.0,
-// 8 and 10 of 400 (7; 256 and 320 blocks) 64.6 / 64.9 and 68.6 / 78.0, 4 and 8 of 520 (9; 160 and 320) 72.0 / 69.3 and 78.3 / 83.2.  A step of a 7B layer with 2 sequences of 396 (32 kv heads, 7 turns, 256 blocks) 2088 / 2098, of 520 (9, 320) 2558 / 2564,
-// where the products of the side stream share the chip.  At 384 blocks of 128-wide heads every SIMD has its second wave already.
-bool two_teams(const int32_t *seg_host, int n_seq, int max_len, int rows, int group, int Hkv, int hd) {
-  if ((long long)Hkv * (rows / 128 + n_seq / 2) > 320) return false;
-  const int longest = cdiv(max_len, TB), turns = group * longest;
-  if (turns < (hd == 64 ? 2 : 8)) return false;
-  long long tiles = 0, blocks = 0;      // query tiles of all blocks of a kv head, for one query head; its blocks
-  for (int s = 0; s < n_seq; ++s)
-    for (int L = seg_host[s + 1] - seg_host[s]; L > 0; L -= 128, ++blocks) tiles += cdiv(L, TB);
-  if (hd != 64 && turns < 12 && Hkv * blocks > 256) return false;
-  return Hkv * tiles <= (long long)longest * (hd == 64 && turns >= 4 ? 256 : 224);
+// waves to itself, so one past that waits for a whole other one.  The blocks are estimated from rows and sequences; light ones at the end of a sequence count half, for they fill in.  Not where
+// the sequences alone are more blocks than CUs, and not with a single turn (query tiles times heads of the group), which leaves the second team nothing.
+// us with one / two teams, 8 kv heads, 32 query heads of 64 unless it says otherwise: 8 sequences of 327 - 505 rows 90 / 58 (a step of one pair of that layer 936 -> 918); 24 of 134 35.6 / 27.8; 32 of 64 rows (256 blocks) 14.8 / 12.6,
+// 36 (288) 16.5 / 21.5, 60 of 10 (480) 14.4 / 17.5; 8 query heads, 16 of 60 (one turn) 6.7 / 7.0, 8 of 396 (7 turns) 19.5 / 17.2.  Of 128-wide heads, the dQ kernel included: 10 sequences of 134 (12 turns) 91.8 / 82.2, of 100 (8) 61.7 / 57.9;
+// about even to a tenth dearer where a second round of light blocks meets few turns (8 query heads, 8 and 10 of 400, 256 and 320 blocks, 64.6 / 64.9 and 68.6 / 78.0; a step of a 7B layer with 2 sequences of 396 2088 / 2098, of 520 2558 / 2564).
+// Those keep two teams: a finer line would give a step at most what its runs differ by.  At 384 blocks of 128-wide heads every SIMD has its second wave already.
+bool two_teams(int n_seq, int max_len, int rows, int group, int Hkv) {
+  return (long long)Hkv * (rows / 128 + n_seq / 2) <= 320 && (long long)Hkv * n_seq <= 256 && group * cdiv(max_len, TB) >= 2;
 }
 
 template <int HD>
 hipError_t launch_t(const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf16_t *o, const bf16_t *d_o,
-                    const float *lse, const int32_t *seg, const int32_t *seg_host, int row_base, int n_seq, int max_len, int rows, int Hq,
+                    const float *lse, const int32_t *seg, int row_base, int n_seq, int max_len, int rows, int Hq,
                     int Hkv, float *dvec, const float2 *cs, bf16_t *dqkv, hipStream_t st, const int32_t *excl_lo,
                     const int32_t *excl_hi) {
   constexpr size_t lds_q = (size_t)2 * (2 * TB * HD) * sizeof(bf16_t);
@@ -402,7 +394,7 @@ hipError_t launch_t(const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf1
   hipLaunchKernelGGL((attn_bwd_dq_kernel<HD>), grid_q, dim3(256), lds_q, st, q, k, v, o, d_o, lse, dvec, seg, row_base, Hq, Hkv, cs, dqkv, excl_lo, excl_hi);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (two_teams(seg_host, n_seq, max_len, rows, Hq / Hkv, Hkv, HD))
+  if (two_teams(n_seq, max_len, rows, Hq / Hkv, Hkv))
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<HD, 2>), grid_k, dim3(512), 2 * lds_k, st, q, k, v, d_o, lse, dvec, seg, row_base, Hq, Hkv, cs, dqkv, excl_lo, excl_hi);
   else
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<HD, 1>), grid_k, dim3(256), lds_k, st, q, k, v, d_o, lse, dvec, seg, row_base, Hq, Hkv, cs, dqkv, excl_lo, excl_hi);
@@ -412,12 +404,12 @@ hipError_t launch_t(const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf1
 }  // namespace
 
 hipError_t launch_attn_bwd(const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf16_t *o, const bf16_t *d_o,
-                           const float *lse, const int32_t *seg, const int32_t *seg_host, int row_base, int n_seq, int max_len, int rows,
+                           const float *lse, const int32_t *seg, int row_base, int n_seq, int max_len, int rows,
                            int Hq, int Hkv, int hd, float *dvec, const float2 *cs, bf16_t *dqkv, hipStream_t st,
                            const int32_t *excl_lo, const int32_t *excl_hi) {
   if (n_seq <= 0 || rows <= 0) return hipSuccess;
   if (n_seq > 65535 || max_len > 65535 * 64 || ((excl_lo == nullptr) != (excl_hi == nullptr))) return hipErrorInvalidValue;
-  if (hd == 64) return launch_t<64>(q, k, v, o, d_o, lse, seg, seg_host, row_base, n_seq, max_len, rows, Hq, Hkv, dvec, cs, dqkv, st, excl_lo, excl_hi);
-  if (hd == 128) return launch_t<128>(q, k, v, o, d_o, lse, seg, seg_host, row_base, n_seq, max_len, rows, Hq, Hkv, dvec, cs, dqkv, st, excl_lo, excl_hi);
+  if (hd == 64) return launch_t<64>(q, k, v, o, d_o, lse, seg, row_base, n_seq, max_len, rows, Hq, Hkv, dvec, cs, dqkv, st, excl_lo, excl_hi);
+  if (hd == 128) return launch_t<128>(q, k, v, o, d_o, lse, seg, row_base, n_seq, max_len, rows, Hq, Hkv, dvec, cs, dqkv, st, excl_lo, excl_hi);
   return hipErrorInvalidValue;
 }

@@ -200,9 +200,8 @@ hipError_t launch_head_norm_stats(const float *norms, const int32_t *t_count, in
 // included: dqkv bf16 [rows, (Hq+2Hkv)*hd] receives dq and dk rotated back by the rows' angles (cs: the
 // table of launch_rope_table, [rows, hd/2]) and dv, i.e. the gradient of the projection output.
 // dvec: fp32 scratch [rows, Hq] (rowsum(dO * O), written by the dq kernel, read by the dk/dv kernel).
-// (seg_host: the same offsets on the host)
 hipError_t launch_attn_bwd(const bf16_t *q, const bf16_t *k, const bf16_t *v, const bf16_t *o, const bf16_t *d_o,
-                           const float *lse, const int32_t *seg, const int32_t *seg_host, int row_base, int n_seq, int max_len, int rows,
+                           const float *lse, const int32_t *seg, int row_base, int n_seq, int max_len, int rows,
                            int Hq, int Hkv, int hd, float *dvec, const float2 *cs, bf16_t *dqkv, hipStream_t st,
                            const int32_t *excl_lo = nullptr, const int32_t *excl_hi = nullptr);
 

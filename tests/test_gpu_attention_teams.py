@@ -27,8 +27,8 @@ def test_one_team(torch_mod):
 # (query heads, kv heads, head width, pairs, prompt, responses, prompt stored once) -> teams of a dK/dV block (test_launch_order holds them to it).  With the
 # prompt stored once, key tiles that later rows do not see: whole and in part, in both forms of the kernel.
 FORMS = {
-    (4, 4, 128, 2, 330, (2, 60), False): 1, (4, 4, 128, 2, 470, (2, 60), False): 2, (8, 2, 128, 2, 90, (5, 70), False): 2, (8, 2, 64, 3, 129, (1, 3), True): 2, (4, 2, 128, 3, 200, (120, 300), True): 2,
-    (4, 4, 128, 3, 129, (60, 90), True): 1, (32, 32, 64, 8, 200, (60, 120), True): 1, (8, 8, 64, 12, 20, (5, 44), False): 1, (16, 16, 128, 6, 300, (100, 260), True): 1,
+    (4, 4, 128, 2, 330, (2, 60), False): 2, (4, 4, 128, 2, 470, (2, 60), False): 2, (8, 2, 128, 2, 90, (5, 70), False): 2, (8, 2, 64, 3, 129, (1, 3), True): 2, (4, 2, 128, 3, 200, (120, 300), True): 2,
+    (4, 4, 128, 3, 129, (60, 90), True): 2, (32, 32, 64, 8, 200, (60, 120), True): 1, (8, 8, 64, 12, 20, (5, 44), False): 1, (16, 16, 128, 6, 300, (100, 260), True): 1,
 }
 
 

@@ -171,16 +171,14 @@ def test_products_outside_the_four_wave_kernel_are_not_priced_as_its_tiles(recor
 @pytest.mark.parametrize("hq,hkv,hd,ft,teams", [
     (32, 8, 64, [505, 470, 327, 400] * 2, 2), (32, 8, 64, [950, 941], 2), (32, 8, 64, [64] * 32, 2), (32, 8, 64, [134] * 24, 2),
     (32, 8, 64, [10] * 60, 1), (32, 8, 64, [30] * 40, 1), (32, 8, 64, [64] * 36, 1),          # many short sequences: more blocks than CUs
-    (32, 8, 128, [396] * 8, 2), (32, 8, 128, [134] * 20, 2), (16, 8, 128, [226] * 10, 2), (8, 8, 128, [520] * 4, 2), (16, 8, 128, [400] * 10, 2),
-    (16, 8, 128, [134] * 16, 1), (32, 32, 128, [396] * 2, 1), (8, 8, 128, [330] * 6, 1),       # 128-wide heads: too few turns
-    (16, 8, 128, [226] * 20, 1), (32, 32, 128, [520] * 2, 1), (8, 8, 128, [400] * 10, 1), (8, 8, 128, [520] * 8, 1),      # a second round of light blocks
-    (32, 8, 128, [10] * 60, 1), (32, 8, 128, [60] * 28, 1), (32, 8, 128, [134] * 24, 1), (16, 8, 128, [134] * 22, 1),
-    (8, 8, 64, [60] * 16, 1), (8, 8, 64, [64] * 36, 1),                                        # one query tile: nothing for a second team
-    (8, 8, 64, [134] * 20, 2), (8, 8, 64, [134] * 22, 1), (8, 8, 64, [396] * 8, 2),
+    (32, 8, 128, [396] * 8, 2), (32, 8, 128, [134] * 20, 2), (32, 32, 128, [396] * 2, 2), (32, 32, 128, [65] * 8, 2),
+    (32, 8, 128, [10] * 60, 1), (32, 32, 128, [65] * 9, 1),
+    (8, 8, 64, [60] * 16, 1), (32, 32, 128, [64] * 2, 1), (16, 8, 128, [64] * 16, 2),          # one query tile: nothing for a second team, but for a group of heads
+    (8, 8, 64, [134] * 20, 2), (8, 8, 64, [396] * 8, 2),
     (32, 32, 64, [456] * 8, 1), (32, 32, 128, [1024] * 4, 1),
 ], ids=lambda v: f"{len(v)}x{v[0]}" if isinstance(v, list) else str(v))
 def test_teams_of_the_attention_backward(recorder, hq, hkv, hd, ft, teams):
-    """A block's second team of waves takes half of its turns where the long blocks fit one a CU; past that, or without turns to share, it costs."""
+    """A block's second team of waves takes half of its turns where there are about as many blocks as CUs; past that, or without turns to share, it costs."""
     rec = recorder("bwd", d=512, hq=hq, hkv=hkv, hd=hd, F=512, ft=ft)
     assert status(rec)["status"] == 0
     (r,) = [r for r in rec if r["op"] == "launch" and "attn_bwd_dkdv_kernel" in r["kernel"]]
